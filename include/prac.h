@@ -140,6 +140,10 @@ int prac_reserve_workspace(prac_ctx* ctx, size_t bytes);
  * product prac_fit_basis issues for that shape (negative: the plan would be too small;
  * the launchers refuse such a product instead of writing past the block). */
 int64_t prac_debug_fit_slab_margin(const prac_call_shape* shape /* [host] */);
+/* Test hook [host]: how a Gram matrix of these rows (prac_gram, and the fit that forms one) reads X, whose address is looked
+ * at but not followed: 0 strided; 1 in whole 16-byte chunks, up to 7 elements past a row's last column; 2 by the same
+ * kernel at the alignment of one element, nothing past a row's last column. */
+int prac_debug_gram_rows(const void* X, int dt, int64_t N, int64_t d, int64_t ldx, int64_t row_stride);
 
 /* ---- per-kernel timing hook (for benchmarks) ---------------------------- */
 /* While a kind other than PRAC_KERNEL_NONE is selected, every launch of that

@@ -961,7 +961,7 @@ int fit_basis_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, in
       if (rc) return rc;
       rc = launch_compress_ws(ctx, Xb, ld, (int)rows, dm, Pf, L.trk_ncb, k, Cpk, 0, true, nullptr, 0, 0, nullptr, 0);
       if (rc) return rc;
-      rc = launch_ctdy_ws(ctx, Cpk, k, (int)rows, 1, &Xb, &ld, &dm, &slabs, L.trk_splits);
+      rc = launch_ctdy_ws(ctx, Cpk, k, (int)rows, 1, &Xb, &ld, &dm, &slabs, L.trk_splits, false);
       if (rc) return rc;
       rc = launch_reduce_transpose_f32(ctx, slabs, L.trk_splits, k, dm, Y, k);
       if (rc) return rc;

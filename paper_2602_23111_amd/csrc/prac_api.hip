@@ -158,18 +158,21 @@ inline GramPlan plan_gram(int n_cu, int64_t rows, int64_t d, int64_t ldg) {
 }  // namespace
 
 namespace {
-// Whether a Gram matrix runs on the bf16 matrix cores: aligned rows always (gram_fast), rows that start on any
-// element when it is large enough for the streaming kernel.
-inline bool gram_mfma(const void* X, prac_dtype xdt, int64_t rows, int64_t d, int64_t ldx, int64_t row_stride) {
-  return gram_fast(X, xdt, rows, ldx, row_stride) ||
-         (stream_any(xdt, d, ldx * row_stride) && rows < ((int64_t)1 << 31) && gram_streaming(rows, d));
+// How a Gram matrix reads its rows: on the bf16 matrix cores in whole 16-byte chunks (aligned rows), there at the
+// alignment of one element (large enough for the streaming kernel), or strided.  ldx itself decides what is aligned, not the
+// pitch ldx * row_stride of the sampled rows: the chunk that holds the last row's end must lie inside that row's ldx elements.
+enum class GramRows { STRIDED = 0, ALIGNED = 1, ANY = 2 };
+inline GramRows gram_rows(const void* X, prac_dtype xdt, int64_t rows, int64_t d, int64_t ldx, int64_t row_stride) {
+  if (gram_fast(X, xdt, rows, ldx, row_stride)) return GramRows::ALIGNED;
+  return stream_any(xdt, d, ldx * row_stride) && rows < ((int64_t)1 << 31) && gram_streaming(rows, d) ? GramRows::ANY
+                                                                                                      : GramRows::STRIDED;
 }
 }  // namespace
 
 size_t gram_scratch_bytes(int n_cu, const void* X, prac_dtype xdt, int64_t N, int64_t d, int64_t ldx,
                           int64_t row_stride, int64_t ldg) {
   const int64_t rows = (N + row_stride - 1) / row_stride;
-  if (!gram_mfma(X, xdt, rows, d, ldx, row_stride)) return 0;
+  if (gram_rows(X, xdt, rows, d, ldx, row_stride) == GramRows::STRIDED) return 0;
   return plan_gram(n_cu, rows, d, ldg).bytes;
 }
 
@@ -177,7 +180,8 @@ size_t gram_scratch_bytes(int n_cu, const void* X, prac_dtype xdt, int64_t N, in
 int gram_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, int64_t d, int64_t ldx, int64_t row_stride,
                 float* G, int64_t ldg, char* scratch) {
   const int64_t rows = (N + row_stride - 1) / row_stride;
-  if (gram_mfma(X, xdt, rows, d, ldx, row_stride)) {
+  const GramRows how = gram_rows(X, xdt, rows, d, ldx, row_stride);
+  if (how != GramRows::STRIDED) {
     const GramPlan gp = plan_gram(ctx->n_cu, rows, d, ldg);
     const int splits = gp.splits;
     const size_t o_part = gp.o_part, o_g = gp.o_g;
@@ -194,7 +198,7 @@ int gram_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, int64_t
       float* out = splits > 1 ? partial : dense;
       {
         ProfScope ps(ctx, PRAC_KERNEL_GRAM);
-        rc = launch_ctdy_ws(ctx, Xpk, dm, (int)rows, 1, &Xb, &ld, &dm, &out, splits);
+        rc = launch_ctdy_ws(ctx, Xpk, dm, (int)rows, 1, &Xb, &ld, &dm, &out, splits, how == GramRows::ANY);
       }
       if (rc) return rc;
     } else {
@@ -768,7 +772,7 @@ int weight_grad_any(prac_ctx* ctx, char* ws, const WgradAnyPlan& q, const void* 
   }
   {
     ProfScope ps(ctx, PRAC_KERNEL_CT_DY);
-    rc = launch_ctdy_ws(ctx, Cpk, c, (int)N, n_out, dYp, lddy, mi, part, q.splits);
+    rc = launch_ctdy_ws(ctx, Cpk, c, (int)N, n_out, dYp, lddy, mi, part, q.splits, true);
   }
   if (rc) return rc;
   for (int h = 0; h < n_out; ++h) {
@@ -873,7 +877,7 @@ int weight_grad_fast(prac_ctx* ctx, char* ws, int* cnt, const WgradPlan& q, cons
   }
   {  // T_h = C^T dY_h as `splits` partial slabs over the token range
     ProfScope ps(ctx, PRAC_KERNEL_CT_DY);
-    rc = launch_ctdy_ws(ctx, Cpk, c, (int)N, n_out, dYp, lddy, mi, part, splits);
+    rc = launch_ctdy_ws(ctx, Cpk, c, (int)N, n_out, dYp, lddy, mi, part, splits, false);
   }
   if (rc) return rc;
   // Slab sum, scaling factor and dW_h = P T_h in one launch where that is the faster form: measured on an
@@ -1206,6 +1210,11 @@ int prac_reserve_workspace(prac_ctx* ctx, size_t bytes) {
   if (bytes == ~(size_t)0) return PRAC_EINVAL;
   if (!ctx) return PRAC_ENOCTX;
   return prac_ws_reserve(ctx, bytes);
+}
+
+int prac_debug_gram_rows(const void* X, int dt, int64_t N, int64_t d, int64_t ldx, int64_t row_stride) {
+  if (!X || !valid_dtype(dt) || bad_tokens(N) || d < 1 || ldx < d || row_stride < 1) return -1;
+  return (int)gram_rows(X, (prac_dtype)dt, (N + row_stride - 1) / row_stride, d, ldx, row_stride);
 }
 
 int64_t prac_debug_fit_slab_margin(const prac_call_shape* sh) {

@@ -167,11 +167,12 @@ inline int wide_groups_per_wg(int n_cu, int tiles_m, int groups) {
 // W (bf16; w_layout 0: d x m, 1: m x d; ldw) -> [nkb][ncb_w][64][8] fragment order, zero padded
 int launch_pack_wfrag(prac_ctx* ctx, const bf16_t* W, int64_t ldw, int w_layout, int64_t d, int m, int nkb,
                       int ncb_w, bf16_t* out);
-// token-split partial sums of C^T dY_h for n_out outputs that share C; slabs[h] is splits x c x m[h].  Rows of dY_h
-// may start on any element (then m[h] >= 8)
+// token-split partial sums of C^T dY_h for n_out outputs that share C; slabs[h] is splits x c x m[h].  any_element: rows of
+// dY_h may start on any element, and a row owns nothing past its last column (then m[h] >= 8); otherwise they are 16-byte
+// aligned and own whole 16-byte chunks (the caller says which: where the rows are a sample of a matrix, their pitch does not)
 #define PRAC_CTDY_MAX_OUT 4
 int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, const bf16_t* const* dY,
-                   const int64_t* lddy, const int* m, float* const* slabs, int splits);
+                   const int64_t* lddy, const int* m, float* const* slabs, int splits, bool any_element);
 // The whole weight gradient in one launch: partial slabs, their sum as T (bf16, fragment order, rows >= k_lo
 // scaled) and dW_h = P T_h, the workgroups of a column tile meeting through `cnt` (PRAC_SYNC_INTS_PER_TILE
 // ints per 128-column tile over all outputs, zero before and after the launch).  `splits` comes from

@@ -1550,22 +1550,20 @@ void fill_ctdy_args(CtdyWsArgs& a, const bf16_t* Cpk, int c, int N, int n_out, c
 }  // namespace
 
 int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, const bf16_t* const* dY,
-                   const int64_t* lddy, const int* m, float* const* slabs, int splits) {
+                   const int64_t* lddy, const int* m, float* const* slabs, int splits, bool any_element) {
   if (n_out < 1 || n_out > PRAC_CTDY_MAX_OUT) return PRAC_EINVAL;
-  bool ua = false;
   for (int h = 0; h < n_out; ++h) {
     if (lddy[h] > PRAC_MAX_STREAM_PITCH) return PRAC_EINVAL;
-    ua = ua || (reinterpret_cast<uintptr_t>(dY[h]) & 15) != 0 || lddy[h] % 8 != 0;
+    // narrower than one 16-byte chunk: callers send it to the strided kernels
+    if (any_element ? m[h] < 8 : (reinterpret_cast<uintptr_t>(dY[h]) & 15) != 0 || lddy[h] % 8 != 0) return PRAC_EINVAL;
   }
-  for (int h = 0; h < n_out; ++h)
-    if (ua && m[h] < 8) return PRAC_EINVAL;  // narrower than one 16-byte chunk: callers send it to the strided kernels
   CtdyWsArgs a{};
   fill_ctdy_args(a, Cpk, c, N, n_out, dY, lddy, m, slabs, splits);
   const size_t smem = (size_t)CW_STAGES * CW_STAGE;
   const int total = a.tiles_n * a.row_groups * splits;
   static bool f1[PRAC_MAX_DEVICES] = {}, f2[PRAC_MAX_DEVICES] = {};
   const dim3 grid(((total + 7) / 8) * 8), block(512);
-  if (ua) {
+  if (any_element) {
     int rc = set_smem(ctx, (ctdy_ws_kernel<0, true>), smem, f2[ctx->device % PRAC_MAX_DEVICES]);
     if (rc) return rc;
     PRAC_LAUNCH(ctx, (ctdy_ws_kernel<0, true>), grid, block, smem, a);

@@ -265,3 +265,20 @@ def test_fit_plan_holds_every_split_product():
                     for N in (32768, 300, 1):
                         sh = prac.call_shape("fit_basis", N, d, k, r, refresh=refresh, **opts)
                         assert lib.prac_debug_fit_slab_margin(C.byref(sh)) >= 0, (N, d, k, r, refresh, opts)
+
+
+def test_gram_of_sampled_rows_stays_inside_them(lib):
+    """Whole 16-byte chunks are read only where the chunk that holds the end of the last sampled row lies inside that row's
+    ldx elements: the pitch of the sample (ldx * row_stride) can be a multiple of 8 elements where ldx is not."""
+    ALIGNED, ANY = 1, 2
+    rows = lambda N, d, ldx, stride, X=0x1000: lib.prac_debug_gram_rows(C.c_void_p(X), 1, N, d, ldx, stride)
+    assert rows(4097, 260, 260, 2) == ANY and rows(16385, 5461, 5461, 8) == ANY
+    assert rows(4097, 260, 264, 2) == ALIGNED and rows(4097, 260, 264, 2, X=0x1002) == ANY
+    for N in (4096, 4097, 16385, 20000):
+        for d in range(256, 273):
+            for ldx in range(d, d + 9):
+                for stride in range(1, 9):
+                    if rows(N, d, ldx, stride) == ALIGNED:
+                        last = (N - 1) // stride * stride * ldx         # first element of the last sampled row
+                        assert last + (d + 7) // 8 * 8 <= N * ldx, (N, d, ldx, stride)
+    assert rows(0, 260, 260, 2) == -1 and rows(4097, 260, 259, 2) == -1 and rows(4097, 260, 260, 0) == -1

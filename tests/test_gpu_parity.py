@@ -252,11 +252,17 @@ def test_rows_that_start_on_any_element(ctx, N, d, m, k, r, end):
     assert rel_fro(si.as_f64(b16), refs[0] - 0.5) < 2.0 ** -8
 
 
-@pytest.mark.parametrize("N,d,stride", [(2049, 257, 1), (4111, 263, 2)])
-def test_gram_of_rows_that_start_on_any_element(ctx, N, d, stride):
+@pytest.mark.parametrize("N,d,stride,aligned_base", [(2049, 257, 1, False), (4111, 263, 2, False),
+                                                     (4097, 260, 2, True)])  # sampled rows 8-element aligned, ldx not
+def test_gram_of_rows_that_start_on_any_element(ctx, N, d, stride, aligned_base):
     """Large enough for the streaming kernel; both triangles from the same fp32 sums."""
     Xt = si.round_to(si.activation(N, d, 0.8, seed=N, n_out=2, out_scale=20.0)[0], "bf16")
-    G = ctx.gram(rows_on_any_element(Xt, d, True), row_stride=stride)
+    Xd = rows_on_any_element(Xt, d, True)
+    if aligned_base:  # what the allocation holds behind the matrix is NaN
+        block = torch.full((N * d + 64,), float("nan"), dtype=torch.bfloat16, device=DEV)
+        Xd = block[:N * d].view(N, d).copy_(Xd)
+        assert Xd.data_ptr() % 16 == 0 and d % 8 != 0
+    G = ctx.gram(Xd, row_stride=stride)
     torch.cuda.synchronize()
     ref = si.as_f64(Xt)[::stride]
     assert rel_fro(si.as_f64(G), ref.T @ ref) < 1e-5
