@@ -32,11 +32,11 @@
  *     1 <= d, m <= 2^20 features.
  *   - bf16 fast paths want 16-byte aligned base pointers and leading
  *     dimensions that are multiples of 8 elements (and at most 2^23, times the
- *     row stride where one applies).  For X (compress, fused forward, large
- *     Gram matrices) and dY whose rows start on any element, the same kernels run
- *     at about half the rate, with P to 16 bits of its mantissa in C and an fp32
- *     P T in the gradient; other unaligned operands, and rows of fewer than 8
- *     elements, run a slower generic kernel (same results to rounding).  Aligned
+ *     row stride where one applies).  X (compress, fused forward, large
+ *     Gram matrices) and dY whose rows start on any element run the same kernels
+ *     at a lower rate, with the fp32 P in C and an fp32 P T in the gradient; other
+ *     unaligned operands, and rows of fewer than 8 elements, run a slower generic
+ *     kernel (same results to rounding).  Aligned
  *     rows are read in whole 16-byte chunks: a matrix of R rows with leading dimension ld must own R * ld
  *     elements (the up to 7 elements after a row's last column may be read,
  *     never used, also in the last row); nothing outside those R * ld elements

@@ -42,8 +42,8 @@ __global__ __launch_bounds__(256) void pack_pfrag_kernel(const float* __restrict
   }
 }
 
-// P to 16 bits of its mantissa in the same order: a row of 2 ncb column blocks, block 2 q holding the bf16 rounding of
-// column block q and block 2 q + 1 the bf16 rounding of the rest
+// The fp32 P exactly, in the same order: a tile of 16 k-blocks three times, as three bf16 parts that add up to it.  A part is
+// what is left with the low half of its bits cut off: 8 bits of the mantissa each, so the third one is exact.
 __global__ __launch_bounds__(256) void pack_pfrag_split_kernel(const float* __restrict__ P, int64_t d, int64_t ldp, int c,
                                                                int nkb, int ncb, bf16_t* __restrict__ out) {
   const int64_t total = (int64_t)nkb * ncb * 64;
@@ -53,23 +53,25 @@ __global__ __launch_bounds__(256) void pack_pfrag_split_kernel(const float* __re
     const int cb = (int)(blk % ncb);
     const int64_t kb = blk / ncb;
     const int col = cb * 32 + j;
-    float hi[8], lo[8];
+    float part[3][8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int64_t kk = kb * 16 + 8 * h + e;
       const float v = (col < c && kk < d) ? P[kk * ldp + col] : 0.f;
-      hi[e] = __uint_as_float((uint32_t)f32_to_bf16(v) << 16);
-      lo[e] = isfinite(hi[e]) ? v - hi[e] : 0.f;
+      const float hi = __uint_as_float(__float_as_uint(v) & 0xFFFF0000u), rest = v - hi;
+      const float mid = __uint_as_float(__float_as_uint(rest) & 0xFFFF0000u);
+      const bool fin = isfinite(v);
+      part[0][e] = fin ? hi : v;
+      part[1][e] = fin ? mid : v;
+      part[2][e] = fin ? rest - mid : v;
     }
-    u32x4 a, b;
 #pragma unroll
-    for (int e2 = 0; e2 < 4; ++e2) {
-      a[e2] = pack2(hi[2 * e2], hi[2 * e2 + 1]);
-      b[e2] = pack2(lo[2 * e2], lo[2 * e2 + 1]);
+    for (int p = 0; p < 3; ++p) {
+      u32x4 w;
+#pragma unroll
+      for (int e2 = 0; e2 < 4; ++e2) w[e2] = pack2(part[p][2 * e2], part[p][2 * e2 + 1]);
+      reinterpret_cast<u32x4*>(out)[(((kb >> 4) * 3 + p) * 16 * ncb + (kb & 15) * ncb + cb) * 64 + lane] = w;
     }
-    u32x4* o = reinterpret_cast<u32x4*>(out) + (kb * ncb + cb) * 128 + lane;
-    o[0] = a;
-    o[64] = b;
   }
 }
 

@@ -501,10 +501,10 @@ int prac_unpack_compressed(prac_ctx* ctx, const void* Cpk, int64_t N, int c, voi
 
 namespace {
 // How a compress / fused-forward call runs: STREAM, the bf16 kernels on aligned rows; STREAM_ANY, the same kernels on
-// rows that start on any element, with P to 16 bits of its mantissa; STRIDED, everything else (fp32 data, rows
+// rows that start on any element, with the fp32 P as three bf16 parts; STRIDED, everything else (fp32 data, rows
 // of fewer than 8 elements, pitches above PRAC_MAX_STREAM_PITCH).  At N = 32768, d = 5461 (contiguous rows), c = 256
-// STREAM_ANY takes 0.19 ms, packing included, where the strided kernel and its cast take 2.5 ms (and STREAM with
-// padded rows 0.11 ms: half the matrix instructions).
+// STREAM_ANY takes 0.25 ms, packing included, where the strided kernel and its cast take 2.5 ms (and STREAM with
+// padded rows 0.11 ms: a third of the matrix instructions).
 enum class CompressPath { STREAM, STREAM_ANY, STRIDED };
 struct CompressPlan {
   size_t o_lp, o_w, o_tmp, o_c, bytes;
@@ -518,8 +518,8 @@ CompressPlan plan_compress(CompressPath path, bool fused, bool packed, bool has_
     const LpLayout l = lp_layout(d, c);
     if (path == CompressPath::STREAM)
       q.o_lp = plan.take(has_lp ? 0 : l.bytes);
-    else  // P as pairs of bf16 blocks, whole groups of 4 column blocks
-      q.o_lp = plan.take((size_t)l.nkb * 2 * round_up64((c + 31) / 32, 4) * 64 * 8 * sizeof(bf16_t));
+    else
+      q.o_lp = plan.take((size_t)l.nkb * 3 * l.ncb * 64 * 8 * sizeof(bf16_t));
     q.ncb_w = fused ? (int)round_up64((m + 31) / 32, 8) : 0;  // whole 256-column groups
     q.o_w = plan.take(fused ? (size_t)l.nkb * q.ncb_w * 64 * 8 * sizeof(bf16_t) : 0);
   } else {
@@ -577,7 +577,7 @@ static int compress_impl(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N
   if (path == CompressPath::STREAM_ANY) {
     const LpLayout l = lp_layout(d, c);
     bf16_t* Ps = reinterpret_cast<bf16_t*>(ctx->ws + q.o_lp);
-    int rc = launch_pack_pfrag_split(ctx, P, d, ldp, c, l.nkb, (int)round_up64((c + 31) / 32, 4), Ps);
+    int rc = launch_pack_pfrag_split(ctx, P, d, ldp, c, l.nkb, l.ncb, Ps);
     if (rc) return rc;
     bf16_t* Wf = nullptr;
     if (fused) {
@@ -586,9 +586,9 @@ static int compress_impl(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N
       if (rc) return rc;
     }
     ProfScope ps(ctx, fused ? PRAC_KERNEL_FUSED_FWD : PRAC_KERNEL_COMPRESS);
-    return launch_compress_ua(ctx, reinterpret_cast<const bf16_t*>(X), ldx, (int)N, (int)d, Ps, c,
+    return launch_compress_ws(ctx, reinterpret_cast<const bf16_t*>(X), ldx, (int)N, (int)d, Ps, l.ncb, c,
                               reinterpret_cast<bf16_t*>(C), ldc, packed, Wf, q.ncb_w, (int)m, reinterpret_cast<bf16_t*>(Y),
-                              ldy);
+                              ldy, true);
   }
   // strided path: fp32 data (P used in fp32), and bf16 rows the streaming kernels do not take
   const bool need_tmp = xdt == PRAC_BF16;

@@ -138,13 +138,11 @@ int launch_cast_out(prac_ctx* ctx, const float* src, int64_t lds, void* dst, pra
 
 // ---- kernels of the per-step path (ws_kernels.hip, hot_kernels.hip) -----------------
 // Wfrag != nullptr: also Y (N x m, ldy) = X W, W in the fragment order of Pfrag with ncb_w column blocks
+// any_element: rows of X start on any element and own nothing past their last column (d >= 8); Pfrag then holds the fp32 P
+// as launch_pack_pfrag_split leaves it
 int launch_compress_ws(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d, const bf16_t* Pfrag, int ncb,
                        int c, bf16_t* C, int64_t ldc, bool packed, const bf16_t* Wfrag, int ncb_w, int m,
-                       bf16_t* Y, int64_t ldy);
-// The same for X whose rows start on any element (d >= 8): Psplit holds P as pairs of bf16 blocks (pack_pfrag_split),
-// [nkb][2 round_up(ceil(c / 32), 4)][64][8]
-int launch_compress_ua(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d, const bf16_t* Psplit, int c, bf16_t* C,
-                       int64_t ldc, bool packed, const bf16_t* Wfrag, int ncb_w, int m, bf16_t* Y, int64_t ldy);
+                       bf16_t* Y, int64_t ldy, bool any_element = false);
 // out_h (N x n[h], bf16) = A (N x c bf16, row-major with lda or packed; c <= 256) B_h for up to PRAC_CTDY_MAX_OUT outputs,
 // B_h in fragment order [nkb][ncb[h]][64][8], zero past row c and column n[h]: nkb = wide_kblocks(c), ncb[h] a multiple
 // of 8 covering n[h]; recon: the reconstruction (one output).  Rows of out_h may start on any element.
@@ -186,7 +184,7 @@ int launch_wgrad_fused(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out
                        int nckb, const int* nmb, bf16_t* const* Tf, const bf16_t* Pa, int d, void* const* dW,
                        const int64_t* lddw, bool out_bf16, float beta, int* cnt);
 int launch_pack_pfrag(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int c, int nkb, int ncb, bf16_t* out);
-// block 2 q of a row of 2 ncb blocks: column block q of P as bf16; block 2 q + 1: bf16 of what that rounding left
+// the fp32 P exactly, as three bf16 parts: [nkb / 16][3][16][ncb][64][8]
 int launch_pack_pfrag_split(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int c, int nkb, int ncb, bf16_t* out);
 int launch_unpack_c(prac_ctx* ctx, const bf16_t* Cpk, int N, int c, bf16_t* C, int64_t ldc);
 int launch_pack_c(prac_ctx* ctx, const bf16_t* C, int64_t ldc, int N, int c, bf16_t* Cpk);

@@ -61,7 +61,7 @@ struct CompressWsArgs {
   const bf16_t* X;
   int64_t ldx;
   int N, d;
-  const bf16_t* Pfrag;  // [nkb][ncb][64][8], nkb = round_up(d,256)/16, zero outside d x c
+  const bf16_t* Pfrag;  // [nkb][ncb][64][8], nkb = round_up(d,256)/16, zero outside d x c; UA: [nkb/16][WS_SPLIT][16][ncb]...
   int ncb;              // 32-column blocks in the padded basis
   int c;
   bf16_t* C;            // row-major (ldc) or packed [ceil(N/128)*8][ccb][64][8]
@@ -85,6 +85,7 @@ constexpr int WS_STAGES = 2;
 constexpr int WS_RB = 32 * WS_LD * 2;        // bytes between 32-row blocks of a stage (16896)
 constexpr int WS_KB = WS_BK / 16;            // k-blocks per tile
 constexpr int WS_NCH = 4, WS_NIF = 2;        // chunks per tile, chunks in flight
+constexpr int WS_SPLIT = 3;                  // bf16 parts of an fp32 P
 
 // One k-block of a 128 x 64 wave tile: acc[2 i + j] += fa[i] * b_j, while the four A fragments
 // at byte offsets O + i * WS_RB from `lds` are read into fn.  The block also issues the two
@@ -198,11 +199,9 @@ __device__ __forceinline__ void drain_mfma(f32x16 (&acc)[NACC], u32x4 (&ring)[8]
   }
 }
 
-// UA: rows of X that start on any element (see frag_utils.h), and P to 16 bits of its mantissa instead of 8:
-// Pfrag then holds, for every 32-column block of P, the block rounded to bf16 and the block of what that rounding
-// left over, next to each other (pack_pfrag_split), a wave's two column blocks are such a pair and their sums are
-// added at the end.  (The strided kernel that served such data multiplied by the fp32 P; C is as close to that
-// product as its own rounding to bf16 allows.)  W of a forward output is bf16 as it is.
+// UA: rows of X that start on any element (see frag_utils.h), and the fp32 P instead of its bf16 copy: Pfrag then holds
+// every k-tile of P as three bf16 tiles that add up to it exactly (pack_pfrag_split), and the tile of X in LDS is
+// multiplied by each of them before the loaders move on.  W of a forward output is bf16 as it is: one step per tile.
 template <int FN, int NCH, int NIF, bool UA>
 __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -224,9 +223,11 @@ __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
   // Step kt of this workgroup works on k-tile act(kt): the sum over k may run in any order, and
   // workgroups that start at different tiles neither ask L2 for the same lines of P at once nor
   // all pull on the same memory channels (their row panels have the same alignment).
-  // (not with a forward output: there workgroups of different row tiles share W through L2 and
-  // should ask for it in the same order)
-  const int rot = a.Wfrag ? 0 : tm % nk;
+  // (not with a forward output, nor with P in three parts: there workgroups of different row tiles share more of W or P
+  // than an L2 holds and should ask for it in the same order; d = 5461, c = 256 from any element 250 against 280 us)
+  const int rot = UA || a.Wfrag ? 0 : tm % nk;
+  const bool fwd = cg < a.w_groups;      // this workgroup's columns belong to Y
+  const int reps = UA && !fwd ? WS_SPLIT : 1;  // steps per k-tile
   auto act = [&](int kt) {
     const int t = min(kt, nk - 1) + rot;
     return t >= nk ? t - nk : t;
@@ -298,6 +299,8 @@ __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
         cload(g + NIF, PRAC_IC((Q + NIF) % NCH));
         __syncthreads();
       });
+      if constexpr (UA)  // the other steps read the same tile
+        for (int e = (reps - 1) * NCH; e > 0; --e) __syncthreads();
     }
 #undef PRAC_IC
     return;
@@ -305,7 +308,6 @@ __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
 
   // -------------------------------------------------------------- matrix waves
   const int lane = tid & 63, li = lane & 31, lh = lane >> 5;
-  const bool fwd = cg < a.w_groups;  // this workgroup's columns belong to Y
   const int cb0 = (fwd ? cg : cg - a.w_groups) * 4 * FN + wave * FN;  // first 32-column block of this wave
   const char* pbase = reinterpret_cast<const char*>(fwd ? a.Wfrag : a.Pfrag);
   const uint32_t boff = (uint32_t)(cb0 * 64 + lane) * 16u;     // this lane's slot in a row of blocks
@@ -323,9 +325,12 @@ __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
   // `preq` is the address of the next k-block to request: it walks down a tile's 16 k-blocks
   // and jumps to the next tile's base after the tile's last one.
   u32x4 rb[8][FN];
-  auto tile_base = [&](int kt) {
-    // past the last tile: tile 0's fragments again (valid memory, an L2 hit, never used)
-    return pbase + (kt < nk ? (int64_t)act(kt) * WS_KB * brow : (int64_t)0);  // uniform
+  const int steps = nk * reps;
+  auto tile_of = [&](int st) { return UA && reps > 1 ? st / WS_SPLIT : st; };
+  auto tile_base = [&](int st) {
+    // past the last step: tile 0's fragments again (valid memory, an L2 hit, never used)
+    const int kt = tile_of(st);
+    return pbase + (st < steps ? (int64_t)(act(kt) * reps + (st - kt * reps)) * WS_KB * brow : (int64_t)0);  // uniform
   };
   const char* preq = tile_base(0);
   const char* next_base = tile_base(1);
@@ -357,9 +362,9 @@ __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
   __builtin_amdgcn_s_barrier();  // tile 0 is in LDS
   PRAC_STAMP(a, 1);
   frag_read4(fa, lds0);
-  for (int kt = 0; kt < nk; ++kt) {
-    const unsigned cur = lds0 + (unsigned)(kt & 1) * WS_STAGE;
-    const unsigned nxt = lds0 + (unsigned)((kt + 1) & 1) * WS_STAGE;
+  for (int st = 0; st < steps; ++st) {
+    const unsigned cur = lds0 + (unsigned)(tile_of(st) & 1) * WS_STAGE;
+    const unsigned nxt = lds0 + (unsigned)(tile_of(st + 1) & 1) * WS_STAGE;
     // k-block j multiplies while the fragments of k-block j+1 are read; its P slot is then refilled.
     // Barriers: one per chunk interval of the loaders; the last one of a tile sits before k-block 15,
     // whose fragment reads are the first from the next stage.
@@ -371,130 +376,114 @@ __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
       else kblock(PRAC_IC(32 * ((J + 1) % WS_KB)), fb, fa, jc, J == WS_KB - 1 ? nxt : cur);
       if constexpr (J % IV == IV - 1 && J != WS_KB - 1) __builtin_amdgcn_s_barrier();
     });
-    next_base = tile_base(kt + 2);
+    next_base = tile_base(st + 2);
     // Drain inside the loop: at the loop's exit the compiler may move accumulators between
     // registers (it has no idea that matrix instructions are still writing them), and such
     // moves must find the pipeline empty.
-    if (kt == nk - 1) drain_mfma<NACC, FN>(acc, rb);
+    if (st == steps - 1) drain_mfma<NACC, FN>(acc, rb);
   }
 #undef PRAC_IC
 
-  // epilogue: block (i, j) = acc[i * FN + j], j < FE; register v of lane (li, lh) is token row
-  // 8*(v/4) + 4*lh + v%4 of row block i, column li of the output's column block ob0 + j.
+  // epilogue: block (i, j) = acc[i * FN + j]; register v of lane (li, lh) is token row
+  // 8*(v/4) + 4*lh + v%4 of row block i, column li of column block cb0 + j.
   PRAC_STAMP(a, 2);
-  auto emit = [&](auto fec, const int ob0) {
-    constexpr int FE = decltype(fec)::value;
-    if (a.packed && !fwd) {
-      // registers v = 8 tb .. 8 tb + 7 are exactly the 8 slots of the 16-token block tb
-      u32x4* Cp = reinterpret_cast<u32x4*>(a.C);
-      if (m0 + WS_BM <= a.N && ob0 + FE <= a.ccb) {
-        // every token row and column block of the wave's tile is inside C: no masks, one base address
-        // (the epilogue is bound by the number of vector instructions issued: 8 register reads and 4
-        // conversions per store here against 45 instructions with the per-element checks below)
-        u32x4* base = Cp + ((int64_t)(m0 / 16) * a.ccb + ob0) * 64 + lane;
-        const int64_t tbs = (int64_t)a.ccb * 64;  // 16-token blocks are ccb * 64 slots apart
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < FE; ++j) {
-            asm volatile("" : "+a"(acc[i * FN + j]) : : "memory");  // one block at a time leaves the accumulators
-#pragma unroll
-            for (int tb = 0; tb < 2; ++tb) {
-              const f32x16& t = acc[i * FN + j];
-              u32x4 o;
-              o.x = pack2_hw(t[8 * tb + 0], t[8 * tb + 1]);
-              o.y = pack2_hw(t[8 * tb + 2], t[8 * tb + 3]);
-              o.z = pack2_hw(t[8 * tb + 4], t[8 * tb + 5]);
-              o.w = pack2_hw(t[8 * tb + 6], t[8 * tb + 7]);
-              stream_store(base + (2 * i + tb) * tbs + j * 64, o);
-            }
-          }
-      } else
+  if (a.packed && !fwd) {
+    // registers v = 8 tb .. 8 tb + 7 are exactly the 8 slots of the 16-token block tb
+    u32x4* Cp = reinterpret_cast<u32x4*>(a.C);
+    if (m0 + WS_BM <= a.N && cb0 + FN <= a.ccb) {
+      // every token row and column block of the wave's tile is inside C: no masks, one base address
+      // (the epilogue is bound by the number of vector instructions issued: 8 register reads and 4
+      // conversions per store here against 45 instructions with the per-element checks below)
+      u32x4* base = Cp + ((int64_t)(m0 / 16) * a.ccb + cb0) * 64 + lane;
+      const int64_t tbs = (int64_t)a.ccb * 64;  // 16-token blocks are ccb * 64 slots apart
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < FE; ++j) {
-          // one block at a time leaves the accumulator registers (keeps the copies short-lived)
-          asm volatile("" : "+a"(acc[i * FN + j]) : : "memory");
+        for (int j = 0; j < FN; ++j) {
+          asm volatile("" : "+a"(acc[i * FN + j]) : : "memory");  // one block at a time leaves the accumulators
 #pragma unroll
           for (int tb = 0; tb < 2; ++tb) {
-            // every token block of the 128-row tile is written: packed C is padded to whole tiles
-            const int gtb = (m0 + i * 32) / 16 + tb, cb = ob0 + j;
-            if (cb < a.ccb) {
-              // slot e of this lane is token 16 gtb + (e < 4 ? 4 lh + e : 8 + 4 lh + e - 4);
-              // tokens past N (computed from a repeated row) are stored as zeros
-              float x[8];
+            const f32x16& t = acc[i * FN + j];
+            u32x4 o;
+            o.x = pack2_hw(t[8 * tb + 0], t[8 * tb + 1]);
+            o.y = pack2_hw(t[8 * tb + 2], t[8 * tb + 3]);
+            o.z = pack2_hw(t[8 * tb + 4], t[8 * tb + 5]);
+            o.w = pack2_hw(t[8 * tb + 6], t[8 * tb + 7]);
+            stream_store(base + (2 * i + tb) * tbs + j * 64, o);
+          }
+        }
+    } else
 #pragma unroll
-              for (int e = 0; e < 8; ++e) {
-                const int tok = gtb * 16 + (e < 4 ? 4 * lh + e : 8 + 4 * lh + (e - 4));
-                x[e] = tok < a.N ? acc[i * FN + j][8 * tb + e] : 0.f;
-              }
-              u32x4 o;
-              o.x = pack2_hw(x[0], x[1]);
-              o.y = pack2_hw(x[2], x[3]);
-              o.z = pack2_hw(x[4], x[5]);
-              o.w = pack2_hw(x[6], x[7]);
-              stream_store(&Cp[((int64_t)gtb * a.ccb + cb) * 64 + lane], o);
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {
+        // one block at a time leaves the accumulator registers (keeps the copies short-lived)
+        asm volatile("" : "+a"(acc[i * FN + j]) : : "memory");
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb) {
+          // every token block of the 128-row tile is written: packed C is padded to whole tiles
+          const int gtb = (m0 + i * 32) / 16 + tb, cb = cb0 + j;
+          if (cb < a.ccb) {
+            // slot e of this lane is token 16 gtb + (e < 4 ? 4 lh + e : 8 + 4 lh + e - 4);
+            // tokens past N (computed from a repeated row) are stored as zeros
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const int tok = gtb * 16 + (e < 4 ? 4 * lh + e : 8 + 4 * lh + (e - 4));
+              x[e] = tok < a.N ? acc[i * FN + j][8 * tb + e] : 0.f;
             }
-          }
-        }
-    } else {
-      // Row-major output: the wave's 128 x (32 FE) tile goes through LDS (the X stages are free
-      // once every matrix wave has left the loop) so that global stores are 16 bytes per lane
-      // along a row.  LDS tile: [128][32 FE] bf16, rows padded by 16 bytes.
-      constexpr int TW = 32 * FE, TLD = TW * 2 + 16;
-      bf16_t* out = fwd ? a.Y : a.C;
-      const int64_t ldo = fwd ? a.ldy : a.ldc;
-      const int ncols = fwd ? a.m : a.c;
-      __builtin_amdgcn_s_barrier();  // the loader waves have exited; they no longer count
-      unsigned char* tile = smem_raw + wave * (128 * TLD);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < FE; ++j) {
-          asm volatile("" : "+a"(acc[i * FN + j]) : : "memory");
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int row = i * 32 + 8 * (v / 4) + 4 * lh + (v % 4);
-            *reinterpret_cast<bf16_t*>(tile + row * TLD + (j * 32 + li) * 2) =
-                (bf16_t)(pack2_hw(acc[i * FN + j][v], 0.f) & 0xFFFFu);
-          }
-        }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      constexpr int CPR = TW / 8;  // 16-byte chunks per row
-      const int n0 = ob0 * 32;
-#pragma unroll
-      for (int it = 0; it < 128 * CPR / 64; ++it) {
-        const int q = it * 64 + lane, row = q / CPR, ch = q % CPR;
-        const int mrow = m0 + row, n = n0 + ch * 8;
-        if (mrow < a.N && n < ncols) {
-          const u32x4 val = *reinterpret_cast<const u32x4*>(tile + row * TLD + ch * 16);
-          bf16_t* o = out + (int64_t)mrow * ldo + n;
-          if (n + 8 <= ncols) {
-            *reinterpret_cast<u32x4_el*>(o) = val;  // rows of the output may start on any element
-          } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              if (n + e < ncols) o[e] = (bf16_t)((val[e >> 1] >> (16 * (e & 1))) & 0xFFFFu);
+            u32x4 o;
+            o.x = pack2_hw(x[0], x[1]);
+            o.y = pack2_hw(x[2], x[3]);
+            o.z = pack2_hw(x[4], x[5]);
+            o.w = pack2_hw(x[6], x[7]);
+            stream_store(&Cp[((int64_t)gtb * a.ccb + cb) * 64 + lane], o);
           }
         }
       }
-    }
-  };
-  if constexpr (UA) {
-    if (fwd) {
-      emit(std::integral_constant<int, FN>{}, cb0);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i * FN][v] += acc[i * FN + 1][v];
-      emit(std::integral_constant<int, 1>{}, cb0 / 2);
-    }
   } else {
-    emit(std::integral_constant<int, FN>{}, cb0);
+    // Row-major output: the wave's 128 x (32 FN) tile goes through LDS (the X stages are free
+    // once every matrix wave has left the loop) so that global stores are 16 bytes per lane
+    // along a row.  LDS tile: [128][32 FN] bf16, rows padded by 16 bytes.
+    constexpr int TW = 32 * FN, TLD = TW * 2 + 16;
+    bf16_t* out = fwd ? a.Y : a.C;
+    const int64_t ldo = fwd ? a.ldy : a.ldc;
+    const int ncols = fwd ? a.m : a.c;
+    __builtin_amdgcn_s_barrier();  // the loader waves have exited; they no longer count
+    unsigned char* tile = smem_raw + wave * (128 * TLD);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {
+        asm volatile("" : "+a"(acc[i * FN + j]) : : "memory");
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int row = i * 32 + 8 * (v / 4) + 4 * lh + (v % 4);
+          *reinterpret_cast<bf16_t*>(tile + row * TLD + (j * 32 + li) * 2) =
+              (bf16_t)(pack2_hw(acc[i * FN + j][v], 0.f) & 0xFFFFu);
+        }
+      }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    constexpr int CPR = TW / 8;  // 16-byte chunks per row
+    const int n0 = cb0 * 32;
+#pragma unroll
+    for (int it = 0; it < 128 * CPR / 64; ++it) {
+      const int q = it * 64 + lane, row = q / CPR, ch = q % CPR;
+      const int mrow = m0 + row, n = n0 + ch * 8;
+      if (mrow < a.N && n < ncols) {
+        const u32x4 val = *reinterpret_cast<const u32x4*>(tile + row * TLD + ch * 16);
+        bf16_t* o = out + (int64_t)mrow * ldo + n;
+        if (n + 8 <= ncols) {
+          *reinterpret_cast<u32x4_el*>(o) = val;  // rows of the output may start on any element
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (n + e < ncols) o[e] = (bf16_t)((val[e >> 1] >> (16 * (e & 1))) & 0xFFFFu);
+        }
+      }
+    }
   }
 #ifdef PRAC_WS_TIMESTAMPS
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1426,8 +1415,9 @@ int set_smem(prac_ctx* ctx, K kern, size_t bytes, bool& done) {
 
 int launch_compress_ws(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d, const bf16_t* Pfrag, int ncb, int c,
                        bf16_t* C, int64_t ldc, bool packed, const bf16_t* Wfrag, int ncb_w, int m, bf16_t* Y,
-                       int64_t ldy) {
-  if (ldx > PRAC_MAX_STREAM_PITCH) return PRAC_EINVAL;  // callers route wider pitches to the strided kernels
+                       int64_t ldy, bool any_element) {
+  // callers route wider pitches, and rows shorter than one 16-byte chunk that start on any element, to the strided kernels
+  if (ldx > PRAC_MAX_STREAM_PITCH || (any_element && d < 8)) return PRAC_EINVAL;
   CompressWsArgs a;
 #ifdef PRAC_WS_TIMESTAMPS
   a.stamps = g_ws_stamps;
@@ -1450,43 +1440,23 @@ int launch_compress_ws(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d
   const size_t smem = (size_t)WS_STAGES * WS_STAGE;
   const int total = a.tiles_m * a.col_groups;
   const dim3 grid(((total + 7) / 8) * 8), block(512);
-  static bool f1[PRAC_MAX_DEVICES] = {}, f2[PRAC_MAX_DEVICES] = {};  // the attribute is per device
-  bool &s1 = f1[ctx->device % PRAC_MAX_DEVICES], &s2 = f2[ctx->device % PRAC_MAX_DEVICES];
-  constexpr auto kern1 = compress_ws_kernel<1, WS_NCH, WS_NIF, false>;
-  constexpr auto kern2 = compress_ws_kernel<2, WS_NCH, WS_NIF, false>;
-  if (FN == 1) {
-    int rc = set_smem(ctx, kern1, smem, s1);
-    if (rc) return rc;
-    PRAC_LAUNCH(ctx, kern1, grid, block, smem, a);
-  } else {
-    int rc = set_smem(ctx, kern2, smem, s2);
-    if (rc) return rc;
-    PRAC_LAUNCH(ctx, kern2, grid, block, smem, a);
+  static bool done_dev[PRAC_MAX_DEVICES][4] = {};  // the attribute is per device
+  bool* done = done_dev[ctx->device % PRAC_MAX_DEVICES];
+#define PRAC_COMPRESS_CASE(I, FN, UA)                                     \
+  case I: {                                                               \
+    constexpr auto kern = compress_ws_kernel<FN, WS_NCH, WS_NIF, UA>;     \
+    int rc = set_smem(ctx, kern, smem, done[I]);                          \
+    if (rc) return rc;                                                    \
+    PRAC_LAUNCH(ctx, kern, grid, block, smem, a);                         \
+    break;                                                                \
   }
-  PRAC_HIP_TRY(ctx, hipGetLastError());
-  return PRAC_OK;
-}
-
-int launch_compress_ua(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d, const bf16_t* Psplit, int c, bf16_t* C,
-                       int64_t ldc, bool packed, const bf16_t* Wfrag, int ncb_w, int m, bf16_t* Y, int64_t ldy) {
-  if (ldx > PRAC_MAX_STREAM_PITCH || d < 8 || !Psplit) return PRAC_EINVAL;  // callers send these to the strided kernels
-  CompressWsArgs a{};
-  a.X = X; a.ldx = ldx; a.N = N; a.d = d; a.Pfrag = Psplit; a.c = c;
-  a.C = C; a.ldc = ldc; a.ccb = (c + 31) / 32; a.packed = packed ? 1 : 0;
-  const int p_groups = (a.ccb + 3) / 4;  // 4 waves x one 32-column block of C (its two halves)
-  a.ncb = 8 * p_groups;
-  a.tiles_m = (N + WS_BM - 1) / WS_BM;
-  a.Wfrag = Wfrag; a.ncb_w = ncb_w; a.m = m; a.Y = Y; a.ldy = ldy;
-  a.w_groups = Wfrag ? ((m + 31) / 32 + 7) / 8 : 0;
-  if (a.w_groups * 8 > ncb_w) return PRAC_EINVAL;
-  a.col_groups = a.w_groups + p_groups;
-  const size_t smem = (size_t)WS_STAGES * WS_STAGE;
-  const int total = a.tiles_m * a.col_groups;
-  static bool f[PRAC_MAX_DEVICES] = {};
-  constexpr auto kern = compress_ws_kernel<2, WS_NCH, WS_NIF, true>;
-  int rc = set_smem(ctx, kern, smem, f[ctx->device % PRAC_MAX_DEVICES]);
-  if (rc) return rc;
-  PRAC_LAUNCH(ctx, kern, dim3(((total + 7) / 8) * 8), dim3(512), smem, a);
+  switch (FN - 1 + (any_element ? 2 : 0)) {
+    PRAC_COMPRESS_CASE(0, 1, false)
+    PRAC_COMPRESS_CASE(1, 2, false)
+    PRAC_COMPRESS_CASE(2, 1, true)
+    PRAC_COMPRESS_CASE(3, 2, true)
+  }
+#undef PRAC_COMPRESS_CASE
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
 }

@@ -216,10 +216,9 @@ def rows_on_any_element(t_cpu: torch.Tensor, ld: int, end: bool) -> torch.Tensor
     (128, 511, 135, 64, 64, True), (1000, 519, 263, 100, 33, False), (130, 1025, 121, 160, 140, True)])
 def test_rows_that_start_on_any_element(ctx, N, d, m, k, r, end):
     """Compress (both layouts, fused forward included) and the weight gradients (alone, and shared with an aligned dY)
-    on bf16 rows without any alignment.  C is the product with P to 16 bits of its mantissa, rounded to bf16: each element
-    within 2^-8 of itself (half an ulp of 8 significant bits) plus 2^-17 of the magnitudes summed for P and at most
-    d 2^-24 < 2^-17 of them for the fp32 sums (P rounded to bf16 would leave 2^-9 of them).  The gradient from that C is
-    all fp32."""
+    on bf16 rows without any alignment.  C is the product with the fp32 P, rounded to bf16: each element within 2^-8 of
+    itself (half an ulp of 8 significant bits) plus 2^-15.9 of the magnitudes summed for the fp32 sums (at most 240 sums of 16
+    products, 2^-24 each; P rounded to bf16 would leave 2^-9 of them).  The gradient from that C is all fp32."""
     from paper_2602_23111_amd.prac import C_PACKED
     c, s = k + r, (d - k) / r
     Xt = si.round_to(si.activation(N, d, 0.8, seed=N + d)[0], "bf16")
@@ -250,6 +249,29 @@ def test_rows_that_start_on_any_element(ctx, N, d, m, k, r, end):
     for got, want in zip(dws, (refs[0], refs[0], refs[0], refs[1])):
         assert rel_fro(si.as_f64(got), want) < 1e-5
     assert rel_fro(si.as_f64(b16), refs[0] - 0.5) < 2.0 ** -8
+
+
+@pytest.mark.parametrize("d,c", [(9, 8), (257, 33), (519, 300), (1025, 128)])
+def test_rows_that_start_on_any_element_meet_the_fp32_basis(ctx, d, c):
+    """Token n is e_2n - e_(2n+1), and rows 2n and 2n + 1 of P differ by 2^-14 to 2^-20 of themselves: C is that difference, which
+    every bf16 part of P but the first two or three cancels.  Products and sums are exact up to the rounding to bf16, but for
+    half an ulp of the fp32 sum each time a part is added."""
+    from paper_2602_23111_amd.prac import C_PACKED
+    g = torch.Generator().manual_seed(d)
+    n = d // 2
+    P = torch.randn((d, c), generator=g)
+    P[1:2 * n:2] = P[0:2 * n:2] * (1 + 2.0 ** -(14 + 6 * torch.rand((n, c), generator=g)))
+    X = torch.zeros((n, d))
+    X[torch.arange(n), 2 * torch.arange(n)], X[torch.arange(n), 2 * torch.arange(n) + 1] = 1.0, -1.0
+    Xd, Pd = rows_on_any_element(X.bfloat16(), d, True), P.to(DEV)
+    ref = P[0:2 * n:2].double() - P[1:2 * n:2].double()
+    bound = 2.0 ** -8 * ref.abs() + 2.0 ** -23 * P[0:2 * n:2].double().abs()
+    W = torch.zeros((16, d), dtype=torch.bfloat16, device=DEV)
+    outs = [ctx.compress(Xd, Pd), ctx.unpack_compressed(ctx.compress(Xd, Pd, layout=C_PACKED), n, c),
+            ctx.compress_fused_fwd(Xd, W, Pd, w_layout=1)[1]]
+    torch.cuda.synchronize()
+    for C in outs:
+        assert ((C.double().cpu() - ref).abs() <= bound).all()
 
 
 @pytest.mark.parametrize("N,d,stride,aligned_base", [(2049, 257, 1, False), (4111, 263, 2, False),
