@@ -43,7 +43,9 @@ __global__ __launch_bounds__(256) void pack_pfrag_kernel(const float* __restrict
 }
 
 // The fp32 P exactly, in the same order: a tile of 16 k-blocks three times, as three bf16 parts that add up to it.  A part is
-// what is left with the low half of its bits cut off: 8 bits of the mantissa each, so the third one is exact.
+// what is left with the low half of its bits cut off: 8 bits of the mantissa each, so the third one is exact.  The parts of a
+// number have its sign, and where one would be zero the part before it is cut into halves (down to 2^-124): an infinite
+// element of X then meets what it would meet in the product with P.
 __global__ __launch_bounds__(256) void pack_pfrag_split_kernel(const float* __restrict__ P, int64_t d, int64_t ldp, int c,
                                                                int nkb, int ncb, bf16_t* __restrict__ out) {
   const int64_t total = (int64_t)nkb * ncb * 64;
@@ -59,11 +61,11 @@ __global__ __launch_bounds__(256) void pack_pfrag_split_kernel(const float* __re
       const int64_t kk = kb * 16 + 8 * h + e;
       const float v = (col < c && kk < d) ? P[kk * ldp + col] : 0.f;
       const float hi = __uint_as_float(__float_as_uint(v) & 0xFFFF0000u), rest = v - hi;
-      const float mid = __uint_as_float(__float_as_uint(rest) & 0xFFFF0000u);
+      const float mid = __uint_as_float(__float_as_uint(rest) & 0xFFFF0000u), lo = rest - mid;
       const bool fin = isfinite(v);
-      part[0][e] = fin ? hi : v;
-      part[1][e] = fin ? mid : v;
-      part[2][e] = fin ? rest - mid : v;
+      part[0][e] = !fin ? v : (rest == 0.f ? 0.5f * v : hi);
+      part[1][e] = !fin ? v : (rest == 0.f ? 0.25f * v : (lo == 0.f ? 0.5f * mid : mid));
+      part[2][e] = !fin ? v : (rest == 0.f ? 0.25f * v : (lo == 0.f ? 0.5f * mid : lo));
     }
 #pragma unroll
     for (int p = 0; p < 3; ++p) {

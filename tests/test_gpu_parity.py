@@ -274,6 +274,33 @@ def test_rows_that_start_on_any_element_meet_the_fp32_basis(ctx, d, c):
         assert ((C.double().cpu() - ref).abs() <= bound).all()
 
 
+def test_infinity_in_rows_that_start_on_any_element(ctx):
+    """An infinite element of X makes its row of C infinite with the signs of the basis, whatever the bits of P (one, some and
+    all of its bf16 parts would be zero), and leaves the other rows alone; a zero of P makes it NaN."""
+    N, d, c = 130, 261, 40
+    g = torch.Generator().manual_seed(1)
+    P = torch.randn((d, c), generator=g)
+    P[:, 8:16] = P[:, 8:16].bfloat16().float()
+    P[:, 16:24] = (P[:, 16:24].double() * 2 ** 16).round().float() * 2.0 ** -16
+    P[:, 24:32] = 2.0 ** torch.randint(-8, 8, (d, 8), generator=g) * torch.where(P[:, 24:32] < 0, -1.0, 1.0)
+    P[P == 0] = 1.0
+    P[7, 39] = 0.0
+    X = torch.randn((N, d), generator=g).bfloat16()
+    at = {0: (7, 1.0), 5: (260, -1.0), 64: (255, 1.0), 129: (256, -1.0)}  # row: (column, sign)
+    for row, (col, sign) in at.items():
+        X[row, col] = sign * float("inf")
+    C = ctx.compress(rows_on_any_element(X, d, True), P.to(DEV))
+    torch.cuda.synchronize()
+    C = C.float().cpu()
+    for row in range(N):
+        if row not in at:
+            assert C[row].isfinite().all()
+            continue
+        col, sign = at[row]
+        want = sign * torch.sign(P[col]) * float("inf")
+        assert torch.equal(C[row][P[col] != 0], want[P[col] != 0]) and C[row][P[col] == 0].isnan().all()
+
+
 @pytest.mark.parametrize("N,d,stride,aligned_base", [(2049, 257, 1, False), (4111, 263, 2, False),
                                                      (4097, 260, 2, True)])  # sampled rows 8-element aligned, ldx not
 def test_gram_of_rows_that_start_on_any_element(ctx, N, d, stride, aligned_base):
