@@ -1244,7 +1244,8 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
     const uint32_t sB = (uint32_t)(kb * 4096 + frag_slot(2 * cc + 1, h) * 16);
 
     u32x4 ry[8], rz[8];
-    // rows past N re-read the last row (finite data) and meet the zero padding of packed C
+    // rows past N re-read the last row and meet the zero padding of packed C; UA: they are zeroed on their way to LDS, so
+    // that what the last row holds (an infinity) does not meet those zeros
     auto gload = [&](int kt, u32x4 (&rr)[8]) {
       const bool live = kt < nk;
       const int t0 = tok_beg + min(kt, nk - 1) * CW_BK;
@@ -1256,9 +1257,15 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
             reinterpret_cast<const std::conditional_t<UA, u32x4_el, u32x4>*>(base + (live ? (uint32_t)row * rowb : 0u)));
       }
     };
-    auto sstore = [&](int stage, u32x4 (&rr)[8]) {
+    auto sstore = [&](int stage, int kt, u32x4 (&rr)[8]) {
       unsigned char* s = smem_raw + stage * CW_STAGE;
       if constexpr (UA) {
+        const int left = a.N - tok_beg - kt * CW_BK;  // rows of this tile
+        if (left < CW_BK) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (16 * kb + c_slot_tok(h, e) >= left) rr[e] = u32x4{0u, 0u, 0u, 0u};
+        }
         if (early > 0) {
 #pragma unroll
           for (int e = 0; e < 8; ++e) rr[e] = shift_down(rr[e], early);
@@ -1282,17 +1289,17 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
     // more are complete in LDS
     gload(0, ry);
     gload(1, rz);
-    sstore(0, ry);
+    sstore(0, 0, ry);
     gload(2, ry);
     // The matrix waves start as soon as tile 0 is in LDS: at a kernel's start all workgroups ask for their
     // first tiles at once, and what holds the first multiplication back is the time HBM needs to deliver
     // them (8 MB per tile over the 256 workgroups of the headline shape).  Tile 1 is first read at k-block 7
     // of tile 0, behind the loop's first barrier, and is stored before that barrier.
     __syncthreads();  // tile 0 is in LDS
-    if (nk > 1) sstore(1, rz);
+    if (nk > 1) sstore(1, 1, rz);
     int stage = 2;
     for (int kt = 0; kt < nk; ++kt) {
-      if (kt + 2 < nk) sstore(stage, ry);
+      if (kt + 2 < nk) sstore(stage, kt + 2, ry);
       stage = stage == CW_STAGES - 1 ? 0 : stage + 1;
       gload(kt + 3, ry);
       __syncthreads();

@@ -301,6 +301,30 @@ def test_infinity_in_rows_that_start_on_any_element(ctx):
         assert torch.equal(C[row][P[col] != 0], want[P[col] != 0]) and C[row][P[col] == 0].isnan().all()
 
 
+def test_infinity_in_the_last_row_that_starts_on_any_element(ctx):
+    """The last token of dY, and of X in a Gram matrix, holds an infinity: the padding of its 128-token tile must not meet it."""
+    d = 261
+    g = torch.Generator().manual_seed(2)
+    P = torch.randn((d, 1), generator=g)
+    for N in (128, 129, 256, 300):
+        m = 137
+        dY = torch.randn((N, m), generator=g).bfloat16()
+        dY[N - 1, 3], dY[N - 1, 136] = float("inf"), -float("inf")
+        Ct = torch.rand((N, 1), generator=g).bfloat16() + 1
+        dW = ctx.weight_grad(Ct.to(DEV), rows_on_any_element(dY, m, True), P.to(DEV), 1, 0, 0.0)
+        torch.cuda.synchronize()
+        dW = dW.cpu()
+        assert torch.equal(dW[:, 3], torch.sign(P[:, 0]) * float("inf")) and torch.equal(dW[:, 136], -dW[:, 3])
+        assert torch.cat([dW[:, :3], dW[:, 4:136]], 1).isfinite().all()
+    N = 2049
+    X = torch.rand((N, d), generator=g).bfloat16() + 1
+    X[N - 1, 9] = float("inf")
+    G = ctx.gram(rows_on_any_element(X, d, True))
+    torch.cuda.synchronize()
+    G = G.cpu()
+    assert (G[9] == float("inf")).all() and (G[:, 9] == float("inf")).all() and G[10:, 10:].isfinite().all()
+
+
 @pytest.mark.parametrize("N,d,stride,aligned_base", [(2049, 257, 1, False), (4111, 263, 2, False),
                                                      (4097, 260, 2, True)])  # sampled rows 8-element aligned, ldx not
 def test_gram_of_rows_that_start_on_any_element(ctx, N, d, stride, aligned_base):
