@@ -750,9 +750,11 @@ __global__ __launch_bounds__(512) void small_wgrad_kernel(SmallWgradArgs a) {
     for (int q = 0; q < 2 * CB; ++q)
       f[q] = t < SW_RB ? (t == 0 ? fp[0][q] : fp[1][q]) : Pa[((int64_t)rb * nkb + min(q, nkb - 1)) * 64];
 #pragma unroll
-    for (int q = 0; q < 2 * CB; ++q)  // (k-blocks past the last one meet zeros of T)
+    for (int q = 0; q < 2 * CB; ++q) {
+      if (q == 2 * CB - 1 && q == nkb) break;  // (uniform) an odd number of k-blocks: what was read here is the one before
       o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(f[q]), as_frag(*reinterpret_cast<const u32x4*>(Tf + (q * 64 + lane) * 8)),
                                                   o, 0, 0, 0);
+    }
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int row = 32 * rb + 8 * (v / 4) + 4 * lh + (v % 4);

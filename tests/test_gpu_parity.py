@@ -435,6 +435,24 @@ def test_weight_grad_of_small_layers(ctx, N, d, c, ms):
         assert ((x[:, :m].double() - (ref - 0.5)).abs() <= bound).all() and (x[:, m:] == 1.0).all()
 
 
+@pytest.mark.parametrize("c", [9, 33, 48, 65, 100, 128])
+def test_weight_grad_of_small_layers_with_an_infinite_basis_element(ctx, c):
+    """An infinite element of P, in the last 16 columns, makes its row of dW infinite with the signs of T and no other."""
+    N, d, m = 200, 130, 70
+    g = torch.Generator().manual_seed(c)
+    Ct, dY = torch.rand((N, c), generator=g).bfloat16() + 1, (torch.rand((N, m), generator=g) + 1).bfloat16()
+    dY[:, 1::2] *= -1
+    P = torch.randn((d, c), generator=g)
+    P[7, c - 1], P[129, (c - 1) // 16 * 16] = float("inf"), -float("inf")
+    dW = ctx.weight_grad(dev_padded(Ct, (c + 7) // 8 * 8), dev_padded(dY, 72), P.to(DEV), c // 2, c - c // 2, 1.5)
+    torch.cuda.synchronize()
+    dW = dW.cpu()
+    sign = torch.ones(m)
+    sign[1::2] = -1.0
+    assert torch.equal(dW[7], sign * float("inf")) and torch.equal(dW[129], -sign * float("inf"))
+    assert dW[[i for i in range(d) if i not in (7, 129)]].isfinite().all()
+
+
 @pytest.mark.parametrize("d,c,ms,pad", [
     (4224, 130, (2085,), 0),          # rows on any element, the last column group 37 wide
     (4100, 129, (2304, 264), 5),      # a ragged row tile, two outputs of different pitch
