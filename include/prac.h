@@ -284,9 +284,12 @@ int prac_weight_grad(prac_ctx* ctx, const void* C, const void* dY, prac_dtype dt
  * part of the library's code object: every GPU the library runs on holds its own copy until the
  * process ends.  The call never calls hipMalloc / hipFree or an allocating routine, never touches the
  * ctx scratch, and is not profiled (prac_profile_select is ignored for it).
- *   - PRAC_ETOOBIG when prac_workspace_bytes of the same call exceeds PRAC_STATIC_SCRATCH_BYTES
- *     (dY rows that start on any element then still run, on the generic kernel, where that one's needs fit)
- *     (the headline shape N = 32768, d = m = 2048, k + r = 256 needs 34.6 MB); nothing is enqueued then.
+ *   - PRAC_ETOOBIG when prac_workspace_bytes of the same call exceeds PRAC_STATIC_SCRATCH_BYTES less 128 KiB for the
+ *     one-launch form's counters (N = 32768, d = m = 2048, k + r = 256 needs 34.6 MB); nothing is enqueued then.  Where
+ *     one plan fits and a larger one is not faster by much, prac_weight_grad runs the one that fits, too.
+ *   - dY rows that start on any element: a row-major C is packed in parts where the whole copy does not fit (same bits).
+ *     Where the partial sums and one part do not fit either, the strided kernel runs if what it needs does
+ *     (one fp32 T, and an unpacked copy of a packed C): the same result but for the order of the fp32 sums.
  *   - All calls on one GPU share that GPU's block, which keeps the last call's contents: the
  *     kernels overwrite what they read, so nothing needs clearing between calls, but two calls that
  *     overlap in time on one GPU (two streams, two threads, two contexts) race.  Stream order on one

@@ -709,20 +709,19 @@ int weight_grad_generic(prac_ctx* ctx, char* ws, float* part32, const void* C, c
   return launch_f32_sum_pt(ctx, P, ldp, T, splits, c, k, scale, (int)d, (int)m, dW, lddw, odt == PRAC_BF16, beta);
 }
 
-// bf16 gradients whose rows start on any element: the token-split partial sums of C^T dY come from the streaming kernel
-// (bf16 products are exact in fp32, so this is the strided kernel's sum in another order), the rest stays in fp32 as
-// for all data that runs the strided kernels.
-struct WgradAnyPlan {
-  int splits;
-  size_t o_part[PRAC_CTDY_MAX_OUT], o_cpk, bytes;
-};
-// Token ranges of C^T dY.  As many as one round of workgroups holds (one per compute unit), or with `rounds` more of them in
+// What prac_weight_grad_static has for scratch.  It and prac_weight_grad run the same plan, so a single gradient takes more token
+// ranges than one round of workgroups, or the wide form of its last product, only where that fits.
+constexpr size_t WGRAD_ROOM = PRAC_STATIC_SCRATCH_BYTES - PRAC_SYNC_BYTES;
+
+// Token ranges of C^T dY.  As many as one round of workgroups holds (one per compute unit), or more of them (that `fits` accepts) in
 // several rounds where the cost rule favours that: a round costs its start (6 us) and 15.6 ns per token of a range (a k-block of 16 takes
 // 0.25 us), a range a write and a read of its partial sums (3 TB/s).  Where the column tiles do not divide the compute
 // units, several short rounds fill them better than one long one.  Measured, one round against the rule's choice, per
 // weight gradient: 86 tiles, N = 32768, c = 256 (up and gate) 2 ranges 294 us, 5 ranges 282; 172 tiles, N = 16384, c = 512 one
-// range 307, 4 ranges 295; the rule keeps 16, 5, 4 and 6 ranges for 16, 48, 64 and 40 tiles (next best 3 to 30 us worse).
-int wgrad_splits(int n_cu, int tune_splits, int c, int n_out, const int64_t* m, int64_t N, bool rounds) {
+// range 307, 4 ranges 295 (90 MB of partial sums, past what a single gradient may use); the rule keeps 16, 5, 4 and 6 ranges for
+// 16, 48, 64 and 40 tiles (next best 3 to 30 us worse).
+template <typename Fits>
+int wgrad_splits(int n_cu, int tune_splits, int c, int n_out, const int64_t* m, int64_t N, Fits fits) {
   if (tune_splits > 0) return tune_splits;
   int64_t tiles = 0, slab = 0;
   for (int h = 0; h < n_out; ++h) {
@@ -734,20 +733,39 @@ int wgrad_splits(int n_cu, int tune_splits, int c, int n_out, const int64_t* m, 
   auto cost = [&](int s) {
     return (double)((tiles * s + n_cu - 1) / n_cu) * (6.0 + 0.0156 * (double)((N + s - 1) / s)) + (double)(2 * slab) * s / 3e6;
   };
-  if (rounds)
-    for (int s = best + 1; s <= most; ++s)
-      if (cost(s) < cost(best)) best = s;
+  for (int s = best + 1; s <= most; ++s)
+    if (cost(s) < cost(best) && fits(s)) best = s;
   return best;
 }
-WgradAnyPlan plan_wgrad_any(int n_cu, int tune_splits, int64_t N, int c, int n_out, const int64_t* m, bool packed,
-                            bool rounds = true) {
+
+// bf16 gradients whose rows start on any element: the token-split partial sums of C^T dY come from the streaming kernel
+// (bf16 products are exact in fp32, so this is the strided kernel's sum in another order), the rest stays in fp32 as
+// for all data that runs the strided kernels.
+struct WgradAnyPlan {
+  int splits, group;  // token ranges; ranges whose rows of a row-major C are packed at a time
+  size_t o_part[PRAC_CTDY_MAX_OUT], o_cpk, bytes;
+};
+WgradAnyPlan layout_wgrad_any(int64_t N, int c, int n_out, const int64_t* m, int splits, int group, bool packed) {
   WgradAnyPlan q{};
-  q.splits = wgrad_splits(n_cu, tune_splits, c, n_out, m, N, rounds);
+  q.splits = splits;
+  q.group = group;
   WsPlan plan;
-  for (int h = 0; h < n_out; ++h) q.o_part[h] = plan.take((size_t)q.splits * c * m[h] * sizeof(float));
-  q.o_cpk = plan.take(packed ? 0 : packed_c_bytes(N, c));
+  for (int h = 0; h < n_out; ++h) q.o_part[h] = plan.take((size_t)splits * c * m[h] * sizeof(float));
+  q.o_cpk = plan.take(packed ? 0 : packed_c_bytes(std::min(N, group * ctdy_range_tokens(N, splits)), c));
   q.bytes = plan.off;
   return q;
+}
+// Within `room` bytes where it can be: the ranges, and with them the bits of dW, do not depend on it.
+WgradAnyPlan plan_wgrad_any(int n_cu, int tune_splits, int64_t N, int c, int n_out, const int64_t* m, bool packed,
+                            size_t room = ~(size_t)0) {
+  int splits = wgrad_splits(n_cu, tune_splits, c, n_out, m, N, [&](int s) {
+    return n_out > 1 || layout_wgrad_any(N, c, n_out, m, s, 1, false).bytes <= WGRAD_ROOM;
+  });
+  const int64_t tok = ctdy_range_tokens(N, splits);
+  splits = (int)((N + tok - 1) / tok);  // no empty ranges
+  int group = splits;
+  while (group > 1 && layout_wgrad_any(N, c, n_out, m, splits, group, packed).bytes > room) --group;
+  return layout_wgrad_any(N, c, n_out, m, splits, group, packed);
 }
 
 int weight_grad_any(prac_ctx* ctx, char* ws, const WgradAnyPlan& q, const void* C, int64_t N, int64_t ldc, bool packed,
@@ -755,26 +773,33 @@ int weight_grad_any(prac_ctx* ctx, char* ws, const WgradAnyPlan& q, const void* 
                     int64_t ldp, int k, int r, float scale, void* const* dW, prac_dtype odt, const int64_t* lddw,
                     float beta) {
   const int c = k + r;
+  const int64_t tok = ctdy_range_tokens(N, q.splits);
   int rc;
-  const bf16_t* Cpk = reinterpret_cast<const bf16_t*>(C);
-  if (!packed) {
-    rc = launch_pack_c(ctx, Cpk, ldc, (int)N, c, reinterpret_cast<bf16_t*>(ws + q.o_cpk));
-    if (rc) return rc;
-    Cpk = reinterpret_cast<const bf16_t*>(ws + q.o_cpk);
-  }
-  const bf16_t* dYp[PRAC_CTDY_MAX_OUT];
   float* part[PRAC_CTDY_MAX_OUT];
   int mi[PRAC_CTDY_MAX_OUT];
   for (int h = 0; h < n_out; ++h) {
-    dYp[h] = reinterpret_cast<const bf16_t*>(dY[h]);
     part[h] = reinterpret_cast<float*>(ws + q.o_part[h]);
     mi[h] = (int)m[h];
   }
-  {
+  for (int s0 = 0; s0 < q.splits; s0 += q.group) {  // (once, unless the packed copy of C has to fit the static block)
+    const int ranges = std::min(q.group, q.splits - s0);
+    const int64_t t0 = s0 * tok, n = std::min(N - t0, ranges * tok);
+    const bf16_t* Cpk = reinterpret_cast<const bf16_t*>(C);
+    if (!packed) {
+      rc = launch_pack_c(ctx, Cpk + t0 * ldc, ldc, (int)n, c, reinterpret_cast<bf16_t*>(ws + q.o_cpk));
+      if (rc) return rc;
+      Cpk = reinterpret_cast<const bf16_t*>(ws + q.o_cpk);
+    }
+    const bf16_t* dYp[PRAC_CTDY_MAX_OUT];
+    float* slabs[PRAC_CTDY_MAX_OUT];
+    for (int h = 0; h < n_out; ++h) {
+      dYp[h] = reinterpret_cast<const bf16_t*>(dY[h]) + t0 * lddy[h];
+      slabs[h] = part[h] + (size_t)s0 * c * m[h];
+    }
     ProfScope ps(ctx, PRAC_KERNEL_CT_DY);
-    rc = launch_ctdy_ws(ctx, Cpk, c, (int)N, n_out, dYp, lddy, mi, part, q.splits, true);
+    rc = launch_ctdy_ws(ctx, Cpk, c, (int)n, n_out, dYp, lddy, mi, slabs, ranges, true, (int)tok);
+    if (rc) return rc;
   }
-  if (rc) return rc;
   for (int h = 0; h < n_out; ++h) {
     rc = launch_f32_sum_pt(ctx, P, ldp, part[h], q.splits, c, k, scale, (int)d, mi[h], dW[h], lddw[h], odt == PRAC_BF16,
                            beta);
@@ -804,25 +829,39 @@ bool wgrad_wide(int n_cu, int64_t d, int c, int n_out, const int64_t* m, prac_dt
   for (int h = 0; h < n_out; ++h) groups += (m[h] + 255) / 256;
   return (d + 127) / 128 * groups > n_cu;
 }
-WgradPlan plan_wgrad_fast(int n_cu, int tune_splits, bool unfused, int64_t N, int64_t d, int c, int n_out,
-                          const int64_t* m, bool packed, bool has_lp, bool wide, bool rounds = true) {
+WgradPlan layout_wgrad_fast(int64_t N, int64_t d, int c, int n_out, const int64_t* m, int splits, bool packed, bool has_lp,
+                            bool wide) {
   WgradPlan q{};
   const LpLayout l = lp_layout(d, c);
-  int splits = unfused ? 0 : wgrad_fused_splits(n_cu, c, n_out, m, N, tune_splits);
-  q.fused = splits > 0;
-  if (!q.fused) splits = wgrad_splits(n_cu, tune_splits, c, n_out, m, N, rounds);
   q.splits = splits;
-  q.wide = wide && !q.fused;
-  q.nkb = q.wide ? wide_kblocks(c) : l.nckb;
+  q.wide = wide;
+  q.nkb = wide ? wide_kblocks(c) : l.nckb;
   WsPlan plan;
   for (int h = 0; h < n_out; ++h) {
-    q.nmb[h] = (int)round_up64((m[h] + 31) / 32, q.wide ? 8 : 4);  // 32-column blocks of T, whole 256- or 128-column tiles
+    q.nmb[h] = (int)round_up64((m[h] + 31) / 32, wide ? 8 : 4);  // 32-column blocks of T, whole 256- or 128-column tiles
     q.o_part[h] = plan.take((size_t)splits * c * m[h] * sizeof(float));
     q.o_t[h] = plan.take((size_t)q.nkb * q.nmb[h] * 64 * 8 * sizeof(bf16_t));
   }
   q.o_lp = plan.take(has_lp ? 0 : l.bytes);
   q.o_cpk = plan.take(packed ? 0 : packed_c_bytes(N, c));
   q.bytes = plan.off;
+  return q;
+}
+// (whether C is packed and P_lp at hand does not change the ranges, and with them the bits of dW)
+WgradPlan plan_wgrad_fast(int n_cu, int tune_splits, bool one_launch, int64_t N, int64_t d, int c, int n_out, const int64_t* m,
+                          prac_dtype odt, float beta, bool packed, bool has_lp) {
+  int splits = one_launch ? wgrad_fused_splits(n_cu, c, n_out, m, N, tune_splits) : 0;
+  const bool fused = splits > 0;
+  if (!fused)
+    splits = wgrad_splits(n_cu, tune_splits, c, n_out, m, N, [&](int s) {
+      return n_out > 1 || layout_wgrad_fast(N, d, c, n_out, m, s, false, false, wide_kblocks(c) == 16).bytes <= WGRAD_ROOM;
+    });
+  WgradPlan q = layout_wgrad_fast(N, d, c, n_out, m, splits, packed, has_lp, false);
+  q.fused = fused;
+  if (!fused && wgrad_wide(n_cu, d, c, n_out, m, odt, beta)) {
+    const WgradPlan w = layout_wgrad_fast(N, d, c, n_out, m, splits, packed, has_lp, true);
+    if (n_out > 1 || w.bytes <= WGRAD_ROOM || q.bytes > WGRAD_ROOM) return w;
+  }
   return q;
 }
 
@@ -962,21 +1001,14 @@ int prac_weight_grad_static(prac_ctx* ctx, const void* C, const void* dY, prac_d
   bool any = !fast && wgrad_is_any(dt, 1, &m, &lddy);
   size_t need, o_part32 = 0;
   if (any) {
-    for (bool rounds : {true, false}) {  // more token ranges need more scratch
-      qa = plan_wgrad_any(ctx->n_cu, ctx->tune_splits, N, k + r, 1, &m, packed, rounds);
-      if (qa.bytes <= PRAC_STATIC_SCRATCH_BYTES - PRAC_SYNC_BYTES) break;
-    }
-    any = qa.bytes <= PRAC_STATIC_SCRATCH_BYTES - PRAC_SYNC_BYTES;  // else the strided kernels, which need less scratch
+    qa = plan_wgrad_any(ctx->n_cu, ctx->tune_splits, N, k + r, 1, &m, packed, WGRAD_ROOM);
+    any = qa.bytes <= WGRAD_ROOM;  // else the strided kernels, which need less scratch
   }
   if (any) {
     need = qa.bytes;
   } else if (fast) {
-    const bool wide = wgrad_wide(ctx->n_cu, d, k + r, 1, &m, odt, beta);
-    for (int t = 0; t < 3; ++t) {  // more token ranges need more scratch, and the wide form's T is padded a little further
-      q = plan_wgrad_fast(ctx->n_cu, ctx->tune_splits, ctx->tune_one_launch == 0, N, d, k + r, 1, &m, packed, P_lp != nullptr,
-                          wide && t < 2, t < 1);
-      if (q.bytes <= PRAC_STATIC_SCRATCH_BYTES - PRAC_SYNC_BYTES) break;
-    }
+    q = plan_wgrad_fast(ctx->n_cu, ctx->tune_splits, ctx->tune_one_launch != 0, N, d, k + r, 1, &m, odt, beta, packed,
+                        P_lp != nullptr);
     need = q.bytes;
   } else {
     need = o_part32 = plan_wgrad_generic(N, m, k + r, packed).bytes;
@@ -985,7 +1017,7 @@ int prac_weight_grad_static(prac_ctx* ctx, const void* C, const void* dY, prac_d
   // the first 128 KB of the block are the counters of the one-launch weight gradient (zero when the code
   // object is loaded, and every launch leaves them zero)
   constexpr size_t kSync = PRAC_SYNC_BYTES;
-  if (need > PRAC_STATIC_SCRATCH_BYTES - kSync) return PRAC_ETOOBIG;
+  if (need > WGRAD_ROOM) return PRAC_ETOOBIG;
   // no event pairs here (creating one allocates): this call is not profiled
   const int prof = ctx->prof_kind;
   ctx->prof_kind = PRAC_KERNEL_NONE;
@@ -1012,8 +1044,8 @@ int prac_weight_grad_shared(prac_ctx* ctx, const void* C, prac_dtype dt, int64_t
   const bool packed = c_layout == PRAC_C_PACKED;
   if (packed && (dt != PRAC_BF16 || !aligned16(C))) return PRAC_EUNSUPPORTED;
   if (wgrad_is_fast(dt, N, n_out, dY, lddy)) {
-    const WgradPlan q = plan_wgrad_fast(ctx->n_cu, ctx->tune_splits, ctx->tune_one_launch == 0, N, d, k + r, n_out, m, packed,
-                                        P_lp != nullptr, wgrad_wide(ctx->n_cu, d, k + r, n_out, m, odt, beta));
+    const WgradPlan q = plan_wgrad_fast(ctx->n_cu, ctx->tune_splits, ctx->tune_one_launch != 0, N, d, k + r, n_out, m, odt, beta,
+                                        packed, P_lp != nullptr);
     rc = prac_ws_reserve(ctx, q.bytes);
     if (rc) return rc;
     return weight_grad_fast(ctx, ctx->ws, ctx->d_sync, q, C, N, ldc, packed, n_out, dY, m, lddy, P, P_lp, d, ldp, k, r, scale, dW, odt,
@@ -1186,9 +1218,9 @@ size_t prac_workspace_bytes(const prac_ctx* ctx, const prac_call_shape* sh) {
         if (sh->m[h] < 1 || sh->m[h] > (1 << 20)) return bad;
       if (fast) {  // beta is not part of the shape: enough for either form of the last product
         size_t need = 0;
-        for (bool wide : {false, wgrad_wide(n_cu, sh->d, c, sh->n_out, sh->m, (prac_dtype)sh->odt, 0.f)})
-          need = std::max(need, plan_wgrad_fast(n_cu, tune, !(ctx && ctx->tune_one_launch), sh->N, sh->d, c, sh->n_out, sh->m,
-                                                packed, sh->have_p_lp != 0, wide).bytes);
+        for (float beta : {0.f, 1.f})
+          need = std::max(need, plan_wgrad_fast(n_cu, tune, ctx && ctx->tune_one_launch, sh->N, sh->d, c, sh->n_out, sh->m,
+                                                (prac_dtype)sh->odt, beta, packed, sh->have_p_lp != 0).bytes);
         return need;
       }
       size_t need = 0;

@@ -170,7 +170,11 @@ int launch_pack_wfrag(prac_ctx* ctx, const bf16_t* W, int64_t ldw, int w_layout,
 // aligned and own whole 16-byte chunks (the caller says which: where the rows are a sample of a matrix, their pitch does not)
 #define PRAC_CTDY_MAX_OUT 4
 int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, const bf16_t* const* dY,
-                   const int64_t* lddy, const int* m, float* const* slabs, int splits, bool any_element);
+                   const int64_t* lddy, const int* m, float* const* slabs, int splits, bool any_element,
+                   int range_tokens = 0);
+// tokens of a range (whole 128-token tiles; the last ranges may be short or empty); launch_ctdy_ws takes another value for a
+// part of the ranges of a longer product
+inline int64_t ctdy_range_tokens(int64_t N, int splits) { return ((N + 127) / 128 + splits - 1) / splits * 128; }
 // The whole weight gradient in one launch: partial slabs, their sum as T (bf16, fragment order, rows >= k_lo
 // scaled) and dW_h = P T_h, the workgroups of a column tile meeting through `cnt` (PRAC_SYNC_INTS_PER_TILE
 // ints per 128-column tile over all outputs, zero before and after the launch).  `splits` comes from

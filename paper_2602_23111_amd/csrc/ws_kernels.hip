@@ -1519,15 +1519,15 @@ void fill_ctdy_args(CtdyWsArgs& a, const bf16_t* Cpk, int c, int N, int n_out, c
     tiles += (m[h] + CW_BN - 1) / CW_BN;
   }
   for (int h = n_out; h <= PRAC_CTDY_MAX_OUT; ++h) a.tile0[h] = tiles;
-  const int ktiles = (N + CW_BK - 1) / CW_BK;
-  a.tok_per_split = ((ktiles + splits - 1) / splits) * CW_BK;
+  static_assert(CW_BK == 128, "ctdy_range_tokens");
+  a.tok_per_split = (int)ctdy_range_tokens(N, splits);
   a.tiles_n = tiles;
   a.row_groups = (a.ccb + 7) / 8;
 }
 }  // namespace
 
 int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, const bf16_t* const* dY,
-                   const int64_t* lddy, const int* m, float* const* slabs, int splits, bool any_element) {
+                   const int64_t* lddy, const int* m, float* const* slabs, int splits, bool any_element, int range_tokens) {
   if (n_out < 1 || n_out > PRAC_CTDY_MAX_OUT) return PRAC_EINVAL;
   for (int h = 0; h < n_out; ++h) {
     if (lddy[h] > PRAC_MAX_STREAM_PITCH) return PRAC_EINVAL;
@@ -1536,6 +1536,7 @@ int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, co
   }
   CtdyWsArgs a{};
   fill_ctdy_args(a, Cpk, c, N, n_out, dY, lddy, m, slabs, splits);
+  if (range_tokens > 0) a.tok_per_split = range_tokens;
   const size_t smem = (size_t)CW_STAGES * CW_STAGE;
   const int total = a.tiles_n * a.row_groups * splits;
   static bool f1[PRAC_MAX_DEVICES] = {}, f2[PRAC_MAX_DEVICES] = {};

@@ -229,6 +229,10 @@ def test_workspace_bytes_matches_the_documented_scratch_of_each_call(lib):
     # row-major C has to be packed first
     extra = int(lib.prac_compressed_bytes(N, c, 1, 1, 0))
     assert ws(prac.call_shape("weight_grad", N, d, k, r, m=[m], c_layout=0)) == 16 * c * m * 4 + c * m * 2 + extra
+    # one output, more ranges than one round of workgroups only while prac_weight_grad_static could run them: 2 of them here, where
+    # 5 in two rounds would be a little faster (as for two outputs, which that entry point does not take)
+    assert ws(prac.call_shape("weight_grad", N, d, k, r, m=[11008])) == 2 * c * 11008 * 4 + c * 11008 * 2
+    assert ws(prac.call_shape("weight_grad", N, d, k, r, m=[5504, 5504])) == 5 * c * 11008 * 4 + c * 5632 * 2 * 2
     # strided kernels (fp32 data): T, and nothing else for an fp32 dW
     assert ws(prac.call_shape("weight_grad", 2048, 512, 32, 32, m=[1376], dt=0, odt=0, c_layout=0)) == up(64 * 1376 * 4)
     # reconstruction: Ps^T in fragment order (k-blocks over 256, column blocks over d)

@@ -53,6 +53,60 @@ def test_static_weight_grad_two_calls_second_smaller(one_launch):   # live in th
         ctx.close()
 
 
+def _random_case(ctx, N, d, m, c, packed, lp, odt, ld_y, beta=0.0):
+    """dW by the ordinary and by the static entry point, data drawn on the device."""
+    from paper_2602_23111_amd.prac import C_PACKED, C_ROWMAJOR
+    g = torch.Generator(device=DEV).manual_seed(N + m)
+    P = torch.randn((d, c), generator=g, device=DEV) * d ** -0.5
+    Cm = torch.randn((N, c), generator=g, device=DEV).bfloat16()
+    if packed:  # any packed buffer is some C (this one has no padding)
+        assert N % 128 == 0 and c % 32 == 0
+        Cm = Cm.reshape(-1)
+    dY = torch.zeros((N, ld_y), dtype=torch.bfloat16, device=DEV)[:, :m]
+    dY.copy_(torch.randn((N, m), generator=g, device=DEV))
+    outs = [torch.full((d, m), 0.25, dtype=odt, device=DEV) for _ in range(2)]
+    for out, static in zip(outs, (False, True)):
+        ctx.weight_grad(Cm, dY, P, c // 2, c - c // 2, 2.0, P_lp=ctx.pack_basis(P) if lp else None, out=out, beta=beta,
+                        layout=C_PACKED if packed else C_ROWMAJOR, static=static)
+    ctx.sync_status()
+    return outs
+
+
+@pytest.mark.parametrize("N,d,m,c,packed,lp,odt,ld_y,beta", [
+    # more token ranges than one round of workgroups would be faster here, and need more than the block
+    (32768, 264, 11008, 256, True, True, torch.bfloat16, 11008, 0.0),
+    (32768, 264, 11008, 256, True, True, torch.float32, 11008, 0.5),
+    (16384, 512, 11008, 512, True, True, torch.bfloat16, 11008, 0.0),
+    # the wide form of the last product: within the block, and 0.1 MiB past it (its T is padded further)
+    (8192, 4224, 2048, 256, True, True, torch.bfloat16, 2048, 0.0),
+    (8192, 20488, 2300, 130, False, False, torch.bfloat16, 2304, 0.0),
+    # rows on any element: packed C, a row-major C that fits, one that has to be packed in parts (its last range is short)
+    (32768, 264, 5461, 256, True, True, torch.bfloat16, 5461, 0.0),
+    (8200, 264, 1029, 100, False, True, torch.float32, 1029, 0.0),
+    (32768, 600, 2049, 512, False, True, torch.bfloat16, 2049, 0.0),
+    (30001, 600, 1111, 600, False, True, torch.float32, 1111, 0.5),
+])
+def test_static_weight_grad_runs_the_plan_of_the_ordinary_one(N, d, m, c, packed, lp, odt, ld_y, beta):
+    from paper_2602_23111_amd.prac import Prac
+    ctx = Prac(0)
+    try:
+        want, got = _random_case(ctx, N, d, m, c, packed, lp, odt, ld_y, beta)
+        assert torch.equal(got, want) and bool(got.isfinite().all())
+    finally:
+        ctx.close()
+
+
+def test_static_weight_grad_on_the_strided_kernel():
+    """Rows on any element whose partial sums exceed the block: fp32 sums of the same products in another order."""
+    from paper_2602_23111_amd.prac import Prac
+    ctx = Prac(0)
+    try:
+        want, got = _random_case(ctx, 32768, 1100, 4097, 1024, False, True, torch.float32, 4097)
+        assert float((got - want).norm() / want.norm()) < 1e-5
+    finally:
+        ctx.close()
+
+
 def test_static_weight_grad_rejects_what_does_not_fit():
     from paper_2602_23111_amd.prac import C_ROWMAJOR, STATIC_SCRATCH_BYTES, Prac, PracError, call_shape
     ctx = Prac(0)
