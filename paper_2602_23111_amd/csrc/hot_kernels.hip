@@ -672,14 +672,12 @@ __global__ __launch_bounds__(512) void small_wgrad_kernel(SmallWgradArgs a) {
   for (int i = 0; i < CB; ++i)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
-  // (up to 128 tokens, one tile of the streaming kernels, wave 0 takes all blocks: the sum those kernels form, in their order)
-  const int step = ntok <= 8 ? 1 : 8;
-  for (int t0 = ntok <= 8 ? (wave == 0 ? 0 : ntok) : wave; t0 < ntok; t0 += step * NB) {
+  for (int t0 = wave; t0 < ntok; t0 += 8 * NB) {
     u32x4 ry[NB], rc[NB][CB];
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
       // blocks past the last one re-read it and are not multiplied; tokens past N are zeroed
-      const int tb = min(t0 + step * q, ntok - 1), tok = min(16 * tb + (lane >> 2), N - 1);
+      const int tb = min(t0 + 8 * q, ntok - 1), tok = min(16 * tb + (lane >> 2), N - 1);
       ry[q] = *reinterpret_cast<const u32x4*>(yrow + (int64_t)tok * lddy);
 #pragma unroll
       for (int i = 0; i < CB; ++i)
@@ -689,8 +687,8 @@ __global__ __launch_bounds__(512) void small_wgrad_kernel(SmallWgradArgs a) {
     }
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
-      if (t0 + step * q >= ntok) break;  // uniform
-      const bool in = 16 * (t0 + step * q) + (lane >> 2) < N;
+      if (t0 + 8 * q >= ntok) break;  // uniform
+      const bool in = 16 * (t0 + 8 * q) + (lane >> 2) < N;
       const u32x4 zero = {0u, 0u, 0u, 0u};
       // the wave's own patch: LDS operations of a wave take effect in order, only the compiler must keep theirs
       __builtin_amdgcn_wave_barrier();

@@ -850,15 +850,12 @@ WgradPlan layout_wgrad_fast(int64_t N, int64_t d, int c, int n_out, const int64_
 // (whether C is packed and P_lp at hand does not change the ranges, and with them the bits of dW)
 WgradPlan plan_wgrad_fast(int n_cu, int tune_splits, bool one_launch, int64_t N, int64_t d, int c, int n_out, const int64_t* m,
                           prac_dtype odt, float beta, bool packed, bool has_lp) {
-  int splits = one_launch ? wgrad_fused_splits(n_cu, c, n_out, m, N, tune_splits) : 0;
-  const bool fused = splits > 0;
-  if (!fused)
-    splits = wgrad_splits(n_cu, tune_splits, c, n_out, m, N, [&](int s) {
-      return n_out > 1 || layout_wgrad_fast(N, d, c, n_out, m, s, false, false, wide_kblocks(c) == 16).bytes <= WGRAD_ROOM;
-    });
+  const int splits = wgrad_splits(n_cu, tune_splits, c, n_out, m, N, [&](int s) {
+    return n_out > 1 || layout_wgrad_fast(N, d, c, n_out, m, s, false, false, wide_kblocks(c) == 16).bytes <= WGRAD_ROOM;
+  });
   WgradPlan q = layout_wgrad_fast(N, d, c, n_out, m, splits, packed, has_lp, false);
-  q.fused = fused;
-  if (!fused && wgrad_wide(n_cu, d, c, n_out, m, odt, beta)) {
+  q.fused = one_launch && wgrad_fused_takes(n_cu, c, n_out, m, splits);
+  if (!q.fused && wgrad_wide(n_cu, d, c, n_out, m, odt, beta)) {
     const WgradPlan w = layout_wgrad_fast(N, d, c, n_out, m, splits, packed, has_lp, true);
     if (n_out > 1 || w.bytes <= WGRAD_ROOM || q.bytes > WGRAD_ROOM) return w;
   }
@@ -879,8 +876,8 @@ int weight_grad_fast(prac_ctx* ctx, char* ws, int* cnt, const WgradPlan& q, cons
     if (rc) return rc;
     lp = ws + q.o_lp;
   }
-  if (small_wgrad_takes(ctx->n_cu, N, d, c, n_out, m) && (packed || (aligned16(C) && ldc % 8 == 0)) && ctx->tune_splits == 0 &&
-      ctx->tune_one_launch == 0 && ctx->tune_tail == 0) {
+  if (small_wgrad_takes(ctx->n_cu, N, d, c, n_out, m) && (packed || (aligned16(C) && ldc % 8 == 0)) && ctx->tune_splits == 0) {
+    // (whatever the other tuning keys say: this form sums in another order than the kernels that they choose among)
     const bf16_t* y[PRAC_CTDY_MAX_OUT];
     int cols[PRAC_CTDY_MAX_OUT];
     for (int h = 0; h < n_out; ++h) {

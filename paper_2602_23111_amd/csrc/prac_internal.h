@@ -177,12 +177,12 @@ int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, co
 inline int64_t ctdy_range_tokens(int64_t N, int splits) { return ((N + 127) / 128 + splits - 1) / splits * 128; }
 // The whole weight gradient in one launch: partial slabs, their sum as T (bf16, fragment order, rows >= k_lo
 // scaled) and dW_h = P T_h, the workgroups of a column tile meeting through `cnt` (PRAC_SYNC_INTS_PER_TILE
-// ints per 128-column tile over all outputs, zero before and after the launch).  `splits` comes from
-// wgrad_fused_splits (0: this shape runs as three launches).
+// ints per 128-column tile over all outputs, zero before and after the launch).  For shapes that
+// wgrad_fused_takes says can.
 #define PRAC_SYNC_TILES 4096
 #define PRAC_SYNC_INTS_PER_TILE 8
 #define PRAC_SYNC_BYTES ((size_t)PRAC_SYNC_TILES * PRAC_SYNC_INTS_PER_TILE * sizeof(int))
-int wgrad_fused_splits(int n_cu, int c, int n_out, const int64_t* m, int64_t N, int tune_splits);
+bool wgrad_fused_takes(int n_cu, int c, int n_out, const int64_t* m, int splits);
 int launch_wgrad_fused(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, const bf16_t* const* dY,
                        const int64_t* lddy, const int* m, float* const* slabs, int splits, int k_lo, float scale_hi,
                        int nckb, const int* nmb, bf16_t* const* Tf, const bf16_t* Pa, int d, void* const* dW,

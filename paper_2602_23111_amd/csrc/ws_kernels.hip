@@ -1554,25 +1554,16 @@ int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, co
   return PRAC_OK;
 }
 
-// Token ranges per column tile for the one-launch weight gradient, or 0 where it cannot run: the
-// workgroups of a column tile (token ranges x row groups) wait for each other, so all of them must be
-// resident - at most one workgroup per compute unit, with the tiles dealt to the 8 XCDs in equal numbers.
-int wgrad_fused_splits(int n_cu, int c, int n_out, const int64_t* m, int64_t N, int tune_splits) {
+// Whether the weight gradient can run as one launch with that many token ranges: the workgroups of a column tile (token
+// ranges x row groups) wait for each other, so all of them must be resident - at most one workgroup per
+// compute unit, with the tiles dealt to the 8 XCDs in equal numbers.
+bool wgrad_fused_takes(int n_cu, int c, int n_out, const int64_t* m, int splits) {
   int64_t tiles = 0;
   for (int h = 0; h < n_out; ++h) tiles += (m[h] + CW_BN - 1) / CW_BN;
-  if (tiles > PRAC_SYNC_TILES) return 0;
+  if (tiles > PRAC_SYNC_TILES) return false;
   const int row_groups = ((c + 31) / 32 + 7) / 8;
-  const int64_t gpx = (tiles + 7) / 8;           // column tiles per XCD
-  const int cu_per_xcd = n_cu / 8;
-  if (gpx * row_groups > cu_per_xcd) return row_groups == 1 ? 1 : 0;  // single-member groups never wait
-  int splits = (int)(cu_per_xcd / (gpx * row_groups));
-  if (tune_splits > 0) {
-    if (tune_splits > splits) return 0;          // the override does not fit: three launches
-    splits = tune_splits;
-  }
-  if (splits > N / 256) splits = (int)(N / 256);
-  if (splits > 64) splits = 64;
-  return splits < 1 ? 1 : splits;
+  // (a column tile that is one workgroup never waits)
+  return splits * row_groups == 1 || (tiles + 7) / 8 * row_groups * splits <= n_cu / 8;
 }
 
 int launch_wgrad_fused(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, const bf16_t* const* dY,

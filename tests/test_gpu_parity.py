@@ -656,12 +656,14 @@ def test_weight_grad_matches_oracle(ctx, dt, N, d, m, k, r, odt):
     (5000, 1100, [96], 10, 23, "f32", 0.0),         # more row tiles of dW than workgroups in a column tile
     (2048, 256, [200, 72, 136], 24, 40, "bf16", 0.0),   # three outputs sharing C
     (100, 64, [40], 4, 4, "f32", 0.0),              # fewer tokens than one tile
+    (17000, 72, [768], 24, 40, "f32", 0.0),         # more ranges by default than the one launch could hold
 ])
 def test_weight_grad_one_launch_equals_three_launches(ctx, N, d, ms, k, r, odt, beta):
     """The one-launch weight gradient (workgroups of a column tile meet to sum their partial slabs and
     to form dW = P T) against the three-launch sequence it replaces: same sums in the same order, so
-    the results are equal bit for bit; the oracle comparison is test_weight_grad_matches_oracle's."""
-    from paper_2602_23111_amd.prac import C_PACKED, TUNE_WGRAD_ONE_LAUNCH
+    the results are equal bit for bit; the oracle comparison is test_weight_grad_matches_oracle's.  With the token ranges
+    set, so that the layers small enough for a kernel of their own run the two forms, and with the built-in choice."""
+    from paper_2602_23111_amd.prac import C_PACKED, TUNE_CTDY_SPLITS, TUNE_WGRAD_ONE_LAUNCH
     c = k + r
     s = orc.scaling_factor(d, k, r)
     X64, _ = si.activation(N, d, 0.8, seed=N + d)
@@ -684,18 +686,20 @@ def test_weight_grad_one_launch_equals_three_launches(ctx, N, d, ms, k, r, odt, 
         ctx.sync_status()
         return outs
 
-    ctx.set_tuning(TUNE_WGRAD_ONE_LAUNCH, 0)
-    want = [run(dYs) for dYs in sets]
-    ctx.set_tuning(TUNE_WGRAD_ONE_LAUNCH, 1)
-    try:
-        for v in (0, 1, 0, 1, 1, 0):
-            for a, b in zip(run(sets[v]), want[v]):
-                assert torch.equal(a, b)
-    finally:
-        ctx.set_tuning(TUNE_WGRAD_ONE_LAUNCH, 0)
-    for dYh, out, b in zip(sets[0], want[0], base):
-        ref = orc.weight_grad(si.as_f64(Ct), si.as_f64(dYh), P64, k, s) + beta * si.as_f64(b)
-        assert rel_fro(si.as_f64(out), ref) < 1e-2
+    for splits in (max(1, min(8, N // 256)), 0):
+        ctx.set_tuning(TUNE_CTDY_SPLITS, splits)
+        want = [run(dYs) for dYs in sets]
+        ctx.set_tuning(TUNE_WGRAD_ONE_LAUNCH, 1)
+        try:
+            for v in (0, 1, 0, 1, 1, 0):
+                for a, b in zip(run(sets[v]), want[v]):
+                    assert torch.equal(a, b)
+        finally:
+            ctx.set_tuning(TUNE_WGRAD_ONE_LAUNCH, 0)
+            ctx.set_tuning(TUNE_CTDY_SPLITS, 0)
+        for dYh, out, b in zip(sets[0], want[0], base):
+            ref = orc.weight_grad(si.as_f64(Ct), si.as_f64(dYh), P64, k, s) + beta * si.as_f64(b)
+            assert rel_fro(si.as_f64(out), ref) < 1e-2
 
 
 @pytest.mark.parametrize("N,d,ms,k,r,odt,beta,splits", [
@@ -750,6 +754,31 @@ def test_weight_grad_tail_one_launch_equals_two(ctx, N, d, ms, k, r, odt, beta, 
     for dYh, out, b in zip(dYs, two, base):
         ref = orc.weight_grad(si.as_f64(Ct), si.as_f64(dYh), P64, k, s) + beta * si.as_f64(b)
         assert rel_fro(si.as_f64(out), ref) < 1e-2
+
+
+@pytest.mark.parametrize("N,d,ms,c", [
+    (100, 64, [40], 8), (1300, 100, [40, 264, 7], 33),  # small layers, of fewer tokens than one tile and of more
+    (17000, 72, [768], 64),                             # more token ranges than the one launch could hold
+    (24576, 264, [5504, 5504], 256),                    # token ranges in several rounds of workgroups
+])
+def test_weight_grad_launch_forms_give_the_same_bits(ctx, N, d, ms, c):
+    """The built-in choice against the launch forms that the tuning keys ask for, none of which changes the token ranges."""
+    from paper_2602_23111_amd.prac import TUNE_WGRAD_ONE_LAUNCH, TUNE_WGRAD_TAIL
+    g = torch.Generator(device=DEV).manual_seed(N)
+    rnd = lambda n, w: torch.randn((n, (w + 7) // 8 * 8), generator=g, device=DEV).bfloat16()[:, :w]
+    C, dYs, P = rnd(N, c), [rnd(N, m) for m in ms], torch.randn((d, c), generator=g, device=DEV)
+    run = lambda: ctx.weight_grad_shared(C, dYs, P, c // 2, c - c // 2, 2.0)
+    want = run()
+    try:
+        for key, value in ((TUNE_WGRAD_ONE_LAUNCH, 1), (TUNE_WGRAD_TAIL, 1), (TUNE_WGRAD_TAIL, 2)):
+            ctx.set_tuning(key, value)
+            got = run()
+            ctx.sync_status()
+            assert all(torch.equal(a, b) for a, b in zip(got, want)), (key, value)
+            ctx.set_tuning(key, 0)
+    finally:
+        ctx.set_tuning(TUNE_WGRAD_ONE_LAUNCH, 0)
+        ctx.set_tuning(TUNE_WGRAD_TAIL, 0)
 
 
 def test_weight_grad_exact_gradient_when_complement_is_full(ctx):
