@@ -173,16 +173,6 @@ __global__ __launch_bounds__(256) void reduce_transpose_f32_kernel(const float* 
   }
 }
 
-// out (rows x cols, dense) = P with the columns from k_lo on multiplied by s
-__global__ __launch_bounds__(256) void scaled_basis_kernel(const float* __restrict__ P, int64_t ldp, int64_t rows, int cols,
-                                                           int k_lo, float s, float* __restrict__ out) {
-  const int64_t total = rows * cols;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-    const int c = (int)(i % cols);
-    out[i] = P[(i / cols) * ldp + c] * (c >= k_lo ? s : 1.f);
-  }
-}
-
 template <bool OUT_BF16>
 __global__ __launch_bounds__(256) void cast_out_kernel(const float* __restrict__ src, int64_t lds, void* dst,
                                                        int64_t ldd, int rows, int cols, float beta) {
@@ -241,13 +231,6 @@ int launch_reduce_slabs(prac_ctx* ctx, const float* part, int splits, int64_t st
 int launch_reduce_transpose_f32(prac_ctx* ctx, const float* part, int splits, int M, int N, float* out, int64_t ldo) {
   dim3 grid((N + 63) / 64, (M + 15) / 16);
   hipLaunchKernelGGL(reduce_transpose_f32_kernel, grid, dim3(256), 0, ctx->stream, part, splits, M, N, out, ldo);
-  PRAC_HIP_TRY(ctx, hipGetLastError());
-  return PRAC_OK;
-}
-
-int launch_scaled_basis(prac_ctx* ctx, const float* P, int64_t ldp, int64_t rows, int cols, int k_lo, float s, float* out) {
-  hipLaunchKernelGGL(scaled_basis_kernel, dim3(grid_for(rows * cols, ctx->n_cu)), dim3(256), 0, ctx->stream, P, ldp, rows,
-                     cols, k_lo, s, out);
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
 }

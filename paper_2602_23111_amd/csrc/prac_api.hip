@@ -1075,7 +1075,7 @@ struct ReconPlan {
   bool fast, direct;
   int nkb, ncb;
   int64_t ldcrm;
-  size_t o_pt, o_c, o_tmp, o_crm, o_ps, bytes;
+  size_t o_pt, o_c, o_tmp, o_crm, bytes;
 };
 ReconPlan plan_reconstruct(bool fast, prac_dtype dt, int64_t N, int64_t d, int c, bool packed, int64_t ldc) {
   ReconPlan q{};
@@ -1091,7 +1091,6 @@ ReconPlan plan_reconstruct(bool fast, prac_dtype dt, int64_t N, int64_t d, int c
   } else {
     q.o_tmp = plan.take(dt == PRAC_BF16 ? (size_t)N * d * sizeof(float) : 0);
     q.o_crm = plan.take(packed ? (size_t)N * c * sizeof(bf16_t) : 0);
-    q.o_ps = plan.take((size_t)d * c * sizeof(float));
   }
   q.bytes = plan.off;
   return q;
@@ -1140,30 +1139,34 @@ int prac_reconstruct(prac_ctx* ctx, const void* C, prac_dtype dt, int64_t N, int
     return launch_compress_ws(ctx, Crm, ldcrm, (int)N, c, nullptr, 0, 0, nullptr, 0, false, Pt, ncb, (int)d,
                               reinterpret_cast<bf16_t*>(Xh), ldxh);
   }
-  // fp32 path: Xh = C Ps^T in one product, the scaling factor in a copy of P (a product per block of P would read and
-  // write Xh twice)
+  // fp32 path: Xh = C1 Q1^T, then Xh += scale C2 Q2^T (a scaled copy of P would make it one product, but fp32 data needs no
+  // scratch here)
   const bool need_tmp = dt == PRAC_BF16;
   const void* Crm = C;
   int64_t ldcrm = ldc;
-  int rc;
   if (packed) {
-    rc = launch_unpack_c(ctx, reinterpret_cast<const bf16_t*>(C), (int)N, c, reinterpret_cast<bf16_t*>(ctx->ws + q.o_crm), c);
+    int rc = launch_unpack_c(ctx, reinterpret_cast<const bf16_t*>(C), (int)N, c,
+                             reinterpret_cast<bf16_t*>(ctx->ws + q.o_crm), c);
     if (rc) return rc;
     Crm = ctx->ws + q.o_crm;
     ldcrm = c;
   }
-  float* Ps = reinterpret_cast<float*>(ctx->ws + q.o_ps);
-  rc = launch_scaled_basis(ctx, P, ldp, d, c, k, scale, Ps);
-  if (rc) return rc;
   float* out = need_tmp ? reinterpret_cast<float*>(ctx->ws + q.o_tmp) : reinterpret_cast<float*>(Xh);
-  GemmGenArgs g{};
-  g.A = Crm; g.adt = dt; g.a_rs = ldcrm; g.a_cs = 1;
-  g.B = Ps; g.bdt = PRAC_F32; g.b_rs = 1; g.b_cs = c;  // B(kk, n) = Ps[n][kk]
-  g.M = (int)N; g.N = (int)d; g.K = c; g.k_stride = 1;
-  g.out = out; g.ldo = need_tmp ? d : ldxh; g.acc64 = false; g.out64 = nullptr;
-  g.alpha = 1.f; g.beta = 0.f;
-  rc = launch_gemm_generic(ctx, g);
-  if (rc) return rc;
+  bool first = true;
+  for (int part = 0; part < 2; ++part) {
+    const int k0 = part == 0 ? 0 : k, kn = part == 0 ? k : r;
+    if (kn == 0) continue;
+    GemmGenArgs g{};
+    g.A = reinterpret_cast<const char*>(Crm) + (size_t)k0 * esize(dt); g.adt = dt; g.a_rs = ldcrm; g.a_cs = 1;
+    g.B = P + k0; g.bdt = PRAC_F32; g.b_rs = 1; g.b_cs = ldp;  // B(kk, n) = P[n][k0 + kk]
+    g.M = (int)N; g.N = (int)d; g.K = kn; g.k_stride = 1;
+    g.out = out; g.ldo = need_tmp ? d : ldxh; g.acc64 = false; g.out64 = nullptr;
+    g.alpha = part == 0 ? 1.f : scale;
+    g.beta = first ? 0.f : 1.f;
+    first = false;
+    int rc = launch_gemm_generic(ctx, g);
+    if (rc) return rc;
+  }
   if (need_tmp) return launch_cast_out(ctx, out, d, Xh, PRAC_BF16, ldxh, (int)N, (int)d, 0.f);
   return PRAC_OK;
 }

@@ -127,8 +127,6 @@ int launch_reduce_slabs(prac_ctx* ctx, const float* part, int splits, int64_t st
                         int64_t n, float alpha, float beta);
 // out (N x M fp32, ld = ldo) = transpose of sum_s part[s][j][n], j < M
 int launch_reduce_transpose_f32(prac_ctx* ctx, const float* part, int splits, int M, int N, float* out, int64_t ldo);
-// out (rows x cols fp32, dense) = P with columns >= k_lo multiplied by s
-int launch_scaled_basis(prac_ctx* ctx, const float* P, int64_t ldp, int64_t rows, int cols, int k_lo, float s, float* out);
 int launch_philox(prac_ctx* ctx, uint64_t seed, uint32_t draw, uint32_t stream, void* out, int64_t n,
                   bool normal);
 int launch_pack_basis(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int c, bf16_t* Pt,

@@ -237,6 +237,9 @@ def test_workspace_bytes_matches_the_documented_scratch_of_each_call(lib):
     assert ws(prac.call_shape("weight_grad", 2048, 512, 32, 32, m=[1376], dt=0, odt=0, c_layout=0)) == up(64 * 1376 * 4)
     # reconstruction: Ps^T in fragment order (k-blocks over 256, column blocks over d)
     assert ws(prac.call_shape("reconstruct", N, d, k, r)) == 16 * 64 * 1024
+    # in fp32 neither it nor the compression needs any, so that both run on a ctx that never allocated (in a graph's capture)
+    for op in ("reconstruct", "compress"):
+        assert ws(prac.call_shape(op, N, d, k, r, dt=0, c_layout=0)) == ws(prac.call_shape(op, 100, 64, 8, 0, dt=0, c_layout=0)) == 0
     # the tracking refit is cheaper than the Gram-based fit, and a random-only refresh cheaper still
     cold = ws(prac.call_shape("fit_basis", N, d, k, r))
     track = ws(prac.call_shape("fit_basis", N, d, k, r, warm_start=True, oversample=-1, iters=2))
