@@ -145,6 +145,10 @@ int64_t prac_debug_fit_slab_margin(const prac_call_shape* shape /* [host] */);
  * kernel at the alignment of one element, nothing past a row's last column. */
 int prac_debug_gram_rows(const void* X, int dt, int64_t N, int64_t d, int64_t ldx, int64_t row_stride);
 
+/* Test hook [host]: the tile (rows * 1000 + columns) that a workgroup of the fp32 product kernel takes for an M x N product over
+ * K in `splits` ranges on 256 compute units. */
+int prac_debug_f32_tile(int M, int N, int64_t K, int splits);
+
 /* ---- per-kernel timing hook (for benchmarks) ---------------------------- */
 /* While a kind other than PRAC_KERNEL_NONE is selected, every launch of that
  * kernel is bracketed by a HIP event pair on the ctx stream.  prac_profile_read

@@ -328,37 +328,45 @@ __global__ __launch_bounds__(512) void f32_sum_pt_kernel(F32SumPtArgs a) {
   }
 }
 
+int64_t f32_k_per_split(int64_t K, int splits) { return std::max<int64_t>(round_up64((K + splits - 1) / splits, 8), 8); }
+
 template <bool AKF, bool BKF>
 void launch_gemm_f32_ops(prac_ctx* ctx, F32Args& a) {
-  auto tiles = [&](int tm, int tn) { return (int64_t)((a.M + tm - 1) / tm) * ((a.N + tn - 1) / tn) * a.splits; };
-  auto grid = [&](int tm, int tn) {
+  auto launch = [&](auto kern, int tm, int tn, int threads) {
     a.tiles_n = (a.N + tn - 1) / tn;
-    return dim3((unsigned)(tiles(tm, tn) / a.splits), 1, a.splits);
+    PRAC_LAUNCH(ctx, kern, dim3((unsigned)((int64_t)((a.M + tm - 1) / tm) * a.tiles_n), 1, a.splits), dim3(threads), 0, a);
   };
-  auto launch = [&](auto kern, dim3 g, int threads) { PRAC_LAUNCH(ctx, kern, g, dim3(threads), 0, a); };
-  // Clocks a tile shape needs: the matrix instructions of a SIMD's waves (256 clocks per 32 x 32 block and 8-k chunk),
-  // or the chain of one wave when there are few (a ring of four chunks takes a memory latency, about 2400 clocks, to come
-  // round), or the bytes through L2 (about 8 KB per clock over the chip); then the stores of a wave's 16 rm rn registers,
-  // or the exchange of the partial tiles where k is split.  Measured at the ends of the range: 2048 x 64
-  // over 512 runs 9 us with 32 x 64 tiles and k split over eight waves against 17 - 23 us with 64 x 64 tiles through
-  // LDS; 8192 x 256 over 2048 takes 84 us (102 TFLOP/s) with 64 x 64 tiles against 143 us.
+  switch (f32_tile(ctx->n_cu, a.M, a.N, a.K, a.splits)) {
+    case F32Tile::T128x128: launch(gemm_f32_kernel<AKF, BKF, 2, 2, 2, 2, 1>, 128, 128, 256); break;
+    case F32Tile::T128x64: launch(gemm_f32_kernel<AKF, BKF, 1, 2, 4, 1, 1>, 128, 64, 256); break;
+    case F32Tile::T64x64: launch(gemm_f32_kernel<AKF, BKF, 2, 2, 1, 1, 4>, 64, 64, 256); break;
+    case F32Tile::T32x64: launch(gemm_f32_kernel<AKF, BKF, 1, 2, 1, 1, 8>, 32, 64, 512); break;
+  }
+}
+
+}  // namespace
+
+// Clocks a tile shape needs: the matrix instructions of a SIMD's waves (256 clocks per 32 x 32 block and 8-k chunk),
+// or the chain of one wave when there are few (a ring of four chunks takes a memory latency, about 2400 clocks, to come
+// round), or the bytes through L2 (about 8 KB per clock over the chip); then the stores of a wave's 16 rm rn registers,
+// or the exchange of the partial tiles where k is split.  Measured at the ends of the range: 2048 x 64
+// over 512 runs 9 us with 32 x 64 tiles and k split over eight waves against 17 - 23 us with 64 x 64 tiles through
+// LDS; 8192 x 256 over 2048 takes 84 us (102 TFLOP/s) with 64 x 64 tiles against 143 us.
+F32Tile f32_tile(int n_cu, int M, int N, int64_t K, int splits) {
+  const int64_t k = std::min(K, f32_k_per_split(K, splits));
   auto cost = [&](int tm, int tn, int rm, int rn, int waves, int sk) {
-    const double chunks = std::ceil((double)std::min(a.K, a.k_per_split) / 8 / sk);
-    const double per_simd = std::ceil((double)tiles(tm, tn) * waves / (4.0 * ctx->n_cu));
-    const double bytes = (double)tiles(tm, tn) * (tm + tn) * 4 * std::min(a.K, a.k_per_split);
+    const int64_t tiles = (int64_t)((M + tm - 1) / tm) * ((N + tn - 1) / tn) * splits;
+    const double chunks = std::ceil((double)k / 8 / sk);
+    const double per_simd = std::ceil((double)tiles * waves / (4.0 * n_cu));
+    const double bytes = (double)tiles * (tm + tn) * 4 * k;
     return std::max({per_simd * chunks * 256 * rm * rn, std::ceil(chunks / 4) * 2400, bytes / 8192}) +
            (sk > 1 ? 1500 : per_simd * rm * rn * 700);
   };
   const double big = cost(128, 128, 2, 2, 4, 1), mid = cost(64, 64, 2, 2, 4, 4), small = cost(32, 64, 1, 2, 8, 8),
                flat = cost(128, 64, 1, 2, 4, 1);
   const double best = std::min({big, mid, small, flat});
-  if (big == best) launch(gemm_f32_kernel<AKF, BKF, 2, 2, 2, 2, 1>, grid(128, 128), 256);
-  else if (flat == best) launch(gemm_f32_kernel<AKF, BKF, 1, 2, 4, 1, 1>, grid(128, 64), 256);
-  else if (mid == best) launch(gemm_f32_kernel<AKF, BKF, 2, 2, 1, 1, 4>, grid(64, 64), 256);
-  else launch(gemm_f32_kernel<AKF, BKF, 1, 2, 1, 1, 8>, grid(32, 64), 512);
+  return big == best ? F32Tile::T128x128 : (flat == best ? F32Tile::T128x64 : (mid == best ? F32Tile::T64x64 : F32Tile::T32x64));
 }
-
-}  // namespace
 
 bool gemm_f32_takes(const GemmGenArgs& g) {
   return g.adt == PRAC_F32 && g.bdt == PRAC_F32 && !g.acc64 && !g.out64 && g.k_stride <= 1 && g.M >= 2 && g.N >= 2 &&
@@ -375,7 +383,7 @@ int launch_gemm_f32(prac_ctx* ctx, const GemmGenArgs& g, int splits) {
   a.M = g.M; a.N = g.N; a.K = g.K;
   a.out = g.out; a.ldo = g.ldo; a.alpha = g.alpha; a.beta = g.beta;
   a.splits = splits;
-  a.k_per_split = std::max<int64_t>(round_up64((g.K + splits - 1) / splits, 8), 8);
+  a.k_per_split = f32_k_per_split(g.K, splits);
   a.slabs = reinterpret_cast<float*>(g.slabs);
   if (akf && bkf) launch_gemm_f32_ops<true, true>(ctx, a);
   else if (akf) launch_gemm_f32_ops<true, false>(ctx, a);

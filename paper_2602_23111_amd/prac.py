@@ -30,7 +30,7 @@ EXPORTS = ["prac_create", "prac_destroy", "prac_set_stream", "prac_sync_status",
            "prac_basis_lp_bytes", "prac_pack_basis", "prac_fit_basis", "prac_compress",
            "prac_compress_fused_fwd", "prac_weight_grad", "prac_weight_grad_shared", "prac_reconstruct",
            "prac_workspace_bytes", "prac_reserve_workspace", "prac_debug_fit_slab_margin", "prac_debug_gram_rows",
-           "prac_weight_grad_static"]
+           "prac_debug_f32_tile", "prac_weight_grad_static"]
 OPS = {"gram": 1, "fit_basis": 2, "compress": 3, "fused_fwd": 4, "weight_grad": 5, "reconstruct": 6}
 
 
@@ -109,6 +109,7 @@ def load_library() -> C.CDLL:
         "prac_reserve_workspace": (i32, [vp, C.c_size_t]),
         "prac_debug_fit_slab_margin": (i64, [C.POINTER(CallShape)]),
         "prac_debug_gram_rows": (i32, [vp, i32, i64, i64, i64, i64]),
+        "prac_debug_f32_tile": (i32, [i32, i32, i64, i32]),
         "prac_weight_grad_shared": (i32, [vp, vp, i32, i64, i64, i32, i32, C.POINTER(vp), C.POINTER(i64),
                                           C.POINTER(i64), vp, vp, i64, i64, i32, i32, f32, C.POINTER(vp), i32,
                                           C.POINTER(i64), f32]),

@@ -289,3 +289,14 @@ def test_gram_of_sampled_rows_stays_inside_them(lib):
                         last = (N - 1) // stride * stride * ldx         # first element of the last sampled row
                         assert last + (d + 7) // 8 * 8 <= N * ldx, (N, d, ldx, stride)
     assert rows(0, 260, 260, 2) == -1 and rows(4097, 260, 259, 2) == -1 and rows(4097, 260, 260, 0) == -1
+
+
+def test_fp32_cases_reach_every_tile(lib):
+    """The products of the fp32 GPU tests select every tile shape of the kernel, so that a change of the rule that picks them does
+    not take one out of the tests."""
+    from test_gpu_parity import F32_CASES, GRAM_CASES
+
+    tile = lambda M, N, K: lib.prac_debug_f32_tile(M, N, K, 1)
+    assert {tile(N, m, d) for N, d, m, _, _ in F32_CASES} == {128128, 128064, 64064, 32064}             # Y, either layout of W
+    assert 128128 in {tile(d, d, N) for dt, N, d, _, stride in GRAM_CASES if dt == "f32" and stride == 1}
+    assert tile(1, 8, 8) == -1 and lib.prac_debug_f32_tile(8, 8, 8, 0) == -1

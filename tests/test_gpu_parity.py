@@ -572,7 +572,9 @@ F32_CASES = [
     (65, 71, 63, 17, 16),       # odd widths (a pair of columns that starts early), seven k in the tail
     (129, 72, 127, 30, 33),     # more chunks than waves that split them, by one
     (2049, 130, 193, 40, 25),   # token ranges of C^T dY with a ragged last one
-    (4097, 24, 1025, 8, 8),     # enough tiles for the 128 x 128 workgroup in Y
+    (4097, 24, 1025, 8, 8),     # 64 x 64 tiles of Y, more than compute units
+    (2049, 9, 65, 3, 2),        # Y: 128 x 64, a row and a column past whole tiles, one k past a chunk
+    (2045, 133, 2045, 30, 33),  # Y: 128 x 128, partial last tiles, five k past whole chunks
 ]
 
 
@@ -795,11 +797,16 @@ def test_weight_grad_exact_gradient_when_complement_is_full(ctx):
 
 
 # --------------------------------------------------------------------- Gram
-@pytest.mark.parametrize("dt,N,d,ldx,stride", [
-    ("f32", 2048, 512, 512, 1), ("f32", 700, 130, 136, 3),
+GRAM_CASES = [
+    ("f32", 2048, 512, 512, 1),
+    ("f32", 133, 2045, 2047, 1),      # 128 x 128 tiles, both operands' rows along memory
+    ("f32", 700, 130, 136, 3),
     ("bf16", 2048, 512, 512, 1), ("bf16", 4100, 264, 264, 1), ("bf16", 3001, 200, 200, 4),
     ("bf16", 500, 77, 77, 2), ("bf16", 4500, 328, 336, 2),    # the last: streaming path, ragged in rows and columns
-])
+]
+
+
+@pytest.mark.parametrize("dt,N,d,ldx,stride", GRAM_CASES)
 def test_gram_matches_oracle(ctx, dt, N, d, ldx, stride):
     Xt = si.round_to(si.activation(N, d, 1.0, seed=d, n_out=2, out_scale=20.0)[0], dt)
     G = ctx.gram(dev_padded(Xt, ldx), row_stride=stride)
