@@ -107,6 +107,7 @@ template <bool AKF, bool BKF, int RM, int RN, int WM, int WN, int SK>
 __global__ __launch_bounds__(64 * WM * WN * SK) void gemm_f32_kernel(F32Args a) {
   constexpr int D = 4;  // chunks in flight
   constexpr int NREG = RM * RN * 16;
+  static_assert(RN == 2, "the epilogue stores pairs of columns");
   static_assert(SK == 1 || (WM == 1 && WN == 1 && NREG % (2 * SK) == 0), "one wave tile per workgroup when k is split");
   __shared__ float red[SK > 1 ? SK * NREG * 64 : 1];
   const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
@@ -170,8 +171,7 @@ __global__ __launch_bounds__(64 * WM * WN * SK) void gemm_f32_kernel(F32Args a) 
   auto store = [&](int r, float x0, float x1) {
     const int i = r / (16 * RN), v = r / RN % 16;
     const int m = m0 + Operand<AKF, RM>::index(i, 8 * (v / 4) + 4 * lh + v % 4);
-    const int j0 = RN == 2 ? 0 : r % RN;
-    const int na = n0 + Operand<BKF, RN>::index(j0, li), nb = n0 + Operand<BKF, RN>::index(1, li);
+    const int na = n0 + Operand<BKF, RN>::index(0, li), nb = n0 + Operand<BKF, RN>::index(1, li);
     if (m >= a.M) return;
     float* o;
     float al = 1.f, be = 0.f;
@@ -182,12 +182,12 @@ __global__ __launch_bounds__(64 * WM * WN * SK) void gemm_f32_kernel(F32Args a) 
       al = a.alpha;
       be = a.beta;
     }
-    if (RN == 2 && !BKF && nb < a.N && be == 0.f) {
+    if (!BKF && nb < a.N && be == 0.f) {
       *reinterpret_cast<f32x2_el*>(o + na) = f32x2{al * x0, al * x1};
       return;
     }
     if (na < a.N) o[na] = be == 0.f ? al * x0 : al * x0 + be * o[na];
-    if (RN == 2 && nb < a.N) o[nb] = be == 0.f ? al * x1 : al * x1 + be * o[nb];
+    if (nb < a.N) o[nb] = be == 0.f ? al * x1 : al * x1 + be * o[nb];
   };
   if constexpr (SK > 1) {
 #pragma unroll
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(64 * WM * WN * SK) void gemm_f32_kernel(F32Args a) 
 #pragma unroll
     for (int i = 0; i < RM; ++i)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) store((i * 16 + v) * RN, acc[i][0][v], acc[i][RN - 1][v]);
+      for (int v = 0; v < 16; ++v) store((i * 16 + v) * RN, acc[i][0][v], acc[i][1][v]);
   }
 }
 
@@ -370,7 +370,7 @@ F32Tile f32_tile(int n_cu, int M, int N, int64_t K, int splits) {
 
 bool gemm_f32_takes(const GemmGenArgs& g) {
   return g.adt == PRAC_F32 && g.bdt == PRAC_F32 && !g.acc64 && !g.out64 && g.k_stride <= 1 && g.M >= 2 && g.N >= 2 &&
-         (g.a_rs == 1 || g.a_cs == 1) && (g.b_rs == 1 || g.b_cs == 1);
+         (g.b_cs == 1 ? (g.a_rs == 1 || g.a_cs == 1) : (g.a_cs == 1 && g.b_rs == 1));  // (no product needs A^T B^T)
 }
 
 int launch_gemm_f32(prac_ctx* ctx, const GemmGenArgs& g, int splits) {
@@ -387,7 +387,6 @@ int launch_gemm_f32(prac_ctx* ctx, const GemmGenArgs& g, int splits) {
   a.slabs = reinterpret_cast<float*>(g.slabs);
   if (akf && bkf) launch_gemm_f32_ops<true, true>(ctx, a);
   else if (akf) launch_gemm_f32_ops<true, false>(ctx, a);
-  else if (bkf) launch_gemm_f32_ops<false, true>(ctx, a);
   else launch_gemm_f32_ops<false, false>(ctx, a);
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
