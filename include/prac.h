@@ -23,8 +23,9 @@
  *     frees the block and allocates a larger one (hipMalloc).  Callers that
  *     must not wait or allocate inside a hot call size the block up front:
  *     prac_workspace_bytes for every call shape they will issue, then one
- *     prac_reserve_workspace with the largest answer.  A ctx must not be used
- *     from two host threads at once.
+ *     prac_reserve_workspace with the largest answer.  prac_create itself
+ *     allocates 8 MiB more (partial sums of fp32 weight gradients).  A ctx must
+ *     not be used from two host threads at once.
  *   - Return value: PRAC_OK (0) or a negative prac_status.  Shape and argument
  *     errors are detected on the host BEFORE anything is enqueued and before
  *     the ctx is looked at, so they can be exercised without a GPU.
@@ -101,9 +102,9 @@ int prac_last_hip_error(const prac_ctx* ctx);   /* last hipError_t seen */
 
 /* ---- scratch sizing ------------------------------------------------------ */
 /* The shape of one call, for prac_workspace_bytes.  Fields an entry point does not
- * take are ignored.  `generic` = 1 says that the call will run the strided kernels
- * (a base pointer that is not 16-byte aligned or a leading dimension that is not a
- * multiple of 8 elements; fp32 data always does). */
+ * take are ignored.  `generic` = 1 says that a base pointer of the call is not 16-byte aligned or a
+ * leading dimension not a multiple of 8 elements; the answer then covers both the streaming kernels on rows
+ * that start on any element and the strided ones.  fp32 data has one path, whatever `generic` says. */
 typedef enum {
   PRAC_OP_GRAM = 1,        /* prac_gram: dt, N, d, fit.row_stride */
   PRAC_OP_FIT_BASIS = 2,   /* prac_fit_basis: dt, N, d, k, r, refresh, fit */
@@ -123,7 +124,7 @@ typedef struct {
   int64_t m[PRAC_MAX_SHARED];  /* their widths */
   int c_layout;                /* prac_c_layout */
   int have_p_lp;               /* 1: the call hands over a packed basis P_lp */
-  int generic;                 /* 1: unaligned operands, the strided kernels run */
+  int generic;                 /* 1: unaligned operands */
   int refresh;                 /* fit: PRAC_REFRESH_* bits */
   prac_fit_opts fit;           /* fit / Gram: options as passed to the call */
 } prac_call_shape;

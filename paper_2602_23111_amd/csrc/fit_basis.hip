@@ -102,8 +102,8 @@ constexpr int CH_MAX = 1024;
 // robin; only panels pass through LDS, two buffers in turn (one holds the panel that the update still reads while the
 // next one is written), so a panel costs two barriers and no trip to memory.  The five waves that factor panels hold
 // six tiles, the others ten: both fit the 128 registers of a wave beside what their phase needs.
-// 83 / 98 us at b = 256 after a panel of 2048 / 4096 rows (148 / 175 us with the trailing matrix in memory
-// and a separate triangular solve): 16 panels of about 2.5 us elimination, 0.2 - 3 us update (the fp64 matrix cores' rate),
+// 84 us per launch at b = 256 in a cold fit of 2048 features, 98 us in a refit of 4096 (148 / 175 us with the trailing matrix in
+// memory and a separate triangular solve; the work depends on b alone, what makes the difference is not known): 16 panels of about 2.5 us elimination, 0.2 - 3 us update (the fp64 matrix cores' rate),
 // and two barriers.
 constexpr int CHR_MAX = 256, CHR_LDP = CHR_MAX + 2;
 constexpr int CHR_PW = (CHR_MAX - CH_NB + CH_GRP - 1) / CH_GRP;  // waves that factor panels

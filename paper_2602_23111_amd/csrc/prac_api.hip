@@ -1185,7 +1185,7 @@ size_t prac_workspace_bytes(const prac_ctx* ctx, const prac_call_shape* sh) {
   const int c = sh->k + sh->r;
   const bool fast = dt == PRAC_BF16 && !sh->generic;
   const bool packed = sh->c_layout == PRAC_C_PACKED;
-  // an unaligned pointer stands for "the strided kernels will run" where a plan looks at alignment
+  // where a plan looks at alignment, an unaligned pointer stands for rows that start on any element
   const void* xptr = sh->generic ? reinterpret_cast<const void*>(uintptr_t(2)) : nullptr;
   const int64_t ldq = sh->generic ? sh->d : round_up64(sh->d, 8);  // row pitch the plan assumes for X
   switch (sh->op) {
