@@ -10,7 +10,7 @@
 // same Q2 that Householder QR with sign normalisation gives.
 #include <algorithm>
 
-#include "prac_internal.h"
+#include "frag_utils.h"
 
 namespace {
 
@@ -40,139 +40,328 @@ __device__ __forceinline__ double chol_diag_max(const double* W, int b, double* 
   return mx;
 }
 
-// A panel of 16 rows (`panel`, ldp doubles apart; column c is column j0 + c of W, wpad of them, the first 16 the
-// diagonal block), factored by one wave for 48 of its columns: lane l < 16 holds column l of the diagonal block, the
-// others the columns 16 + 48 g .. of group g, and one elimination over the 16 rows factors the former and solves the
-// latter, so that there is no separate triangular solve (every group repeats the diagonal block, bit for bit).  The
-// elimination divides by the pivots (L D L^T: four dependent operations after the reciprocal's estimate); their square
-// roots are taken once at the end, a pivot per lane.  Multipliers go through scalar registers.  The finished rows go
-// to W, the solved columns also back to the panel.  Non-finite or non-positive pivots raise *flag and count as `tiny`.
-constexpr int CH_GRP = 48;
-__device__ __forceinline__ void chol_panel_group(double* panel, int ldp, int wpad, int g, double tiny, double* W, int b,
-                                                 int j0, int* flag) {
-  const int lane = threadIdx.x & 63;
-  const int c = lane < 16 ? lane : CH_GRP * g + lane;  // 16 + 48 g + (lane - 16)
-  const bool in = c < wpad;
-  double col[16];
-#pragma unroll
-  for (int u = 0; u < 16; ++u) col[u] = in ? panel[u * ldp + c] : 0.0;
-  double piv = 1.0;
-  bool bad = false;
-  chol_static_for<16>([&](auto tc) {
+// Elimination of a panel of 16 rows in one wave.  Every row of 16 lanes holds the diagonal block (lane l & 15: its column, rows
+// u <= l & 15 of it; what is below is never read) in `diag` and 16 other columns of the panel in `col`, which become R^-T times
+// themselves (R = R_jj).  It divides by the pivots (L D L^T) and takes their square roots at the end, a pivot per lane.
+// The time is the chain from one pivot to the next and the issue of the updates, so: a multiplier is broadcast to the row of
+// lanes by the multiply-add that uses it (DPP row_newbcast; two lane reads into scalar registers and a multiply-add take three
+// times as long: 14 to 21 cycles against 5), the reciprocal is one third-order step on the hardware's estimate (2^-23, cubed), and
+// the order is fixed by hand: next pivot first, the other updates behind it (the empty statements pin it).  A pivot that is not
+// above `tiny`, or not finite, is replaced; returns whether there was one.  after_six() runs behind the sixth pivot.
+// (the instructions below read lanes of a register that may have been written just before: two wait states)
+template <int L>
+__device__ __forceinline__ double row_bcast_f64(double x) {
+  double r;
+  asm volatile("s_nop 1\nv_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf\n" : "=v"(r) : "v"(x), "n"(L));
+  return r;
+}
+template <int L, bool FRESH>  // acc += (x of lane L) * y; FRESH: x may have been written just before
+__device__ __forceinline__ void row_fma_f64(double& acc, const double& x, const double& y) {
+  if constexpr (FRESH)
+    asm volatile("s_nop 1\nv_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf\n"
+                 : "+v"(acc) : "v"(x), "v"(y), "n"(L));
+  else
+    asm volatile("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf\n" : "+v"(acc) : "v"(x), "v"(y), "n"(L));
+}
+template <typename Mid>
+__device__ __forceinline__ bool chol_eliminate(double (&diag)[16], double (&col)[16], double tiny, Mid&& after_six) {
+  const double big = 1.7e308;
+  auto clamp = [&](double x) __attribute__((always_inline)) {  // (a NaN becomes tiny)
+    asm volatile("v_max_f64 %0, %0, %1\nv_min_f64 %0, %0, %2\n" : "+v"(x) : "v"(tiny), "v"(big));
+    return x;
+  };
+  auto pin = [](double& x) __attribute__((always_inline)) { asm volatile("" : "+v"(x)); };
+  double p = clamp(row_bcast_f64<0>(diag[0]));
+  double inv = __builtin_amdgcn_rcp(p);
+  {
+    const double e = fma(-p, inv, 1.0);
+    inv = fma(inv, fma(e, e, e), inv);
+  }
+  chol_static_for<15>([&](auto tc) __attribute__((always_inline)) {
     constexpr int T = decltype(tc)::value;
-    double p = readlane_f64(col[T], T);
-    if (!(p > tiny) || !isfinite(p)) {
-      bad = true;
-      p = tiny;
+    double s = -(diag[T] * inv);
+    pin(s);
+    row_fma_f64<T + 1, true>(diag[T + 1], s, diag[T]);
+    p = clamp(row_bcast_f64<T + 1>(diag[T + 1]));
+    double x = __builtin_amdgcn_rcp(p);
+    pin(x);
+    row_fma_f64<T + 1, false>(col[T + 1], s, col[T]);
+    if constexpr (T + 2 < 16) {
+      row_fma_f64<T + 2, false>(diag[T + 2], s, diag[T]);
+      row_fma_f64<T + 2, false>(col[T + 2], s, col[T]);
     }
-    if (lane == T) col[T] = piv = p;
-    double inv = __builtin_amdgcn_rcp(p);
-    inv = fma(inv, fma(-p, inv, 1.0), inv);
-    inv = fma(inv, fma(-p, inv, 1.0), inv);
-    const double s = -(col[T] * inv);
-    chol_static_for<15 - T>([&](auto uc) {
-      constexpr int U = T + 1 + decltype(uc)::value;
-      // (lanes left of column T hold no element of R here; what they compute is never read)
-      col[U] = fma(readlane_f64(s, U), col[T], col[U]);
-    });
+    double e = fma(-p, x, 1.0);
+    pin(e);
+    double e2 = fma(e, e, e);
+    pin(e2);
+    inv = fma(x, e2, x);
+    pin(inv);
+    if constexpr (T + 3 < 16)
+      chol_static_for<13 - T>([&](auto ic) __attribute__((always_inline)) {
+        constexpr int U = T + 3 + decltype(ic)::value;
+        row_fma_f64<U, false>(diag[U], s, diag[T]);
+        row_fma_f64<U, false>(col[U], s, col[T]);
+      });
+    if constexpr (T == 5) after_six();
   });
+  const int l = threadIdx.x & 15;
+  double piv = 1.0;
+#pragma unroll
+  for (int u = 0; u < 16; ++u) piv = l == u ? diag[u] : piv;
+  const bool bad = __any(!(piv > tiny) || !isfinite(piv));
+  piv = clamp(piv);
   double rs = __builtin_amdgcn_rsq(piv);
   rs = rs * (1.5 - 0.5 * piv * rs * rs);
   rs = rs * (1.5 - 0.5 * piv * rs * rs);
-#pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    col[u] *= readlane_f64(rs, u);
-    if (lane >= 16 && in) panel[u * ldp + c] = col[u];
-    if (in && j0 + u < b && j0 + c < b && (lane >= 16 || (g == 0 && lane >= u))) W[(int64_t)(j0 + u) * b + j0 + c] = col[u];
-  }
-  if (g == 0 && bad && lane == 0) atomicOr(flag, 1);
+  chol_static_for<16>([&](auto uc) __attribute__((always_inline)) {
+    constexpr int U = decltype(uc)::value;
+    col[U] *= row_bcast_f64<U>(rs);
+  });
+  return bad;
 }
 
-// Both kernels below: in place on the row-major b x b fp64 matrix W (the upper triangle is read, rows of R
-// are written to it): W = R^T R.  `shift_rel` * max diag(W) is added to the diagonal first.
-// One workgroup of 1024 threads.  Per panel of 16 rows: the rows go to LDS (columns padded to a multiple of 16 with the
-// identity), chol_panel_group factors them, and the trailing matrix takes its rank-16 update as 16 x 16 tiles
+// The same for a panel in LDS (`panel`, ldp doubles apart; column c is column j0 + c of W, wpad of them, the first 16 the
+// diagonal block), 64 of its columns per wave (every wave repeats the diagonal block, bit for bit): group g holds the columns
+// 16 + 64 g .., and they go to W and back to the panel.  Group -1 takes the identity instead and writes the diagonal block's place
+// in W: R_jj^-1 (what the triangular solve multiplies with).  Non-finite or non-positive pivots raise *flag.
+constexpr int CH_GRP = 64;
+__device__ __forceinline__ void chol_panel_group(double* panel, int ldp, int wpad, int g, double tiny, double* W, int b,
+                                                 int j0, int* flag) {
+  const int lane = threadIdx.x & 63, i = lane & 15;
+  const int c = g < 0 ? 0 : 16 + CH_GRP * g + lane;
+  const bool in = c < wpad;
+  double diag[16], col[16];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    diag[u] = panel[u * ldp + i];
+    col[u] = g < 0 ? (i == u ? 1.0 : 0.0) : (in ? panel[u * ldp + c] : 0.0);
+  }
+  const bool bad = chol_eliminate(diag, col, tiny, [] {});
+  if (g < 0) {
+    if (lane < 16 && j0 + i < b) {
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        if (j0 + u < b) W[(int64_t)(j0 + i) * b + j0 + u] = col[u];  // (below the diagonal: zeros)
+    }
+    if (bad && lane == 0) atomicOr(flag, 1);
+  } else if (in) {
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      panel[u * ldp + c] = col[u];
+      if (j0 + u < b && j0 + c < b) W[(int64_t)(j0 + u) * b + j0 + c] = col[u];
+    }
+  }
+}
+
+// Both kernels below: in place on the row-major b x b fp64 matrix W, the upper triangle of W = R^T R (`shift_rel` * max diag(W) is
+// added to its diagonal first) becomes R, with the inverse of every 16 x 16 diagonal block of R in that block's place.
+// One workgroup of 1024 threads, the columns padded to a multiple of 16 with the identity; products and updates are 16 x 16 tiles
 // on v_mfma_f64_16x16x4_f64.
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
 constexpr int CH_NB = 16;  // panel height = block size of the fp64 matrix instruction
 constexpr int CH_TB = 4;   // trailing tiles a wave has in flight
 constexpr int CH_MAX = 1024;
 
-// b <= 256: the whole matrix stays in registers as 16 x 16 upper-triangular tiles (136 of them at most), dealt round
-// robin; only panels pass through LDS, two buffers in turn (one holds the panel that the update still reads while the
-// next one is written), so a panel costs two barriers and no trip to memory.  The five waves that factor panels hold
-// six tiles, the others ten: both fit the 128 registers of a wave beside what their phase needs.
-// 84 us per launch at b = 256 in a cold fit of 2048 features, 98 us in a refit of 4096 (148 / 175 us with the trailing matrix in
-// memory and a separate triangular solve; the work depends on b alone, what makes the difference is not known): 16 panels of about 2.5 us elimination, 0.2 - 3 us update (the fp64 matrix cores' rate),
-// and two barriers.
-constexpr int CHR_MAX = 256, CHR_LDP = CHR_MAX + 2;
-constexpr int CHR_PW = (CHR_MAX - CH_NB + CH_GRP - 1) / CH_GRP;  // waves that factor panels
-constexpr int CHR_PT = 6, CHR_UT = 10;                           // tiles of such a wave and of the others
-static_assert(16 * CHR_PT + (16 - CHR_PW) * (CHR_UT - CHR_PT) >= 136, "every tile has an owner");
+// b <= 256: the whole matrix stays in registers as 16 x 16 upper-triangular tiles.  Wave 0 eliminates the diagonal blocks, with
+// the identity beside them, which leaves R_jj^-T; the other 15 waves hold the tiles (round robin, nine at most: both fit the 128
+// registers of a wave), multiply their tiles of row j by R_jj^-T and update their trailing tiles with the result.  A tile's
+// accumulators are, register by register, also its operand layout in both products (element (4 v + fk, fi) is register v
+// of lane (fi, fk) as a result, and k = 4 v + fk, m or n = fi as an operand), so tiles pass through LDS in lane order, untransposed.
+// What bounds it is the chain of 256 pivots, so wave 0 waits for nothing else: tiles (j, j + 1) and (j + 1, j + 1), updated up to
+// panel j - 1, are handed to it while it eliminates block j, and it forms the next diagonal block from them itself; the
+// trailing update of panel j - 1 runs beside that elimination.  Two barriers per panel.
+// 53 us per launch at b = 256 in a cold fit of 2048 features, 59 in a refit of 4096 (84 / 98 us before: the elimination's multipliers
+// through scalar registers, five waves eliminating and everything else waiting for them, no update beside it): 16 panels of 5600
+// cycles (elimination 3600), the first nine up to 13000, where the update is bound by the fp64 matrix cores' rate.
+constexpr int CHR_MAX = 256, CHR_NBK = CHR_MAX / CH_NB, CHR_W = 15, CHR_UT = 9;
+constexpr int CHR_SPARE = 9;  // block rows that leave three tiles to the waves beside wave 0, if the others cannot hold all
+static_assert(12 * CHR_UT + 3 * CHR_SPARE >= CHR_NBK * (CHR_NBK + 1) / 2 - 1, "every tile but the first has an owner");
+constexpr int CHR_ML = CH_NB + 2;  // pitch of the 16 x 16 blocks that change layout in LDS
 
-template <bool PANEL>
-__device__ __forceinline__ void chol_reg_wave(double* panels, double* W, int b, double shift, double tiny, int wave,
-                                              int* flag) {
-  constexpr int NT = PANEL ? CHR_PT : CHR_UT;
+struct __align__(16) CholRegLds {
+  double diag[CH_NB * CHR_ML];     // wave 0's next diagonal block on its way from tile layout to a column per lane
+  double m[CH_NB * CHR_ML];        // R_jj^-T, element (u, c) at c * CHR_ML + u
+  double hand[2][256];             // the tiles handed to wave 0, in lane order: (j, j + 1), (j + 1, j + 1)
+  double panel[CHR_NBK][256];      // row j of R, a tile per block column, in lane order
+  double red[16];
+};
+
+// a + f^T x for 16 x 16 tiles, as two chains of matrix instructions (one depends on the other's result for about 100 cycles)
+__device__ __forceinline__ f64x4_t chol_mul(const f64x4_t& f, const f64x4_t& x, f64x4_t a) {
+  f64x4_t b = {0.0, 0.0, 0.0, 0.0};
+  a = __builtin_amdgcn_mfma_f64_16x16x4f64(f[0], x[0], a, 0, 0, 0);
+  b = __builtin_amdgcn_mfma_f64_16x16x4f64(f[1], x[1], b, 0, 0, 0);
+  a = __builtin_amdgcn_mfma_f64_16x16x4f64(f[2], x[2], a, 0, 0, 0);
+  b = __builtin_amdgcn_mfma_f64_16x16x4f64(f[3], x[3], b, 0, 0, 0);
+  return a + b;
+}
+
+// tile (I, J) of W (element (4 v + fk, fi) in register v), and the shift of its diagonal, with the identity outside b x b
+__device__ __forceinline__ f64x4_t chol_load_tile(const double* W, int b, int I, int J) {
+  const int fi = threadIdx.x & 15, fk = (threadIdx.x & 63) >> 4;
+  const char* const base = reinterpret_cast<const char*>(W);
+  const unsigned c = min(CH_NB * J + fi, b - 1);
+  f64x4_t t;
+#pragma unroll
+  for (int v = 0; v < 4; ++v)  // (32-bit offsets: one register per address)
+    t[v] = *reinterpret_cast<const double*>(base + 8u * (unsigned)(min(CH_NB * I + 4 * v + fk, b - 1) * b + c));
+  return t;
+}
+__device__ __forceinline__ void chol_border(f64x4_t& t, int b, double shift, int I, int J) {
+  const int fi = threadIdx.x & 15, fk = (threadIdx.x & 63) >> 4, c = CH_NB * J + fi;
+  if (I == J) {  // uniform
+#pragma unroll
+    for (int v = 0; v < 4; ++v) t[v] += 4 * v + fk == fi ? shift : 0.0;
+  }
+  if (CH_NB * (J + 1) > b) {  // uniform
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int row = CH_NB * I + 4 * v + fk;
+      if (row >= b || c >= b) t[v] = row == c ? 1.0 : 0.0;
+    }
+  }
+}
+
+__device__ __forceinline__ void chol_wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ __forceinline__ void chol_pivot_wave(CholRegLds& s, const double* W, int b, double shift, double tiny, int* flag) {
+  const int lane = threadIdx.x & 63, fi = lane & 15, fk = lane >> 4;
+  const int nb = (b + CH_NB - 1) / CH_NB;
+  bool bad = false;
+  __builtin_amdgcn_s_setprio(3);
+  f64x4_t t = chol_load_tile(W, b, 0, 0);
+  chol_border(t, b, shift, 0, 0);
+  for (int j = 0; j < nb; ++j) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) s.diag[fi * CHR_ML + 4 * v + fk] = t[v];
+    chol_wave_sync();
+    double diag[16], col[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      diag[u] = s.diag[fi * CHR_ML + u];
+      col[u] = fi == u ? 1.0 : 0.0;
+    }
+    bad = chol_eliminate(diag, col, tiny, [&] {
+            if (j > 0) __syncthreads();  // B of panel j - 1, which this wave does not need: the others are there by now
+          }) || bad;
+    if (lane < 16) {
+#pragma unroll
+      for (int u = 0; u < 16; ++u) s.m[fi * CHR_ML + u] = col[u];
+    }
+    __syncthreads();  // A: R_jj^-T and the handed tiles are in LDS
+    if (j + 1 < nb) {
+      f64x4_t m, h;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        m[v] = s.m[(4 * v + fk) * CHR_ML + fi];
+        h[v] = s.hand[0][64 * v + lane];
+        t[v] = s.hand[1][64 * v + lane];
+      }
+      const f64x4_t x = chol_mul(m, h, f64x4_t{0.0, 0.0, 0.0, 0.0});
+      t = chol_mul(-x, x, t);
+    }
+  }
+  __syncthreads();  // B of the last panel
+  if (bad && lane == 0) atomicOr(flag, 1);
+}
+
+__device__ __forceinline__ void chol_tile_wave(CholRegLds& s, double* W, int b, double shift, int wave) {
   const int lane = threadIdx.x & 63, fi = lane & 15, fk = lane >> 4;
   const int nb = (b + CH_NB - 1) / CH_NB, ntiles = nb * (nb + 1) / 2;
-  // tile (I, J), I <= J: register v of lane (fi, fk) is element (16 I + 4 v + fk, 16 J + fi)
-  f64x4_t acc[NT];
-  int ti[NT], tj[NT];
+  f64x4_t acc[CHR_UT];
+  int tile[CHR_UT];  // 16 I + J, -1: none
+  // Waves 4, 8 and 12 share a SIMD with wave 0, whose chain every fp64 instruction of theirs delays (64 cycles each): they get only
+  // what the other twelve cannot hold, the last three tiles of block rows 1 - 9.
+  const bool spare = (wave & 3) == 0;
+  const int n_rows = ntiles - 1 > 12 * CHR_UT ? CHR_SPARE : 0;  // b > 224
+  const int others = wave - (wave >> 2);                        // 1 .. 12
 #pragma unroll
-  for (int e = 0; e < NT; ++e) {
-    int q = e < CHR_PT ? wave + 16 * e : 16 * CHR_PT + (wave - CHR_PW) + (16 - CHR_PW) * (e - CHR_PT), I = 0;
-    const bool live = q < ntiles;
+  for (int e = 0; e < CHR_UT; ++e) {
+    // tile number q, row by row: row I starts at I nb - I (I - 1) / 2
+    int q = others + 12 * e, I = 0;
+    bool live;
+    if (spare) {
+      live = e < n_rows;
+      q = (e + 2) * nb - (e + 2) * (e + 1) / 2 - (wave >> 2);
+    } else {
+      for (int t = 1; t <= n_rows; ++t)  // step over the tiles of the spare waves
+        if (q >= (t + 1) * nb - t * (t + 1) / 2 - 3) q += 3;
+      live = q < ntiles;
+    }
     if (!live) q = 0;
     while (q >= nb - I) {  // block row I holds nb - I tiles
       q -= nb - I;
       ++I;
     }
-    ti[e] = live ? I : -1;
-    tj[e] = I + q;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int row = CH_NB * I + 4 * v + fk, c = CH_NB * tj[e] + fi;
-      double x = row == c ? 1.0 : 0.0;
-      if (live && row < b && c < b && row <= c) x = W[(int64_t)row * b + c] + (row == c ? shift : 0.0);
-      acc[e][v] = x;
-    }
+    tile[e] = live ? 16 * I + I + q : -1;
+    acc[e] = chol_load_tile(W, b, I, I + q);
   }
-  for (int j = 0; j < nb; ++j) {
-    double* panel = panels + (j & 1) * (CH_NB * CHR_LDP);
+  auto hand = [&](int t, int j, const f64x4_t& x) {  // tiles (j, j + 1) and (j + 1, j + 1) go to wave 0
+    if (t == 17 * j + 1 || t == 17 * j + 17) {       // uniform
+      double* h = s.hand[t == 17 * j + 17];
 #pragma unroll
-    for (int e = 0; e < NT; ++e)
-      if (ti[e] == j) {  // uniform
-#pragma unroll
-        for (int v = 0; v < 4; ++v) panel[(4 * v + fk) * CHR_LDP + CH_NB * (tj[e] - j) + fi] = acc[e][v];
-      }
-    __syncthreads();
-    const int wpad = (nb - j) * CH_NB;
-    if constexpr (PANEL) {
-      if (wave == 0 || 16 + CH_GRP * wave < wpad) chol_panel_group(panel, CHR_LDP, wpad, wave, tiny, W, b, j * CH_NB, flag);
+      for (int v = 0; v < 4; ++v) h[64 * v + lane] = x[v];
     }
-    __syncthreads();
+  };
 #pragma unroll
-    for (int e = 0; e < NT; ++e) {
-      if (ti[e] <= j) continue;  // uniform
-      const double* pa = panel + fk * CHR_LDP + CH_NB * (ti[e] - j) + fi;
-      const double* pb = panel + fk * CHR_LDP + CH_NB * (tj[e] - j) + fi;
+  for (int e = 0; e < CHR_UT; ++e)
+    if (tile[e] >= 0) {  // uniform
+      chol_border(acc[e], b, shift, tile[e] >> 4, tile[e] & 15);
+      hand(tile[e], 0, acc[e]);
+    }
+  for (int j = 0; j < nb; ++j) {
+    __syncthreads();  // A
+    f64x4_t m;
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
-        acc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(-pa[4 * s * CHR_LDP], pb[4 * s * CHR_LDP], acc[e], 0, 0, 0);
+    for (int v = 0; v < 4; ++v) m[v] = s.m[(4 * v + fk) * CHR_ML + fi];
+#pragma unroll
+    for (int e = 0; e < CHR_UT; ++e) {
+      int t = tile[e];
+      asm("" : "+s"(t));
+      if (t >> 4 != j || t == 17 * j) continue;  // uniform
+      const f64x4_t x = chol_mul(m, acc[e], f64x4_t{0.0, 0.0, 0.0, 0.0});
+#pragma unroll
+      for (int v = 0; v < 4; ++v) s.panel[t & 15][64 * v + lane] = x[v];
+      const int c = CH_NB * (t & 15) + fi;
+      double* const w = W + (CH_NB * j + fk) * b + c;
+      if (c < b) {  // (a row block with another one behind it is whole)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) w[4 * v * b] = x[v];
+      }
+    }
+    if (wave == CHR_W && CH_NB * j + fi < b) {  // element (4 v + fk, fi) of R_jj^-1
+      double* const w = W + CH_NB * j * b + CH_NB * j + fi;
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (CH_NB * j + 4 * v + fk < b) w[(4 * v + fk) * b] = m[v];
+    }
+    __syncthreads();  // B: row j of R is in LDS
+#pragma unroll
+    for (int e = 0; e < CHR_UT; ++e) {
+      int t = tile[e];
+      asm("" : "+s"(t));  // (LDS addresses are formed here, not kept in registers across panels)
+      if (t < 16 * (j + 1) || t == 17 * (j + 1)) continue;  // uniform; (j + 1, j + 1): wave 0 has it
+      const double* const pi = s.panel[t >> 4] + lane;
+      const double* const pj = s.panel[t & 15] + lane;
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        acc[e] = __builtin_amdgcn_mfma_f64_16x16x4f64(-pi[64 * v], pj[64 * v], acc[e], 0, 0, 0);
+      hand(t, j + 1, acc[e]);
     }
   }
 }
 
 __global__ __launch_bounds__(1024) void chol_upper_reg_kernel(double* W, int b, double shift_rel, int* flag) {
-  extern __shared__ __align__(16) unsigned char chol_smem[];
-  double* panels = reinterpret_cast<double*>(chol_smem);  // [2][CH_NB][CHR_LDP]
-  __shared__ double s_red[16];
+  __shared__ CholRegLds s;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const double mx = chol_diag_max(W, b, s_red);
+  const double mx = chol_diag_max(W, b, s.red);
   const double shift = shift_rel * mx, tiny = 1e-300 + 1e-30 * mx;
-  if (wave < CHR_PW) chol_reg_wave<true>(panels, W, b, shift, tiny, wave, flag);
-  else chol_reg_wave<false>(panels, W, b, shift, tiny, wave, flag);
+  if (wave == 0) chol_pivot_wave(s, W, b, shift, tiny, flag);
+  else chol_tile_wave(s, W, b, shift, wave);
 }
 
 // 256 < b <= 1024: the trailing matrix stays in memory; its tiles are dealt to the 16 waves four at a time so that their
@@ -199,7 +388,7 @@ __global__ __launch_bounds__(1024) void chol_upper_kernel(double* W, int b, doub
         panel[u * ldp + c] = v;
       }
     __syncthreads();
-    for (int g = wave; g == 0 || 16 + CH_GRP * g < wpad; g += 16) chol_panel_group(panel, ldp, wpad, g, tiny, W, b, j0, flag);
+    for (int g = wave - 1; g < 0 || 16 + CH_GRP * g < wpad; g += 16) chol_panel_group(panel, ldp, wpad, g, tiny, W, b, j0, flag);
     __syncthreads();
     // trailing update, tile (I, J), I <= J, of the 16 x 16 blocks behind the panel:
     // W[i][c] -= sum_t R[t][i] R[t][c].  Lane (fi, fk) holds A(m = fi, k = fk), B(k = fk, n = fi);
@@ -247,137 +436,115 @@ __global__ __launch_bounds__(1024) void chol_upper_kernel(double* W, int b, doub
   }
 }
 
-// dst (rows x n, fp32) = src * R^-1 for the upper-triangular R (row-major n x n fp64, upper part):
-// forward substitution along the columns, 16 rows per workgroup held in LDS, 16 threads per row
-// (a row never spans two waves).  R is staged through LDS 16 rows at a time as fp32, with the
-// reciprocal of the diagonal, so that the substitution loop never waits for global memory.
-constexpr int TR_ROWS = 16, TR_CH = 16;
-__global__ __launch_bounds__(256) void trsm_right_upper_kernel(const float* __restrict__ src, const double* __restrict__ R,
+// dst (rows x n, fp32) = src * R^-1 for the upper-triangular R (row-major n x n fp64, its 16 x 16 diagonal blocks inverted),
+// in fp64 on the matrix cores.  A workgroup of eight waves solves 16 rows, as the transpose R^-T src^T: wave w holds the column
+// tiles w, w + 8, ... of its rows as 16 x 16 accumulators Z_J (a result's registers are its operand layout, see above).  Step j:
+// X_j = R_jj^-T Z_j, then Z_J -= R_jJ^T X_j for every J > j.  The wave that holds tile j + 1 updates it first, solves it and
+// puts X_{j+1} into LDS before it updates its other tiles, so the chain of a step is eight matrix instructions and one trip through
+// LDS; the parts of R for step j + 1 are requested a step ahead.  Within a tile, hardware index 4 a + b stands for
+// column 4 b + a: a lane then holds four neighbouring columns of its row.
+// 18.5 us at 2048 x 256, 9 us at 2048 x 128 (42 / 16.5 us in fp32 on the vector units, columns of R staged through LDS); R's lines not
+// requested ahead 64 us.
+constexpr int TR_ROWS = 16, TR_W = 8;
+template <int NT>
+__global__ __launch_bounds__(64 * TR_W) void trsm_right_upper_kernel(const float* __restrict__ src, const double* __restrict__ R,
                                                                float* __restrict__ dst, int64_t rows, int n) {
-  extern __shared__ __align__(16) unsigned char trsm_smem[];
-  float* y = reinterpret_cast<float*>(trsm_smem);  // [TR_ROWS][n]
-  float* rch = y + TR_ROWS * n;                    // [TR_CH][n]: rows t0 .. t0+15 of R, diagonal inverted
-  const int tid = threadIdx.x, r = tid >> 4, cl = tid & 15;
-  const int64_t row = (int64_t)blockIdx.x * TR_ROWS + r;
-  const bool ok = row < rows;
-  for (int c = cl; c < n; c += 16) y[r * n + c] = ok ? src[row * n + c] : 0.f;
-  for (int t0 = 0; t0 < n; t0 += TR_CH) {
-    const int nt = min(TR_CH, n - t0);
-    __syncthreads();  // previous chunk fully used (and y loaded)
-    for (int e = tid; e < nt * n; e += 256) {
-      const int u = e / n, c = e % n;
-      const double v = c >= t0 + u ? R[(int64_t)(t0 + u) * n + c] : 0.0;
-      rch[u * n + c] = c == t0 + u ? (float)(1.0 / v) : (float)v;
-    }
-    __syncthreads();
-    for (int u = 0; u < nt; ++u) {
-      const int t = t0 + u;
-      const float vt = y[r * n + t] * rch[u * n + t];
-      __builtin_amdgcn_wave_barrier();
-      if (cl == 0) y[r * n + t] = vt;
-      for (int c = t + 1 + cl; c < n; c += 16) y[r * n + c] -= vt * rch[u * n + c];
-      __syncthreads();
-    }
-  }
-  if (ok)
-    for (int c = cl; c < n; c += 16) dst[row * n + c] = y[r * n + c];
-}
-
-// value of x in lane U of each row of 16 lanes
-template <int U>
-__device__ __forceinline__ float row_share(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x150 + U, 0xf, 0xf, false));
-}
-
-// steps U .. 15 of chunk JC (columns 16 JC .. 16 JC + 15) of the register-resident triangular solve
-// (see the kernel below)
-template <int U, int JC, int NPT>
-__device__ __forceinline__ void trsm_steps(float (&y)[NPT], const float* __restrict__ rch, int nt, int cl) {
-  if constexpr (U < 16) {
-    if (U < nt) {  // uniform
-      // no per-element conditions: the staged rows are zero past column n, so every read and
-      // multiply-add below is unconditional and the reads of a step are issued together
-      const float* ru = rch + U * (16 * NPT);
-      const float vt = row_share<U>(y[JC]) * ru[16 * JC + U];
-      const float upd = y[JC] - vt * ru[16 * JC + cl];
-      y[JC] = cl == U ? vt : (cl > U ? upd : y[JC]);
+  __shared__ double s_x[2][256];
+  const int lane = threadIdx.x & 63, fi = lane & 15, fk = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nb = (n + 15) / 16;
+  const int64_t row = (int64_t)blockIdx.x * TR_ROWS + fi;
+  const float* const srow = src + (row < rows ? row : rows - 1) * n;
+  // R was written by one compute unit a moment ago and is in no L2 but perhaps its own: ask for every line of its upper half at once,
+  // instead of meeting a trip to memory at every step
+  double touched = 0.0;
+  for (int i = 4 * wave + fk; i < n; i += 4 * TR_W)
+    for (int c = 16 * fi; c < n; c += 256)
+      if (c + 15 >= i) touched += R[i * n + c];
+  const int pfi = 4 * (fi & 3) + (fi >> 2);  // the column that hardware index fi stands for
+  f64x4_t z[NT];
 #pragma unroll
-      for (int j = JC + 1; j < NPT; ++j) y[j] -= vt * ru[cl + 16 * j];
-      trsm_steps<U + 1, JC, NPT>(y, rch, nt, cl);
+  for (int t = 0; t < NT; ++t) {
+    const int c = 16 * (wave + TR_W * t) + 4 * fk;
+    if (c + 4 <= n) {
+      const f32x4_el v = *reinterpret_cast<const f32x4_el*>(srow + c);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) z[t][q] = (double)v[q];
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) z[t][q] = c + q < n ? (double)srow[c + q] : 0.0;
     }
   }
-}
-
-// row t0 + r of R, columns cl, cl + 16, ... into registers (thread (r, cl) of the workgroup)
-template <int NPT>
-__device__ __forceinline__ void trsm_fetch(double (&nx)[NPT], const double* __restrict__ R, int n, int t0, int r, int cl) {
+  // block (I, J) of R as the operand of Z_J: element k = 4 v + fk, m = fi, i.e. row 16 I + 4 fk + v, column 16 J + pfi
+  auto load_r = [&](int I, int J) __attribute__((always_inline)) {
+    const int c = 16 * J + pfi, r0 = 16 * I + 4 * fk;
+    // (past n: other elements of R, whose products end in columns that are not stored and are zeroed before the last block is
+    // solved; no selects here, the loaded registers are not to be touched before their step)
+    const int cc = min(c, n - 1);
+    auto at = [&](int r) { return R[min(r, n - 1) * n + cc]; };
+    return f64x4_t{at(r0), at(r0 + 1), at(r0 + 2), at(r0 + 3)};
+  };
+  auto put = [&](int j, const f64x4_t& x) __attribute__((always_inline)) {
 #pragma unroll
-  for (int j = 0; j < NPT; ++j) {
-    const int c = cl + 16 * j, t = t0 + r;
-    nx[j] = (t < n && c < n && c >= t) ? R[(int64_t)t * n + c] : 0.0;
+    for (int v = 0; v < 4; ++v) s_x[j & 1][64 * v + lane] = -x[v];
+  };
+  const f64x4_t zero = {0.0, 0.0, 0.0, 0.0};
+  if (wave == 0) {
+    z[0] = chol_mul(load_r(0, 0), z[0], zero);
+    put(0, z[0]);
   }
-}
-
-// ... and from there into LDS as fp32, the diagonal inverted
-template <int NPT>
-__device__ __forceinline__ void trsm_stage(const double (&nx)[NPT], float* rch, int n, int t0, int r, int cl) {
+  f64x4_t r[NT], d;  // blocks (j, J) of this wave's tiles, and its next diagonal block
 #pragma unroll
-  for (int j = 0; j < NPT; ++j) {
-    const int c = cl + 16 * j;
-    double v = nx[j];  // zero below the diagonal and past row / column n
-    if (c == t0 + r) v = c < n ? 1.0 / v : 0.0;
-    rch[r * (16 * NPT) + c] = (float)v;
-  }
-}
-
-// chunks JC .. NPT-1: the 16 steps of chunk JC run while the rows of R for chunk JC + 1 are in flight
-template <int JC, int NPT>
-__device__ __forceinline__ void trsm_chunks(float (&y)[NPT], double (&nx)[NPT], float* rch, const double* __restrict__ R,
-                                            int n, int r, int cl) {
-  if constexpr (JC < NPT) {
-    constexpr int t0 = 16 * JC;
-    if (t0 < n) {  // uniform
-      const int nt = min(16, n - t0);
-      __syncthreads();  // previous chunk fully used
-      trsm_stage<NPT>(nx, rch, n, t0, r, cl);
-      __syncthreads();
-      if (t0 + 16 < n) trsm_fetch<NPT>(nx, R, n, t0 + 16, r, cl);
-      trsm_steps<0, JC, NPT>(y, rch, nt, cl);
-      trsm_chunks<JC + 1, NPT>(y, nx, rch, R, n, r, cl);
+  for (int t = 0; t < NT; ++t)
+    if (wave + TR_W * t < nb) r[t] = load_r(0, wave + TR_W * t);
+  const int first = min(wave == 0 ? TR_W : wave, nb - 1);
+  d = load_r(first, first);
+  chol_static_for<NT>([&](auto tc) {
+    constexpr int T = decltype(tc)::value;
+#pragma unroll 1
+    for (int q = 0; q < TR_W; ++q) {
+      const int j = TR_W * T + q;
+      if (j + 1 >= nb) break;  // uniform
+      __syncthreads();  // X_j is in LDS
+      f64x4_t x;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) x[v] = s_x[j & 1][64 * v + lane];
+      auto step = [&](auto uc) {
+        constexpr int U = decltype(uc)::value;
+        const int J = wave + TR_W * U;
+        if (J <= j || J >= nb) return;  // uniform
+        z[U] = chol_mul(r[U], x, z[U]);
+        r[U] = load_r(j + 1, J);  // (not needed again if the tile is solved now)
+        if (J == j + 1) {
+          if (16 * (J + 1) > n) {  // uniform
+#pragma unroll
+            for (int v = 0; v < 4; ++v) z[U][v] = 16 * J + 4 * fk + v < n ? z[U][v] : 0.0;
+          }
+          z[U] = chol_mul(d, z[U], zero);
+          put(j + 1, z[U]);
+          const int D = min(J + TR_W, nb - 1);
+          d = load_r(D, D);
+        }
+      };
+      chol_static_for<NT - T>([&](auto uc) { step(std::integral_constant<int, T + decltype(uc)::value>{}); });
     }
-  }
-}
-
-// dst (rows x n, fp32) = src * R^-1 as above for n <= 16 NPT, with the rows of y in registers: 16
-// threads per row, thread cl holds columns cl, cl + 16, ...  Step t multiplies column t by
-// 1 / R[t][t] (a DPP row share broadcasts it to the row's 16 lanes) and subtracts it, times row t of
-// R, from the columns to its right.  No barrier and no LDS round trip per step.  Chunks and steps
-// are unrolled, so every register index and every broadcast lane is a constant.  R is staged
-// through LDS 16 rows at a time as fp32 with the diagonal inverted (two barriers per chunk), the
-// next chunk's rows being fetched while the current chunk's steps run.
-template <int NPT>
-__global__ __launch_bounds__(256) void trsm_right_upper_reg_kernel(const float* __restrict__ src,
-                                                                   const double* __restrict__ R, float* __restrict__ dst,
-                                                                   int64_t rows, int n) {
-  extern __shared__ __align__(16) unsigned char trsm_smem[];
-  float* rch = reinterpret_cast<float*>(trsm_smem);  // [TR_CH][16 NPT]: rows t0 .. t0+15 of R, diagonal inverted, zero padded
-  const int tid = threadIdx.x, r = tid >> 4, cl = tid & 15;
-  const int64_t row = (int64_t)blockIdx.x * TR_ROWS + r;
-  const bool ok = row < rows;
-  float y[NPT];
+  });
+  asm volatile("" : : "v"(touched));
+  if (row < rows) {
+    float* const drow = dst + row * n;
 #pragma unroll
-  for (int j = 0; j < NPT; ++j) {
-    const int c = cl + 16 * j;
-    y[j] = (ok && c < n) ? src[row * n + c] : 0.f;
-  }
-  double nx[NPT];
-  trsm_fetch<NPT>(nx, R, n, 0, r, cl);
-  trsm_chunks<0, NPT>(y, nx, rch, R, n, r, cl);
-  if (ok) {
+    for (int t = 0; t < NT; ++t) {
+      const int c = 16 * (wave + TR_W * t) + 4 * fk;
+      if (c + 4 <= n) {
+        f32x4_el v;
 #pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-      const int c = cl + 16 * j;
-      if (c < n) dst[row * n + c] = y[j];
+        for (int q = 0; q < 4; ++q) v[q] = (float)z[t][q];
+        *reinterpret_cast<f32x4_el*>(drow + c) = v;
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (c + q < n) drow[c + q] = (float)z[t][q];
+      }
     }
   }
 }
@@ -740,17 +907,13 @@ FitWs plan_fit(int64_t d, int k, int r, const prac_fit_opts& o, int n_cu, bool n
   return w;
 }
 
-// the two panel kernels keep up to 128 KB / 64 KB in LDS (n <= 1024)
+// the Cholesky of wide blocks keeps up to 128 KB in LDS (n <= 1024)
 int set_dyn_smem(prac_ctx* ctx) {
   static bool done_dev[PRAC_MAX_DEVICES] = {};  // the attribute is per device
   bool& done = done_dev[ctx->device % PRAC_MAX_DEVICES];
   if (!done) {
     PRAC_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(chol_upper_kernel),
                                           hipFuncAttributeMaxDynamicSharedMemorySize, CH_NB * (CH_MAX + 2) * 8));
-    PRAC_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(chol_upper_reg_kernel),
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, 2 * CH_NB * CHR_LDP * 8));
-    PRAC_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(trsm_right_upper_kernel),
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, (TR_ROWS + TR_CH) * 1024 * 4));
     done = true;
   }
   return PRAC_OK;
@@ -804,24 +967,15 @@ int cholqr_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int
   if (rc) return rc;
   if (n > CH_MAX) return PRAC_EUNSUPPORTED;
   if (n <= CHR_MAX)
-    hipLaunchKernelGGL(chol_upper_reg_kernel, dim3(1), dim3(1024), (size_t)2 * CH_NB * CHR_LDP * sizeof(double), ctx->stream,
-                       W64, n, shift, ctx->d_flag);
+    hipLaunchKernelGGL(chol_upper_reg_kernel, dim3(1), dim3(1024), 0, ctx->stream, W64, n, shift, ctx->d_flag);
   else
     hipLaunchKernelGGL(chol_upper_kernel, dim3(1), dim3(1024),
                        (size_t)CH_NB * (round_up64(n, CH_NB) + 2) * sizeof(double), ctx->stream, W64, n, shift, ctx->d_flag);
-  const dim3 tgrid((unsigned)((d + TR_ROWS - 1) / TR_ROWS));
-  if (n <= 128)
-    hipLaunchKernelGGL(trsm_right_upper_reg_kernel<8>, tgrid, dim3(256), (size_t)TR_CH * 128 * sizeof(float), ctx->stream,
-                       src, W64, dst, d, n);
-  else if (n <= 256)
-    hipLaunchKernelGGL(trsm_right_upper_reg_kernel<16>, tgrid, dim3(256), (size_t)TR_CH * 256 * sizeof(float), ctx->stream,
-                       src, W64, dst, d, n);
-  else if (n <= 512)
-    hipLaunchKernelGGL(trsm_right_upper_reg_kernel<32>, tgrid, dim3(256), (size_t)TR_CH * 512 * sizeof(float), ctx->stream,
-                       src, W64, dst, d, n);
-  else
-    hipLaunchKernelGGL(trsm_right_upper_kernel, tgrid, dim3(256), (size_t)(TR_ROWS + TR_CH) * n * sizeof(float),
-                       ctx->stream, src, W64, dst, d, n);
+  const dim3 tgrid((unsigned)((d + TR_ROWS - 1) / TR_ROWS)), tblock(64 * TR_W);
+  if (n <= 128) hipLaunchKernelGGL(trsm_right_upper_kernel<1>, tgrid, tblock, 0, ctx->stream, src, W64, dst, d, n);
+  else if (n <= 256) hipLaunchKernelGGL(trsm_right_upper_kernel<2>, tgrid, tblock, 0, ctx->stream, src, W64, dst, d, n);
+  else if (n <= 512) hipLaunchKernelGGL(trsm_right_upper_kernel<4>, tgrid, tblock, 0, ctx->stream, src, W64, dst, d, n);
+  else hipLaunchKernelGGL(trsm_right_upper_kernel<8>, tgrid, tblock, 0, ctx->stream, src, W64, dst, d, n);
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
 }

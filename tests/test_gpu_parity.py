@@ -872,6 +872,19 @@ def test_fit_basis_block_orthonormalisation_widths(ctx, r):
     assert np.abs(got.T @ got - np.eye(r)).max() < 1e-5
 
 
+@pytest.mark.parametrize("r", [15, 33, 113, 128, 129, 224, 225, 240, 241, 255, 511, 513, 1000])
+def test_fit_basis_orthonormalisation_at_tile_edges(ctx, r):
+    # block counts around each form of the factorisation (tiles beside the pivot wave from 225 columns on) and of the
+    # triangular solve (1, 2, 4, 8 column tiles per wave: 128, 256, 512), partial last blocks, and a partial last row tile
+    d = 1101
+    P, _, _ = ctx.fit_basis(None, 0, r, seed=4, draw=1, d=d, P=torch.zeros((d, r), dtype=torch.float32, device=DEV), pack=False)
+    ctx.sync_status()
+    got = si.as_f64(P)
+    assert np.abs(got.T @ got - np.eye(r)).max() < 1e-5
+    if r <= 255:  # (up to where Q2's own conditioning keeps it within the draw's 4e-6 of the oracle's)
+        assert np.abs(got - orc.complement_basis(np.zeros((d, 0)), orc.gaussian_matrix(4, 1, d, r))).max() < 2e-5
+
+
 @pytest.mark.parametrize("b", [9, 16, 17, 32, 33, 48, 255, 257, 320])
 def test_fit_basis_ritz_block_widths(ctx, b):
     # the eigen-iteration at block widths of one column block, of two, of an odd number, with a partial last one, and
