@@ -603,7 +603,7 @@ __global__ __launch_bounds__(1024) void symmetrize64_kernel(double* H, int b, do
 // The rotation that makes columns p and q orthogonal, from their squared norms al, be and inner product ga:
 // p' = cs p - sn q, q' = sn p + cs q.  True if the pair needs one (|ga| > tol sqrt(al be), compared as squares).  The angle may
 // be approximate (the iteration corrects it), so tan comes from the hardware reciprocal / square root estimates; (cs, sn)
-// must be a rotation to full precision, so cs = (1 + tan^2)^-1/2 gets Newton steps on top of its estimate.
+// must be a rotation to full precision, so cs = (1 + tan^2)^-1/2 gets a third-order step on top of its estimate (2^-23, cubed).
 __device__ __forceinline__ bool needs_rotation(double al, double be, double ga, double tol) {
   return ga * ga > tol * tol * al * be && fabs(ga) > 1e-300;
 }
@@ -613,21 +613,46 @@ __device__ __forceinline__ void rotation(double al, double be, double ga, double
   const double tt = copysign(__builtin_amdgcn_rcp(az + __builtin_amdgcn_sqrt(1.0 + az * az)), zeta);
   const double w = 1.0 + tt * tt;
   double c = __builtin_amdgcn_rsq(w);
-  c = c * (1.5 - 0.5 * w * c * c);
-  c = c * (1.5 - 0.5 * w * c * c);
+  const double e = fma(-w * c, c, 1.0);
+  c = fma(c * e, fma(e, 0.375, 0.5), c);
   const bool rot = needs_rotation(al, be, ga, tol);
   cs = rot ? c : 1.0;
   sn = rot ? c * tt : 0.0;
 }
 
-// 8 waves: 0 - 3 rotate the Gram matrix (thread (i, j): the 2 x 2 block of column pairs i and j), 4 - 7 the accumulated
-// rotation; every thread computes the angles it needs itself, so an inner step is one barrier long.
-// 29 us per launch at b = 256 (31 inner steps of 0.7 us: the latency of one angle and its LDS round trip), 7 us without a
-// rotation; 54 us with the columns themselves in LDS, where every inner step moved all 64 KB of them.  Six to seven
-// sweeps, so 2.7 against 5.0 ms.
+// x of lane g of lane row g, in every lane of that row
+__device__ __forceinline__ double row_diag_f64(double x) {
+  double r;
+  asm volatile(
+      "s_nop 1\n"
+      "v_mov_b64_dpp %0, %1 row_newbcast:0 row_mask:0x1 bank_mask:0xf\n"
+      "v_mov_b64_dpp %0, %1 row_newbcast:1 row_mask:0x2 bank_mask:0xf\n"
+      "v_mov_b64_dpp %0, %1 row_newbcast:2 row_mask:0x4 bank_mask:0xf\n"
+      "v_mov_b64_dpp %0, %1 row_newbcast:3 row_mask:0x8 bank_mask:0xf\n"
+      : "=&v"(r) : "v"(x));
+  return r;
+}
+// x of a neighbouring lane of the row of 16 (CTRL 0x101: the next one, 0x111: the one before; `edge` where there is none;
+// 0x12f: the next one, lane 0 for the last)
+template <int CTRL>
+__device__ __forceinline__ double row_shift_f64(double x, double edge) {
+  return __hiloint2double(
+      __builtin_amdgcn_update_dpp(__double2hiint(edge), __double2hiint(x), CTRL, 0xf, 0xf, false),
+      __builtin_amdgcn_update_dpp(__double2loint(edge), __double2loint(x), CTRL, 0xf, 0xf, false));
+}
+
+// 8 waves: 0 - 3 rotate the Gram matrix in LDS (a step reads one buffer and writes the other: one barrier), 4 - 7 the
+// accumulated rotation in registers.  What bounds it is the issue of a step's instructions (two waves per SIMD) and one round trip
+// through LDS, so no address is computed in it, and a row of 16 lanes passes its rotations on by DPP.
+// At b = 256: 21 us per launch with all pairs, 16 us across the blocks, 7 us without a rotation (29 us before, with every address and
+// every thread's rotations computed in the step); 1.7 ms for the seven sweeps of the first step's fit, 2.7 before.
 constexpr int JB_NB = 16, JB_M = 2 * JB_NB;   // columns per block and per workgroup
 constexpr int JB_CW = 256, JB_CS = JB_CW + 4; // elements of each column in LDS at a time, their pitch
 constexpr int JB_GS = JB_M + 1;               // pitch of the Gram matrices and of J
+// Every fifth launch of a sweep rotates all pairs of its 32 columns, the others those across the two blocks: half the inner steps.
+// (Simulated on three spectra of the cases at b = 256, launches weighted by their times: every launch full 1.67 - 1.81 ms in six to seven
+// sweeps, every third 1.38 - 1.52, every fifth 1.32 - 1.47, the first of a sweep only 1.61 in eight.)
+constexpr int JB_FULL = 5;
 constexpr size_t JB_SMEM = (size_t)(JB_M * JB_CS + 4 * JB_M * JB_GS) * sizeof(double);
 __global__ __launch_bounds__(512) void jacobi_block_kernel(double* H, int b, int nblk_even, int step, int sweep, int inner_sweeps,
                                                            double tol, unsigned* counts, const double* hmax) {
@@ -635,6 +660,7 @@ __global__ __launch_bounds__(512) void jacobi_block_kernel(double* H, int b, int
   double* cols = reinterpret_cast<double*>(jac_smem);  // [JB_M][JB_CS]: one chunk of the columns
   double* gram = cols + JB_M * JB_CS;                  // [3][JB_M][JB_GS]
   double* J = gram + 3 * JB_M * JB_GS;                 // [JB_M][JB_GS]: new column c = sum_l J[l][c] column l
+  __shared__ double2 cs_lds[32];                       // cosines and sines of this step and the one before
   if (sweep > 0 && counts[sweep - 1] == 0) return;  // converged in the previous sweep
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int fi = lane & 15, fk = lane >> 4;
@@ -674,13 +700,14 @@ __global__ __launch_bounds__(512) void jacobi_block_kernel(double* H, int b, int
   // rotated but does not count towards convergence: such a column is rounding noise and its cosines never settle
   const double floor2 = 1e-26 * *hmax * *hmax;
   bool rot = false, counted = false;
+  const bool full = step % JB_FULL == 0;
+  auto place = [&](int l) { return l < 16 || !full ? l : 16 + (JB_M - 1 - l); };  // of column l when the inner tournament starts
 #pragma unroll
   for (int e = 0; e < 2; ++e) {
     const int r = (tid >> 5) + 16 * e, c = tid & 31;
     auto g = [&](int i, int j) { return gram[i * JB_GS + j] + gram[(JB_M + i) * JB_GS + j]; };
     const double ga = g(r, c), al = g(r, r), be = g(c, c);
-    gram[(2 * JB_M + r) * JB_GS + c] = ga;
-    J[r * JB_GS + c] = r == c ? 1.0 : 0.0;
+    gram[(2 * JB_M + place(r)) * JB_GS + place(c)] = ga;
     if (r < c && needs_rotation(al, be, ga, tol)) {
       rot = true;
       counted = counted || fmin(al, be) > floor2;
@@ -689,49 +716,78 @@ __global__ __launch_bounds__(512) void jacobi_block_kernel(double* H, int b, int
   const bool any_counted = __syncthreads_or(counted);
   if (!__syncthreads_or(rot)) return;
   if (any_counted && tid == 0) atomicAdd(&counts[sweep], 1u);
-  const double* cur = gram + 2 * JB_M * JB_GS;
-  double* nxt = gram;
-  const int t = tid & 255, i = t >> 4, j = t & 15;
-  for (int it = 0; it < inner_sweeps; ++it)
-    for (int s = 0; s < JB_M - 1; ++s) {
-      int pj, qj;
-      tournament_pair(s, j, JB_M, pj, qj);
+  // Inner tournament.  The 32 players sit in places, pair j in places j and 16 + j, and move on after a step.  All pairs (`full`):
+  // place j -> j - 1 (0 -> 17) and 16 + j -> 16 + j + 1 (31 -> 15; 16 stays), 31 steps.  Pairs across the two blocks only: the
+  // lower places stay, 16 + j -> 16 + j - 1 (16 -> 31), 16 steps.  Then everybody is home.  The matrix is kept by place, so a
+  // thread's addresses never change.
+  const int steps = full ? inner_sweeps * (JB_M - 1) : JB_NB;
+  if (wave < 4) {
+    // thread (i, j): the 2 x 2 block of row pair i and column pair j.  Lane l of a row holds j = l + 4 wave (mod 16), so that the
+    // rotation of row pair i = 4 wave + g is in lane g of lane row g.
+    const int i = 4 * wave + (lane >> 4), j = ((lane & 15) + 4 * wave) & 15;
+    auto next_top = [&](int x) { return full ? (x == 0 ? 17 : x - 1) : x; };
+    auto next_bottom = [&](int x) { return full ? (x == 0 ? 16 : (x == 15 ? 15 : 17 + x)) : 16 + ((x + 15) & 15); };
+    const int r_al = j * JB_GS + j, r_be = (16 + j) * JB_GS + 16 + j, r_ga = j * JB_GS + 16 + j;
+    const int r_a = i * JB_GS + j, r_c = (16 + i) * JB_GS + j;
+    const int ti = next_top(i), tj = next_top(j), bi = next_bottom(i), bj = next_bottom(j);
+    const int w_tt = ti * JB_GS + tj, w_bt = bi * JB_GS + tj, w_tb = ti * JB_GS + bj, w_bb = bi * JB_GS + bj;
+    auto step = [&](const double* cur, double* nxt, double2* cs) {
+      const double al = cur[r_al], be = cur[r_be], ga = cur[r_ga];
+      const double a = cur[r_a], bb = cur[r_a + 16], c = cur[r_c], d = cur[r_c + 16];
       double cj, sj;
-      if (wave < 4) {
-        int pi, qi;
-        tournament_pair(s, i, JB_M, pi, qi);
-        const double alj = cur[pj * JB_GS + pj], bej = cur[qj * JB_GS + qj], gaj = cur[pj * JB_GS + qj];
-        const double ali = cur[pi * JB_GS + pi], bei = cur[qi * JB_GS + qi], gai = cur[pi * JB_GS + qi];
-        const double a = cur[pi * JB_GS + pj], bb = cur[pi * JB_GS + qj];
-        const double c = cur[qi * JB_GS + pj], d = cur[qi * JB_GS + qj];
-        double ci, si;
-        rotation(alj, bej, gaj, tol, cj, sj);
-        rotation(ali, bei, gai, tol, ci, si);
-        const double a1 = cj * a - sj * bb, b1 = sj * a + cj * bb, c1 = cj * c - sj * d, d1 = sj * c + cj * d;
-        nxt[pi * JB_GS + pj] = ci * a1 - si * c1;
-        nxt[qi * JB_GS + pj] = si * a1 + ci * c1;
-        nxt[pi * JB_GS + qj] = ci * b1 - si * d1;
-        nxt[qi * JB_GS + qj] = si * b1 + ci * d1;
-      } else {
-        double x[2], y[2];
+      rotation(al, be, ga, tol, cj, sj);
+      if (wave == 0 && lane < 16) cs[j] = make_double2(cj, sj);
+      const double ci = row_diag_f64(cj), si = row_diag_f64(sj);
+      const double a1 = cj * a - sj * bb, b1 = sj * a + cj * bb, c1 = cj * c - sj * d, d1 = sj * c + cj * d;
+      nxt[w_tt] = ci * a1 - si * c1;
+      nxt[w_bt] = si * a1 + ci * c1;
+      nxt[w_tb] = ci * b1 - si * d1;
+      nxt[w_bb] = si * b1 + ci * d1;
+      __syncthreads();
+    };
+    double* const g0 = gram + 2 * JB_M * JB_GS;
+    for (int s = 0; s + 1 < steps; s += 2) {
+      step(g0, gram, cs_lds);
+      step(gram, g0, cs_lds + 16);
+    }
+    if (steps & 1) step(g0, gram, cs_lds);
+  } else {
+    // The accumulated rotation J stays in registers, two of its rows per lane row, lane j the columns of the players in places j and
+    // 16 + j, and follows one step behind.
+    const int j = lane & 15, r0 = 8 * (wave - 4) + 2 * (lane >> 4), home = full ? JB_M - 1 - j : JB_NB + j;
+    double x[2], y[2];
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          x[e] = J[(i + 16 * e) * JB_GS + pj];
-          y[e] = J[(i + 16 * e) * JB_GS + qj];
-        }
-        rotation(cur[pj * JB_GS + pj], cur[qj * JB_GS + qj], cur[pj * JB_GS + qj], tol, cj, sj);
+    for (int e = 0; e < 2; ++e) {
+      x[e] = r0 + e == j ? 1.0 : 0.0;
+      y[e] = r0 + e == home ? 1.0 : 0.0;
+    }
+    auto step = [&](const double2* cs) {
+      __syncthreads();
+      const double2 r = cs[j];
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          J[(i + 16 * e) * JB_GS + pj] = cj * x[e] - sj * y[e];
-          J[(i + 16 * e) * JB_GS + qj] = sj * x[e] + cj * y[e];
+      for (int e = 0; e < 2; ++e) {
+        const double p = r.x * x[e] - r.y * y[e], q = r.y * x[e] + r.x * y[e];
+        if (full) {
+          x[e] = row_shift_f64<0x101>(p, q);
+          y[e] = row_shift_f64<0x111>(j == 0 ? p : q, q);
+        } else {
+          x[e] = p;
+          y[e] = row_shift_f64<0x12f>(q, q);
         }
       }
-      __syncthreads();
-      // the two partial-sum buffers are free by now: the matrix alternates between the third and the first
-      double* o = const_cast<double*>(cur);
-      cur = nxt;
-      nxt = o;
+    };
+    for (int s = 0; s + 1 < steps; s += 2) {
+      step(cs_lds);
+      step(cs_lds + 16);
     }
+    if (steps & 1) step(cs_lds);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      J[(r0 + e) * JB_GS + j] = x[e];
+      J[(r0 + e) * JB_GS + home] = y[e];
+    }
+  }
+  __syncthreads();
   // columns <- J^T columns, 32 elements of every column per wave and chunk
   for (int ch = 0; ch < nch; ++ch) {
     if (nch > 1) {

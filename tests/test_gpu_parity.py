@@ -901,6 +901,23 @@ def test_fit_basis_ritz_block_widths(ctx, b):
     assert np.abs(np.abs(np.sum(si.as_f64(P)[:, :k] * Q1, axis=0)) - 1.0).max() < 5e-7
 
 
+@pytest.mark.parametrize("b", [64, 97, 160, 512])
+def test_fit_basis_ritz_vectors_come_out_diagonal_and_ordered(ctx, b):
+    # the eigen-iteration where a sweep holds launches of both kinds (all pairs; pairs across two blocks), on a spectrum without
+    # gaps: Q1^T G Q1 must be diagonal with descending entries.  Off-diagonal cosines: the rotation's 1e-10, the basis' fp32
+    # rounding 2^-24 times the ratio of the extreme Ritz values' roots (here below 9), some roundings: below 1e-5
+    N, d = 2048, 640
+    k = b // 2
+    Xt = si.round_to(si.activation(N, d, 0.4, 11)[0], "f32")
+    P, _, _ = ctx.fit_basis(Xt.to(DEV), k, 8, seed=1, draw=0, oversample=b - k, pack=False)
+    ctx.sync_status()
+    Q = si.as_f64(P)[:, :k]
+    H = Q.T @ orc.gram(si.as_f64(Xt)) @ Q
+    lam = np.diag(H)
+    assert (np.diff(lam) <= 1e-5 * lam[:-1]).all()
+    assert np.abs(H / np.sqrt(np.outer(lam, lam)) - np.eye(k)).max() < 1e-5
+
+
 def test_fit_basis_rac_and_full_complement(ctx):
     d = 96
     # k = 0: purely random basis, scale d / r
