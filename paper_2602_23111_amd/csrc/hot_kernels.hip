@@ -190,41 +190,51 @@ __global__ __launch_bounds__(256) void pack_c_kernel(const bf16_t* __restrict__ 
 struct ReduceTfArgs {
   int n_out, splits, c, k_lo, nkb;
   float scale_hi;
-  const float* slabs[PRAC_CTDY_MAX_OUT];  // [splits][c][m_h]
+  const float* slabs[PRAC_CTDY_MAX_OUT];  // [parts][c][sld_h] from column 128 col0 on
+  int sld[PRAC_CTDY_MAX_OUT];
   bf16_t* Tf[PRAC_CTDY_MAX_OUT];          // [nkb][nmb_h][64][8]
   int m[PRAC_CTDY_MAX_OUT];
   int nmb[PRAC_CTDY_MAX_OUT];
+  int col0, pairs;                        // pairs of column blocks of this launch, from the pair 2 col0 on
+  int tile0[PRAC_CTDY_MAX_OUT], tiles_n;  // column tiles of 128, as C^T dY counts them
+  CtdyTails tails;                        // main == 0: `splits` parts everywhere
   int pair0[PRAC_CTDY_MAX_OUT + 1];       // first pair of column blocks of output h in the launch
 };
 
 __global__ __launch_bounds__(256) void reduce_to_tfrag_kernel(ReduceTfArgs a) {
   __shared__ float patch[16][68];
   const int bid = touch_kernel_args<sizeof(ReduceTfArgs)>(blockIdx.x);
-  const int pairs = a.pair0[a.n_out];
-  const int kb = bid / pairs, gp = bid % pairs;
+  const int kb = bid / a.pairs, gp = 2 * a.col0 + bid % a.pairs;
   int h = 0;
 #pragma unroll
   for (int q = 1; q < PRAC_CTDY_MAX_OUT; ++q)
     if (q < a.n_out && gp >= a.pair0[q]) h = q;
   const int np = gp - a.pair0[h];
   const float* __restrict__ slabs = a.slabs[h];
-  const int m = a.m[h], nmb = a.nmb[h], c = a.c, splits = a.splits;
+  const int m = a.m[h], nmb = a.nmb[h], c = a.c, sld = a.sld[h];
+  // parts of the tile of T that this patch lies in
+  int parts = a.splits;
+  if (a.tails.main > 0)
+    parts = a.tails.main + ctdy_tail_parts(a.tails, kb / 16 * a.tiles_n + min(a.tile0[h] + np / 2, a.tiles_n - 1));
   const int tid = threadIdx.x;
   const int row = tid >> 4, col = (tid & 15) * 4;
   const int k = kb * 16 + row, n = np * 64 + col;
-  const int64_t slab = (int64_t)c * m;
+  const int64_t slab = (int64_t)c * sld;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   if (k < c && n < m) {
-    const float* p = slabs + (int64_t)k * m + n;
-    if (n + 3 < m && (m & 3) == 0) {
+    const float* p = slabs + (int64_t)k * sld + n - 128 * a.col0;
+    if ((sld & 3) == 0) {
 #pragma unroll 8
-      for (int z = 0; z < splits; ++z) {
+      for (int z = 0; z < parts; ++z) {
         // read once
         const f32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(p + z * slab));
         s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
       }
+      if (n + 1 >= m) s.y = 0.f;  // (past m: whatever the last quad's products were)
+      if (n + 2 >= m) s.z = 0.f;
+      if (n + 3 >= m) s.w = 0.f;
     } else {
-      for (int z = 0; z < splits; ++z) {
+      for (int z = 0; z < parts; ++z) {
         s.x += p[z * slab];
         if (n + 1 < m) s.y += p[z * slab + 1];
         if (n + 2 < m) s.z += p[z * slab + 2];
@@ -1060,18 +1070,24 @@ int launch_pack_c(prac_ctx* ctx, const bf16_t* C, int64_t ldc, int N, int c, bf1
 }
 
 int launch_reduce_to_tfrag(prac_ctx* ctx, int n_out, const float* const* slabs, int splits, int c, const int* m, int k_lo,
-                           float scale_hi, int nkb, const int* nmb, bf16_t* const* Tf) {
-  if (n_out < 1 || n_out > PRAC_CTDY_MAX_OUT) return PRAC_EINVAL;
+                           float scale_hi, int nkb, const int* nmb, bf16_t* const* Tf, const int* sld, const CtdyTails& tails,
+                           int col0, int col1) {
+  if (n_out < 1 || n_out > PRAC_CTDY_MAX_OUT || (col0 > 0 && n_out > 1)) return PRAC_EINVAL;
   ReduceTfArgs a{};
-  a.n_out = n_out; a.splits = splits; a.c = c; a.k_lo = k_lo; a.nkb = nkb; a.scale_hi = scale_hi;
+  a.n_out = n_out; a.splits = splits; a.c = c; a.k_lo = k_lo; a.nkb = nkb; a.scale_hi = scale_hi; a.tails = tails;
   int pairs = 0;
   for (int h = 0; h < n_out; ++h) {
-    a.slabs[h] = slabs[h]; a.Tf[h] = Tf[h]; a.m[h] = m[h]; a.nmb[h] = nmb[h];
+    a.slabs[h] = slabs[h]; a.sld[h] = sld[h]; a.Tf[h] = Tf[h]; a.m[h] = m[h]; a.nmb[h] = nmb[h];
     a.pair0[h] = pairs;
+    a.tile0[h] = a.tiles_n;
     pairs += nmb[h] / 2;
+    a.tiles_n += (m[h] + 127) / 128;
   }
   for (int h = n_out; h <= PRAC_CTDY_MAX_OUT; ++h) a.pair0[h] = pairs;
-  PRAC_LAUNCH(ctx, reduce_to_tfrag_kernel, dim3(nkb * pairs), dim3(256), 0, a);
+  a.col0 = col0;
+  a.pairs = (col1 >= a.tiles_n ? pairs : 2 * col1) - 2 * col0;
+  if (a.pairs < 1) return PRAC_EINVAL;
+  PRAC_LAUNCH(ctx, reduce_to_tfrag_kernel, dim3(nkb * a.pairs), dim3(256), 0, a);
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
 }

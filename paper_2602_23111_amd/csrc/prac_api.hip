@@ -720,22 +720,57 @@ constexpr size_t WGRAD_ROOM = PRAC_STATIC_SCRATCH_BYTES - PRAC_SYNC_BYTES;
 // weight gradient: 86 tiles, N = 32768, c = 256 (up and gate) 2 ranges 294 us, 5 ranges 282; 172 tiles, N = 16384, c = 512 one
 // range 307, 4 ranges 295 (90 MB of partial sums, past what a single gradient may use); the rule keeps 16, 5, 4 and 6 ranges for
 // 16, 48, 64 and 40 tiles (next best 3 to 30 us worse).
+struct WgradWork {
+  int64_t tiles = 0, slab = 0;  // 256 x 128 tiles of T, bytes of one set of partial sums
+  WgradWork(int c, int n_out, const int64_t* m) {
+    for (int h = 0; h < n_out; ++h) {
+      tiles += (int64_t)((c + 255) / 256) * ((m[h] + 127) / 128);
+      slab += (int64_t)c * m[h] * 4;
+    }
+  }
+  static double round_us(double tokens) { return 6.0 + 0.0156 * tokens; }
+  double equal_us(int n_cu, int64_t N, int s) const {
+    return (double)((tiles * s + n_cu - 1) / n_cu) * round_us((double)((N + s - 1) / s)) + (double)(2 * slab) * s / 3e6;
+  }
+};
 template <typename Fits>
 int wgrad_splits(int n_cu, int tune_splits, int c, int n_out, const int64_t* m, int64_t N, Fits fits) {
   if (tune_splits > 0) return tune_splits;
-  int64_t tiles = 0, slab = 0;
-  for (int h = 0; h < n_out; ++h) {
-    tiles += (int64_t)((c + 255) / 256) * ((m[h] + 127) / 128);
-    slab += (int64_t)c * m[h] * 4;
-  }
+  const WgradWork w(c, n_out, m);
   const int most = (int)std::max<int64_t>(1, std::min<int64_t>(64, N / 256));
-  int best = (int)std::max<int64_t>(1, std::min<int64_t>(most, n_cu / tiles));
-  auto cost = [&](int s) {
-    return (double)((tiles * s + n_cu - 1) / n_cu) * (6.0 + 0.0156 * (double)((N + s - 1) / s)) + (double)(2 * slab) * s / 3e6;
-  };
+  int best = (int)std::max<int64_t>(1, std::min<int64_t>(most, n_cu / w.tiles));
   for (int s = best + 1; s <= most; ++s)
-    if (cost(s) < cost(best) && fits(s)) best = s;
+    if (w.equal_us(n_cu, N, s) < w.equal_us(n_cu, N, best) && fits(s)) best = s;
   return best;
+}
+
+// Unequal token ranges in one round (see CtdyTails) where they are at least 3 % cheaper than `splits` equal ones.  A helper's next
+// piece costs it what 3 units cost (its stores and its first tile), so main ranges are the shortest that no helper exceeds.
+// Measured, equal ranges against these, C^T dY alone and the whole weight gradient: 86 tiles of
+// 256 units (up and gate) 5 ranges in two rounds 237 / 320 us, unequal 217 / 294; 172 tiles of 128 units (LLaMA-7B up projection)
+// one range 226 / 320, unequal 183 / 281.  Pieces priced at 0, 8 and 16 units instead: 228, 220 and 225 us on the former's
+// C^T dY, 200, 193 and 203 on the latter's (190 with 3, in the same run).
+CtdyTails wgrad_tails(int n_cu, int c, int n_out, const int64_t* m, int64_t N, int splits) {
+  const WgradWork w(c, n_out, m);
+  const int64_t units = (N + 127) / 128;
+  CtdyTails t;
+  t.main = (int)(n_cu / w.tiles);
+  const int64_t idle = n_cu - t.main * w.tiles;
+  if (t.main < 1 || idle < 1) return {};
+  for (int64_t len = (w.tiles * units + n_cu - 1) / n_cu; len * t.main < units; ++len) {
+    const int64_t tail = units - len * t.main, run = (w.tiles * tail + idle - 1) / idle;
+    const int64_t pieces = (run + tail - 2) / tail + 1;
+    if (run + 3 * (pieces - 1) > len) continue;
+    t.len = (int)len;
+    t.tail = (int)tail;
+    t.run = (int)run;
+    t.helpers = (int)((w.tiles * tail + run - 1) / run);
+    t.tail_parts = (int)((tail + run - 2) / run + 1);
+    const double us = WgradWork::round_us(128.0 * (double)len) +
+                      (double)(2 * w.slab) * ((double)t.main + 1.0 + (double)t.helpers / (double)w.tiles) / 3e6;
+    return us < 0.97 * w.equal_us(n_cu, N, splits) ? t : CtdyTails{};
+  }
+  return {};
 }
 
 // bf16 gradients whose rows start on any element: the token-split partial sums of C^T dY come from the streaming kernel
@@ -814,9 +849,13 @@ struct WgradPlan {
   int splits;
   bool fused;  // one launch (see launch_wgrad_fused) instead of three
   bool wide;   // dW = P T by launch_wide_ws
+  CtdyTails tails;  // unequal token ranges (main > 0), else `splits` equal ones
+  int cols;    // column tiles formed at a time (all, unless the partial sums have to fit the static block)
+  int sld[PRAC_CTDY_MAX_OUT];  // row pitch of the partial sums: whole quads, so that they move 16 bytes at a time at any width
   int nkb;     // 16-row k-blocks of T
   int nmb[PRAC_CTDY_MAX_OUT];
   size_t o_part[PRAC_CTDY_MAX_OUT], o_t[PRAC_CTDY_MAX_OUT], o_lp, o_cpk, bytes;
+  size_t equal_bytes;  // what equal ranges with tight partial sums would take: decides what the static entry point refuses
 };
 // dW = P T by the kernel that walks column groups (launch_wide_ws) or by the tiled ones (launch_pt): the former for bf16
 // results that overwrite dW, 128 < c <= 256 and more tiles of 128 x 256 than compute units.  Measured, tiled against
@@ -829,36 +868,59 @@ bool wgrad_wide(int n_cu, int64_t d, int c, int n_out, const int64_t* m, prac_dt
   for (int h = 0; h < n_out; ++h) groups += (m[h] + 255) / 256;
   return (d + 127) / 128 * groups > n_cu;
 }
-WgradPlan layout_wgrad_fast(int64_t N, int64_t d, int c, int n_out, const int64_t* m, int splits, bool packed, bool has_lp,
-                            bool wide) {
+// cols > 0: partial sums of that many column tiles (one output); otherwise of all, with rows of m (tight) or of whole quads
+WgradPlan layout_wgrad_fast(int64_t N, int64_t d, int c, int n_out, const int64_t* m, int splits, const CtdyTails& tails, bool packed,
+                            bool has_lp, bool wide, bool tight, int cols = 0) {
   WgradPlan q{};
   const LpLayout l = lp_layout(d, c);
   q.splits = splits;
+  q.tails = tails;
   q.wide = wide;
   q.nkb = wide ? wide_kblocks(c) : l.nckb;
+  const size_t parts = tails.main > 0 ? tails.main + tails.tail_parts : splits;
   WsPlan plan;
   for (int h = 0; h < n_out; ++h) {
     q.nmb[h] = (int)round_up64((m[h] + 31) / 32, wide ? 8 : 4);  // 32-column blocks of T, whole 256- or 128-column tiles
-    q.o_part[h] = plan.take((size_t)splits * c * m[h] * sizeof(float));
+    q.sld[h] = (int)(cols > 0 ? 128 * cols : tight ? m[h] : round_up64(m[h], 4));
+    q.cols += (int)((m[h] + 127) / 128);
+    q.o_part[h] = plan.take(parts * c * q.sld[h] * sizeof(float));
     q.o_t[h] = plan.take((size_t)q.nkb * q.nmb[h] * 64 * 8 * sizeof(bf16_t));
   }
+  if (cols > 0) q.cols = cols;
   q.o_lp = plan.take(has_lp ? 0 : l.bytes);
   q.o_cpk = plan.take(packed ? 0 : packed_c_bytes(N, c));
   q.bytes = plan.off;
   return q;
 }
-// (whether C is packed and P_lp at hand does not change the ranges, and with them the bits of dW)
+// (whether C is packed and P_lp at hand does not change the ranges, and with them the bits of dW; nor does `room`, in which a
+// single gradient is planned if equal_bytes fits it)
 WgradPlan plan_wgrad_fast(int n_cu, int tune_splits, bool one_launch, int64_t N, int64_t d, int c, int n_out, const int64_t* m,
-                          prac_dtype odt, float beta, bool packed, bool has_lp) {
+                          prac_dtype odt, float beta, bool packed, bool has_lp, size_t room = ~(size_t)0) {
+  const CtdyTails none;
   const int splits = wgrad_splits(n_cu, tune_splits, c, n_out, m, N, [&](int s) {
-    return n_out > 1 || layout_wgrad_fast(N, d, c, n_out, m, s, false, false, wide_kblocks(c) == 16).bytes <= WGRAD_ROOM;
+    return n_out > 1 ||
+           layout_wgrad_fast(N, d, c, n_out, m, s, none, false, false, wide_kblocks(c) == 16, true).bytes <= WGRAD_ROOM;
   });
-  WgradPlan q = layout_wgrad_fast(N, d, c, n_out, m, splits, packed, has_lp, false);
-  q.fused = one_launch && wgrad_fused_takes(n_cu, c, n_out, m, splits);
-  if (!q.fused && wgrad_wide(n_cu, d, c, n_out, m, odt, beta)) {
-    const WgradPlan w = layout_wgrad_fast(N, d, c, n_out, m, splits, packed, has_lp, true);
-    if (n_out > 1 || w.bytes <= WGRAD_ROOM || q.bytes > WGRAD_ROOM) return w;
+  const CtdyTails tails = tune_splits > 0 ? none : wgrad_tails(n_cu, c, n_out, m, N, splits);
+  size_t equal = layout_wgrad_fast(N, d, c, n_out, m, splits, none, packed, has_lp, false, true).bytes;
+  if (tails.main == 0 && one_launch && wgrad_fused_takes(n_cu, c, n_out, m, splits)) {
+    WgradPlan q = layout_wgrad_fast(N, d, c, n_out, m, splits, none, packed, has_lp, false, true);
+    q.fused = true;
+    q.equal_bytes = equal;
+    return q;
   }
+  bool wide = wgrad_wide(n_cu, d, c, n_out, m, odt, beta);
+  if (wide) {
+    const size_t w = layout_wgrad_fast(N, d, c, n_out, m, splits, none, packed, has_lp, true, true).bytes;
+    wide = n_out > 1 || w <= WGRAD_ROOM || equal > WGRAD_ROOM;
+    if (wide) equal = w;
+  }
+  WgradPlan q = layout_wgrad_fast(N, d, c, n_out, m, splits, tails, packed, has_lp, wide, false);
+  if (q.bytes > room && n_out == 1) {
+    int cols = q.cols;
+    while (cols > 1 && q.bytes > room) q = layout_wgrad_fast(N, d, c, n_out, m, splits, tails, packed, has_lp, wide, false, --cols);
+  }
+  q.equal_bytes = equal;
   return q;
 }
 
@@ -911,11 +973,18 @@ int weight_grad_fast(prac_ctx* ctx, char* ws, int* cnt, const WgradPlan& q, cons
                               reinterpret_cast<const bf16_t*>(lp + l.off_pa), (int)d, dW, lddw, odt == PRAC_BF16, beta,
                               cnt);
   }
-  {  // T_h = C^T dY_h as `splits` partial slabs over the token range
+  // T_h = C^T dY_h as partial slabs over token ranges, formed for all column tiles at once or for q.cols of them at a time
+  int tiles = 0;
+  for (int h = 0; h < n_out; ++h) tiles += (mi[h] + 127) / 128;
+  auto ct_dy = [&](int col0, int col1) {
     ProfScope ps(ctx, PRAC_KERNEL_CT_DY);
-    rc = launch_ctdy_ws(ctx, Cpk, c, (int)N, n_out, dYp, lddy, mi, part, splits, false);
-  }
-  if (rc) return rc;
+    return launch_ctdy_ws(ctx, Cpk, c, (int)N, n_out, dYp, lddy, mi, part, splits, false, 0, q.sld, &q.tails, col0, col1);
+  };
+  // T_h in fragment order (bf16): slabs summed, random rows weighted by the scaling factor
+  auto reduce = [&](int col0, int col1) {
+    ProfScope ps(ctx, PRAC_KERNEL_T_REDUCE);
+    return launch_reduce_to_tfrag(ctx, n_out, part, splits, c, mi, k, scale, q.nkb, q.nmb, Tf, q.sld, q.tails, col0, col1);
+  };
   // Slab sum, scaling factor and dW_h = P T_h in one launch where that is the faster form: measured on an
   // MI355X it is for c > 256 (rank 512 + 512 at d = m = 2048: 159 against 179 us per weight gradient), where
   // the two launches move a large T through memory and run the LDS-staged product; at c <= 256 the two
@@ -923,16 +992,20 @@ int weight_grad_fast(prac_ctx* ctx, char* ws, int* cnt, const WgradPlan& q, cons
   // (every 512 rows of dW are one more workgroup per column block that repeats the slab sum: at d = 11008,
   // 22 of them, the one launch takes 180 us against 98 us for the two, so it is limited to d <= 2048)
   const bool tail_one = ctx->tune_tail == 2 || (ctx->tune_tail == 0 && l.nckb > 16 && d <= 2048);  // (never with q.wide: c > 256)
-  if (tail_one && sum_pt_eligible(n_out, mi, splits)) {
+  if (tail_one && q.tails.main == 0 && q.cols >= tiles && sum_pt_eligible(n_out, mi, splits)) {
+    rc = ct_dy(0, tiles);
+    if (rc) return rc;
     ProfScope ps(ctx, PRAC_KERNEL_SUM_P_T);
     return launch_sum_pt(ctx, reinterpret_cast<const bf16_t*>(lp + l.off_pa), n_out, part, splits, c, k, scale, l.nckb,
                          (int)d, mi, dW, lddw, odt == PRAC_BF16, beta);
   }
-  {  // T_h in fragment order (bf16): slabs summed, random rows weighted by the scaling factor
-    ProfScope ps(ctx, PRAC_KERNEL_T_REDUCE);
-    rc = launch_reduce_to_tfrag(ctx, n_out, part, splits, c, mi, k, scale, q.nkb, q.nmb, Tf);
+  for (int col0 = 0; col0 < tiles; col0 += q.cols) {
+    const int col1 = std::min(tiles, col0 + q.cols);
+    rc = ct_dy(col0, col1);
+    if (rc) return rc;
+    rc = reduce(col0, col1);
+    if (rc) return rc;
   }
-  if (rc) return rc;
   {
     ProfScope ps(ctx, PRAC_KERNEL_P_T);  // dW_h = P T_h, all outputs in one launch
     if (q.wide) {
@@ -1005,8 +1078,8 @@ int prac_weight_grad_static(prac_ctx* ctx, const void* C, const void* dY, prac_d
     need = qa.bytes;
   } else if (fast) {
     q = plan_wgrad_fast(ctx->n_cu, ctx->tune_splits, ctx->tune_one_launch != 0, N, d, k + r, 1, &m, odt, beta, packed,
-                        P_lp != nullptr);
-    need = q.bytes;
+                        P_lp != nullptr, WGRAD_ROOM);
+    need = std::max(q.bytes, q.equal_bytes);
   } else {
     need = o_part32 = plan_wgrad_generic(N, m, k + r, packed).bytes;
     if (dt == PRAC_F32 && wgrad_f32_splits(ctx->n_cu, N, m, k + r) > 1) need += PRAC_PART32_BYTES;

@@ -165,13 +165,29 @@ inline int wide_groups_per_wg(int n_cu, int tiles_m, int groups) {
 // W (bf16; w_layout 0: d x m, 1: m x d; ldw) -> [nkb][ncb_w][64][8] fragment order, zero padded
 int launch_pack_wfrag(prac_ctx* ctx, const bf16_t* W, int64_t ldw, int w_layout, int64_t d, int m, int nkb,
                       int ncb_w, bf16_t* out);
-// token-split partial sums of C^T dY_h for n_out outputs that share C; slabs[h] is splits x c x m[h].  any_element: rows of
+// Token ranges of unequal length, for one round of workgroups where the tiles of T (256 x 128) do not divide the compute units.
+// Every tile gets `main` workgroups of `len` units of 128 tokens each; what is left at the end of its tokens, `tail` units, goes
+// to `helpers` workgroups, which share the tails of all tiles in equal runs of `run` units (tile after tile), so a tile's tail is
+// in up to `tail_parts` parts.  main == 0: equal ranges.
+struct CtdyTails {
+  int main = 0, len = 0, tail = 0, helpers = 0, run = 0, tail_parts = 0;
+};
+// parts of the tail of tile t: first helper that works on it, and how many do
+static inline __host__ __device__ int ctdy_tail_first(const CtdyTails& p, int t) { return (int)((int64_t)t * p.tail / p.run); }
+static inline __host__ __device__ int ctdy_tail_parts(const CtdyTails& p, int t) {
+  return (int)(((int64_t)(t + 1) * p.tail - 1) / p.run) - ctdy_tail_first(p, t) + 1;
+}
+// token-split partial sums of C^T dY_h for n_out outputs that share C; slabs[h] is parts x c x sld[h] (sld: row pitch, m[h]
+// where nullptr).  any_element: rows of
 // dY_h may start on any element, and a row owns nothing past its last column (then m[h] >= 8); otherwise they are 16-byte
-// aligned and own whole 16-byte chunks (the caller says which: where the rows are a sample of a matrix, their pitch does not)
+// aligned and own whole 16-byte chunks (the caller says which: where the rows are a sample of a matrix, their pitch does not).
+// tails: unequal ranges (then `splits` is not looked at).  Only column tiles col0 .. col1 - 1 (128 columns each, counted over
+// all outputs) are formed; the slabs then hold those alone (one output).
 #define PRAC_CTDY_MAX_OUT 4
 int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, const bf16_t* const* dY,
                    const int64_t* lddy, const int* m, float* const* slabs, int splits, bool any_element,
-                   int range_tokens = 0);
+                   int range_tokens = 0, const int* sld = nullptr, const CtdyTails* tails = nullptr, int col0 = 0,
+                   int col1 = 1 << 30);
 // tokens of a range (whole 128-token tiles; the last ranges may be short or empty); launch_ctdy_ws takes another value for a
 // part of the ranges of a longer product
 inline int64_t ctdy_range_tokens(int64_t N, int splits) { return ((N + 127) / 128 + splits - 1) / splits * 128; }
@@ -193,8 +209,10 @@ int launch_pack_pfrag_split(prac_ctx* ctx, const float* P, int64_t d, int64_t ld
 int launch_unpack_c(prac_ctx* ctx, const bf16_t* Cpk, int N, int c, bf16_t* C, int64_t ldc);
 int launch_pack_c(prac_ctx* ctx, const bf16_t* C, int64_t ldc, int N, int c, bf16_t* Cpk);
 
+// (sld, tails, col0, col1 as for launch_ctdy_ws; the last column tile's padding in Tf is written with it)
 int launch_reduce_to_tfrag(prac_ctx* ctx, int n_out, const float* const* slabs, int splits, int c, const int* m, int k_lo,
-                           float scale_hi, int nkb, const int* nmb, bf16_t* const* Tf);
+                           float scale_hi, int nkb, const int* nmb, bf16_t* const* Tf, const int* sld, const CtdyTails& tails,
+                           int col0 = 0, int col1 = 1 << 30);
 int launch_pack_pafrag(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int c, int nrb, int nkb, bf16_t* out);
 // dW_h (d x m_h) = P T_h (+ beta dW_h) for n_out <= PRAC_CTDY_MAX_OUT outputs in one launch
 int launch_pt(prac_ctx* ctx, const bf16_t* Pa, int n_out, const bf16_t* const* Tf, int d, const int* m, int nkb,

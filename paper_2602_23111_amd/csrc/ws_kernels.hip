@@ -804,11 +804,14 @@ struct CtdyWsArgs {
   int64_t lddy[PRAC_CTDY_MAX_OUT];
   int m[PRAC_CTDY_MAX_OUT];
   int tile0[PRAC_CTDY_MAX_OUT + 1];
-  float* slabs[PRAC_CTDY_MAX_OUT];  // [splits][c][m_h] each
+  float* slabs[PRAC_CTDY_MAX_OUT];  // [parts][c][sld_h] each, from column 128 col0 on
+  int sld[PRAC_CTDY_MAX_OUT];       // row pitch of the slabs
   int splits;
   int tok_per_split;   // multiple of 128
   int tiles_n;         // column tiles of 128 over all outputs
   int row_groups;      // groups of 8 column blocks (256 rows of T) over c
+  int col0, cols;      // MODE 0: column tiles col0 .. col0 + cols - 1 are formed
+  CtdyTails tails;     // TAILS
   int groups_per_xcd;  // MODE > 0: column tiles per XCD
   // ---- whole weight gradient in this launch (MODE > 0): the workgroups of one column tile sum their
   // partial slabs into T (bf16, fragment order, random rows scaled) and form dW = P T for that tile
@@ -1182,23 +1185,31 @@ __device__ __forceinline__ void wgrad_tail(const CtdyWsArgs& a, unsigned char* s
 }
 
 // MODE 0: partial slabs only; 1 / 2: the whole weight gradient (dW in fp32 / bf16).  UA: rows of dY that start on
-// any element (see frag_utils.h).
-template <int MODE, bool UA>
+// any element (see frag_utils.h).  TAILS (MODE 0): token ranges of unequal length (see CtdyTails); a helper works through the
+// tails of two or three tiles one after the other, its loaders a segment ahead of the matrix waves' stores.
+template <int MODE, bool UA, bool TAILS>
 __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int bid = touch_kernel_args<(MODE == 0 ? offsetof(CtdyWsArgs, cnt) : sizeof(CtdyWsArgs))>(blockIdx.x);
 
-  int tn, rg, split;
+  int tn = 0, rg = 0, split = 0;
+  int run_beg = 0, run_end = 0;  // helpers: units of the tails of all tiles
   if constexpr (MODE == 0) {
-    const int per_split = a.tiles_n * a.row_groups;
-    const int total = per_split * a.splits;
+    const int per_split = a.cols * a.row_groups;
+    const int mains = per_split * (TAILS ? a.tails.main : a.splits);
+    const int total = mains + (TAILS ? a.tails.helpers : 0);
     const int per_xcd = (total + 7) / 8;
     const int xcd = bid & 7, slot = bid >> 3;
     const int logical = xcd * per_xcd + slot;
     if (slot >= per_xcd || logical >= total) return;
-    tn = logical % a.tiles_n;
-    rg = (logical / a.tiles_n) % a.row_groups;
-    split = logical / per_split;
+    if (TAILS && logical >= mains) {
+      run_beg = (logical - mains) * a.tails.run;
+      run_end = min(run_beg + a.tails.run, a.tiles_n * a.row_groups * a.tails.tail);
+    } else {
+      tn = a.col0 + logical % a.cols;
+      rg = (logical / a.cols) % a.row_groups;
+      split = logical / per_split;
+    }
   } else {
     // the workgroups of a column tile (its token ranges and row groups) take neighbouring slots of one XCD
     const int members = a.splits * a.row_groups;
@@ -1214,24 +1225,58 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   PRAC_STAMP(a, 0);
-  // which output this column tile belongs to
-  int h = 0;
+  int n0 = 0, tok_beg = 0, tok_end = 0, nk = 0, hout = 0, part = 0;
+  // The next piece of work (uniform; false: no more): a column tile, which output it belongs to, and a range of tokens.
+  bool first_segment = true;
+  auto next_segment = [&]() {
+    if constexpr (TAILS) {
+      if (run_end > 0) {
+        const CtdyTails& p = a.tails;
+        int len;
+        do {
+          if (run_beg >= run_end) return false;
+          const int t = run_beg / p.tail, off = run_beg - t * p.tail;
+          len = min(p.tail - off, run_end - run_beg);
+          tn = t % a.tiles_n;
+          rg = t / a.tiles_n;
+          tok_beg = (p.main * p.len + off) * CW_BK;
+          part = p.main + run_beg / p.run - ctdy_tail_first(p, t);
+          run_beg += len;
+        } while (tn < a.col0 || tn >= a.col0 + a.cols);
+        tok_end = tok_beg + len * CW_BK;
+      } else {
+        if (!first_segment) return false;
+        tok_beg = split * a.tails.len * CW_BK;
+        tok_end = tok_beg + a.tails.len * CW_BK;
+        part = split;
+      }
+    } else {
+      if (!first_segment) return false;
+      tok_beg = split * a.tok_per_split;
+      tok_end = tok_beg + a.tok_per_split;
+      part = split;
+    }
+    first_segment = false;
+    tok_end = min(a.N, tok_end);
+    nk = tok_end > tok_beg ? (tok_end - tok_beg + CW_BK - 1) / CW_BK : 0;
+    hout = 0;
 #pragma unroll
-  for (int q = 1; q < PRAC_CTDY_MAX_OUT; ++q)
-    if (q < a.n_out && tn >= a.tile0[q]) h = q;
-  const bf16_t* const dYh = a.dY[h];
-  const int64_t lddyh = a.lddy[h];
-  const int mh = a.m[h];
-  const int n0 = (tn - a.tile0[h]) * CW_BN;
-  const int tok_beg = split * a.tok_per_split;
-  const int tok_end = min(a.N, tok_beg + a.tok_per_split);
-  const int nk = tok_end > tok_beg ? (tok_end - tok_beg + CW_BK - 1) / CW_BK : 0;
+    for (int q = 1; q < PRAC_CTDY_MAX_OUT; ++q)
+      if (q < a.n_out && tn >= a.tile0[q]) hout = q;
+    n0 = (tn - a.tile0[hout]) * CW_BN;
+    return true;
+  };
+  if (!next_segment()) return;
   // All workgroups of a split walk its tiles in the same order: they then ask for the same blocks
   // of packed C at about the same time, which keeps those blocks in L2 between uses.
 
   if (wave >= 4) {
     // ------------------------------------------------------------ loader waves
-    if (nk > 0) {
+    do {
+    if (nk == 0) continue;
+    const bf16_t* const dYh = a.dY[hout];
+    const int64_t lddyh = a.lddy[hout];
+    const int mh = a.m[hout];
     const int lt = tid - 256;
     const int cc = lt & 15, tg = lt >> 4, kb = tg >> 1, h = tg & 1;
     const int last_chunk = UA ? mh - 8 : ((mh - 1) / 8) * 8;
@@ -1304,11 +1349,12 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
       gload(kt + 3, ry);
       __syncthreads();
     }
-    }
+    } while (TAILS && next_segment());
     if constexpr (MODE == 0) return;
   } else {
   // -------------------------------------------------------------- matrix waves
   const int lane = tid & 63, li = lane & 31, lh = lane >> 5;
+  do {
   const int cb0 = rg * 8 + wave * 2;  // this wave's two 32-row blocks of T (column blocks of C)
   f32x16 acc[8];
 #pragma unroll
@@ -1377,8 +1423,10 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
   // epilogue: acc[4 i + j], register v of lane (li, lh): T row 32 (cb0 + i) + 8*(v/4) + 4*lh + v%4,
   // column n0 + 4 li + j
   PRAC_STAMP(a, 6);
-  float* out = a.slabs[h] + (int64_t)split * a.c * mh;
-  const int n = n0 + 4 * li;
+  const int sld = a.sld[hout], mh = a.m[hout];
+  float* out = a.slabs[hout] + (int64_t)part * a.c * sld;
+  const int n = n0 + 4 * li, ns = n - a.col0 * CW_BN;  // column of T, and of the slab (a.col0 > 0: one output)
+  const bool vec = (sld & 3) == 0 && n + 3 < (mh + 3) / 4 * 4;  // (a pitch of whole quads has room for the last one)
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     asm volatile("" : "+a"(acc[4 * i]), "+a"(acc[4 * i + 1]), "+a"(acc[4 * i + 2]), "+a"(acc[4 * i + 3]) : : "memory");
@@ -1386,8 +1434,8 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
     for (int v = 0; v < 16; ++v) {
       const int row = (cb0 + i) * 32 + 8 * (v / 4) + 4 * lh + (v % 4);
       if (row < a.c) {
-        float* o = out + (int64_t)row * mh + n;
-        if (n + 3 < mh && (mh & 3) == 0) {
+        float* o = out + (int64_t)row * sld + ns;
+        if (vec) {
           *reinterpret_cast<float4*>(o) =
               make_float4(acc[4 * i][v], acc[4 * i + 1][v], acc[4 * i + 2][v], acc[4 * i + 3][v]);
         } else {
@@ -1398,11 +1446,12 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
       }
     }
   }
+  } while (TAILS && next_segment());
   }
   if constexpr (MODE != 0) {
     // all eight waves: the slabs of this column tile -> T -> dW (see wgrad_tail)
     const int members = a.splits * a.row_groups;
-    wgrad_tail<MODE == 2>(a, smem_raw, tn, h, n0, split * a.row_groups + rg, members);
+    wgrad_tail<MODE == 2>(a, smem_raw, tn, hout, n0, split * a.row_groups + rg, members);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     PRAC_STAMP(a, 5);
   }
@@ -1510,11 +1559,12 @@ int launch_wide_ws(prac_ctx* ctx, bool recon, const bf16_t* A, int64_t lda, bool
 
 namespace {
 void fill_ctdy_args(CtdyWsArgs& a, const bf16_t* Cpk, int c, int N, int n_out, const bf16_t* const* dY, const int64_t* lddy,
-                    const int* m, float* const* slabs, int splits) {
+                    const int* m, float* const* slabs, int splits, const int* sld) {
   a.Cpk = Cpk; a.ccb = (c + 31) / 32; a.c = c; a.N = N; a.n_out = n_out; a.splits = splits;
   int tiles = 0;
   for (int h = 0; h < n_out; ++h) {
     a.dY[h] = dY[h]; a.lddy[h] = lddy[h]; a.m[h] = m[h]; a.slabs[h] = slabs[h];
+    a.sld[h] = sld ? sld[h] : m[h];
     a.tile0[h] = tiles;
     tiles += (m[h] + CW_BN - 1) / CW_BN;
   }
@@ -1523,11 +1573,14 @@ void fill_ctdy_args(CtdyWsArgs& a, const bf16_t* Cpk, int c, int N, int n_out, c
   a.tok_per_split = (int)ctdy_range_tokens(N, splits);
   a.tiles_n = tiles;
   a.row_groups = (a.ccb + 7) / 8;
+  a.col0 = 0;
+  a.cols = tiles;
 }
 }  // namespace
 
 int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, const bf16_t* const* dY,
-                   const int64_t* lddy, const int* m, float* const* slabs, int splits, bool any_element, int range_tokens) {
+                   const int64_t* lddy, const int* m, float* const* slabs, int splits, bool any_element, int range_tokens,
+                   const int* sld, const CtdyTails* tails, int col0, int col1) {
   if (n_out < 1 || n_out > PRAC_CTDY_MAX_OUT) return PRAC_EINVAL;
   for (int h = 0; h < n_out; ++h) {
     if (lddy[h] > PRAC_MAX_STREAM_PITCH) return PRAC_EINVAL;
@@ -1535,21 +1588,38 @@ int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, co
     if (any_element ? m[h] < 8 : (reinterpret_cast<uintptr_t>(dY[h]) & 15) != 0 || lddy[h] % 8 != 0) return PRAC_EINVAL;
   }
   CtdyWsArgs a{};
-  fill_ctdy_args(a, Cpk, c, N, n_out, dY, lddy, m, slabs, splits);
+  fill_ctdy_args(a, Cpk, c, N, n_out, dY, lddy, m, slabs, splits, sld);
   if (range_tokens > 0) a.tok_per_split = range_tokens;
-  const size_t smem = (size_t)CW_STAGES * CW_STAGE;
-  const int total = a.tiles_n * a.row_groups * splits;
-  static bool f1[PRAC_MAX_DEVICES] = {}, f2[PRAC_MAX_DEVICES] = {};
-  const dim3 grid(((total + 7) / 8) * 8), block(512);
-  if (any_element) {
-    int rc = set_smem(ctx, (ctdy_ws_kernel<0, true>), smem, f2[ctx->device % PRAC_MAX_DEVICES]);
-    if (rc) return rc;
-    PRAC_LAUNCH(ctx, (ctdy_ws_kernel<0, true>), grid, block, smem, a);
-  } else {
-    int rc = set_smem(ctx, (ctdy_ws_kernel<0, false>), smem, f1[ctx->device % PRAC_MAX_DEVICES]);
-    if (rc) return rc;
-    PRAC_LAUNCH(ctx, (ctdy_ws_kernel<0, false>), grid, block, smem, a);
+  a.col0 = col0;
+  a.cols = std::min(col1, a.tiles_n) - col0;
+  if (col0 < 0 || a.cols < 1 || (col0 > 0 && n_out > 1)) return PRAC_EINVAL;
+  const bool uneven = tails && tails->main > 0;
+  if (uneven) {
+    // every token of every tile belongs to one main range or to a tail
+    if (any_element || tails->tail < 1 || tails->run < 1 || (int64_t)tails->helpers * tails->run < (int64_t)a.tiles_n * a.row_groups * tails->tail ||
+        (int64_t)(tails->main * tails->len + tails->tail) * CW_BK < N)
+      return PRAC_EINVAL;
+    a.tails = *tails;
   }
+  const size_t smem = (size_t)CW_STAGES * CW_STAGE;
+  const int total = a.cols * a.row_groups * (uneven ? tails->main : splits) + (uneven ? tails->helpers : 0);
+  static bool done_dev[PRAC_MAX_DEVICES][3] = {};
+  bool* done = done_dev[ctx->device % PRAC_MAX_DEVICES];
+  const dim3 grid(((total + 7) / 8) * 8), block(512);
+#define PRAC_CTDY_CASE(I, UA, TAILS)                                        \
+  case I: {                                                                 \
+    constexpr auto kern = ctdy_ws_kernel<0, UA, TAILS>;                     \
+    int rc = set_smem(ctx, kern, smem, done[I]);                            \
+    if (rc) return rc;                                                      \
+    PRAC_LAUNCH(ctx, kern, grid, block, smem, a);                           \
+    break;                                                                  \
+  }
+  switch (any_element ? 1 : (uneven ? 2 : 0)) {
+    PRAC_CTDY_CASE(0, false, false)
+    PRAC_CTDY_CASE(1, true, false)
+    PRAC_CTDY_CASE(2, false, true)
+  }
+#undef PRAC_CTDY_CASE
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
 }
@@ -1572,7 +1642,7 @@ int launch_wgrad_fused(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out
                        const int64_t* lddw, bool out_bf16, float beta, int* cnt) {
   if (n_out < 1 || n_out > PRAC_CTDY_MAX_OUT) return PRAC_EINVAL;
   CtdyWsArgs a{};
-  fill_ctdy_args(a, Cpk, c, N, n_out, dY, lddy, m, slabs, splits);
+  fill_ctdy_args(a, Cpk, c, N, n_out, dY, lddy, m, slabs, splits, nullptr);
   a.groups_per_xcd = (a.tiles_n + 7) / 8;
   const int per_xcd = a.groups_per_xcd * splits * a.row_groups;
   // refuse a launch whose waiting workgroups might not all be resident
@@ -1590,13 +1660,13 @@ int launch_wgrad_fused(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out
   bool &s1 = f1[ctx->device % PRAC_MAX_DEVICES], &s2 = f2[ctx->device % PRAC_MAX_DEVICES];
   const dim3 grid(8 * per_xcd), block(512);
   if (out_bf16) {
-    int rc = set_smem(ctx, (ctdy_ws_kernel<2, false>), smem, s2);
+    int rc = set_smem(ctx, (ctdy_ws_kernel<2, false, false>), smem, s2);
     if (rc) return rc;
-    PRAC_LAUNCH(ctx, (ctdy_ws_kernel<2, false>), grid, block, smem, a);
+    PRAC_LAUNCH(ctx, (ctdy_ws_kernel<2, false, false>), grid, block, smem, a);
   } else {
-    int rc = set_smem(ctx, (ctdy_ws_kernel<1, false>), smem, s1);
+    int rc = set_smem(ctx, (ctdy_ws_kernel<1, false, false>), smem, s1);
     if (rc) return rc;
-    PRAC_LAUNCH(ctx, (ctdy_ws_kernel<1, false>), grid, block, smem, a);
+    PRAC_LAUNCH(ctx, (ctdy_ws_kernel<1, false, false>), grid, block, smem, a);
   }
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;

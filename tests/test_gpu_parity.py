@@ -483,6 +483,49 @@ def test_weight_grad_of_wide_layers(ctx, d, c, ms, pad):
         assert (buf[d:] == 7.0).all() and (buf[:, m:] == 7.0).all()
 
 
+@pytest.mark.parametrize("N,c,ms,pad,static", [
+    (2000, 70, (19163,), 8, True),          # 150 tiles: one main range each, tails in parts; short last range, partial last tile
+    (2048, 256, (19200,), 0, True),         # their sums exceed the static block: column tiles in turns there
+    (1999, 300, (8001, 1200), 0, False),    # two row groups of T, two outputs, odd width
+    (32768, 64, (11008,), 0, True),         # 86 tiles: two main ranges each
+])
+def test_weight_grad_over_unequal_token_ranges(ctx, N, c, ms, pad, static):
+    """T's tiles in one round of workgroups with token ranges of unequal length: every element against the product of the same
+    operands.  T's sums are fp32 (N products in any order: a relative N 2^-24 at most, 2e-3; far less in fact), then one ulp of
+    T (2^-8) either way, and one of dW."""
+    d, k = 264, c // 2
+    s = (d - k) / (c - k) if c <= d else 2.0
+    d = max(d, c)
+    g = torch.Generator(device=DEV).manual_seed(N + c)
+    Ct = torch.randn((N, c), generator=g, device=DEV).bfloat16()
+    P = torch.randn((d, c), generator=g, device=DEV) * d ** -0.5
+    dYs = []
+    for m in ms:
+        buf = torch.full((N, (m + 7) // 8 * 8 + pad), 3.0, dtype=torch.bfloat16, device=DEV)[:, :m]
+        buf.copy_(torch.randn((N, m), generator=g, device=DEV) * 1e-2)
+        dYs.append(buf)
+    lp = ctx.pack_basis(P)
+    ldc = (c + 7) // 8 * 8
+    Cd = torch.zeros((N, ldc), dtype=torch.bfloat16, device=DEV)[:, :c]
+    Cd.copy_(Ct)
+    if len(ms) == 1:
+        outs = [ctx.weight_grad(Cd, dYs[0], P, k, c - k, s, P_lp=lp, out_dtype=torch.float32)]
+        if static:
+            again = torch.full((d, ms[0]), float("nan"), dtype=torch.float32, device=DEV)
+            ctx.weight_grad(Cd, dYs[0], P, k, c - k, s, P_lp=lp, out=again, static=True)
+            assert torch.equal(again, outs[0])
+    else:
+        outs = ctx.weight_grad_shared(Cd, dYs, P, k, c - k, s, P_lp=lp, out_dtype=torch.float32)
+    ctx.sync_status()
+    Pb = P.bfloat16().double()
+    for y, dW, m in zip(dYs, outs, ms):
+        for a in range(0, m, 4096):
+            T = Ct.double().t().contiguous() @ y[:, a:a + 4096].double()
+            T[k:] *= s
+            ref, mag = Pb @ T, Pb.abs() @ T.abs()
+            assert ((dW[:, a:a + 4096].double() - ref).abs() <= 2.0 ** -7 * mag).all()
+
+
 # ------------------------------------------------------------- reconstruction
 RECON_CASES = [
     # dtype, N, d, k, r, ldc, ldxh
