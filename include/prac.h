@@ -295,8 +295,9 @@ int prac_weight_grad(prac_ctx* ctx, const void* C, const void* dY, prac_dtype dt
  *   - PRAC_ETOOBIG when T, the packed copies and the partial sums over equal token ranges exceed
  *     PRAC_STATIC_SCRATCH_BYTES less 128 KiB for the one-launch form's counters (N = 32768, d = m = 2048, k + r = 256
  *     needs 34.6 MB); nothing is enqueued then.  Where prac_weight_grad takes unequal ranges, whose partial sums are more
- *     (prac_workspace_bytes tells), the column tiles of T are formed a few at a time here: the same sums.  Where one
- *     plan fits and a larger one is not faster by much, prac_weight_grad runs the one that fits, too.
+ *     (a ctx holds 128 KiB per compute unit for them besides what prac_workspace_bytes tells), the tiles of T are formed
+ *     some at a time here where need be: the same sums.  Where one plan fits and a larger one is not faster by much,
+ *     prac_weight_grad runs the one that fits, too.
  *   - dY rows that start on any element: a row-major C is packed in parts where the whole copy does not fit (same bits).
  *     Where the partial sums and one part do not fit either, the strided kernel runs if what it needs does
  *     (one fp32 T, and an unpacked copy of a packed C): the same result but for the order of the fp32 sums.

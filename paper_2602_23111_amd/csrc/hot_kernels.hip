@@ -190,57 +190,65 @@ __global__ __launch_bounds__(256) void pack_c_kernel(const bf16_t* __restrict__ 
 struct ReduceTfArgs {
   int n_out, splits, c, k_lo, nkb;
   float scale_hi;
-  const float* slabs[PRAC_CTDY_MAX_OUT];  // [parts][c][sld_h] from column 128 col0 on
+  const float* slabs[PRAC_CTDY_MAX_OUT];  // [splits][c][sld_h]
   int sld[PRAC_CTDY_MAX_OUT];
   bf16_t* Tf[PRAC_CTDY_MAX_OUT];          // [nkb][nmb_h][64][8]
   int m[PRAC_CTDY_MAX_OUT];
   int nmb[PRAC_CTDY_MAX_OUT];
-  int col0, pairs;                        // pairs of column blocks of this launch, from the pair 2 col0 on
   int tile0[PRAC_CTDY_MAX_OUT], tiles_n;  // column tiles of 128, as C^T dY counts them
-  CtdyTails tails;                        // main == 0: `splits` parts everywhere
+  CtdyTails tails;                        // main > 0: blocks instead of slabs
   int pair0[PRAC_CTDY_MAX_OUT + 1];       // first pair of column blocks of output h in the launch
 };
 
 __global__ __launch_bounds__(256) void reduce_to_tfrag_kernel(ReduceTfArgs a) {
   __shared__ float patch[16][68];
   const int bid = touch_kernel_args<sizeof(ReduceTfArgs)>(blockIdx.x);
-  const int kb = bid / a.pairs, gp = 2 * a.col0 + bid % a.pairs;
+  const int pairs = a.pair0[a.n_out];
+  const int kb = bid / pairs, gp = bid % pairs;
   int h = 0;
 #pragma unroll
   for (int q = 1; q < PRAC_CTDY_MAX_OUT; ++q)
     if (q < a.n_out && gp >= a.pair0[q]) h = q;
   const int np = gp - a.pair0[h];
-  const float* __restrict__ slabs = a.slabs[h];
-  const int m = a.m[h], nmb = a.nmb[h], c = a.c, sld = a.sld[h];
-  // parts of the tile of T that this patch lies in
-  int parts = a.splits;
-  if (a.tails.main > 0)
-    parts = a.tails.main + ctdy_tail_parts(a.tails, kb / 16 * a.tiles_n + min(a.tile0[h] + np / 2, a.tiles_n - 1));
+  const int m = a.m[h], nmb = a.nmb[h], c = a.c, splits = a.splits;
+  // the tile of T that this patch lies in (padding behind an output's last tile: that one)
+  const int t = min(kb / 16, (c - 1) / 256) * a.tiles_n + a.tile0[h] + min(np / 2, (m - 1) / 128);
+  if (a.tails.main > 0 && (t < a.tails.t0 || t >= a.tails.t1)) return;
   const int tid = threadIdx.x;
   const int row = tid >> 4, col = (tid & 15) * 4;
   const int k = kb * 16 + row, n = np * 64 + col;
-  const int64_t slab = (int64_t)c * sld;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   if (k < c && n < m) {
-    const float* p = slabs + (int64_t)k * sld + n - 128 * a.col0;
-    if ((sld & 3) == 0) {
+    auto add4 = [&](const float* p, int parts, int64_t stride) {
 #pragma unroll 8
       for (int z = 0; z < parts; ++z) {
         // read once
-        const f32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(p + z * slab));
+        const f32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(p + z * stride));
         s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
       }
-      if (n + 1 >= m) s.y = 0.f;  // (past m: whatever the last quad's products were)
-      if (n + 2 >= m) s.z = 0.f;
-      if (n + 3 >= m) s.w = 0.f;
+    };
+    const int sld = a.sld[h];
+    if (a.tails.main > 0) {
+      const CtdyTails& p = a.tails;
+      const int64_t block = (int64_t)p.block_rows * 128;
+      const int in = (k & 255) * 128 + (n & 127);
+      add4(p.blocks + (t - p.t0) * block + in, p.main, (p.t1 - p.t0) * block);
+      add4(p.tail_blocks + ctdy_tail_block(p, t, ctdy_tail_first(p, t)) * block + in, ctdy_tail_parts(p, t), block);
+    } else if ((sld & 3) == 0) {
+      add4(a.slabs[h] + (int64_t)k * sld + n, splits, (int64_t)c * sld);
     } else {
-      for (int z = 0; z < parts; ++z) {
+      const float* p = a.slabs[h] + (int64_t)k * sld + n;
+      const int64_t slab = (int64_t)c * sld;
+      for (int z = 0; z < splits; ++z) {
         s.x += p[z * slab];
         if (n + 1 < m) s.y += p[z * slab + 1];
         if (n + 2 < m) s.z += p[z * slab + 2];
         if (n + 3 < m) s.w += p[z * slab + 3];
       }
     }
+    if (n + 1 >= m) s.y = 0.f;  // (past m: whatever the last quad's products were)
+    if (n + 2 >= m) s.z = 0.f;
+    if (n + 3 >= m) s.w = 0.f;
     const float w = k >= a.k_lo ? a.scale_hi : 1.f;
     s.x *= w; s.y *= w; s.z *= w; s.w *= w;
   }
@@ -1070,9 +1078,8 @@ int launch_pack_c(prac_ctx* ctx, const bf16_t* C, int64_t ldc, int N, int c, bf1
 }
 
 int launch_reduce_to_tfrag(prac_ctx* ctx, int n_out, const float* const* slabs, int splits, int c, const int* m, int k_lo,
-                           float scale_hi, int nkb, const int* nmb, bf16_t* const* Tf, const int* sld, const CtdyTails& tails,
-                           int col0, int col1) {
-  if (n_out < 1 || n_out > PRAC_CTDY_MAX_OUT || (col0 > 0 && n_out > 1)) return PRAC_EINVAL;
+                           float scale_hi, int nkb, const int* nmb, bf16_t* const* Tf, const int* sld, const CtdyTails& tails) {
+  if (n_out < 1 || n_out > PRAC_CTDY_MAX_OUT) return PRAC_EINVAL;
   ReduceTfArgs a{};
   a.n_out = n_out; a.splits = splits; a.c = c; a.k_lo = k_lo; a.nkb = nkb; a.scale_hi = scale_hi; a.tails = tails;
   int pairs = 0;
@@ -1084,10 +1091,7 @@ int launch_reduce_to_tfrag(prac_ctx* ctx, int n_out, const float* const* slabs, 
     a.tiles_n += (m[h] + 127) / 128;
   }
   for (int h = n_out; h <= PRAC_CTDY_MAX_OUT; ++h) a.pair0[h] = pairs;
-  a.col0 = col0;
-  a.pairs = (col1 >= a.tiles_n ? pairs : 2 * col1) - 2 * col0;
-  if (a.pairs < 1) return PRAC_EINVAL;
-  PRAC_LAUNCH(ctx, reduce_to_tfrag_kernel, dim3(nkb * a.pairs), dim3(256), 0, a);
+  PRAC_LAUNCH(ctx, reduce_to_tfrag_kernel, dim3(nkb * pairs), dim3(256), 0, a);
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
 }

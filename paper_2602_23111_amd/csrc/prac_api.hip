@@ -278,17 +278,19 @@ int prac_create(prac_ctx** out, int device, void* hip_stream) {
   c->tune_tail = 0;
   c->d_sync = nullptr;
   c->part32 = nullptr;
+  c->tails = nullptr;
   hipDeviceProp_t prop;
   c->n_cu = (hipGetDeviceProperties(&prop, device) == hipSuccess) ? prop.multiProcessorCount : 256;
-  // failure flag (256 bytes), the counters of the one-launch weight gradient, the fp32 partial sums
+  // failure flag (256 bytes), the counters of the one-launch weight gradient, the fp32 partial sums, the blocks of unequal ranges' tails
   const size_t flag_bytes = 256 + PRAC_SYNC_BYTES;
-  if (hipMalloc(reinterpret_cast<void**>(&c->d_flag), flag_bytes + PRAC_PART32_BYTES) != hipSuccess) {
+  if (hipMalloc(reinterpret_cast<void**>(&c->d_flag), flag_bytes + PRAC_PART32_BYTES + (size_t)c->n_cu * PRAC_TAIL_BYTES) != hipSuccess) {
     (void)hipGetLastError();
     delete c;
     return PRAC_EHIP;
   }
   c->d_sync = c->d_flag + 64;
   c->part32 = reinterpret_cast<float*>(reinterpret_cast<char*>(c->d_flag) + flag_bytes);
+  c->tails = c->part32 + PRAC_PART32_BYTES / sizeof(float);
   if (hipMemset(c->d_flag, 0, flag_bytes) != hipSuccess) {
     (void)hipGetLastError();
     (void)hipFree(c->d_flag);
@@ -747,8 +749,8 @@ int wgrad_splits(int n_cu, int tune_splits, int c, int n_out, const int64_t* m, 
 // Unequal token ranges in one round (see CtdyTails) where they are at least 3 % cheaper than `splits` equal ones.  A helper's next
 // piece costs it what 3 units cost (its stores and its first tile), so main ranges are the shortest that no helper exceeds.
 // Measured, equal ranges against these, C^T dY alone and the whole weight gradient: 86 tiles of
-// 256 units (up and gate) 5 ranges in two rounds 237 / 320 us, unequal 217 / 294; 172 tiles of 128 units (LLaMA-7B up projection)
-// one range 226 / 320, unequal 183 / 281.  Pieces priced at 0, 8 and 16 units instead: 228, 220 and 225 us on the former's
+// 256 units (up and gate) 5 ranges in two rounds 237 / 320 us, unequal 217 / 292; 172 tiles of 128 units (LLaMA-7B up projection)
+// one range 226 / 319, unequal 183 / 282.  Pieces priced at 0, 8 and 16 units instead: 228, 220 and 225 us on the former's
 // C^T dY, 200, 193 and 203 on the latter's (190 with 3, in the same run).
 CtdyTails wgrad_tails(int n_cu, int c, int n_out, const int64_t* m, int64_t N, int splits) {
   const WgradWork w(c, n_out, m);
@@ -765,7 +767,8 @@ CtdyTails wgrad_tails(int n_cu, int c, int n_out, const int64_t* m, int64_t N, i
     t.tail = (int)tail;
     t.run = (int)run;
     t.helpers = (int)((w.tiles * tail + run - 1) / run);
-    t.tail_parts = (int)((tail + run - 2) / run + 1);
+    t.block_rows = std::min(c, 256);
+    t.t1 = (int)w.tiles;
     const double us = WgradWork::round_us(128.0 * (double)len) +
                       (double)(2 * w.slab) * ((double)t.main + 1.0 + (double)t.helpers / (double)w.tiles) / 3e6;
     return us < 0.97 * w.equal_us(n_cu, N, splits) ? t : CtdyTails{};
@@ -850,11 +853,11 @@ struct WgradPlan {
   bool fused;  // one launch (see launch_wgrad_fused) instead of three
   bool wide;   // dW = P T by launch_wide_ws
   CtdyTails tails;  // unequal token ranges (main > 0), else `splits` equal ones
-  int cols;    // column tiles formed at a time (all, unless the partial sums have to fit the static block)
+  int tiles;   // unequal ranges: tiles of T formed at a time (all, unless the partial sums have to fit the static block)
   int sld[PRAC_CTDY_MAX_OUT];  // row pitch of the partial sums: whole quads, so that they move 16 bytes at a time at any width
   int nkb;     // 16-row k-blocks of T
   int nmb[PRAC_CTDY_MAX_OUT];
-  size_t o_part[PRAC_CTDY_MAX_OUT], o_t[PRAC_CTDY_MAX_OUT], o_lp, o_cpk, bytes;
+  size_t o_part[PRAC_CTDY_MAX_OUT], o_blocks, o_tails, o_t[PRAC_CTDY_MAX_OUT], o_lp, o_cpk, bytes;
   size_t equal_bytes;  // what equal ranges with tight partial sums would take: decides what the static entry point refuses
 };
 // dW = P T by the kernel that walks column groups (launch_wide_ws) or by the tiled ones (launch_pt): the former for bf16
@@ -868,63 +871,70 @@ bool wgrad_wide(int n_cu, int64_t d, int c, int n_out, const int64_t* m, prac_dt
   for (int h = 0; h < n_out; ++h) groups += (m[h] + 255) / 256;
   return (d + 127) / 128 * groups > n_cu;
 }
-// cols > 0: partial sums of that many column tiles (one output); otherwise of all, with rows of m (tight) or of whole quads
-WgradPlan layout_wgrad_fast(int64_t N, int64_t d, int c, int n_out, const int64_t* m, int splits, const CtdyTails& tails, bool packed,
-                            bool has_lp, bool wide, bool tight, int cols = 0) {
+// Equal ranges: partial sums in rows of m (tight) or of whole quads.  Unequal ones: the blocks of `tiles` tiles at a time; those of
+// the tails are here only if `own_tails`, otherwise in the ctx's block for them (PRAC_TAIL_BYTES).
+WgradPlan layout_wgrad_fast(int64_t N, int64_t d, int c, int n_out, const int64_t* m, int splits, bool packed, bool has_lp, bool wide,
+                            bool tight, const CtdyTails& tails = {}, int tiles = 0, bool own_tails = false) {
   WgradPlan q{};
   const LpLayout l = lp_layout(d, c);
   q.splits = splits;
   q.tails = tails;
+  q.tiles = tiles;
   q.wide = wide;
   q.nkb = wide ? wide_kblocks(c) : l.nckb;
-  const size_t parts = tails.main > 0 ? tails.main + tails.tail_parts : splits;
   WsPlan plan;
   for (int h = 0; h < n_out; ++h) {
     q.nmb[h] = (int)round_up64((m[h] + 31) / 32, wide ? 8 : 4);  // 32-column blocks of T, whole 256- or 128-column tiles
-    q.sld[h] = (int)(cols > 0 ? 128 * cols : tight ? m[h] : round_up64(m[h], 4));
-    q.cols += (int)((m[h] + 127) / 128);
-    q.o_part[h] = plan.take(parts * c * q.sld[h] * sizeof(float));
+    q.sld[h] = (int)(tight ? m[h] : round_up64(m[h], 4));
+    q.o_part[h] = plan.take(tails.main > 0 ? 0 : (size_t)splits * c * q.sld[h] * sizeof(float));
     q.o_t[h] = plan.take((size_t)q.nkb * q.nmb[h] * 64 * 8 * sizeof(bf16_t));
   }
-  if (cols > 0) q.cols = cols;
+  if (tails.main > 0) {
+    const size_t block = (size_t)tails.block_rows * 128 * sizeof(float);
+    size_t tail_blocks = 0;
+    for (int t = 0; t < tails.t1; t += tiles)
+      tail_blocks = std::max<size_t>(tail_blocks, ctdy_tail_blocks(tails, t, std::min(tails.t1, t + tiles)));
+    q.o_blocks = plan.take(tails.main * tiles * block);
+    q.o_tails = plan.take(own_tails ? tail_blocks * block : 0);
+  }
   q.o_lp = plan.take(has_lp ? 0 : l.bytes);
   q.o_cpk = plan.take(packed ? 0 : packed_c_bytes(N, c));
   q.bytes = plan.off;
   return q;
 }
-// (whether C is packed and P_lp at hand does not change the ranges, and with them the bits of dW; nor does `room`, in which a
-// single gradient is planned if equal_bytes fits it)
+// (whether C is packed and P_lp at hand does not change the ranges, and with them the bits of dW; nor does `room`, which is what a
+// call has that brings all of its scratch (0: as much as it asks for, and the ctx's block for the tails))
 WgradPlan plan_wgrad_fast(int n_cu, int tune_splits, bool one_launch, int64_t N, int64_t d, int c, int n_out, const int64_t* m,
-                          prac_dtype odt, float beta, bool packed, bool has_lp, size_t room = ~(size_t)0) {
-  const CtdyTails none;
+                          prac_dtype odt, float beta, bool packed, bool has_lp, size_t room = 0) {
   const int splits = wgrad_splits(n_cu, tune_splits, c, n_out, m, N, [&](int s) {
-    return n_out > 1 ||
-           layout_wgrad_fast(N, d, c, n_out, m, s, none, false, false, wide_kblocks(c) == 16, true).bytes <= WGRAD_ROOM;
+    return n_out > 1 || layout_wgrad_fast(N, d, c, n_out, m, s, false, false, wide_kblocks(c) == 16, true).bytes <= WGRAD_ROOM;
   });
-  const CtdyTails tails = tune_splits > 0 ? none : wgrad_tails(n_cu, c, n_out, m, N, splits);
-  size_t equal = layout_wgrad_fast(N, d, c, n_out, m, splits, none, packed, has_lp, false, true).bytes;
+  const CtdyTails tails = tune_splits > 0 ? CtdyTails{} : wgrad_tails(n_cu, c, n_out, m, N, splits);
+  WgradPlan tight = layout_wgrad_fast(N, d, c, n_out, m, splits, packed, has_lp, false, true);
+  tight.equal_bytes = tight.bytes;
   if (tails.main == 0 && one_launch && wgrad_fused_takes(n_cu, c, n_out, m, splits)) {
-    WgradPlan q = layout_wgrad_fast(N, d, c, n_out, m, splits, none, packed, has_lp, false, true);
-    q.fused = true;
-    q.equal_bytes = equal;
-    return q;
+    tight.fused = true;
+    return tight;
   }
-  bool wide = wgrad_wide(n_cu, d, c, n_out, m, odt, beta);
-  if (wide) {
-    const size_t w = layout_wgrad_fast(N, d, c, n_out, m, splits, none, packed, has_lp, true, true).bytes;
-    wide = n_out > 1 || w <= WGRAD_ROOM || equal > WGRAD_ROOM;
-    if (wide) equal = w;
+  if (wgrad_wide(n_cu, d, c, n_out, m, odt, beta)) {
+    WgradPlan w = layout_wgrad_fast(N, d, c, n_out, m, splits, packed, has_lp, true, true);
+    w.equal_bytes = w.bytes;
+    if (n_out > 1 || w.bytes <= WGRAD_ROOM || tight.bytes > WGRAD_ROOM) tight = w;
   }
-  WgradPlan q = layout_wgrad_fast(N, d, c, n_out, m, splits, tails, packed, has_lp, wide, false);
-  if (q.bytes > room && n_out == 1) {
-    int cols = q.cols;
-    while (cols > 1 && q.bytes > room) q = layout_wgrad_fast(N, d, c, n_out, m, splits, tails, packed, has_lp, wide, false, --cols);
+  WgradPlan q;
+  if (tails.main > 0) {
+    int tiles = tails.t1;
+    do q = layout_wgrad_fast(N, d, c, n_out, m, splits, packed, has_lp, tight.wide, false, tails, tiles, room > 0);
+    while (room > 0 && q.bytes > room && --tiles > 0);
+  } else {
+    q = layout_wgrad_fast(N, d, c, n_out, m, splits, packed, has_lp, tight.wide, false);
+    if (room > 0 && q.bytes > room) q = tight;
   }
-  q.equal_bytes = equal;
+  q.equal_bytes = tight.bytes;
   return q;
 }
 
-int weight_grad_fast(prac_ctx* ctx, char* ws, int* cnt, const WgradPlan& q, const void* C, int64_t N, int64_t ldc, bool packed,
+int weight_grad_fast(prac_ctx* ctx, char* ws, int* cnt, float* tail_blocks, const WgradPlan& q, const void* C, int64_t N, int64_t ldc, bool packed,
                      int n_out, const void* const* dY, const int64_t* m, const int64_t* lddy, const float* P,
                      const void* P_lp, int64_t d, int64_t ldp, int k, int r, float scale, void* const* dW,
                      prac_dtype odt, const int64_t* lddw, float beta) {
@@ -973,17 +983,18 @@ int weight_grad_fast(prac_ctx* ctx, char* ws, int* cnt, const WgradPlan& q, cons
                               reinterpret_cast<const bf16_t*>(lp + l.off_pa), (int)d, dW, lddw, odt == PRAC_BF16, beta,
                               cnt);
   }
-  // T_h = C^T dY_h as partial slabs over token ranges, formed for all column tiles at once or for q.cols of them at a time
-  int tiles = 0;
-  for (int h = 0; h < n_out; ++h) tiles += (mi[h] + 127) / 128;
-  auto ct_dy = [&](int col0, int col1) {
+  CtdyTails tails = q.tails;
+  if (tails.main > 0) {
+    tails.blocks = reinterpret_cast<float*>(ws + q.o_blocks);
+    tails.tail_blocks = tail_blocks ? tail_blocks : reinterpret_cast<float*>(ws + q.o_tails);
+  }
+  auto ct_dy = [&] {  // T_h = C^T dY_h as partial sums over token ranges
     ProfScope ps(ctx, PRAC_KERNEL_CT_DY);
-    return launch_ctdy_ws(ctx, Cpk, c, (int)N, n_out, dYp, lddy, mi, part, splits, false, 0, q.sld, &q.tails, col0, col1);
+    return launch_ctdy_ws(ctx, Cpk, c, (int)N, n_out, dYp, lddy, mi, part, splits, false, 0, q.sld, &tails);
   };
-  // T_h in fragment order (bf16): slabs summed, random rows weighted by the scaling factor
-  auto reduce = [&](int col0, int col1) {
+  auto reduce = [&] {  // T_h in fragment order (bf16): partial sums added up, random rows weighted by the scaling factor
     ProfScope ps(ctx, PRAC_KERNEL_T_REDUCE);
-    return launch_reduce_to_tfrag(ctx, n_out, part, splits, c, mi, k, scale, q.nkb, q.nmb, Tf, q.sld, q.tails, col0, col1);
+    return launch_reduce_to_tfrag(ctx, n_out, part, splits, c, mi, k, scale, q.nkb, q.nmb, Tf, q.sld, tails);
   };
   // Slab sum, scaling factor and dW_h = P T_h in one launch where that is the faster form: measured on an
   // MI355X it is for c > 256 (rank 512 + 512 at d = m = 2048: 159 against 179 us per weight gradient), where
@@ -992,19 +1003,22 @@ int weight_grad_fast(prac_ctx* ctx, char* ws, int* cnt, const WgradPlan& q, cons
   // (every 512 rows of dW are one more workgroup per column block that repeats the slab sum: at d = 11008,
   // 22 of them, the one launch takes 180 us against 98 us for the two, so it is limited to d <= 2048)
   const bool tail_one = ctx->tune_tail == 2 || (ctx->tune_tail == 0 && l.nckb > 16 && d <= 2048);  // (never with q.wide: c > 256)
-  if (tail_one && q.tails.main == 0 && q.cols >= tiles && sum_pt_eligible(n_out, mi, splits)) {
-    rc = ct_dy(0, tiles);
+  if (tail_one && tails.main == 0 && sum_pt_eligible(n_out, mi, splits)) {
+    rc = ct_dy();
     if (rc) return rc;
     ProfScope ps(ctx, PRAC_KERNEL_SUM_P_T);
     return launch_sum_pt(ctx, reinterpret_cast<const bf16_t*>(lp + l.off_pa), n_out, part, splits, c, k, scale, l.nckb,
                          (int)d, mi, dW, lddw, odt == PRAC_BF16, beta);
   }
-  for (int col0 = 0; col0 < tiles; col0 += q.cols) {
-    const int col1 = std::min(tiles, col0 + q.cols);
-    rc = ct_dy(col0, col1);
+  const int all = q.tails.t1;  // (equal ranges: 0)
+  for (int t = 0; t == 0 || t < all; t += q.tiles) {
+    tails.t0 = t;
+    tails.t1 = std::min(all, t + q.tiles);
+    rc = ct_dy();
     if (rc) return rc;
-    rc = reduce(col0, col1);
+    rc = reduce();
     if (rc) return rc;
+    if (tails.main == 0) break;
   }
   {
     ProfScope ps(ctx, PRAC_KERNEL_P_T);  // dW_h = P T_h, all outputs in one launch
@@ -1093,7 +1107,7 @@ int prac_weight_grad_static(prac_ctx* ctx, const void* C, const void* dY, prac_d
   ctx->prof_kind = PRAC_KERNEL_NONE;
   char* ws = ctx->static_scratch + kSync;
   if (fast)
-    rc = weight_grad_fast(ctx, ws, reinterpret_cast<int*>(ctx->static_scratch), q, C, N, ldc, packed, 1, &dY, &m, &lddy, P, P_lp, d, ldp, k, r, scale, &dW, odt, &lddw,
+    rc = weight_grad_fast(ctx, ws, reinterpret_cast<int*>(ctx->static_scratch), nullptr, q, C, N, ldc, packed, 1, &dY, &m, &lddy, P, P_lp, d, ldp, k, r, scale, &dW, odt, &lddw,
                           beta);
   else if (any)
     rc = weight_grad_any(ctx, ws, qa, C, N, ldc, packed, 1, &dY, &m, &lddy, P, d, ldp, k, r, scale, &dW, odt, &lddw, beta);
@@ -1118,7 +1132,7 @@ int prac_weight_grad_shared(prac_ctx* ctx, const void* C, prac_dtype dt, int64_t
                                         packed, P_lp != nullptr);
     rc = prac_ws_reserve(ctx, q.bytes);
     if (rc) return rc;
-    return weight_grad_fast(ctx, ctx->ws, ctx->d_sync, q, C, N, ldc, packed, n_out, dY, m, lddy, P, P_lp, d, ldp, k, r, scale, dW, odt,
+    return weight_grad_fast(ctx, ctx->ws, ctx->d_sync, ctx->tails, q, C, N, ldc, packed, n_out, dY, m, lddy, P, P_lp, d, ldp, k, r, scale, dW, odt,
                             lddw, beta);
   }
   if (wgrad_is_any(dt, n_out, m, lddy)) {
@@ -1292,8 +1306,11 @@ size_t prac_workspace_bytes(const prac_ctx* ctx, const prac_call_shape* sh) {
       if (fast) {  // beta is not part of the shape: enough for either form of the last product
         size_t need = 0;
         for (float beta : {0.f, 1.f})
-          need = std::max(need, plan_wgrad_fast(n_cu, tune, ctx && ctx->tune_one_launch, sh->N, sh->d, c, sh->n_out, sh->m,
-                                                (prac_dtype)sh->odt, beta, packed, sh->have_p_lp != 0).bytes);
+        {
+          const WgradPlan q = plan_wgrad_fast(n_cu, tune, ctx && ctx->tune_one_launch, sh->N, sh->d, c, sh->n_out, sh->m,
+                                              (prac_dtype)sh->odt, beta, packed, sh->have_p_lp != 0);
+          need = std::max(need, std::max(q.bytes, q.tails.main > 0 ? q.equal_bytes : 0));
+        }
         return need;
       }
       size_t need = 0;

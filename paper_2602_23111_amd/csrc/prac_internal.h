@@ -31,6 +31,7 @@ struct prac_ctx {
   float* part32;        // PRAC_PART32_BYTES for the token-split partial sums of the fp32 weight gradient (part of the ctx,
                         // not of the scratch block that grows: the split, and with it the bits of dW, never depends on
                         // what the ctx ran before)
+  float* tails;         // n_cu * PRAC_TAIL_BYTES for the partial sums of CtdyTails' helpers (part of the ctx)
   int prof_kind;      // kernel kind bracketed by events (0: none), see prac_profile_select
   int prof_stride;    // every prof_stride-th launch of that kind carries the event pair
   int64_t prof_seen;  // launches of that kind since the selection
@@ -40,6 +41,7 @@ struct prac_ctx {
 };
 
 #define PRAC_PART32_BYTES ((size_t)8 << 20)
+#define PRAC_TAIL_BYTES ((size_t)256 * 128 * 4)  // a 256 x 128 tile of partial sums, one per compute unit
 
 // Brackets the launches issued during its lifetime with a HIP event pair on the ctx
 // stream when the ctx is profiling this kernel kind.
@@ -167,27 +169,37 @@ int launch_pack_wfrag(prac_ctx* ctx, const bf16_t* W, int64_t ldw, int w_layout,
                       int ncb_w, bf16_t* out);
 // Token ranges of unequal length, for one round of workgroups where the tiles of T (256 x 128) do not divide the compute units.
 // Every tile gets `main` workgroups of `len` units of 128 tokens each; what is left at the end of its tokens, `tail` units, goes
-// to `helpers` workgroups, which share the tails of all tiles in equal runs of `run` units (tile after tile), so a tile's tail is
-// in up to `tail_parts` parts.  main == 0: equal ranges.
+// to `helpers` workgroups, which share the tails of all tiles in equal runs of `run` units (tile after tile).  main == 0: equal
+// ranges.  Partial sums are blocks of block_rows x 128, a tile each: `blocks` holds [main][t1 - t0], `tail_blocks` the pieces
+// of the tails in order (tile t's piece by helper q is number t + q, less that of the first).  Only tiles t0 .. t1 - 1 (row groups of
+// T after each other) are formed.
 struct CtdyTails {
-  int main = 0, len = 0, tail = 0, helpers = 0, run = 0, tail_parts = 0;
+  int main = 0, len = 0, tail = 0, helpers = 0, run = 0;
+  int block_rows = 0, t0 = 0, t1 = 0;
+  float* blocks = nullptr;
+  float* tail_blocks = nullptr;
 };
-// parts of the tail of tile t: first helper that works on it, and how many do
+// first helper that works on tile t's tail, and how many do
 static inline __host__ __device__ int ctdy_tail_first(const CtdyTails& p, int t) { return (int)((int64_t)t * p.tail / p.run); }
 static inline __host__ __device__ int ctdy_tail_parts(const CtdyTails& p, int t) {
   return (int)(((int64_t)(t + 1) * p.tail - 1) / p.run) - ctdy_tail_first(p, t) + 1;
 }
-// token-split partial sums of C^T dY_h for n_out outputs that share C; slabs[h] is parts x c x sld[h] (sld: row pitch, m[h]
+static inline __host__ __device__ int ctdy_tail_block(const CtdyTails& p, int t, int q) {
+  return t + q - p.t0 - ctdy_tail_first(p, p.t0);
+}
+// blocks that the tails of tiles t0 .. t1 - 1 take at most; no more than compute units for all of them
+static inline int ctdy_tail_blocks(const CtdyTails& p, int t0, int t1) {
+  return t1 - 1 + (int)(((int64_t)t1 * p.tail - 1) / p.run) - t0 - ctdy_tail_first(p, t0) + 1;
+}
+// token-split partial sums of C^T dY_h for n_out outputs that share C; slabs[h] is splits x c x sld[h] (sld: row pitch, m[h]
 // where nullptr).  any_element: rows of
 // dY_h may start on any element, and a row owns nothing past its last column (then m[h] >= 8); otherwise they are 16-byte
 // aligned and own whole 16-byte chunks (the caller says which: where the rows are a sample of a matrix, their pitch does not).
-// tails: unequal ranges (then `splits` is not looked at).  Only column tiles col0 .. col1 - 1 (128 columns each, counted over
-// all outputs) are formed; the slabs then hold those alone (one output).
+// tails with main > 0: unequal ranges instead (slabs, splits and sld are not looked at).
 #define PRAC_CTDY_MAX_OUT 4
 int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, const bf16_t* const* dY,
                    const int64_t* lddy, const int* m, float* const* slabs, int splits, bool any_element,
-                   int range_tokens = 0, const int* sld = nullptr, const CtdyTails* tails = nullptr, int col0 = 0,
-                   int col1 = 1 << 30);
+                   int range_tokens = 0, const int* sld = nullptr, const CtdyTails* tails = nullptr);
 // tokens of a range (whole 128-token tiles; the last ranges may be short or empty); launch_ctdy_ws takes another value for a
 // part of the ranges of a longer product
 inline int64_t ctdy_range_tokens(int64_t N, int splits) { return ((N + 127) / 128 + splits - 1) / splits * 128; }
@@ -209,10 +221,10 @@ int launch_pack_pfrag_split(prac_ctx* ctx, const float* P, int64_t d, int64_t ld
 int launch_unpack_c(prac_ctx* ctx, const bf16_t* Cpk, int N, int c, bf16_t* C, int64_t ldc);
 int launch_pack_c(prac_ctx* ctx, const bf16_t* C, int64_t ldc, int N, int c, bf16_t* Cpk);
 
-// (sld, tails, col0, col1 as for launch_ctdy_ws; the last column tile's padding in Tf is written with it)
+// (sld and tails as for launch_ctdy_ws; with tails only the part of T_h in tiles t0 .. t1 - 1, and the padding behind a row group's
+// last tile with that)
 int launch_reduce_to_tfrag(prac_ctx* ctx, int n_out, const float* const* slabs, int splits, int c, const int* m, int k_lo,
-                           float scale_hi, int nkb, const int* nmb, bf16_t* const* Tf, const int* sld, const CtdyTails& tails,
-                           int col0 = 0, int col1 = 1 << 30);
+                           float scale_hi, int nkb, const int* nmb, bf16_t* const* Tf, const int* sld, const CtdyTails& tails);
 int launch_pack_pafrag(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int c, int nrb, int nkb, bf16_t* out);
 // dW_h (d x m_h) = P T_h (+ beta dW_h) for n_out <= PRAC_CTDY_MAX_OUT outputs in one launch
 int launch_pt(prac_ctx* ctx, const bf16_t* Pa, int n_out, const bf16_t* const* Tf, int d, const int* m, int nkb,

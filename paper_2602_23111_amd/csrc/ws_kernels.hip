@@ -804,13 +804,12 @@ struct CtdyWsArgs {
   int64_t lddy[PRAC_CTDY_MAX_OUT];
   int m[PRAC_CTDY_MAX_OUT];
   int tile0[PRAC_CTDY_MAX_OUT + 1];
-  float* slabs[PRAC_CTDY_MAX_OUT];  // [parts][c][sld_h] each, from column 128 col0 on
+  float* slabs[PRAC_CTDY_MAX_OUT];  // [splits][c][sld_h] each
   int sld[PRAC_CTDY_MAX_OUT];       // row pitch of the slabs
   int splits;
   int tok_per_split;   // multiple of 128
   int tiles_n;         // column tiles of 128 over all outputs
   int row_groups;      // groups of 8 column blocks (256 rows of T) over c
-  int col0, cols;      // MODE 0: column tiles col0 .. col0 + cols - 1 are formed
   CtdyTails tails;     // TAILS
   int groups_per_xcd;  // MODE > 0: column tiles per XCD
   // ---- whole weight gradient in this launch (MODE > 0): the workgroups of one column tile sum their
@@ -1193,9 +1192,9 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
   const int bid = touch_kernel_args<(MODE == 0 ? offsetof(CtdyWsArgs, cnt) : sizeof(CtdyWsArgs))>(blockIdx.x);
 
   int tn = 0, rg = 0, split = 0;
-  int run_beg = 0, run_end = 0;  // helpers: units of the tails of all tiles
+  int run_beg = 0, run_end = -1;  // helpers: units of the tails of all tiles
   if constexpr (MODE == 0) {
-    const int per_split = a.cols * a.row_groups;
+    const int per_split = TAILS ? a.tails.t1 - a.tails.t0 : a.tiles_n * a.row_groups;
     const int mains = per_split * (TAILS ? a.tails.main : a.splits);
     const int total = mains + (TAILS ? a.tails.helpers : 0);
     const int per_xcd = (total + 7) / 8;
@@ -1204,10 +1203,12 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
     if (slot >= per_xcd || logical >= total) return;
     if (TAILS && logical >= mains) {
       run_beg = (logical - mains) * a.tails.run;
-      run_end = min(run_beg + a.tails.run, a.tiles_n * a.row_groups * a.tails.tail);
+      run_end = min(run_beg + a.tails.run, a.tails.t1 * a.tails.tail);
+      run_beg = max(run_beg, a.tails.t0 * a.tails.tail);
     } else {
-      tn = a.col0 + logical % a.cols;
-      rg = (logical / a.cols) % a.row_groups;
+      const int t = (TAILS ? a.tails.t0 : 0) + logical % per_split;
+      tn = t % a.tiles_n;
+      rg = t / a.tiles_n;
       split = logical / per_split;
     }
   } else {
@@ -1225,36 +1226,32 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   PRAC_STAMP(a, 0);
-  int n0 = 0, tok_beg = 0, tok_end = 0, nk = 0, hout = 0, part = 0;
+  int n0 = 0, tok_beg = 0, tok_end = 0, nk = 0, hout = 0;
+  float* block = nullptr;  // TAILS: where this piece's partial sums go
   // The next piece of work (uniform; false: no more): a column tile, which output it belongs to, and a range of tokens.
   bool first_segment = true;
   auto next_segment = [&]() {
     if constexpr (TAILS) {
-      if (run_end > 0) {
-        const CtdyTails& p = a.tails;
-        int len;
-        do {
-          if (run_beg >= run_end) return false;
-          const int t = run_beg / p.tail, off = run_beg - t * p.tail;
-          len = min(p.tail - off, run_end - run_beg);
-          tn = t % a.tiles_n;
-          rg = t / a.tiles_n;
-          tok_beg = (p.main * p.len + off) * CW_BK;
-          part = p.main + run_beg / p.run - ctdy_tail_first(p, t);
-          run_beg += len;
-        } while (tn < a.col0 || tn >= a.col0 + a.cols);
+      const CtdyTails& p = a.tails;
+      if (run_end >= 0) {
+        if (run_beg >= run_end) return false;
+        const int t = run_beg / p.tail, off = run_beg - t * p.tail, len = min(p.tail - off, run_end - run_beg);
+        tn = t % a.tiles_n;
+        rg = t / a.tiles_n;
+        tok_beg = (p.main * p.len + off) * CW_BK;
         tok_end = tok_beg + len * CW_BK;
+        block = p.tail_blocks + (int64_t)ctdy_tail_block(p, t, run_beg / p.run) * p.block_rows * CW_BN;
+        run_beg += len;
       } else {
         if (!first_segment) return false;
-        tok_beg = split * a.tails.len * CW_BK;
-        tok_end = tok_beg + a.tails.len * CW_BK;
-        part = split;
+        tok_beg = split * p.len * CW_BK;
+        tok_end = tok_beg + p.len * CW_BK;
+        block = p.blocks + (int64_t)(split * (p.t1 - p.t0) + rg * a.tiles_n + tn - p.t0) * p.block_rows * CW_BN;
       }
     } else {
       if (!first_segment) return false;
       tok_beg = split * a.tok_per_split;
       tok_end = tok_beg + a.tok_per_split;
-      part = split;
     }
     first_segment = false;
     tok_end = min(a.N, tok_end);
@@ -1423,10 +1420,16 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
   // epilogue: acc[4 i + j], register v of lane (li, lh): T row 32 (cb0 + i) + 8*(v/4) + 4*lh + v%4,
   // column n0 + 4 li + j
   PRAC_STAMP(a, 6);
-  const int sld = a.sld[hout], mh = a.m[hout];
-  float* out = a.slabs[hout] + (int64_t)part * a.c * sld;
-  const int n = n0 + 4 * li, ns = n - a.col0 * CW_BN;  // column of T, and of the slab (a.col0 > 0: one output)
-  const bool vec = (sld & 3) == 0 && n + 3 < (mh + 3) / 4 * 4;  // (a pitch of whole quads has room for the last one)
+  const int sld = TAILS ? CW_BN : a.sld[hout], mh = a.m[hout];
+  const int n = n0 + 4 * li;
+  float* out;
+  bool vec = true;  // (a block holds all 128 columns of its tile)
+  if constexpr (TAILS) {
+    out = block - (int64_t)rg * 256 * CW_BN + 4 * li;
+  } else {
+    out = a.slabs[hout] + (int64_t)split * a.c * sld + n;
+    vec = (sld & 3) == 0 && n < mh;  // (a pitch of whole quads has room for the last one)
+  }
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     asm volatile("" : "+a"(acc[4 * i]), "+a"(acc[4 * i + 1]), "+a"(acc[4 * i + 2]), "+a"(acc[4 * i + 3]) : : "memory");
@@ -1434,7 +1437,7 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
     for (int v = 0; v < 16; ++v) {
       const int row = (cb0 + i) * 32 + 8 * (v / 4) + 4 * lh + (v % 4);
       if (row < a.c) {
-        float* o = out + (int64_t)row * sld + ns;
+        float* o = out + (int64_t)row * sld;
         if (vec) {
           *reinterpret_cast<float4*>(o) =
               make_float4(acc[4 * i][v], acc[4 * i + 1][v], acc[4 * i + 2][v], acc[4 * i + 3][v]);
@@ -1573,14 +1576,12 @@ void fill_ctdy_args(CtdyWsArgs& a, const bf16_t* Cpk, int c, int N, int n_out, c
   a.tok_per_split = (int)ctdy_range_tokens(N, splits);
   a.tiles_n = tiles;
   a.row_groups = (a.ccb + 7) / 8;
-  a.col0 = 0;
-  a.cols = tiles;
 }
 }  // namespace
 
 int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, const bf16_t* const* dY,
                    const int64_t* lddy, const int* m, float* const* slabs, int splits, bool any_element, int range_tokens,
-                   const int* sld, const CtdyTails* tails, int col0, int col1) {
+                   const int* sld, const CtdyTails* tails) {
   if (n_out < 1 || n_out > PRAC_CTDY_MAX_OUT) return PRAC_EINVAL;
   for (int h = 0; h < n_out; ++h) {
     if (lddy[h] > PRAC_MAX_STREAM_PITCH) return PRAC_EINVAL;
@@ -1590,19 +1591,19 @@ int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, co
   CtdyWsArgs a{};
   fill_ctdy_args(a, Cpk, c, N, n_out, dY, lddy, m, slabs, splits, sld);
   if (range_tokens > 0) a.tok_per_split = range_tokens;
-  a.col0 = col0;
-  a.cols = std::min(col1, a.tiles_n) - col0;
-  if (col0 < 0 || a.cols < 1 || (col0 > 0 && n_out > 1)) return PRAC_EINVAL;
   const bool uneven = tails && tails->main > 0;
   if (uneven) {
-    // every token of every tile belongs to one main range or to a tail
-    if (any_element || tails->tail < 1 || tails->run < 1 || (int64_t)tails->helpers * tails->run < (int64_t)a.tiles_n * a.row_groups * tails->tail ||
-        (int64_t)(tails->main * tails->len + tails->tail) * CW_BK < N)
+    // every token of every tile belongs to one main range or to a tail, every tile of the launch has its blocks
+    const int64_t tiles = (int64_t)a.tiles_n * a.row_groups;
+    if (any_element || tails->tail < 1 || tails->run < 1 || (int64_t)tails->helpers * tails->run < tiles * tails->tail ||
+        tiles * tails->tail > INT32_MAX || (int64_t)(tails->main * tails->len + tails->tail) * CW_BK < N || tails->t0 < 0 ||
+        tails->t0 >= tails->t1 || tails->t1 > tiles || !tails->blocks || !tails->tail_blocks ||
+        tails->block_rows < std::min(256, c))
       return PRAC_EINVAL;
     a.tails = *tails;
   }
   const size_t smem = (size_t)CW_STAGES * CW_STAGE;
-  const int total = a.cols * a.row_groups * (uneven ? tails->main : splits) + (uneven ? tails->helpers : 0);
+  const int total = uneven ? (tails->t1 - tails->t0) * tails->main + tails->helpers : a.tiles_n * a.row_groups * splits;
   static bool done_dev[PRAC_MAX_DEVICES][3] = {};
   bool* done = done_dev[ctx->device % PRAC_MAX_DEVICES];
   const dim3 grid(((total + 7) / 8) * 8), block(512);
