@@ -436,7 +436,8 @@ __global__ __launch_bounds__(1024) void chol_upper_kernel(double* W, int b, doub
   }
 }
 
-// dst (rows x n, fp32) = src * R^-1 for the upper-triangular R (row-major n x n fp64, its 16 x 16 diagonal blocks inverted),
+// dst (rows x n fp32, pitch ldd) = src * R^-1 (src pitch n; dst may be src: a workgroup reads its rows before it writes them)
+// for the upper-triangular R (row-major n x n fp64, its 16 x 16 diagonal blocks inverted),
 // in fp64 on the matrix cores.  A workgroup of eight waves solves 16 rows, as the transpose R^-T src^T: wave w holds the column
 // tiles w, w + 8, ... of its rows as 16 x 16 accumulators Z_J (a result's registers are its operand layout, see above).  Step j:
 // X_j = R_jj^-T Z_j, then Z_J -= R_jJ^T X_j for every J > j.  The wave that holds tile j + 1 updates it first, solves it and
@@ -447,8 +448,8 @@ __global__ __launch_bounds__(1024) void chol_upper_kernel(double* W, int b, doub
 // requested ahead 64 us.
 constexpr int TR_ROWS = 16, TR_W = 8;
 template <int NT>
-__global__ __launch_bounds__(64 * TR_W) void trsm_right_upper_kernel(const float* __restrict__ src, const double* __restrict__ R,
-                                                               float* __restrict__ dst, int64_t rows, int n) {
+__global__ __launch_bounds__(64 * TR_W) void trsm_right_upper_kernel(const float* src, const double* __restrict__ R, float* dst,
+                                                                     int64_t ldd, int64_t rows, int n) {
   __shared__ double s_x[2][256];
   const int lane = threadIdx.x & 63, fi = lane & 15, fk = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -531,7 +532,7 @@ __global__ __launch_bounds__(64 * TR_W) void trsm_right_upper_kernel(const float
   });
   asm volatile("" : : "v"(touched));
   if (row < rows) {
-    float* const drow = dst + row * n;
+    float* const drow = dst + row * ldd;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const int c = 16 * (wave + TR_W * t) + 4 * fk;
@@ -867,6 +868,137 @@ __global__ __launch_bounds__(256) void copy_cols_kernel(const float* __restrict_
     dst[(i / cols) * ldd + i % cols] = src[(i / cols) * lds + i % cols];
 }
 
+// ------------------------------------------------------- Gram matrices of the panels
+// src^T src for a d x n fp32 block (pitch n) with fp64 sums on the matrix cores: the 64 x 64 tiles of the upper triangle (all that the
+// factorisation reads) times ranges of rows, as many as fill the chip; 32 x 32 per wave, 32 rows per step, the next step's
+// operands requested before this one's are multiplied.  Partial tiles go to `slabs` in register order.
+// 8.8 us at 2048 x 256, 13 us at 4096 x 256 (21 and 38 us with all tiles, four times the partial sums and each step's operands
+// requested when the step before was done); the sum 4.7 us.
+constexpr int PG_K = 32, PG_TILE = 64 * 64;
+static inline int pg_tiles(int n) { return ((n + 63) / 64) * ((n + 63) / 64 + 1) / 2; }
+__global__ __launch_bounds__(256) void panel_gram64_kernel(const float* __restrict__ src, int64_t d, int n, int64_t rows_per_split,
+                                                           double* __restrict__ slabs) {
+  const int lane = threadIdx.x & 63, fi = lane & 15, fk = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nb = (n + 63) / 64;
+  int J = blockIdx.x, I = 0;  // tile number -> (I, J), I <= J
+  while (J >= nb - I) {
+    J -= nb - I;
+    ++I;
+  }
+  J += I;
+  const int64_t kbeg = (int64_t)blockIdx.y * rows_per_split, kend = min(d, kbeg + rows_per_split);
+  const float* pa[2];
+  const float* pb[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {  // columns past n repeat the last one: their products are not used
+    pa[t] = src + min(64 * I + 32 * (wave >> 1) + 16 * t + fi, n - 1);
+    pb[t] = src + min(64 * J + 32 * (wave & 1) + 16 * t + fi, n - 1);
+  }
+  f64x4_t acc[2][2] = {};
+  struct Step {
+    float a[PG_K / 4][2], b[PG_K / 4][2];
+  };
+  auto load = [&](Step& s, int64_t k0, int64_t last) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < PG_K / 4; ++u) {
+      const int64_t o = min(k0 + 4 * u + fk, last) * n;
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        s.a[u][t] = pa[t][o];
+        s.b[u][t] = pb[t][o];
+      }
+    }
+  };
+  auto mul = [&](const Step& s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < PG_K / 4; ++u)
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+          acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)s.a[u][x], (double)s.b[u][y], acc[x][y], 0, 0, 0);
+  };
+  const int64_t full = (kend - kbeg) / PG_K, last = kend - 1;
+  Step s0, s1;
+  load(s0, kbeg, last);
+  int64_t i = 0;
+  for (; i + 2 <= full; i += 2) {
+    load(s1, kbeg + (i + 1) * PG_K, last);
+    mul(s0);
+    load(s0, kbeg + (i + 2) * PG_K, last);  // (past the range: its last row again, not used)
+    mul(s1);
+  }
+  if (i < full) {
+    load(s1, kbeg + (i + 1) * PG_K, last);
+    mul(s0);
+    s0 = s1;
+  }
+  if (kbeg + full * PG_K < kend) {  // fewer than 32 rows: the others are zero
+#pragma unroll
+    for (int u = 0; u < PG_K / 4; ++u)
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+        if (kbeg + full * PG_K + 4 * u + fk > last) s0.a[u][t] = s0.b[u][t] = 0.f;
+    mul(s0);
+  }
+  double* const o = slabs + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * PG_TILE + wave * 1024 + lane;
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) o[((2 * x + y) * 4 + v) * 64] = acc[x][y][v];
+}
+
+// W (n x n) = sum over the ranges, tiles of the upper triangle
+__global__ __launch_bounds__(256) void panel_gram64_sum_kernel(const double* __restrict__ slabs, int splits, int n,
+                                                               double* __restrict__ W) {
+  const int nb = (n + 63) / 64, tiles = gridDim.x / 16;
+  const int tile = blockIdx.x >> 4, e = (blockIdx.x & 15) * 256 + threadIdx.x;
+  int J = tile, I = 0;
+  while (J >= nb - I) {
+    J -= nb - I;
+    ++I;
+  }
+  J += I;
+  const int lane = e & 63, v = (e >> 6) & 3, y = (e >> 8) & 1, x = (e >> 9) & 1, wave = e >> 10;
+  const int row = 64 * I + 32 * (wave >> 1) + 16 * x + 4 * v + (lane >> 4), c = 64 * J + 32 * (wave & 1) + 16 * y + (lane & 15);
+  double s = 0.0;
+  const double* p = slabs + (int64_t)tile * PG_TILE + e;
+#pragma unroll 8
+  for (int z = 0; z < splits; ++z) s += p[(int64_t)z * tiles * PG_TILE];
+  if (row < n && c < n) W[(int64_t)row * n + c] = s;
+}
+
+// The sum of the fp32 partial Gram matrices of a block, as fp64 (W64 != nullptr) or as the factor 1.5 I - 0.5 W of a Newton-Schulz step.
+// For the latter W is the Gram matrix of a block that should be close to orthonormal: an entry further than `limit` from the
+// identity (or not finite) raises bit 1 of *flag - the step that follows squares the distance, so a block that far off
+// does not come out orthonormal to fp32 rounding.  (slabs may be M32 itself)
+__global__ __launch_bounds__(256) void panel_gram32_sum_kernel(const float* slabs, int splits, int n, double* W64, float* M32,
+                                                               float limit, int* flag) {
+  bool off = false;
+  const int total = n * n;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+    float w = 0.f;
+#pragma unroll 8
+    for (int z = 0; z < splits; ++z) w += slabs[(int64_t)z * total + i];
+    if (W64) {
+      W64[i] = (double)w;
+    } else {
+      const float id = i / n == i % n ? 1.f : 0.f;
+      off = off || !(fabsf(w - id) <= limit);
+      M32[i] = 1.5f * id - 0.5f * w;
+    }
+  }
+  if (off) atomicOr(flag, 1);
+}
+
+// row ranges of panel_gram64_kernel: whole steps, one workgroup per compute unit
+int pg_splits(int n_cu, int64_t d, int n) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>(n_cu / pg_tiles(n), (d + PG_K - 1) / PG_K));
+}
+
 struct FitWs {
   size_t G, V, Y, W64, X64, Rinv, lam, Z, S, T, slabs, slab_bytes, gram, total;
   size_t trk_pf, trk_c, trk_slabs;  // tracking refit: V in fragment order, packed X V, slabs of (X V)^T X
@@ -944,6 +1076,8 @@ FitWs plan_fit(int64_t d, int k, int r, const prac_fit_opts& o, int n_cu, bool n
   const size_t slab_bb = (size_t)s * bb * bb * 8, slab_gv = sg > 1 ? (size_t)sg * d * b * 4 : 0;
   const size_t slab_kr = (size_t)s * k * rf * 4;  // also the completion's Q1^T S (kq x fill)
   w.slab_bytes = std::max(slab_bb, std::max(slab_gv, slab_kr));
+  for (int n : {b, kq, k - kq, r})  // the panel Gram matrices with fp64 sums
+    if (n > 0) w.slab_bytes = std::max(w.slab_bytes, (size_t)pg_splits(n_cu, d, n) * pg_tiles(n) * PG_TILE * 8);
   w.slabs = p.take(w.slab_bytes);
   w.gram = p.take(gram_bytes);
   if (track) {
@@ -975,50 +1109,53 @@ int set_dyn_smem(prac_ctx* ctx) {
   return PRAC_OK;
 }
 
-__global__ __launch_bounds__(256) void f32_to_f64_kernel(const float* __restrict__ src, double* __restrict__ dst, int n) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) dst[i] = (double)src[i];
+// src^T src for a d x n block (ld = n) with fp64 sums: the upper triangle of W64
+int panel_gram64(prac_ctx* ctx, const FitWs& w, const float* src, int64_t d, int n, double* W64) {
+  const int tiles = pg_tiles(n), splits = pg_splits(ctx->n_cu, d, n);
+  if ((size_t)splits * tiles * PG_TILE * 8 > w.slab_bytes) return PRAC_EINVAL;
+  double* slabs = reinterpret_cast<double*>(ctx->ws + w.slabs);
+  const int64_t per = round_up64((d + splits - 1) / splits, PG_K);
+  const int used = (int)((d + per - 1) / per);
+  hipLaunchKernelGGL(panel_gram64_kernel, dim3(tiles, used), dim3(256), 0, ctx->stream, src, d, n, per, slabs);
+  hipLaunchKernelGGL(panel_gram64_sum_kernel, dim3(tiles * 16), dim3(256), 0, ctx->stream, slabs, used, n, W64);
+  PRAC_HIP_TRY(ctx, hipGetLastError());
+  return PRAC_OK;
 }
 
-// W (n x n) <- 1.5 I - 0.5 W.  W is the Gram matrix of a block that should be close to orthonormal: an entry
-// further than `limit` from the identity (or not finite) raises bit 1 of *flag - the step that follows squares
-// the distance, so a block that far off does not come out orthonormal to fp32 rounding.
-__global__ __launch_bounds__(256) void newton_schulz_factor_kernel(float* W, int n, float limit, int* flag) {
-  bool off = false;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n * n; i += gridDim.x * blockDim.x) {
-    const float id = i / n == i % n ? 1.f : 0.f;
-    off = off || !(fabsf(W[i] - id) <= limit);
-    W[i] = 1.5f * id - 0.5f * W[i];
-  }
-  if (off) atomicOr(flag, 1);
-}
-
-// M (n x n) = src^T src for a d x n block (ld = n): fp64 sums into W64, or fp32 sums on the matrix
-// cores into M32 (enough for a block whose condition number is small)
-int panel_gram(prac_ctx* ctx, const FitWs& w, const float* src, int64_t d, int n, double* W64, float* M32) {
+// src^T src with fp32 sums on the matrix cores (enough for a block whose condition number is small), as fp64 or as the factor
+// of a Newton-Schulz step
+int panel_gram32(prac_ctx* ctx, const FitWs& w, const float* src, int64_t d, int n, double* W64, float* factor, float limit) {
   GemmGenArgs g{};
   g.A = src; g.B = src; g.adt = PRAC_F32; g.bdt = PRAC_F32;
   g.a_rs = 1; g.a_cs = n; g.b_rs = n; g.b_cs = 1;
   g.M = n; g.N = n; g.K = d; g.k_stride = 1;
   g.ldo = n; g.alpha = 1.f; g.beta = 0.f;
-  g.splits = w.splits_bb; g.slabs = ctx->ws + w.slabs; g.slab_bytes = w.slab_bytes;
-  if (W64) { g.out = nullptr; g.out64 = W64; g.acc64 = true; }
-  else { g.out = M32; g.out64 = nullptr; g.acc64 = false; }
-  return launch_gemm_generic(ctx, g);
+  float* M32 = reinterpret_cast<float*>(ctx->ws + w.Rinv);
+  const float* sums = M32;
+  int splits = 1, rc;
+  if (gemm_f32_takes(g)) {
+    splits = w.splits_bb;
+    if (splits > 1 && (size_t)splits * n * n * 4 > w.slab_bytes) return PRAC_EINVAL;
+    g.out = M32;
+    g.slabs = ctx->ws + w.slabs;
+    rc = launch_gemm_f32(ctx, g, splits);
+    if (splits > 1) sums = reinterpret_cast<const float*>(g.slabs);
+  } else {
+    g.out = M32;
+    rc = launch_gemm_generic(ctx, g);
+  }
+  if (rc) return rc;
+  hipLaunchKernelGGL(panel_gram32_sum_kernel, dim3((n * n + 255) / 256), dim3(256), 0, ctx->stream, sums, splits, n, W64, factor,
+                     limit, ctx->d_flag);
+  PRAC_HIP_TRY(ctx, hipGetLastError());
+  return PRAC_OK;
 }
 
-// dst = src R^-1 with R^T R = src^T src (+ shift): one Cholesky-QR pass
-int cholqr_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int64_t d, int n, double shift, bool gram64) {
+// dst (pitch ldd; may be src) = src R^-1 with R^T R = src^T src (+ shift): one Cholesky-QR pass
+int cholqr_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int64_t ldd, int64_t d, int n, double shift, bool gram64) {
   double* W64 = reinterpret_cast<double*>(ctx->ws + w.W64);
-  int rc;
-  if (gram64) {
-    rc = panel_gram(ctx, w, src, d, n, W64, nullptr);
-    if (rc) return rc;
-  } else {
-    float* M32 = reinterpret_cast<float*>(ctx->ws + w.Rinv);
-    rc = panel_gram(ctx, w, src, d, n, nullptr, M32);
-    if (rc) return rc;
-    hipLaunchKernelGGL(f32_to_f64_kernel, dim3((n * n + 255) / 256), dim3(256), 0, ctx->stream, M32, W64, n * n);
-  }
+  int rc = gram64 ? panel_gram64(ctx, w, src, d, n, W64) : panel_gram32(ctx, w, src, d, n, W64, nullptr, 0.f);
+  if (rc) return rc;
   rc = set_dyn_smem(ctx);
   if (rc) return rc;
   if (n > CH_MAX) return PRAC_EUNSUPPORTED;
@@ -1028,60 +1165,53 @@ int cholqr_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int
     hipLaunchKernelGGL(chol_upper_kernel, dim3(1), dim3(1024),
                        (size_t)CH_NB * (round_up64(n, CH_NB) + 2) * sizeof(double), ctx->stream, W64, n, shift, ctx->d_flag);
   const dim3 tgrid((unsigned)((d + TR_ROWS - 1) / TR_ROWS)), tblock(64 * TR_W);
-  if (n <= 128) hipLaunchKernelGGL(trsm_right_upper_kernel<1>, tgrid, tblock, 0, ctx->stream, src, W64, dst, d, n);
-  else if (n <= 256) hipLaunchKernelGGL(trsm_right_upper_kernel<2>, tgrid, tblock, 0, ctx->stream, src, W64, dst, d, n);
-  else if (n <= 512) hipLaunchKernelGGL(trsm_right_upper_kernel<4>, tgrid, tblock, 0, ctx->stream, src, W64, dst, d, n);
-  else hipLaunchKernelGGL(trsm_right_upper_kernel<8>, tgrid, tblock, 0, ctx->stream, src, W64, dst, d, n);
+  if (n <= 128) hipLaunchKernelGGL(trsm_right_upper_kernel<1>, tgrid, tblock, 0, ctx->stream, src, W64, dst, ldd, d, n);
+  else if (n <= 256) hipLaunchKernelGGL(trsm_right_upper_kernel<2>, tgrid, tblock, 0, ctx->stream, src, W64, dst, ldd, d, n);
+  else if (n <= 512) hipLaunchKernelGGL(trsm_right_upper_kernel<4>, tgrid, tblock, 0, ctx->stream, src, W64, dst, ldd, d, n);
+  else hipLaunchKernelGGL(trsm_right_upper_kernel<8>, tgrid, tblock, 0, ctx->stream, src, W64, dst, ldd, d, n);
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
 }
 
-// dst = src (1.5 I - 0.5 src^T src): one Newton-Schulz step towards orthonormal columns.  For a block
+// dst (pitch ldd) = src (1.5 I - 0.5 src^T src): one Newton-Schulz step towards orthonormal columns.  For a block
 // with ||src^T src - I|| = e the result has 0.75 e^2: the cheap second pass after a Cholesky-QR pass,
 // made of two products and no factorisation.
-int polish_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int64_t d, int n, float limit) {
+int polish_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int64_t ldd, int64_t d, int n, float limit) {
   float* M32 = reinterpret_cast<float*>(ctx->ws + w.Rinv);
-  int rc = panel_gram(ctx, w, src, d, n, nullptr, M32);
+  int rc = panel_gram32(ctx, w, src, d, n, nullptr, M32, limit);
   if (rc) return rc;
-  hipLaunchKernelGGL(newton_schulz_factor_kernel, dim3((n * n + 255) / 256), dim3(256), 0, ctx->stream, M32, n, limit,
-                     ctx->d_flag);
-  PRAC_HIP_TRY(ctx, hipGetLastError());
   GemmGenArgs g{};
   g.A = src; g.B = M32; g.adt = PRAC_F32; g.bdt = PRAC_F32;
   g.a_rs = n; g.a_cs = 1; g.b_rs = n; g.b_cs = 1;
   g.M = (int)d; g.N = n; g.K = n; g.k_stride = 1;
-  g.out = dst; g.ldo = n; g.alpha = 1.f; g.beta = 0.f; g.acc64 = false; g.out64 = nullptr;
+  g.out = dst; g.ldo = ldd; g.alpha = 1.f; g.beta = 0.f; g.acc64 = false; g.out64 = nullptr;
   return launch_gemm_generic(ctx, g);
 }
 
-// V (d x n, ld = n, fp32) <- orth(Y): `passes` rounds of Cholesky-QR (the first one shifted), then
-// `polish` Newton-Schulz steps; ping-pongs between Y and V, result always ends in `V`.
+// out (d x n fp32, pitch ldo) <- orth(Y): `passes` rounds of Cholesky-QR (the first one shifted), then
+// `polish` Newton-Schulz steps.  Y is overwritten, and so is the work space V; out may be V or somewhere else.
 // gram64_first = false: the first Gram matrix is summed in fp32 (well-conditioned blocks only).
-int cholqr(prac_ctx* ctx, const FitWs& w, float* Y, float* V, int64_t d, int n, int passes, double first_shift,
-           int polish = 0, bool gram64_first = true) {
+int cholqr(prac_ctx* ctx, const FitWs& w, float* Y, float* V, int64_t d, int n, int passes, double first_shift, float* out,
+           int64_t ldo, int polish = 0, bool gram64_first = true) {
   float* src = Y;
-  float* dst = V;
   for (int pass = 0; pass < passes + polish; ++pass) {
+    const bool last = pass == passes + polish - 1;
+    // a solve may stay where it is, a product may not
+    float* dst = last ? out : (src == Y ? V : Y);
+    const int64_t ldd = last ? ldo : n;
+    if (pass >= passes && dst == src) return PRAC_EINVAL;
     // Later passes work on a block that is orthonormal up to the first pass's error, except in
     // directions where the input was rank deficient: there the Gram matrix is zero up to rounding
     // (a few 1e-16), and the shift has to be safely above that for the pivot to stay positive.
     // the last Newton-Schulz step must start within 3e-3 of orthonormal to end below 1e-5 (0.75 e^2); earlier
     // ones may start anywhere inside the step's region of convergence
-    int rc = pass < passes ? cholqr_pass(ctx, w, src, dst, d, n, pass == 0 ? first_shift : 1e-13, pass > 0 || gram64_first)
-                           : polish_pass(ctx, w, src, dst, d, n, pass == passes + polish - 1 ? 3e-3f : 0.5f);
+    int rc = pass < passes ? cholqr_pass(ctx, w, src, dst, ldd, d, n, pass == 0 ? first_shift : 1e-13, pass > 0 || gram64_first)
+                           : polish_pass(ctx, w, src, dst, ldd, d, n, last ? 3e-3f : 0.5f);
     if (rc) return rc;
-    float* t = src; src = dst; dst = t;
-  }
-  // result is in `src` after the swap
-  if (src != V) {
-    hipLaunchKernelGGL(copy_cols_kernel, dim3(ctx->n_cu * 4), dim3(256), 0, ctx->stream, src, (int64_t)n, V,
-                       (int64_t)n, d, n);
-    PRAC_HIP_TRY(ctx, hipGetLastError());
+    src = dst;
   }
   return PRAC_OK;
 }
-
-
 
 // The scratch plan of one fit: which path runs (tracking / Gram-based) and where everything lives.
 struct FitPlan {
@@ -1121,6 +1251,7 @@ int64_t fit_slab_margin(int n_cu, prac_dtype xdt, int64_t N, int64_t d, int k, i
   size_t need = 0;
   auto product = [&](int splits, int64_t M, int64_t Nn, size_t esz) {
     if (splits > 1) need = std::max(need, (size_t)splits * M * Nn * esz);
+    if (M == Nn) need = std::max(need, (size_t)pg_splits(n_cu, d, (int)M) * pg_tiles((int)M) * PG_TILE * 8);
   };
   if (f.do_q1) {
     const int n = L.b;  // block width of the iteration (k when tracking)
@@ -1179,11 +1310,10 @@ int fit_basis_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, in
       // lambda_k, within reach of a Cholesky factor of the fp64 Gram matrix with a shift just above its
       // rounding (so that a rank-deficient batch still factors); the last
       // iteration then gets two Newton-Schulz steps in place of a second factorisation.
-      rc = cholqr(ctx, L, Y, V, d, k, 1, 1e-14, it == o.iters - 1 ? 2 : 0);
+      const bool last = it == o.iters - 1;
+      rc = cholqr(ctx, L, Y, V, d, k, 1, 1e-14, last ? P : V, last ? ldp : (int64_t)k, last ? 2 : 0);
       if (rc) return rc;
     }
-    hipLaunchKernelGGL(copy_cols_kernel, dim3(ctx->n_cu * 4), dim3(256), 0, st, V, (int64_t)k, P, ldp, d, k);
-    PRAC_HIP_TRY(ctx, hipGetLastError());
   } else if (do_q1) {
     const int b = L.b;
     const int k = L.kq;  // the columns this iteration computes: all of Q1 unless the batch has fewer rows than that
@@ -1191,33 +1321,28 @@ int fit_basis_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, in
     if (rc) return rc;
 
     // start block: Gaussian (stream 0); warm start puts the previous Q1 in front
-    rc = launch_philox(ctx, seed, draw, 0u, Y, d * b, true);
+    rc = launch_philox(ctx, seed, draw, 0u, V, d * b, true);
     if (rc) return rc;
     if (o.warm_start) {
-      hipLaunchKernelGGL(copy_cols_kernel, dim3(ctx->n_cu * 4), dim3(256), 0, st, P, ldp, Y, (int64_t)b, d, k);
+      hipLaunchKernelGGL(copy_cols_kernel, dim3(ctx->n_cu * 4), dim3(256), 0, st, P, ldp, V, (int64_t)b, d, k);
       PRAC_HIP_TRY(ctx, hipGetLastError());
     }
     // The start block goes into the first product as it is: a Gaussian block and the previous
     // (orthonormal) Q1 are both well conditioned, and every product is orthonormalised anyway.
     for (int it = 0; it <= o.iters; ++it) {
-      // Y = G V  (first round: V is the start block, still in Y's buffer, so the roles swap)
+      // Y = G V
       GemmGenArgs g{};
-      g.A = G; g.B = it == 0 ? Y : V; g.adt = PRAC_F32; g.bdt = PRAC_F32;
+      g.A = G; g.B = V; g.adt = PRAC_F32; g.bdt = PRAC_F32;
       g.a_rs = 1; g.a_cs = d; g.b_rs = b; g.b_cs = 1;  // G(m, k) read as G[k][m]: G is symmetric
       g.M = (int)d; g.N = b; g.K = d; g.k_stride = 1;
       g.splits = L.splits_gv; g.slabs = ctx->ws + L.slabs; g.slab_bytes = L.slab_bytes;
-      g.out = it == 0 ? V : Y; g.ldo = b; g.alpha = 1.f; g.beta = 0.f; g.acc64 = false; g.out64 = nullptr;
+      g.out = Y; g.ldo = b; g.alpha = 1.f; g.beta = 0.f; g.acc64 = false; g.out64 = nullptr;
       rc = launch_gemm_generic(ctx, g);
       if (rc) return rc;
-      if (it == 0) {
-        // product landed in V: move it to Y so that orth() below reads Y and writes V as always
-        hipLaunchKernelGGL(copy_cols_kernel, dim3(ctx->n_cu * 4), dim3(256), 0, st, V, (int64_t)b, Y, (int64_t)b, d, b);
-        PRAC_HIP_TRY(ctx, hipGetLastError());
-      }
       if (it == o.iters) break;  // the last product feeds Rayleigh-Ritz
       // one shifted pass keeps the block well conditioned; the last iteration orthonormalises fully
       // (two passes: the second starts from a block whose condition number is already near one)
-      rc = cholqr(ctx, L, Y, V, d, b, it == o.iters - 1 ? 2 : 1, 1e-11);
+      rc = cholqr(ctx, L, Y, V, d, b, it == o.iters - 1 ? 2 : 1, 1e-11, V, b);
       if (rc) return rc;
     }
     // Rayleigh-Ritz: H = V^T (G V), eigenvectors of H, Q1 = V Z[:, :k]
@@ -1273,10 +1398,8 @@ int fit_basis_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, in
     // tidy the rounding of the last product (two Cholesky-QR passes and a Newton-Schulz step: with more
     // Ritz vectors asked for than the data has rank, the surplus ones are rounding noise, far from
     // orthogonal to each other, and one pass leaves 1e-4 or more), then store Q1 into P[:, :k]
-    rc = cholqr(ctx, L, Y, V, d, k, 2, 1e-13, 1);
+    rc = cholqr(ctx, L, Y, V, d, k, 2, 1e-13, P, ldp, 1);
     if (rc) return rc;
-    hipLaunchKernelGGL(copy_cols_kernel, dim3(ctx->n_cu * 4), dim3(256), 0, st, V, (int64_t)k, P, ldp, d, k);
-    PRAC_HIP_TRY(ctx, hipGetLastError());
   }
 
   // P[:, kk : kk + rr] = orth((I - Q Q^T)^2 S) for Q = P[:, :kk] and the Gaussian d x rr block S of Philox
@@ -1311,12 +1434,8 @@ int fit_basis_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, in
     // each other): fp32 sums are enough for its Gram matrix, and one Newton-Schulz step finishes it
     // (up to r = d/4, where the ratio of the extreme singular values reaches 3; wider blocks keep two
     // Cholesky-QR passes over fp64 Gram matrices)
-    if ((int64_t)4 * r <= d - k) rc = cholqr(ctx, L, S, V, d, r, 1, 1e-13, 1, false);
-    else rc = cholqr(ctx, L, S, V, d, r, 2, 1e-13);
-    if (rc) return rc;
-    hipLaunchKernelGGL(copy_cols_kernel, dim3(ctx->n_cu * 4), dim3(256), 0, st, V, (int64_t)r, P + k, ldp, d, r);
-    PRAC_HIP_TRY(ctx, hipGetLastError());
-    return PRAC_OK;
+    if ((int64_t)4 * r <= d - k) return cholqr(ctx, L, S, V, d, r, 1, 1e-13, P + k, ldp, 1, false);
+    return cholqr(ctx, L, S, V, d, r, 2, 1e-13, P + k, ldp);
   };
   // the columns of Q1 that the batch's rows do not define (stream 2), then Q2 (stream 1) against all of Q1
   if (do_q1 && L.kq < k) {
