@@ -454,18 +454,24 @@ __global__ __launch_bounds__(256) void pt_kernel(PtArgs a) {
 
 // The same product for shapes with many tiles or a long K (c of several hundred, a wide or
 // tall dW): operands go through LDS so that each fragment crosses L2 -> L1 once per workgroup
-// instead of once per wave.  TM x 128 tile, 2 x 2 waves of (TM/2) x 64, K in chunks of
-// PT2_KC k-blocks; the next chunk is fetched into registers while the current one is
+// instead of once per wave.  128 x 128 tile, 2 x 2 waves of 64 x 64, K in chunks of
+// KC k-blocks; the next chunk is fetched into registers while the current one is
 // multiplied and written to the other LDS stage afterwards.  Fragments are stored in
 // fragment order, so the copy is a straight 16 bytes per lane and every LDS access of a wave
 // covers one contiguous 1 KB block.
-constexpr int PT2_KC = 4;
-constexpr int PT2_ELD = 64 + 4;  // floats per row of a wave's output staging tile (64 x 64)
-template <int TM, bool OUT_BF16>
-__global__ __launch_bounds__(256) void pt_tiled_kernel(PtArgs a) {
+// It is bound by latency (a chunk's loads, the stores of a tile), so what counts is how many workgroups a compute unit holds:
+// four with two k-blocks per chunk (35 KB of LDS, half a wave tile staged at a time), two with four.  The latter is the better one where
+// a tile is a few chunks: last product alone, N = 2048, four k-blocks / two, and two workgroups with whole wave tiles staged before:
+// d = 4096, m = 5000, c = 128 20.6 / 22.6, 21.6; 3000, 8192, 128 in fp32 46.4 / 51.6, 48.9; 8192, 8192, 64 33.6 / 28.3, 35.1;
+// 2048, 8192, 512 33.0 / 30.6, 35.1; 4096, 11008, 512 81.1 / 65.0, 89.6; 8192, 8192, 1024 in fp32 229 / 208, 247.
+// (Tiles of 256 x 256, one workgroup of 8 waves per compute unit: 75.0 at 4096, 11008, 512, but 276 at the last and 78.6 at the second.)
+constexpr int PT2_ELD = 64 + 4;  // floats per row of a wave's output staging tile (32 x 64)
+template <int KC, bool OUT_BF16>
+__global__ __launch_bounds__(256, 8 / KC) void pt_tiled_kernel(PtArgs a) {
+  constexpr int TM = 128;
   constexpr int RB = TM / 32;  // 32-row blocks of the tile
   constexpr int RI = TM / 64;  // A fragments per wave and k-block
-  constexpr int A_BYTES = RB * PT2_KC * 1024, B_BYTES = PT2_KC * 4 * 1024, STAGE = A_BYTES + B_BYTES;
+  constexpr int A_BYTES = RB * KC * 1024, B_BYTES = KC * 4 * 1024, STAGE = A_BYTES + B_BYTES;
   constexpr int A_LD = A_BYTES / 4096, B_LD = B_BYTES / 4096;  // 16-byte loads per thread and chunk
   extern __shared__ __align__(16) unsigned char pt_smem[];
 
@@ -475,7 +481,13 @@ __global__ __launch_bounds__(256) void pt_tiled_kernel(PtArgs a) {
   const int xcd = bid & 7, slot = bid >> 3;
   const int logical = xcd * per_xcd + slot;
   if (slot >= per_xcd || logical >= total) return;
-  const int tn_g = logical % a.tiles_n, tm = logical / a.tiles_n;
+  // c > 256: groups of eight row tiles, a group's tiles column by column, so that an XCD's run of tiles needs eight row tiles of P
+  // and part of T instead of all of T for every row tile.  Narrower products are bound by the write of dW and
+  // stay row by row (d = 4096, m = 11008, c = 512 90.5 against 73.9 us; d = 3000, m = 8192, c = 128 in fp32 47.7 against 62.4).
+  const int group_rows = a.nkb > 16 ? 8 : 1;
+  const int group = logical / (group_rows * a.tiles_n), in = logical - group * group_rows * a.tiles_n;
+  const int rows = min(group_rows, a.tiles_m - group * group_rows);
+  const int tn_g = in / rows, tm = group * group_rows + in - tn_g * rows;
   const int h = pt_output_of(a, tn_g), tn = tn_g - a.tile0[h];
   const u32x4* __restrict__ Tf = reinterpret_cast<const u32x4*>(a.Tf[h]);
   void* const odW = a.dW[h];
@@ -495,22 +507,21 @@ __global__ __launch_bounds__(256) void pt_tiled_kernel(PtArgs a) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  // sweep s of A: row block s of the tile, its PT2_KC k-blocks (4 KB, contiguous in Pa); sweep s
-  // of B: k-block s of the chunk, the tile's four column blocks (4 KB, contiguous in Tf).
+  // Block s of a wave's share of A is number 4 s + wave of [row block][k-block], of B the same of [k-block][column block].
   // k-blocks past the end re-read the last one and are not multiplied; row blocks past the
   // end re-read the last one and their rows are not stored.
   u32x4 ra[A_LD], rb[B_LD];
-  const int sub = tid >> 6;  // which 1 KB block of a sweep this thread copies
+  const int wv = __builtin_amdgcn_readfirstlane(wave);
   auto gload = [&](int kb0) {
 #pragma unroll
     for (int s = 0; s < A_LD; ++s) {
-      const int rbg = min(tm * RB + s, nrb - 1), kb = min(kb0 + sub, a.nkb - 1);
+      const int q = 4 * s + wv, rbg = min(tm * RB + q / KC, nrb - 1), kb = min(kb0 + q % KC, a.nkb - 1);
       ra[s] = Pa[((int64_t)rbg * a.nkb + kb) * 64 + lane];
     }
 #pragma unroll
     for (int s = 0; s < B_LD; ++s) {
       const int kb = min(kb0 + s, a.nkb - 1);
-      rb[s] = Tf[((int64_t)kb * onmb + tn * 4 + sub) * 64 + lane];
+      rb[s] = Tf[((int64_t)kb * onmb + tn * 4 + wv) * 64 + lane];
     }
   };
   auto sstore = [&](int stage) {
@@ -525,18 +536,18 @@ __global__ __launch_bounds__(256) void pt_tiled_kernel(PtArgs a) {
   sstore(0);
   __syncthreads();
   int stage = 0;
-  for (int kb0 = 0; kb0 < a.nkb; kb0 += PT2_KC) {
-    const bool more = kb0 + PT2_KC < a.nkb;
-    if (more) gload(kb0 + PT2_KC);
+  for (int kb0 = 0; kb0 < a.nkb; kb0 += KC) {
+    const bool more = kb0 + KC < a.nkb;
+    if (more) gload(kb0 + KC);
     const unsigned char* st = pt_smem + stage * STAGE;
-    const int kbs = min(PT2_KC, a.nkb - kb0);
+    const int kbs = min(KC, a.nkb - kb0);
 #pragma unroll
-    for (int q = 0; q < PT2_KC; ++q) {
+    for (int q = 0; q < KC; ++q) {
       if (q < kbs) {
         u32x4 fa[RI], fb[2];
 #pragma unroll
         for (int i = 0; i < RI; ++i)
-          fa[i] = *reinterpret_cast<const u32x4*>(st + ((wr * RI + i) * PT2_KC + q) * 1024 + lane * 16);
+          fa[i] = *reinterpret_cast<const u32x4*>(st + ((wr * RI + i) * KC + q) * 1024 + lane * 16);
 #pragma unroll
         for (int j = 0; j < 2; ++j)
           fb[j] = *reinterpret_cast<const u32x4*>(st + A_BYTES + (q * 4 + wc * 2 + j) * 1024 + lane * 16);
@@ -552,24 +563,22 @@ __global__ __launch_bounds__(256) void pt_tiled_kernel(PtArgs a) {
     __syncthreads();
   }
 
-  // epilogue: each wave stages 64 x 64 of its tile at a time through its own LDS region (fp32, padded
+  // epilogue: each wave stages 32 x 64 of its tile at a time through its own LDS region (fp32, padded
   // rows) and stores 16-byte chunks along rows.  Block (i, j): register v of lane (li, lh) is row
   // 32 i + 8 (v / 4) + 4 lh + v % 4, column 32 j + li of the wave tile.
-  float* tile = reinterpret_cast<float*>(pt_smem) + wave * (64 * PT2_ELD);
+  float* tile = reinterpret_cast<float*>(pt_smem) + wave * (32 * PT2_ELD);
   const int er = lane >> 3, ec = (lane & 7) * 8;  // 8 lanes per row, 8 rows per step
 #pragma unroll
-  for (int p = 0; p < RI / 2; ++p) {
+  for (int i = 0; i < RI; ++i) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int v = 0; v < 16; ++v)
+        tile[(8 * (v / 4) + 4 * lh + (v % 4)) * PT2_ELD + 32 * j + li] = acc[i][j][v];
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
-          tile[(32 * i + 8 * (v / 4) + 4 * lh + (v % 4)) * PT2_ELD + 32 * j + li] = acc[2 * p + i][j][v];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
+    for (int q = 0; q < 4; ++q) {
       const int row = er + 8 * q;
-      const int grow = tm * TM + wr * (TM / 2) + p * 64 + row, gcol = tn * 128 + wc * 64 + ec;
+      const int grow = tm * TM + wr * (TM / 2) + i * 32 + row, gcol = tn * 128 + wc * 64 + ec;
       const float4 lo = *reinterpret_cast<const float4*>(tile + row * PT2_ELD + ec);
       const float4 hi = *reinterpret_cast<const float4*>(tile + row * PT2_ELD + ec + 4);
       if (grow >= a.d || gcol >= om) continue;
@@ -1122,12 +1131,13 @@ int launch_pt(prac_ctx* ctx, const bf16_t* Pa, int n_out, const bf16_t* const* T
   a.tiles_m = (d + 127) / 128;
   const int total = a.tiles_m * a.tiles_n;
   const bool tiled = total > ctx->n_cu || nkb > PT_PD;
+  const int kc = nkb > 4 && nkb <= PT_PD ? 4 : 2;  // k-blocks per chunk of the staged one
   const dim3 grid(((total + 7) / 8) * 8), block(256);
   const size_t smem = !tiled ? (size_t)128 * PT_TLD * sizeof(float)
-                             : std::max((size_t)2 * (128 / 32 + 4) * PT2_KC * 1024, (size_t)4 * 64 * PT2_ELD * sizeof(float));
-  static bool done_dev[PRAC_MAX_DEVICES][4] = {};  // the attribute is per device
+                             : std::max((size_t)2 * (128 / 32 + 4) * kc * 1024, (size_t)4 * 32 * PT2_ELD * sizeof(float));
+  static bool done_dev[PRAC_MAX_DEVICES][6] = {};  // the attribute is per device
   bool* done = done_dev[ctx->device % PRAC_MAX_DEVICES];
-  const int idx = (tiled ? 2 : 0) + (out_bf16 ? 1 : 0);
+  const int idx = (!tiled ? 0 : kc == 4 ? 2 : 4) + (out_bf16 ? 1 : 0);
 #define PRAC_PT_CASE(I, KERN)                          \
   case I: {                                            \
     constexpr auto kern = KERN;                        \
@@ -1139,8 +1149,10 @@ int launch_pt(prac_ctx* ctx, const bf16_t* Pa, int n_out, const bf16_t* const* T
   switch (idx) {
     PRAC_PT_CASE(0, pt_kernel<false>)
     PRAC_PT_CASE(1, pt_kernel<true>)
-    PRAC_PT_CASE(2, (pt_tiled_kernel<128, false>))
-    PRAC_PT_CASE(3, (pt_tiled_kernel<128, true>))
+    PRAC_PT_CASE(2, (pt_tiled_kernel<4, false>))
+    PRAC_PT_CASE(3, (pt_tiled_kernel<4, true>))
+    PRAC_PT_CASE(4, (pt_tiled_kernel<2, false>))
+    PRAC_PT_CASE(5, (pt_tiled_kernel<2, true>))
   }
 #undef PRAC_PT_CASE
   PRAC_HIP_TRY(ctx, hipGetLastError());
