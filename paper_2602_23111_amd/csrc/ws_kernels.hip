@@ -77,6 +77,9 @@ struct CompressWsArgs {
   int m;                // columns of Y
   bf16_t* Y;            // row-major N x m
   int64_t ldy;
+  // few tiles: the sum over d in `splits` ranges of `kt_per` k-tiles, partial sums to `part` (compress_sum_kernel adds them up)
+  int splits, kt_per;
+  float* part;          // [splits][tiles_m][col_groups][4 waves][4 FN blocks][4 register quads][64 lanes][4]
 };
 
 constexpr int WS_BM = 128, WS_BK = 256, WS_LD = WS_BK + 8;
@@ -208,18 +211,24 @@ __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
   const int bid = touch_kernel_args<sizeof(CompressWsArgs)>(blockIdx.x);
 
   // XCD-aware order: consecutive logical tiles (same rows, next column group) on one XCD
-  const int total = a.tiles_m * a.col_groups;
+  const int total = a.tiles_m * a.col_groups * a.splits;
   const int per_xcd = (total + 7) / 8;
   const int xcd = bid & 7, slot = bid >> 3;
   const int logical = xcd * per_xcd + slot;
   if (slot >= per_xcd || logical >= total) return;
-  const int cg = logical % a.col_groups, tm = logical / a.col_groups;
+  int tm = logical / a.col_groups, kt0 = 0;
+  const int cg = logical - tm * a.col_groups;
+  if (a.splits > 1) {
+    const int range = tm / a.tiles_m;
+    tm -= range * a.tiles_m;
+    kt0 = range * a.kt_per;  // its first k-tile
+  }
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   PRAC_STAMP(a, 0);
   const int m0 = tm * WS_BM;
-  const int nk = (a.d + WS_BK - 1) / WS_BK;
+  const int nk = a.splits > 1 ? min((a.d + WS_BK - 1) / WS_BK - kt0, a.kt_per) : (a.d + WS_BK - 1) / WS_BK;
   // Step kt of this workgroup works on k-tile act(kt): the sum over k may run in any order, and
   // workgroups that start at different tiles neither ask L2 for the same lines of P at once nor
   // all pull on the same memory channels (their row panels have the same alignment).
@@ -230,7 +239,7 @@ __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
   const int reps = UA && !fwd ? WS_SPLIT : 1;  // steps per k-tile
   auto act = [&](int kt) {
     const int t = min(kt, nk - 1) + rot;
-    return t >= nk ? t - nk : t;
+    return kt0 + (t >= nk ? t - nk : t);
   };
 
   if (wave >= 4) {
@@ -387,6 +396,17 @@ __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
   // epilogue: block (i, j) = acc[i * FN + j]; register v of lane (li, lh) is token row
   // 8*(v/4) + 4*lh + v%4 of row block i, column li of column block cb0 + j.
   PRAC_STAMP(a, 2);
+  if (a.splits > 1) {
+    f32x4_t* out = reinterpret_cast<f32x4_t*>(a.part) + ((int64_t)logical * 4 + wave) * (NACC * 256) + lane;
+#pragma unroll
+    for (int i = 0; i < NACC; ++i) {
+      asm volatile("" : "+a"(acc[i]) : : "memory");
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        out[(i * 4 + q) * 64] = f32x4_t{acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]};
+    }
+    return;
+  }
   if (a.packed && !fwd) {
     // registers v = 8 tb .. 8 tb + 7 are exactly the 8 slots of the 16-token block tb
     u32x4* Cp = reinterpret_cast<u32x4*>(a.C);
@@ -489,6 +509,47 @@ __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   PRAC_STAMP(a, 3);
 #endif
+}
+
+// C, and Y of a fused forward, from the partial sums of the ranges of d (in their order).  A thread adds up eight tokens of one
+// column: the eight slots of a lane of a packed 16-token block.
+template <int FN>
+__global__ __launch_bounds__(256) void compress_sum_kernel(CompressWsArgs a) {
+  constexpr int NACC = 4 * FN;
+  const int tiles = a.tiles_m * a.col_groups;
+  const int q = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
+  const int tb = q & 1, i = (q >> 1) % NACC, wave = (q >> 1) / NACC % 4, tile = (q >> 1) / (4 * NACC);
+  if (tile >= tiles) return;
+  const f32x4_t* p = reinterpret_cast<const f32x4_t*>(a.part) + (((int64_t)tile * 4 + wave) * NACC + i) * 256 + 128 * tb + lane;
+  const int64_t stride = (int64_t)tiles * 4 * NACC * 256;
+  f32x4_t x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0;
+#pragma unroll 4
+  for (int z = 0; z < a.splits; ++z) {
+    x0 += __builtin_nontemporal_load(p + z * stride);
+    x1 += __builtin_nontemporal_load(p + z * stride + 64);
+  }
+  const int cg = tile % a.col_groups, tm = tile / a.col_groups;
+  const bool fwd = cg < a.w_groups;
+  const int cb = (fwd ? cg : cg - a.w_groups) * NACC + wave * FN + i % FN, t0 = tm * WS_BM + 32 * (i / FN) + 16 * tb;
+  float x[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+  if (a.packed && !fwd) {
+    if (cb >= a.ccb) return;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (t0 + (e < 4 ? 4 * lh + e : 8 + 4 * lh + (e - 4)) >= a.N) x[e] = 0.f;
+    const u32x4 o = {pack2_hw(x[0], x[1]), pack2_hw(x[2], x[3]), pack2_hw(x[4], x[5]), pack2_hw(x[6], x[7])};
+    stream_store(reinterpret_cast<u32x4*>(a.C) + ((int64_t)(t0 / 16) * a.ccb + cb) * 64 + lane, o);
+  } else {
+    const int col = cb * 32 + li;
+    if (col >= (fwd ? a.m : a.c)) return;
+    bf16_t* const out = (fwd ? a.Y : a.C) + col;
+    const int64_t ldo = fwd ? a.ldy : a.ldc;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int row = t0 + (e < 4 ? 4 * lh + e : 8 + 4 * lh + (e - 4));
+      if (row < a.N) out[(int64_t)row * ldo] = (bf16_t)(pack2_hw(x[e], 0.f) & 0xFFFFu);
+    }
+  }
 }
 
 // ------------------------------------------------------------------ reconstruction
@@ -1472,6 +1533,22 @@ int set_smem(prac_ctx* ctx, K kern, size_t bytes, bool& done) {
 
 }  // namespace
 
+// Ranges of d for a product with few tiles (batches of a few thousand tokens): a launch takes its start and end (9 us) and its
+// k-tiles one after the other, so where tiles leave compute units idle, ranges of the k-tiles go to those.  A range more costs a write and
+// a read of its partial sums (3 TB/s), their sum a launch (5 us).  No more workgroups than compute units: then the partial sums, 64 FN KB
+// each, fit the ctx's block of 128 KiB per compute unit.  Whole call, one range against these (N, d, c):
+// step 7463, 8025 on any element, 35 233 / 132 us; 1018, 5376, 836 106 / 87; 1479, 6208, 694 84 / 61; 4812, 4800, 24 78 / 54; fused forward
+// 905, 6848, 63 with m = 2304 103 / 68; 532, 1344, 48 with m = 547 27.3 / 17.4; a refit's product 4096, 4096, 256 34 / 23 alone.
+static void compress_ranges(int n_cu, int tiles, int nk, int fn, bool parts, int& splits, int& kt_per) {
+  const double tile_us = (fn == 2 ? 3.4 : 2.2) * (parts ? WS_SPLIT : 1), part_us = 2.0 * tiles * fn * 65536.0 / 3e6;
+  auto cost = [&](int s) { return tile_us * ((nk + s - 1) / s) + (s > 1 ? 5.0 + part_us * s : 0.0); };
+  int best = 1;
+  for (int s = 2; s <= nk && (int64_t)s * tiles <= n_cu; ++s)
+    if (cost(s) < 0.9 * cost(1) && cost(s) < cost(best)) best = s;
+  kt_per = (nk + best - 1) / best;
+  splits = (nk + kt_per - 1) / kt_per;  // no empty range
+}
+
 int launch_compress_ws(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d, const bf16_t* Pfrag, int ncb, int c,
                        bf16_t* C, int64_t ldc, bool packed, const bf16_t* Wfrag, int ncb_w, int m, bf16_t* Y,
                        int64_t ldy, bool any_element) {
@@ -1496,8 +1573,11 @@ int launch_compress_ws(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d
   a.w_groups = Wfrag ? ((m + 31) / 32 + 4 * FN - 1) / (4 * FN) : 0;
   if (a.w_groups * 4 * FN > ncb_w) return PRAC_EINVAL;
   a.col_groups = a.w_groups + p_groups;
+  const int tiles = a.tiles_m * a.col_groups;
+  compress_ranges(ctx->n_cu, tiles, (d + WS_BK - 1) / WS_BK, FN, any_element, a.splits, a.kt_per);
+  a.part = ctx->tails;
   const size_t smem = (size_t)WS_STAGES * WS_STAGE;
-  const int total = a.tiles_m * a.col_groups;
+  const int total = tiles * a.splits;
   const dim3 grid(((total + 7) / 8) * 8), block(512);
   static bool done_dev[PRAC_MAX_DEVICES][4] = {};  // the attribute is per device
   bool* done = done_dev[ctx->device % PRAC_MAX_DEVICES];
@@ -1516,6 +1596,11 @@ int launch_compress_ws(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d
     PRAC_COMPRESS_CASE(3, 2, true)
   }
 #undef PRAC_COMPRESS_CASE
+  if (a.splits > 1) {
+    const dim3 sgrid(tiles * 4 * 4 * FN * 2 / 4);
+    if (FN == 1) hipLaunchKernelGGL(compress_sum_kernel<1>, sgrid, dim3(256), 0, ctx->stream, a);
+    else hipLaunchKernelGGL(compress_sum_kernel<2>, sgrid, dim3(256), 0, ctx->stream, a);
+  }
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
 }

@@ -363,6 +363,45 @@ def test_compress_packed_layout(ctx, N, d, c):
     assert not flat.cpu()[pad].float().abs().any()          # padding rows / columns are zeros
 
 
+@pytest.mark.parametrize("N,d,c,ld", [
+    (300, 4100, 40, 4104),     # 3 row tiles, 17 k-tiles: the last range shorter, the last k-tile partial
+    (1, 2048, 128, 2048),      # one tile
+    (1000, 3000, 300, 3000),   # wide wave tiles, two column groups
+    (2100, 1300, 200, 1304),   # 17 row tiles, few k-tiles
+    (515, 5461, 33, 5461),     # rows on any element: three parts of P
+    (700, 2999, 500, 2999),
+])
+@pytest.mark.parametrize("m", [0, 333])
+def test_compress_over_ranges_of_features(ctx, N, d, c, ld, m):
+    """Few tiles: the sum over d runs in ranges on several workgroups.  Every element of C (and of a fused forward's Y) in both
+    layouts against the product of the same operands; sums over d in fp32 in any order (bounded by d 2^-24 <= 4e-4 of the sum
+    of magnitudes), then one rounding to bf16 (2^-9, 2^-8 allowed)."""
+    from paper_2602_23111_amd.prac import C_PACKED
+    g = torch.Generator(device=DEV).manual_seed(N + d)
+    X = torch.full((N, ld), float("nan"), dtype=torch.bfloat16, device=DEV)[:, :d]
+    X.copy_(torch.randn((N, d), generator=g, device=DEV))
+    P = torch.randn((d, c), generator=g, device=DEV) * d ** -0.5
+    lp = ctx.pack_basis(P)
+    any_element = ld % 8 != 0
+    Pd = P.double() if any_element else P.bfloat16().double()
+    W = (torch.randn((m, d), generator=g, device=DEV) * d ** -0.5).bfloat16() if m else None
+    for layout in ("rows", "packed"):
+        kw = dict(layout=C_PACKED) if layout == "packed" else {}
+        if m:
+            Y = torch.full((N + 1, m + 2), 7.0, dtype=torch.bfloat16, device=DEV)
+            _, Cm = ctx.compress_fused_fwd(X, W, P, w_layout=1, P_lp=lp, Y=Y[:N, :m], **kw)
+            ref, mag = X.double() @ W.double().t().contiguous(), X.double().abs() @ W.double().abs().t().contiguous()
+            assert ((Y[:N, :m].double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 4e-4 * mag).all()
+            assert (Y[N:] == 7.0).all() and (Y[:, m:] == 7.0).all()
+        else:
+            Cm = ctx.compress(X, P, P_lp=lp, **kw)
+        ctx.sync_status()
+        if layout == "packed":
+            Cm = ctx.unpack_compressed(Cm, N, c)
+        ref, mag = X.double() @ Pd, X.double().abs() @ Pd.abs()
+        assert ((Cm.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 4e-4 * mag).all()
+
+
 def test_compress_identity_columns_bit_exact(ctx):
     # P = first c columns of the identity: products by 0 and 1 only
     N, d, c = 500, 256, 40
