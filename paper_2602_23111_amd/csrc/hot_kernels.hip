@@ -424,8 +424,7 @@ __global__ __launch_bounds__(256) void pt_kernel(PtArgs a) {
         o.w = pack2_hw(x[6], x[7]);
         stream_store_el(q, o);
       } else {
-        for (int e = 0; e < 8 && gcol + e < om; ++e)
-          q[e] = f32_to_bf16(a.beta == 0.f ? x[e] : x[e] + a.beta * __uint_as_float(((uint32_t)q[e]) << 16));
+        store_first(q, x, om - gcol, a.beta);
       }
     }
   } else {
@@ -445,8 +444,8 @@ __global__ __launch_bounds__(256) void pt_kernel(PtArgs a) {
         }
         stream_store_el(q, f32x4_t{x.x, x.y, x.z, x.w});
       } else {
-        const float xs[4] = {x.x, x.y, x.z, x.w};
-        for (int e = 0; e < 4 && gcol + e < om; ++e) q[e] = a.beta == 0.f ? xs[e] : xs[e] + a.beta * q[e];
+        float xs[4] = {x.x, x.y, x.z, x.w};
+        store_first(q, xs, om - gcol, a.beta);
       }
     }
   }
@@ -599,8 +598,7 @@ __global__ __launch_bounds__(256, 8 / KC) void pt_tiled_kernel(PtArgs a) {
           w.w = pack2_hw(x[6], x[7]);
           stream_store_el(o, w);
         } else {
-          for (int e = 0; e < 8 && gcol + e < om; ++e)
-            o[e] = f32_to_bf16(a.beta == 0.f ? x[e] : x[e] + a.beta * __uint_as_float(((uint32_t)o[e]) << 16));
+          store_first(o, x, om - gcol, a.beta);
         }
       } else {
         float* o = reinterpret_cast<float*>(odW) + (int64_t)grow * olddw + gcol;
@@ -613,7 +611,7 @@ __global__ __launch_bounds__(256, 8 / KC) void pt_tiled_kernel(PtArgs a) {
           stream_store_el(o, f32x4_t{x[0], x[1], x[2], x[3]});
           stream_store_el(o + 4, f32x4_t{x[4], x[5], x[6], x[7]});
         } else {
-          for (int e = 0; e < 8 && gcol + e < om; ++e) o[e] = a.beta == 0.f ? x[e] : x[e] + a.beta * o[e];
+          store_first(o, x, om - gcol, a.beta);
         }
       }
     }
@@ -991,8 +989,7 @@ __global__ __launch_bounds__(512) void sum_pt_kernel(SumPtArgs a) {
           w.w = pack2_hw(x[6], x[7]);
           stream_store_el(o, w);
         } else {
-          for (int e = 0; e < 8 && gcol + e < mh; ++e)
-            o[e] = f32_to_bf16(a.beta == 0.f ? x[e] : x[e] + a.beta * __uint_as_float(((uint32_t)o[e]) << 16));
+          store_first(o, x, mh - gcol, a.beta);
         }
       }
     } else {
@@ -1010,8 +1007,8 @@ __global__ __launch_bounds__(512) void sum_pt_kernel(SumPtArgs a) {
           }
           stream_store_el(o, f32x4_t{x.x, x.y, x.z, x.w});
         } else {
-          const float xs[4] = {x.x, x.y, x.z, x.w};
-          for (int e = 0; e < 4 && gcol + e < mh; ++e) o[e] = a.beta == 0.f ? xs[e] : xs[e] + a.beta * o[e];
+          float xs[4] = {x.x, x.y, x.z, x.w};
+          store_first(o, xs, mh - gcol, a.beta);
         }
       }
     }

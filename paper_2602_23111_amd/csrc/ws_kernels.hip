@@ -1214,8 +1214,7 @@ __device__ __forceinline__ void wgrad_tail(const CtdyWsArgs& a, unsigned char* s
           w.w = pack2_hw(x[6], x[7]);
           stream_store(reinterpret_cast<u32x4*>(o), w);
         } else {
-          for (int e = 0; e < 8 && gcol + e < mh; ++e)
-            o[e] = f32_to_bf16(a.beta == 0.f ? x[e] : x[e] + a.beta * __uint_as_float(((uint32_t)o[e]) << 16));
+          store_first(o, x, mh - gcol, a.beta);
         }
       }
     } else {
@@ -1233,8 +1232,8 @@ __device__ __forceinline__ void wgrad_tail(const CtdyWsArgs& a, unsigned char* s
           }
           stream_store(reinterpret_cast<f32x4_t*>(o), f32x4_t{x.x, x.y, x.z, x.w});
         } else {
-          const float xs[4] = {x.x, x.y, x.z, x.w};
-          for (int e = 0; e < 4 && gcol + e < mh; ++e) o[e] = a.beta == 0.f ? xs[e] : xs[e] + a.beta * o[e];
+          float xs[4] = {x.x, x.y, x.z, x.w};
+          store_first(o, xs, mh - gcol, a.beta);
         }
       }
     }
