@@ -233,17 +233,18 @@ struct F32SumPtArgs {
   float beta;
   int tiles_n;
 };
-template <bool OUT_BF16>
-__global__ __launch_bounds__(512) void f32_sum_pt_kernel(F32SumPtArgs a) {
-  __shared__ float T[FP_K][64];
+template <int WC, bool OUT_BF16>
+__global__ __launch_bounds__(256 * WC) void f32_sum_pt_kernel(F32SumPtArgs a) {
+  constexpr int TN = 32 * WC;
+  __shared__ float T[FP_K][TN];
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int m0 = (blockIdx.x / a.tiles_n) * 128 + (wave >> 1) * 32, n0 = (blockIdx.x % a.tiles_n) * 64, wc = (wave & 1) * 32;
+  const int m0 = (blockIdx.x / a.tiles_n) * 128 + wave / WC * 32, n0 = (blockIdx.x % a.tiles_n) * TN, wc = wave % WC * 32;
   const float* prow = a.P + (int64_t)min(m0 + li, a.d - 1) * a.ldp;
   f32x16 acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-  const int sr = tid >> 4, sc = (tid & 15) * 4;  // summing: rows sr, sr + 32, columns sc .. sc + 3
+  const int sr = tid / (TN / 4), sc = tid % (TN / 4) * 4;  // summing: rows sr, sr + 32, columns sc .. sc + 3
   const int64_t slab = (int64_t)a.c * a.m;
   for (int k0 = 0; k0 < a.c; k0 += FP_K) {
     f32x4_t fp[FP_K / 8];  // P[row][k0 + 8 q + 4 lh .. + 3]; requested before the sum, which they do not depend on
@@ -261,10 +262,30 @@ __global__ __launch_bounds__(512) void f32_sum_pt_kernel(F32SumPtArgs a) {
     const float* const q0 = a.slabs + (int64_t)min(k0 + sr, a.c - 1) * a.m + n0 + sc;
     const float* const q1 = a.slabs + (int64_t)min(k0 + sr + 32, a.c - 1) * a.m + n0 + sc;
     if (n0 + sc + 4 <= a.m) {
+      if constexpr (WC == 1) {
+        // Eight slabs in flight, the last ones too (past the end: the last again, not added).  Its registers halve the waves that
+        // fit, so where the launch fills the chip the plain loop below stays ahead (23.6 us against 30.5 with 480 workgroups).
+        for (int z0 = 0; z0 < a.splits; z0 += 8) {
+          f32x4_t x[8], y[8];
+#pragma unroll
+          for (int z = 0; z < 8; ++z) {
+            const int64_t o = min(z0 + z, a.splits - 1) * slab;
+            x[z] = *reinterpret_cast<const f32x4_el*>(q0 + o);
+            y[z] = *reinterpret_cast<const f32x4_el*>(q1 + o);
+          }
+#pragma unroll
+          for (int z = 0; z < 8; ++z)
+            if (z0 + z < a.splits) {
+              sum[0] += x[z];
+              sum[1] += y[z];
+            }
+        }
+      } else {
 #pragma unroll 8
-      for (int z = 0; z < a.splits; ++z) {  // eight slabs in flight
-        sum[0] += *reinterpret_cast<const f32x4_el*>(q0 + z * slab);
-        sum[1] += *reinterpret_cast<const f32x4_el*>(q1 + z * slab);
+        for (int z = 0; z < a.splits; ++z) {  // eight slabs in flight
+          sum[0] += *reinterpret_cast<const f32x4_el*>(q0 + z * slab);
+          sum[1] += *reinterpret_cast<const f32x4_el*>(q1 + z * slab);
+        }
       }
     } else {
       for (int z = 0; z < a.splits; ++z)
@@ -397,8 +418,10 @@ int launch_f32_sum_pt(prac_ctx* ctx, const float* P, int64_t ldp, float* slabs, 
   F32SumPtArgs a;
   a.P = P; a.ldp = ldp; a.slabs = slabs; a.splits = splits; a.c = c; a.k_lo = k_lo; a.scale_hi = scale_hi;
   a.d = d; a.m = m; a.dW = dW; a.lddw = lddw; a.beta = beta;
-  a.tiles_n = (m + 63) / 64;
-  const int64_t total = (int64_t)a.tiles_n * ((d + 127) / 128);
+  const int rows = (d + 127) / 128;
+  const bool narrow = (int64_t)((m + 63) / 64) * rows < ctx->n_cu;
+  a.tiles_n = narrow ? (m + 31) / 32 : (m + 63) / 64;
+  const int64_t total = (int64_t)a.tiles_n * rows;
   if (total > INT32_MAX) return PRAC_EINVAL;
   // The sum of the slabs is repeated by every row tile; past a few dozen reads of each slab element's bytes a pass of
   // its own (into the first slab, in place) is cheaper.
@@ -408,8 +431,11 @@ int launch_f32_sum_pt(prac_ctx* ctx, const float* P, int64_t ldp, float* slabs, 
     a.splits = 1;
   }
   const dim3 grid((unsigned)total);
-  if (out_bf16) PRAC_LAUNCH(ctx, f32_sum_pt_kernel<true>, grid, dim3(512), 0, a);
-  else PRAC_LAUNCH(ctx, f32_sum_pt_kernel<false>, grid, dim3(512), 0, a);
+  auto launch = [&](auto kern, int threads) { PRAC_LAUNCH(ctx, kern, grid, dim3(threads), 0, a); };
+  if (narrow && out_bf16) launch(f32_sum_pt_kernel<1, true>, 256);
+  else if (narrow) launch(f32_sum_pt_kernel<1, false>, 256);
+  else if (out_bf16) launch(f32_sum_pt_kernel<2, true>, 512);
+  else launch(f32_sum_pt_kernel<2, false>, 512);
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
 }
