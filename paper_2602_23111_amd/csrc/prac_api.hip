@@ -746,7 +746,8 @@ int wgrad_splits(int n_cu, int tune_splits, int c, int n_out, const int64_t* m, 
   return best;
 }
 
-// Unequal token ranges in one round (see CtdyTails) where they are at least 3 % cheaper than `splits` equal ones.  A helper's next
+// Unequal token ranges in one round (see CtdyTails) where they are at least 3 % and 2.5 us cheaper than `splits` equal ones (96
+// tiles of 33 units, c = 44: 1.9 us cheaper by the estimate, 58.4 us against 56.1 with the rest of the call).  A helper's next
 // piece costs it what 3 units cost (its stores and its first tile), so main ranges are the shortest that no helper exceeds.
 // Measured, equal ranges against these, C^T dY alone and the whole weight gradient: 86 tiles of
 // 256 units (up and gate) 5 ranges in two rounds 237 / 320 us, unequal 217 / 292; 172 tiles of 128 units (LLaMA-7B up projection)
@@ -771,7 +772,8 @@ CtdyTails wgrad_tails(int n_cu, int c, int n_out, const int64_t* m, int64_t N, i
     t.t1 = (int)w.tiles;
     const double us = WgradWork::round_us(128.0 * (double)len) +
                       (double)(2 * w.slab) * ((double)t.main + 1.0 + (double)t.helpers / (double)w.tiles) / 3e6;
-    return us < 0.97 * w.equal_us(n_cu, N, splits) ? t : CtdyTails{};
+    const double equal = w.equal_us(n_cu, N, splits);
+    return us < 0.97 * equal && us < equal - 2.5 ? t : CtdyTails{};
   }
   return {};
 }

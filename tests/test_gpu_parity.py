@@ -546,9 +546,9 @@ def test_weight_grad_last_product_in_chunks(ctx, c, odt):
 
 
 @pytest.mark.parametrize("N,c,ms,pad,static", [
-    (2000, 70, (19163,), 8, True),          # 150 tiles: one main range each, tails in parts; short last range, partial last tile
-    (2048, 256, (19200,), 0, True),         # their sums exceed the static block: column tiles in turns there
-    (1999, 300, (8001, 1200), 0, False),    # two row groups of T, two outputs, odd width
+    (4000, 70, (19163,), 8, True),          # 150 tiles: one main range each, tails in parts; short last range, partial last tile
+    (8192, 256, (19200,), 0, True),         # their sums exceed the static block: column tiles in turns there
+    (5999, 300, (8001, 1200), 0, False),    # two row groups of T, two outputs, odd width
     (32768, 64, (11008,), 0, True),         # 86 tiles: two main ranges each
 ])
 def test_weight_grad_over_unequal_token_ranges(ctx, N, c, ms, pad, static):
