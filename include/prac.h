@@ -24,8 +24,15 @@
  *     must not wait or allocate inside a hot call size the block up front:
  *     prac_workspace_bytes for every call shape they will issue, then one
  *     prac_reserve_workspace with the largest answer.  prac_create itself
- *     allocates 8 MiB more (partial sums of fp32 weight gradients).  A ctx must
- *     not be used from two host threads at once.
+ *     allocates 8 MiB more (partial sums of fp32 weight gradients) and 128 KiB
+ *     per compute unit (partial sums of bf16 products; 32 MiB on an MI355X).
+ *     A ctx must not be used from two host threads at once.
+ *   - Calls that need scratch (prac_workspace_bytes not 0), and replays of
+ *     graphs captured from them, all work in that one ctx's memory: they must
+ *     not overlap in time with each other (prac_set_stream orders nothing).  Those that need none
+ *     (a compress of aligned bf16 rows with P_lp, fp32 compress, fused forward and
+ *     reconstruction, packing and unpacking, the Gaussian draw) touch no memory of the ctx: on different
+ *     streams, or as replays beside other calls, they may overlap with anything.
  *   - Return value: PRAC_OK (0) or a negative prac_status.  Shape and argument
  *     errors are detected on the host BEFORE anything is enqueued and before
  *     the ctx is looked at, so they can be exercised without a GPU.

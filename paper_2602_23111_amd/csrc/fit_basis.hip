@@ -1300,7 +1300,8 @@ int fit_basis_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, in
     for (int it = 0; it < o.iters; ++it) {
       rc = launch_pack_pfrag(ctx, it == 0 ? P : V, d, it == 0 ? ldp : (int64_t)k, k, L.trk_nkb, L.trk_ncb, Pf);
       if (rc) return rc;
-      rc = launch_compress_ws(ctx, Xb, ld, (int)rows, dm, Pf, L.trk_ncb, k, Cpk, 0, true, nullptr, 0, 0, nullptr, 0);
+      rc = launch_compress_ws(ctx, Xb, ld, (int)rows, dm, Pf, L.trk_ncb, k, Cpk, 0, true, nullptr, 0, 0, nullptr, 0, false,
+                              ctx->tails);
       if (rc) return rc;
       rc = launch_ctdy_ws(ctx, Cpk, k, (int)rows, 1, &Xb, &ld, &dm, &slabs, L.trk_splits, false);
       if (rc) return rc;

@@ -281,7 +281,7 @@ int prac_create(prac_ctx** out, int device, void* hip_stream) {
   c->tails = nullptr;
   hipDeviceProp_t prop;
   c->n_cu = (hipGetDeviceProperties(&prop, device) == hipSuccess) ? prop.multiProcessorCount : 256;
-  // failure flag (256 bytes), the counters of the one-launch weight gradient, the fp32 partial sums, the blocks of unequal ranges' tails
+  // failure flag (256 bytes), the counters of the one-launch weight gradient, the fp32 partial sums, the block `tails`
   const size_t flag_bytes = 256 + PRAC_SYNC_BYTES;
   if (hipMalloc(reinterpret_cast<void**>(&c->d_flag), flag_bytes + PRAC_PART32_BYTES + (size_t)c->n_cu * PRAC_TAIL_BYTES) != hipSuccess) {
     (void)hipGetLastError();
@@ -574,7 +574,7 @@ static int compress_impl(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N
     ProfScope ps(ctx, PRAC_KERNEL_FUSED_FWD);
     return launch_compress_ws(ctx, reinterpret_cast<const bf16_t*>(X), ldx, (int)N, (int)d, Pf, l.ncb, c,
                               reinterpret_cast<bf16_t*>(C), ldc, packed, Wf, ncb_w, (int)m,
-                              reinterpret_cast<bf16_t*>(Y), ldy);
+                              reinterpret_cast<bf16_t*>(Y), ldy, false, ctx->tails);
   }
   if (path == CompressPath::STREAM_ANY) {
     const LpLayout l = lp_layout(d, c);
@@ -590,7 +590,7 @@ static int compress_impl(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N
     ProfScope ps(ctx, fused ? PRAC_KERNEL_FUSED_FWD : PRAC_KERNEL_COMPRESS);
     return launch_compress_ws(ctx, reinterpret_cast<const bf16_t*>(X), ldx, (int)N, (int)d, Ps, l.ncb, c,
                               reinterpret_cast<bf16_t*>(C), ldc, packed, Wf, q.ncb_w, (int)m, reinterpret_cast<bf16_t*>(Y),
-                              ldy, true);
+                              ldy, true, ctx->tails);
   }
   // strided path: fp32 data (P used in fp32), and bf16 rows the streaming kernels do not take
   const bool need_tmp = xdt == PRAC_BF16;
@@ -1226,7 +1226,7 @@ int prac_reconstruct(prac_ctx* ctx, const void* C, prac_dtype dt, int64_t N, int
     }
     ProfScope ps(ctx, PRAC_KERNEL_RECONSTRUCT);
     return launch_compress_ws(ctx, Crm, ldcrm, (int)N, c, nullptr, 0, 0, nullptr, 0, false, Pt, ncb, (int)d,
-                              reinterpret_cast<bf16_t*>(Xh), ldxh);
+                              reinterpret_cast<bf16_t*>(Xh), ldxh, false, ctx->tails);
   }
   // fp32 path: Xh = C1 Q1^T, then Xh += scale C2 Q2^T (a scaled copy of P would make it one product, but fp32 data needs no
   // scratch here)

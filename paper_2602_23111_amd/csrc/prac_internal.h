@@ -31,7 +31,8 @@ struct prac_ctx {
   float* part32;        // PRAC_PART32_BYTES for the token-split partial sums of the fp32 weight gradient (part of the ctx,
                         // not of the scratch block that grows: the split, and with it the bits of dW, never depends on
                         // what the ctx ran before)
-  float* tails;         // n_cu * PRAC_TAIL_BYTES for the partial sums of CtdyTails' helpers (part of the ctx)
+  float* tails;         // n_cu * PRAC_TAIL_BYTES for the partial sums of CtdyTails' helpers and of launch_compress_ws (part of the ctx;
+                        // only for calls that work in the scratch block too, see prac_workspace_bytes)
   int prof_kind;      // kernel kind bracketed by events (0: none), see prac_profile_select
   int prof_stride;    // every prof_stride-th launch of that kind carries the event pair
   int64_t prof_seen;  // launches of that kind since the selection
@@ -41,7 +42,7 @@ struct prac_ctx {
 };
 
 #define PRAC_PART32_BYTES ((size_t)8 << 20)
-#define PRAC_TAIL_BYTES ((size_t)256 * 128 * 4)  // a 256 x 128 tile of partial sums, one per compute unit
+#define PRAC_TAIL_BYTES ((size_t)256 * 128 * 4)  // a 256 x 128 tile of fp32 partial sums, one per compute unit
 
 // Brackets the launches issued during its lifetime with a HIP event pair on the ctx
 // stream when the ctx is profiling this kernel kind.
@@ -141,10 +142,11 @@ int launch_cast_out(prac_ctx* ctx, const float* src, int64_t lds, void* dst, pra
 // ---- kernels of the per-step path (ws_kernels.hip, hot_kernels.hip) -----------------
 // Wfrag != nullptr: also Y (N x m, ldy) = X W, W in the fragment order of Pfrag with ncb_w column blocks
 // any_element: rows of X start on any element and own nothing past their last column (d >= 8); Pfrag then holds the fp32 P
-// as launch_pack_pfrag_split leaves it
+// as launch_pack_pfrag_split leaves it.  part: n_cu * PRAC_TAIL_BYTES of partial sums, for a product with few tiles (nullptr: one launch,
+// which writes nothing but its outputs)
 int launch_compress_ws(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d, const bf16_t* Pfrag, int ncb,
                        int c, bf16_t* C, int64_t ldc, bool packed, const bf16_t* Wfrag, int ncb_w, int m,
-                       bf16_t* Y, int64_t ldy, bool any_element = false);
+                       bf16_t* Y, int64_t ldy, bool any_element = false, float* part = nullptr);
 // out_h (N x n[h], bf16) = A (N x c bf16, row-major with lda or packed; c <= 256) B_h for up to PRAC_CTDY_MAX_OUT outputs,
 // B_h in fragment order [nkb][ncb[h]][64][8], zero past row c and column n[h]: nkb = wide_kblocks(c), ncb[h] a multiple
 // of 8 covering n[h]; recon: the reconstruction (one output).  Rows of out_h may start on any element.

@@ -1536,8 +1536,11 @@ int set_smem(prac_ctx* ctx, K kern, size_t bytes, bool& done) {
 // k-tiles one after the other, so where tiles leave compute units idle, ranges of the k-tiles go to those.  A range more costs a write and
 // a read of its partial sums (3 TB/s), their sum a launch (5 us).  No more workgroups than compute units: then the partial sums, 64 FN KB
 // each, fit the ctx's block of 128 KiB per compute unit.  Whole call, one range against these (N, d, c):
-// step 7463, 8025 on any element, 35 233 / 132 us; 1018, 5376, 836 106 / 87; 1479, 6208, 694 84 / 61; 4812, 4800, 24 78 / 54; fused forward
-// 905, 6848, 63 with m = 2304 103 / 68; 532, 1344, 48 with m = 547 27.3 / 17.4; a refit's product 4096, 4096, 256 34 / 23 alone.
+// step 7463, 8025 on any element, 35 233 / 132 us; fused forward 905, 6848, 63 with m = 2304 103 / 68; 532, 1344, 48 with m = 547
+// 27.3 / 17.4; a refit's product 4096, 4096, 256 34 / 23 alone.
+// Only for calls that work in the ctx's scratch anyway (`part`): a compress of aligned rows with a packed basis keeps nothing in the
+// ctx, so that calls on several streams, and replays of graphs beside them, may overlap; it stays one launch (with ranges, a step of
+// 1018, 5376, 836 took 87 us instead of 106, of 4812, 4800, 24 54 instead of 78).
 static void compress_ranges(int n_cu, int tiles, int nk, int fn, bool parts, int& splits, int& kt_per) {
   const double tile_us = (fn == 2 ? 3.4 : 2.2) * (parts ? WS_SPLIT : 1), part_us = 2.0 * tiles * fn * 65536.0 / 3e6;
   auto cost = [&](int s) { return tile_us * ((nk + s - 1) / s) + (s > 1 ? 5.0 + part_us * s : 0.0); };
@@ -1550,7 +1553,7 @@ static void compress_ranges(int n_cu, int tiles, int nk, int fn, bool parts, int
 
 int launch_compress_ws(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d, const bf16_t* Pfrag, int ncb, int c,
                        bf16_t* C, int64_t ldc, bool packed, const bf16_t* Wfrag, int ncb_w, int m, bf16_t* Y,
-                       int64_t ldy, bool any_element) {
+                       int64_t ldy, bool any_element, float* part) {
   // callers route wider pitches, and rows shorter than one 16-byte chunk that start on any element, to the strided kernels
   if (ldx > PRAC_MAX_STREAM_PITCH || (any_element && d < 8)) return PRAC_EINVAL;
   CompressWsArgs a;
@@ -1573,8 +1576,11 @@ int launch_compress_ws(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d
   if (a.w_groups * 4 * FN > ncb_w) return PRAC_EINVAL;
   a.col_groups = a.w_groups + p_groups;
   const int tiles = a.tiles_m * a.col_groups;
-  compress_ranges(ctx->n_cu, tiles, (d + WS_BK - 1) / WS_BK, FN, any_element, a.splits, a.kt_per);
-  a.part = ctx->tails;
+  const int nk = (d + WS_BK - 1) / WS_BK;
+  a.splits = 1;
+  a.kt_per = nk;
+  a.part = part;
+  if (part) compress_ranges(ctx->n_cu, tiles, nk, FN, any_element, a.splits, a.kt_per);
   const size_t smem = (size_t)WS_STAGES * WS_STAGE;
   const int total = tiles * a.splits;
   const dim3 grid(((total + 7) / 8) * 8), block(512);

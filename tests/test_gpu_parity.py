@@ -373,7 +373,7 @@ def test_compress_packed_layout(ctx, N, d, c):
 ])
 @pytest.mark.parametrize("m", [0, 333])
 def test_compress_over_ranges_of_features(ctx, N, d, c, ld, m):
-    """Few tiles: the sum over d runs in ranges on several workgroups.  Every element of C (and of a fused forward's Y) in both
+    """Few tiles: the sum over d runs in ranges on several workgroups (fused forward, rows on any element).  Every element of C (and of a fused forward's Y) in both
     layouts against the product of the same operands; sums over d in fp32 in any order (bounded by d 2^-24 <= 4e-4 of the sum
     of magnitudes), then one rounding to bf16 (2^-9, 2^-8 allowed)."""
     from paper_2602_23111_amd.prac import C_PACKED
@@ -400,6 +400,38 @@ def test_compress_over_ranges_of_features(ctx, N, d, c, ld, m):
             Cm = ctx.unpack_compressed(Cm, N, c)
         ref, mag = X.double() @ Pd, X.double().abs() @ Pd.abs()
         assert ((Cm.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 4e-4 * mag).all()
+
+
+def graph_nodes(ctx, stream, launches):
+    """How many nodes `launches` captures on `stream`."""
+    import ctypes
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    main_stream = torch.cuda.current_stream()
+    ctx.set_stream(stream)
+    try:
+        with torch.cuda.graph(g, stream=stream):
+            launches()
+    finally:
+        ctx.set_stream(main_stream)
+    count = ctypes.c_size_t(0)
+    assert ctx.lib.hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(count)) == 0
+    return count.value
+
+
+@pytest.mark.parametrize("N,d,c", [(300, 4100, 40), (1, 2048, 128), (1000, 3000, 300), (4812, 4800, 24)])
+def test_compress_that_needs_no_scratch_is_one_launch(ctx, N, d, c):
+    """A compress with a packed basis asks for no scratch and may overlap with other calls of its ctx (another stream, a replayed
+    graph): whatever the shape it is a single kernel, so nothing of it waits in the ctx between two launches."""
+    from paper_2602_23111_amd.prac import C_PACKED, call_shape
+    ld = (d + 7) // 8 * 8
+    X = torch.zeros((N, ld), dtype=torch.bfloat16, device=DEV)[:, :d]
+    P = torch.zeros((d, c), device=DEV)
+    lp = ctx.pack_basis(P)
+    assert ctx.workspace_bytes(call_shape("compress", N, d, c, 0)) == 0
+    out = torch.zeros(ctx.compressed_bytes(N, c) // 2, dtype=torch.bfloat16, device=DEV)
+    launch = lambda: ctx.compress(X, P, P_lp=lp, out=out, layout=C_PACKED)
+    launch()
+    assert graph_nodes(ctx, torch.cuda.Stream(), launch) == 1
 
 
 def test_compress_identity_columns_bit_exact(ctx):
