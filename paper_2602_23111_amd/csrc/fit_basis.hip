@@ -652,21 +652,26 @@ constexpr int JB_CW = 256, JB_CS = JB_CW + 4; // elements of each column in LDS 
 constexpr int JB_GS = JB_M + 1;               // pitch of the Gram matrices and of J
 // Every fifth launch of a sweep rotates all pairs of its 32 columns, the others those across the two blocks: half the inner steps.
 // (Simulated on three spectra of the cases at b = 256, launches weighted by their times: every launch full 1.67 - 1.81 ms in six to seven
-// sweeps, every third 1.38 - 1.52, every fifth 1.32 - 1.47, the first of a sweep only 1.61 in eight.)
-constexpr int JB_FULL = 5;
+// sweeps, every third 1.38 - 1.52, every fifth 1.32 - 1.47, the first of a sweep only 1.61 in eight.)  Steep spectra with few power
+// iterations take up to four sweeps more that way (singular values ~ i^-2.5, some channels 100 times the others, one iteration, b = 80: 12
+// with every launch full, 14 to 16; with all pairs from the ninth sweep on 14), so the ninth sweep and later ones rotate all
+// pairs and the limit lies four sweeps above the twelve that all-pair launches had.
+constexpr int JB_FULL = 5, JB_FULL_FROM = 8;
+// Sweeps before the iteration gives up.  Up to b = 256 the last four are one launch of one workgroup: they are hardly ever needed, and
+// 60 launches that return at once cost 90 us.  Wider blocks launch all of them: there a sweep in one workgroup takes too long (2016
+// pairs at b = 1024), and idle launches are few beside the work.
+constexpr int JB_SWEEPS = 16, JB_REST = 12, JB_REST_BLOCKS = 16;
 constexpr size_t JB_SMEM = (size_t)(JB_M * JB_CS + 4 * JB_M * JB_GS) * sizeof(double);
-__global__ __launch_bounds__(512) void jacobi_block_kernel(double* H, int b, int nblk_even, int step, int sweep, int inner_sweeps,
-                                                           double tol, unsigned* counts, const double* hmax) {
+// One pair of blocks; *count goes up by one if a pair of columns needed a rotation.  Returns whether it did (uniform).
+__device__ __forceinline__ bool jacobi_pair(double* H, int b, int bp, int bq, bool full, int inner_sweeps, double tol,
+                                            unsigned* count, const double* hmax) {
   extern __shared__ __align__(16) unsigned char jac_smem[];
   double* cols = reinterpret_cast<double*>(jac_smem);  // [JB_M][JB_CS]: one chunk of the columns
   double* gram = cols + JB_M * JB_CS;                  // [3][JB_M][JB_GS]
   double* J = gram + 3 * JB_M * JB_GS;                 // [JB_M][JB_GS]: new column c = sum_l J[l][c] column l
   __shared__ double2 cs_lds[32];                       // cosines and sines of this step and the one before
-  if (sweep > 0 && counts[sweep - 1] == 0) return;  // converged in the previous sweep
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int fi = lane & 15, fk = lane >> 4;
-  int bp, bq;
-  tournament_pair(step, blockIdx.x, nblk_even, bp, bq);
   // local column l is column grow(l) of H; blocks past the end are byes, columns past the end are zero
   auto grow = [&](int l) { return (l < JB_NB ? bp : bq) * JB_NB + (l & (JB_NB - 1)); };
   const int nch = (b + JB_CW - 1) / JB_CW;
@@ -701,7 +706,6 @@ __global__ __launch_bounds__(512) void jacobi_block_kernel(double* H, int b, int
   // rotated but does not count towards convergence: such a column is rounding noise and its cosines never settle
   const double floor2 = 1e-26 * *hmax * *hmax;
   bool rot = false, counted = false;
-  const bool full = step % JB_FULL == 0;
   auto place = [&](int l) { return l < 16 || !full ? l : 16 + (JB_M - 1 - l); };  // of column l when the inner tournament starts
 #pragma unroll
   for (int e = 0; e < 2; ++e) {
@@ -715,8 +719,8 @@ __global__ __launch_bounds__(512) void jacobi_block_kernel(double* H, int b, int
     }
   }
   const bool any_counted = __syncthreads_or(counted);
-  if (!__syncthreads_or(rot)) return;
-  if (any_counted && tid == 0) atomicAdd(&counts[sweep], 1u);
+  if (!__syncthreads_or(rot)) return false;
+  if (any_counted && tid == 0) atomicAdd(count, 1u);
   // Inner tournament.  The 32 players sit in places, pair j in places j and 16 + j, and move on after a step.  All pairs (`full`):
   // place j -> j - 1 (0 -> 17) and 16 + j -> 16 + j + 1 (31 -> 15; 16 stays), 31 steps.  Pairs across the two blocks only: the
   // lower places stay, 16 + j -> 16 + j - 1 (16 -> 31), 16 steps.  Then everybody is home.  The matrix is kept by place, so a
@@ -817,6 +821,29 @@ __global__ __launch_bounds__(512) void jacobi_block_kernel(double* H, int b, int
           const int c = ch * JB_CW + 32 * wave + 16 * ni + fi;
           if (row < b && c < b) H[(int64_t)row * b + c] = acc[mi][ni][v];
         }
+      }
+  }
+  return any_counted;
+}
+__global__ __launch_bounds__(512) void jacobi_block_kernel(double* H, int b, int nblk_even, int step, int sweep, int inner_sweeps,
+                                                           double tol, unsigned* counts, const double* hmax) {
+  if (sweep > 0 && counts[sweep - 1] == 0) return;  // converged in the previous sweep
+  int bp, bq;
+  tournament_pair(step, blockIdx.x, nblk_even, bp, bq);
+  jacobi_pair(H, b, bp, bq, step % JB_FULL == 0 || sweep >= JB_FULL_FROM, inner_sweeps, tol, &counts[sweep], hmax);
+}
+// sweeps JB_REST .. JB_SWEEPS - 1, pair after pair
+__global__ __launch_bounds__(512) void jacobi_rest_kernel(double* H, int b, int nblk_even, int inner_sweeps, double tol,
+                                                          unsigned* counts, const double* hmax) {
+  bool any = counts[JB_REST - 1] != 0;
+  for (int sweep = JB_REST; sweep < JB_SWEEPS && any; ++sweep) {
+    any = false;
+    for (int step = 0; step < nblk_even - 1; ++step)
+      for (int i = 0; i < nblk_even / 2; ++i) {
+        int bp, bq;
+        tournament_pair(step, i, nblk_even, bp, bq);
+        any |= jacobi_pair(H, b, bp, bq, true, inner_sweeps, tol, &counts[sweep], hmax);
+        __syncthreads();  // its columns are in H, its LDS is free
       }
   }
 }
@@ -1362,7 +1389,6 @@ int fit_basis_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, in
     }
     {
       const int nblk = (b + JB_NB - 1) / JB_NB, nblk_even = nblk + (nblk & 1);
-      constexpr int MAX_SWEEPS = 12;
       // columns count as orthogonal below this cosine: the Ritz vectors are re-orthonormalised in
       // fp32 afterwards, so anything far below fp32 rounding is spent effort
       constexpr double JACOBI_TOL = 1e-10;
@@ -1370,20 +1396,23 @@ int fit_basis_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, in
       static bool smem_dev[PRAC_MAX_DEVICES] = {};
       bool& smem_set = smem_dev[ctx->device % PRAC_MAX_DEVICES];
       if (!smem_set) {
-        PRAC_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(jacobi_block_kernel),
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)JB_SMEM));
+        for (const void* kern : {reinterpret_cast<const void*>(jacobi_block_kernel), reinterpret_cast<const void*>(jacobi_rest_kernel)})
+          PRAC_HIP_TRY(ctx, hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)JB_SMEM));
         smem_set = true;
       }
-      hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(64), 0, st, counts, MAX_SWEEPS);
-      double* hmax = reinterpret_cast<double*>(counts + 16);
+      hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(64), 0, st, counts, JB_SWEEPS);
+      double* hmax = reinterpret_cast<double*>(counts + JB_SWEEPS);
       hipLaunchKernelGGL(symmetrize64_kernel, dim3(16), dim3(1024), 0, st, H, b, hmax);
       // one or two blocks are one workgroup's job: it sweeps twice per launch there
       const int inner = nblk_even == 2 ? 2 : 1;
-      for (int sweep = 0; sweep < MAX_SWEEPS; ++sweep)
+      const bool rest = nblk_even <= JB_REST_BLOCKS;
+      for (int sweep = 0; sweep < (rest ? JB_REST : JB_SWEEPS); ++sweep)
         for (int step = 0; step < nblk_even - 1; ++step)
           hipLaunchKernelGGL(jacobi_block_kernel, dim3(nblk_even / 2), dim3(512), JB_SMEM, st, H, b, nblk_even, step, sweep,
                              inner, JACOBI_TOL, counts, hmax);
-      hipLaunchKernelGGL(jacobi_finish_kernel, dim3(16), dim3(1024), 0, st, H, b, lam, counts, MAX_SWEEPS - 1, ctx->d_flag);
+      if (rest)
+        hipLaunchKernelGGL(jacobi_rest_kernel, dim3(1), dim3(512), JB_SMEM, st, H, b, nblk_even, inner, JACOBI_TOL, counts, hmax);
+      hipLaunchKernelGGL(jacobi_finish_kernel, dim3(16), dim3(1024), 0, st, H, b, lam, counts, JB_SWEEPS - 1, ctx->d_flag);
     }
     hipLaunchKernelGGL(select_top_kernel, dim3((b + 3) / 4), dim3(256), 0, st, H, lam, b, k, Z);
     PRAC_HIP_TRY(ctx, hipGetLastError());

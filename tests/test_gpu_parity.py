@@ -1056,6 +1056,27 @@ def test_fit_basis_ritz_vectors_come_out_diagonal_and_ordered(ctx, b):
     assert np.abs(H / np.sqrt(np.outer(lam, lam)) - np.eye(k)).max() < 1e-5
 
 
+@pytest.mark.parametrize("b,spectrum,outliers", [(48, "power", 8), (80, "power", 0), (80, "geometric", 0), (320, "geometric", 0)])
+def test_fit_basis_settles_on_steep_spectra(ctx, b, spectrum, outliers):
+    """One power iteration on singular values ~ i^-2.5 (some channels scaled up) or 0.8^i: the eigen-iteration needs more than twelve
+    sweeps with launches of both kinds, which is no failure.  Q1^T G Q1 diagonal to the Gram matrix' tolerance, 2e-5 lambda_1, and the
+    fp32 rounding of the basis (below 1e-6 lambda_1 each side)."""
+    N, d, k = 2048, 512, b // 2
+    i = np.arange(1, d + 1.0)
+    sig = i ** -2.5 if spectrum == "power" else np.maximum(0.8 ** i, 1e-7)
+    for seed in range(4):
+        rng = np.random.default_rng(seed)
+        M = sig[:, None] * np.linalg.qr(rng.standard_normal((d, d)))[0]
+        M[:, rng.choice(d, outliers, replace=False)] *= 100.0
+        Xt = torch.from_numpy((rng.standard_normal((N, d)) @ M).astype(np.float32))
+        P, _, _ = ctx.fit_basis(Xt.to(DEV), k, 8, seed=seed, draw=0, iters=1, oversample=b - k, pack=False)
+        ctx.sync_status()
+        P64 = si.as_f64(P)
+        assert np.abs(P64.T @ P64 - np.eye(k + 8)).max() < 1e-5
+        H = P64[:, :k].T @ orc.gram(si.as_f64(Xt)) @ P64[:, :k]
+        assert np.abs(H - np.diag(np.diag(H))).max() < 2.5e-5 * H[0, 0]
+
+
 def test_fit_basis_rac_and_full_complement(ctx):
     d = 96
     # k = 0: purely random basis, scale d / r
