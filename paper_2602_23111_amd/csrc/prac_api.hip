@@ -753,13 +753,18 @@ int wgrad_splits(int n_cu, int tune_splits, int c, int n_out, const int64_t* m, 
 // 256 units (up and gate) 5 ranges in two rounds 237 / 320 us, unequal 217 / 292; 172 tiles of 128 units (LLaMA-7B up projection)
 // one range 226 / 319, unequal 183 / 282.  Pieces priced at 0, 8 and 16 units instead: 228, 220 and 225 us on the former's
 // C^T dY, 200, 193 and 203 on the latter's (190 with 3, in the same run).
+// Their partial sums are whole blocks of 256 (or c) x 128, however little of a tile T fills, so scratch bounds them too: where the
+// blocks of the main ranges take more than 5/4 of what the equal ranges' sums do (m far below 128, c just above 256: up to 20 times),
+// ranges stay equal (whole weight gradient, unequal against equal: N = 337601, d = 6638, c = 737, m = 24 133 / 123 us with 34 against
+// 5 MB; 25102, 570, 283, 3324 101.5 / 105 with 29 against 17 MB).  Then one tile's blocks at a time, the least a call with a fixed scratch can do, are always the smaller of the two.
 CtdyTails wgrad_tails(int n_cu, int c, int n_out, const int64_t* m, int64_t N, int splits) {
   const WgradWork w(c, n_out, m);
   const int64_t units = (N + 127) / 128;
   CtdyTails t;
   t.main = (int)(n_cu / w.tiles);
   const int64_t idle = n_cu - t.main * w.tiles;
-  if (t.main < 1 || idle < 1) return {};
+  t.block_rows = std::min(c, 256);
+  if (t.main < 1 || idle < 1 || 4 * t.main * w.tiles * t.block_rows * 128 * (int64_t)sizeof(float) > 5 * splits * w.slab) return {};
   for (int64_t len = (w.tiles * units + n_cu - 1) / n_cu; len * t.main < units; ++len) {
     const int64_t tail = units - len * t.main, run = (w.tiles * tail + idle - 1) / idle;
     const int64_t pieces = (run + tail - 2) / tail + 1;
@@ -768,7 +773,6 @@ CtdyTails wgrad_tails(int n_cu, int c, int n_out, const int64_t* m, int64_t N, i
     t.tail = (int)tail;
     t.run = (int)run;
     t.helpers = (int)((w.tiles * tail + run - 1) / run);
-    t.block_rows = std::min(c, 256);
     t.t1 = (int)w.tiles;
     const double us = WgradWork::round_us(128.0 * (double)len) +
                       (double)(2 * w.slab) * ((double)t.main + 1.0 + (double)t.helpers / (double)w.tiles) / 3e6;

@@ -233,6 +233,11 @@ def test_workspace_bytes_matches_the_documented_scratch_of_each_call(lib):
     # 5 in two rounds would be a little faster (as for two outputs, which that entry point does not take)
     assert ws(prac.call_shape("weight_grad", N, d, k, r, m=[11008])) == 2 * c * 11008 * 4 + c * 11008 * 2
     assert ws(prac.call_shape("weight_grad", N, d, k, r, m=[5504, 5504])) == 5 * c * 11008 * 4 + c * 5632 * 2 * 2
+    # unequal token ranges, whose partial sums are whole tiles: never much more than equal ranges' (5 and 4 of them; T behind them)
+    for N1, d1, c1, m1, ranges in ((60994, 271, 271, 3045, 5), (25102, 570, 283, 3324, 4), (337601, 6638, 737, 24, 64)):
+        sh = prac.call_shape("weight_grad", N1, d1, c1 // 2, c1 - c1 // 2, m=[m1])
+        t_bytes = (c1 + 255) // 256 * 256 * (m1 + 255) // 256 * 256 * 2
+        assert ranges * c1 * m1 * 4 < ws(sh) <= 1.25 * ranges * c1 * m1 * 4 + t_bytes
     # strided kernels (fp32 data): T, and nothing else for an fp32 dW
     assert ws(prac.call_shape("weight_grad", 2048, 512, 32, 32, m=[1376], dt=0, odt=0, c_layout=0)) == up(64 * 1376 * 4)
     # reconstruction: Ps^T in fragment order (k-blocks over 256, column blocks over d)

@@ -620,6 +620,25 @@ def test_weight_grad_over_unequal_token_ranges(ctx, N, c, ms, pad, static):
             assert ((dW[:, a:a + 4096].double() - ref).abs() <= 2.0 ** -7 * mag).all()
 
 
+@pytest.mark.parametrize("N,d,c,m,beta", [(337601, 6638, 737, 24, 1.0)])
+def test_static_weight_grad_takes_narrow_outputs_of_many_tokens(ctx, N, d, c, m, beta):
+    """A few columns under many tokens: the partial sums of equal token ranges fit the static block where whole tiles of unequal
+    ones would not.  The call is taken, and gives the bits of prac_weight_grad."""
+    from paper_2602_23111_amd.prac import C_PACKED
+    k = c // 2
+    g = torch.Generator(device=DEV).manual_seed(N)
+    Cp = torch.zeros(ctx.compressed_bytes(N, c) // 2, dtype=torch.bfloat16, device=DEV).normal_(generator=g)
+    P = torch.randn((d, c), generator=g, device=DEV) * d ** -0.5
+    dY = (torch.randn((N, m), generator=g, device=DEV) * 1e-2).bfloat16()
+    old = torch.randn((d, m), generator=g, device=DEV)
+    lp = ctx.pack_basis(P)
+    outs = []
+    for static in (False, True):
+        outs.append(ctx.weight_grad(Cp, dY, P, k, c - k, 2.0, P_lp=lp, out=old.clone(), beta=beta, layout=C_PACKED, static=static))
+    ctx.sync_status()
+    assert torch.equal(*outs) and not torch.equal(outs[0], old)
+
+
 # ------------------------------------------------------------- reconstruction
 RECON_CASES = [
     # dtype, N, d, k, r, ldc, ldxh
