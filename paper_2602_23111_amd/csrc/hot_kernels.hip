@@ -302,6 +302,7 @@ struct PtArgs {
   // up to PRAC_CTDY_MAX_OUT products sharing P (layers reading the same input, Section 5.1):
   // output h owns the column tiles tile0[h] .. tile0[h+1]-1 of the launch
   int n_out;
+  int group_rows;        // row tiles of a group (see pt_tiled_kernel)
   const bf16_t* Tf[PRAC_CTDY_MAX_OUT];  // [nkb][nmb_h][64][8]
   void* dW[PRAC_CTDY_MAX_OUT];
   int64_t lddw[PRAC_CTDY_MAX_OUT];
@@ -463,6 +464,8 @@ __global__ __launch_bounds__(256) void pt_kernel(PtArgs a) {
 // a tile is a few chunks: last product alone, N = 2048, four k-blocks / two, and two workgroups with whole wave tiles staged before:
 // d = 4096, m = 5000, c = 128 20.6 / 22.6, 21.6; 3000, 8192, 128 in fp32 46.4 / 51.6, 48.9; 8192, 8192, 64 33.6 / 28.3, 35.1;
 // 2048, 8192, 512 33.0 / 30.6, 35.1; 4096, 11008, 512 81.1 / 65.0, 89.6; 8192, 8192, 1024 in fp32 229 / 208, 247.
+// Up to two tiles per compute unit four workgroups have nothing to do there, so chunks stay long (c > 256, N = 1024, two k-blocks / four):
+// d = 6638, m = 24, c = 737 16.2 / 14.0; 2500, 1000, 1024 20.8 / 17.6; 4096, 2048, 512 in fp32 33.8 / 25.7.
 // (Tiles of 256 x 256, one workgroup of 8 waves per compute unit: 75.0 at 4096, 11008, 512, but 276 at the last and 78.6 at the second.)
 constexpr int PT2_ELD = 64 + 4;  // floats per row of a wave's output staging tile (32 x 64)
 template <int KC, bool OUT_BF16>
@@ -480,10 +483,11 @@ __global__ __launch_bounds__(256, 8 / KC) void pt_tiled_kernel(PtArgs a) {
   const int xcd = bid & 7, slot = bid >> 3;
   const int logical = xcd * per_xcd + slot;
   if (slot >= per_xcd || logical >= total) return;
-  // c > 256: groups of eight row tiles, a group's tiles column by column, so that an XCD's run of tiles needs eight row tiles of P
+  // c > 256 and more than two tiles per compute unit: groups of eight row tiles, a group's tiles column by column, so that an XCD's run of tiles needs eight row tiles of P
   // and part of T instead of all of T for every row tile.  Narrower products are bound by the write of dW and
-  // stay row by row (d = 4096, m = 11008, c = 512 90.5 against 73.9 us; d = 3000, m = 8192, c = 128 in fp32 47.7 against 62.4).
-  const int group_rows = a.nkb > 16 ? 8 : 1;
+  // stay row by row (d = 4096, m = 11008, c = 512 90.5 against 73.9 us; d = 3000, m = 8192, c = 128 in fp32 47.7 against 62.4), and so do
+  // fewer tiles (4096, 2048, 512 in fp32 25.7 against 33.7).
+  const int group_rows = a.group_rows;
   const int group = logical / (group_rows * a.tiles_n), in = logical - group * group_rows * a.tiles_n;
   const int rows = min(group_rows, a.tiles_m - group * group_rows);
   const int tn_g = in / rows, tm = group * group_rows + in - tn_g * rows;
@@ -1128,7 +1132,8 @@ int launch_pt(prac_ctx* ctx, const bf16_t* Pa, int n_out, const bf16_t* const* T
   a.tiles_m = (d + 127) / 128;
   const int total = a.tiles_m * a.tiles_n;
   const bool tiled = total > ctx->n_cu || nkb > PT_PD;
-  const int kc = nkb > 4 && nkb <= PT_PD ? 4 : 2;  // k-blocks per chunk of the staged one
+  const int kc = nkb > 4 && (nkb <= PT_PD || total <= 2 * ctx->n_cu) ? 4 : 2;  // k-blocks per chunk of the staged one
+  a.group_rows = nkb > PT_PD && total > 2 * ctx->n_cu ? 8 : 1;
   const dim3 grid(((total + 7) / 8) * 8), block(256);
   const size_t smem = !tiled ? (size_t)128 * PT_TLD * sizeof(float)
                              : std::max((size_t)2 * (128 / 32 + 4) * kc * 1024, (size_t)4 * 32 * PT2_ELD * sizeof(float));

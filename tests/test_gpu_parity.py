@@ -555,16 +555,17 @@ def test_weight_grad_of_wide_layers(ctx, d, c, ms, pad):
 
 
 @pytest.mark.parametrize("odt", ["f32", "bf16"])
-@pytest.mark.parametrize("c", [17, 63, 65, 120, 257, 300])   # 2 to 19 k-blocks: chunks of two and of four, whole and partial
-def test_weight_grad_last_product_in_chunks(ctx, c, odt):
+@pytest.mark.parametrize("c,m", [(17, 2197), (63, 2197), (65, 2197), (120, 2197), (257, 2197), (300, 2197),   # 2 to 19 k-blocks: chunks
+                                 (257, 4201), (300, 4201)])   # of two and of four, whole and partial; more than two tiles per compute unit
+def test_weight_grad_last_product_in_chunks(ctx, c, m, odt):
     """dW = P T over more tiles of 128 x 128 than compute units, ragged at both ends (row tiles in a partial group too), with
     beta: every element against the product of the same operands.  T: one ulp (2^-8) either way; dW: one of its own."""
-    d, m, N, k = 2100, 2197, 300, c // 2
+    d, N, k = 2100, 300, c // 2
     s = (d - k) / (c - k)
     g = torch.Generator(device=DEV).manual_seed(c)
     Ct = torch.randn((N, c), generator=g, device=DEV).bfloat16()
     P = torch.randn((d, c), generator=g, device=DEV) * d ** -0.5
-    dY = torch.zeros((N, 2200), dtype=torch.bfloat16, device=DEV)[:, :m]
+    dY = torch.zeros((N, (m + 7) // 8 * 8), dtype=torch.bfloat16, device=DEV)[:, :m]
     dY.copy_(torch.randn((N, m), generator=g, device=DEV) * 1e-2)
     buf = torch.full((d + 1, m + 3), 0.5, dtype=torch.float32 if odt == "f32" else torch.bfloat16, device=DEV)
     ctx.weight_grad(Ct, dY, P, k, c - k, s, P_lp=ctx.pack_basis(P), out=buf[:d, :m], beta=2.0)
