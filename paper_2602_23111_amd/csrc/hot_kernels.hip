@@ -195,14 +195,21 @@ struct ReduceTfArgs {
   bf16_t* Tf[PRAC_CTDY_MAX_OUT];          // [nkb][nmb_h][64][8]
   int m[PRAC_CTDY_MAX_OUT];
   int nmb[PRAC_CTDY_MAX_OUT];
-  int tile0[PRAC_CTDY_MAX_OUT], tiles_n;  // column tiles of 128, as C^T dY counts them
-  CtdyTails tails;                        // main > 0: blocks instead of slabs
   int pair0[PRAC_CTDY_MAX_OUT + 1];       // first pair of column blocks of output h in the launch
 };
+struct ReduceTfTailArgs : ReduceTfArgs {  // unequal token ranges: blocks instead of slabs
+  int tile0[PRAC_CTDY_MAX_OUT], tiles_n;  // column tiles of 128, as C^T dY counts them
+  CtdyTails tails;
+};
 
-__global__ __launch_bounds__(256) void reduce_to_tfrag_kernel(ReduceTfArgs a) {
+// Bound by latency (a workgroup reads 4 KB per slab), so eight slabs are in flight, then four; equal and unequal ranges have a form
+// each (one for both took 78 registers, 6 waves per SIMD): 7.2 us -> 7.0 at c = 256, m = 2048 (16 slabs), 11.5 -> 10.6 for the unequal
+// ranges of 2 x 5461 columns; with loads as the compiler orders the plain loop, 8.2.
+template <typename Args>
+__global__ __launch_bounds__(256) void reduce_to_tfrag_kernel(Args a) {
+  constexpr bool TAILS = std::is_same_v<Args, ReduceTfTailArgs>;
   __shared__ float patch[16][68];
-  const int bid = touch_kernel_args<sizeof(ReduceTfArgs)>(blockIdx.x);
+  const int bid = touch_kernel_args<sizeof(Args)>(blockIdx.x);
   const int pairs = a.pair0[a.n_out];
   const int kb = bid / pairs, gp = bid % pairs;
   int h = 0;
@@ -211,24 +218,33 @@ __global__ __launch_bounds__(256) void reduce_to_tfrag_kernel(ReduceTfArgs a) {
     if (q < a.n_out && gp >= a.pair0[q]) h = q;
   const int np = gp - a.pair0[h];
   const int m = a.m[h], nmb = a.nmb[h], c = a.c, splits = a.splits;
-  // the tile of T that this patch lies in (padding behind an output's last tile: that one)
-  const int t = min(kb / 16, (c - 1) / 256) * a.tiles_n + a.tile0[h] + min(np / 2, (m - 1) / 128);
-  if (a.tails.main > 0 && (t < a.tails.t0 || t >= a.tails.t1)) return;
+  int t = 0;  // the tile of T that this patch lies in (padding behind an output's last tile: that one)
+  if constexpr (TAILS) {
+    t = min(kb / 16, (c - 1) / 256) * a.tiles_n + a.tile0[h] + min(np / 2, (m - 1) / 128);
+    if (t < a.tails.t0 || t >= a.tails.t1) return;
+  }
   const int tid = threadIdx.x;
   const int row = tid >> 4, col = (tid & 15) * 4;
   const int k = kb * 16 + row, n = np * 64 + col;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   if (k < c && n < m) {
-    auto add4 = [&](const float* p, int parts, int64_t stride) {
-#pragma unroll 8
-      for (int z = 0; z < parts; ++z) {
-        // read once
-        const f32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(p + z * stride));
-        s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-      }
+    auto add4 = [&](const float* p, int parts, int64_t stride) __attribute__((always_inline)) {
+      auto batch = [&](auto count) __attribute__((always_inline)) {  // that many in flight; read once
+        constexpr int B = decltype(count)::value;
+        f32x4_t v[B];
+#pragma unroll
+        for (int z = 0; z < B; ++z) v[z] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(p + z * stride));
+#pragma unroll
+        for (int z = 0; z < B; ++z) s.x += v[z].x, s.y += v[z].y, s.z += v[z].z, s.w += v[z].w;
+        p += B * stride;
+      };
+      int z = 0;
+      for (; z + 8 <= parts; z += 8) batch(std::integral_constant<int, 8>{});
+      if (z + 4 <= parts) batch(std::integral_constant<int, 4>{}), z += 4;
+      for (; z < parts; ++z) batch(std::integral_constant<int, 1>{});
     };
     const int sld = a.sld[h];
-    if (a.tails.main > 0) {
+    if constexpr (TAILS) {
       const CtdyTails& p = a.tails;
       const int64_t block = (int64_t)p.block_rows * 128;
       const int in = (k & 255) * 128 + (n & 127);
@@ -1090,7 +1106,7 @@ int launch_pack_c(prac_ctx* ctx, const bf16_t* C, int64_t ldc, int N, int c, bf1
 int launch_reduce_to_tfrag(prac_ctx* ctx, int n_out, const float* const* slabs, int splits, int c, const int* m, int k_lo,
                            float scale_hi, int nkb, const int* nmb, bf16_t* const* Tf, const int* sld, const CtdyTails& tails) {
   if (n_out < 1 || n_out > PRAC_CTDY_MAX_OUT) return PRAC_EINVAL;
-  ReduceTfArgs a{};
+  ReduceTfTailArgs a{};
   a.n_out = n_out; a.splits = splits; a.c = c; a.k_lo = k_lo; a.nkb = nkb; a.scale_hi = scale_hi; a.tails = tails;
   int pairs = 0;
   for (int h = 0; h < n_out; ++h) {
@@ -1101,7 +1117,8 @@ int launch_reduce_to_tfrag(prac_ctx* ctx, int n_out, const float* const* slabs, 
     a.tiles_n += (m[h] + 127) / 128;
   }
   for (int h = n_out; h <= PRAC_CTDY_MAX_OUT; ++h) a.pair0[h] = pairs;
-  PRAC_LAUNCH(ctx, reduce_to_tfrag_kernel, dim3(nkb * pairs), dim3(256), 0, a);
+  if (tails.main > 0) PRAC_LAUNCH(ctx, reduce_to_tfrag_kernel<ReduceTfTailArgs>, dim3(nkb * pairs), dim3(256), 0, a);
+  else PRAC_LAUNCH(ctx, reduce_to_tfrag_kernel<ReduceTfArgs>, dim3(nkb * pairs), dim3(256), 0, static_cast<const ReduceTfArgs&>(a));
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
 }

@@ -1249,7 +1249,8 @@ __device__ __forceinline__ void wgrad_tail(const CtdyWsArgs& a, unsigned char* s
 template <int MODE, bool UA, bool TAILS>
 __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int bid = touch_kernel_args<(MODE == 0 ? offsetof(CtdyWsArgs, cnt) : sizeof(CtdyWsArgs))>(blockIdx.x);
+  const int bid = touch_kernel_args<(MODE != 0 ? sizeof(CtdyWsArgs) : TAILS ? offsetof(CtdyWsArgs, cnt)
+                                                                            : offsetof(CtdyWsArgs, tails))>(blockIdx.x);
 
   int tn = 0, rg = 0, split = 0;
   int run_beg = 0, run_end = -1;  // helpers: units of the tails of all tiles
