@@ -898,11 +898,13 @@ __global__ __launch_bounds__(256) void copy_cols_kernel(const float* __restrict_
 // ------------------------------------------------------- Gram matrices of the panels
 // src^T src for a d x n fp32 block (pitch n) with fp64 sums on the matrix cores: the 64 x 64 tiles of the upper triangle (all that the
 // factorisation reads) times ranges of rows, as many as fill the chip; 32 x 32 per wave, 32 rows per step, the next step's
-// operands requested before this one's are multiplied.  Partial tiles go to `slabs` in register order.
+// operands requested before this one's are multiplied.  Partial sums go to `slabs` as the 16 x 16 blocks of the upper triangle, in
+// register order.
 // 8.8 us at 2048 x 256, 13 us at 4096 x 256 (21 and 38 us with all tiles, four times the partial sums and each step's operands
 // requested when the step before was done); the sum 4.7 us.
-constexpr int PG_K = 32, PG_TILE = 64 * 64;
+constexpr int PG_K = 32;
 static inline int pg_tiles(int n) { return ((n + 63) / 64) * ((n + 63) / 64 + 1) / 2; }
+static inline size_t pg_bytes(int n) { return (size_t)(((n + 15) / 16) * ((n + 15) / 16 + 1) / 2) * 256 * 8; }  // of one range
 __global__ __launch_bounds__(256) void panel_gram64_kernel(const float* __restrict__ src, int64_t d, int n, int64_t rows_per_split,
                                                            double* __restrict__ slabs) {
   const int lane = threadIdx.x & 63, fi = lane & 15, fk = lane >> 4;
@@ -969,32 +971,34 @@ __global__ __launch_bounds__(256) void panel_gram64_kernel(const float* __restri
         if (kbeg + full * PG_K + 4 * u + fk > last) s0.a[u][t] = s0.b[u][t] = 0.f;
     mul(s0);
   }
-  double* const o = slabs + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * PG_TILE + wave * 1024 + lane;
+  const int nb16 = (n + 15) / 16;
+  double* const o = slabs + (int64_t)blockIdx.y * (nb16 * (nb16 + 1) / 2) * 256 + lane;
 #pragma unroll
   for (int x = 0; x < 2; ++x)
 #pragma unroll
-    for (int y = 0; y < 2; ++y)
+    for (int y = 0; y < 2; ++y) {
+      const int bi = 4 * I + 2 * (wave >> 1) + x, bj = 4 * J + 2 * (wave & 1) + y;
+      if (bi > bj || bj >= nb16) continue;  // uniform
 #pragma unroll
-      for (int v = 0; v < 4; ++v) o[((2 * x + y) * 4 + v) * 64] = acc[x][y][v];
+      for (int v = 0; v < 4; ++v) o[(bi * nb16 - bi * (bi + 1) / 2 + bj) * 256 + v * 64] = acc[x][y][v];
+    }
 }
 
-// W (n x n) = sum over the ranges, tiles of the upper triangle
+// W (n x n) = sum over the ranges, a workgroup per block of the upper triangle
 __global__ __launch_bounds__(256) void panel_gram64_sum_kernel(const double* __restrict__ slabs, int splits, int n,
                                                                double* __restrict__ W) {
-  const int nb = (n + 63) / 64, tiles = gridDim.x / 16;
-  const int tile = blockIdx.x >> 4, e = (blockIdx.x & 15) * 256 + threadIdx.x;
-  int J = tile, I = 0;
-  while (J >= nb - I) {
-    J -= nb - I;
+  const int nb16 = (n + 15) / 16, lane = threadIdx.x & 63;
+  int J = blockIdx.x, I = 0;
+  while (J >= nb16 - I) {
+    J -= nb16 - I;
     ++I;
   }
   J += I;
-  const int lane = e & 63, v = (e >> 6) & 3, y = (e >> 8) & 1, x = (e >> 9) & 1, wave = e >> 10;
-  const int row = 64 * I + 32 * (wave >> 1) + 16 * x + 4 * v + (lane >> 4), c = 64 * J + 32 * (wave & 1) + 16 * y + (lane & 15);
+  const int row = 16 * I + 4 * (threadIdx.x >> 6) + (lane >> 4), c = 16 * J + (lane & 15);
   double s = 0.0;
-  const double* p = slabs + (int64_t)tile * PG_TILE + e;
+  const double* p = slabs + (int64_t)blockIdx.x * 256 + threadIdx.x;
 #pragma unroll 8
-  for (int z = 0; z < splits; ++z) s += p[(int64_t)z * tiles * PG_TILE];
+  for (int z = 0; z < splits; ++z) s += p[(int64_t)z * gridDim.x * 256];
   if (row < n && c < n) W[(int64_t)row * n + c] = s;
 }
 
@@ -1021,10 +1025,18 @@ __global__ __launch_bounds__(256) void panel_gram32_sum_kernel(const float* slab
   if (off) atomicOr(flag, 1);
 }
 
-// row ranges of panel_gram64_kernel: whole steps, one workgroup per compute unit
-int pg_splits(int n_cu, int64_t d, int n) {
-  return (int)std::max<int64_t>(1, std::min<int64_t>(n_cu / pg_tiles(n), (d + PG_K - 1) / PG_K));
+// row ranges of a split panel product of width n
+int panel_splits(int n_cu, int64_t d, int n) {
+  const int tiles = ((n + 63) / 64) * ((n + 63) / 64);
+  return (int)std::max<int64_t>(1, std::min<int64_t>({(2 * n_cu + tiles - 1) / tiles, d / 64, 64}));
 }
+// row ranges of panel_gram64_kernel: whole steps, one workgroup per compute unit, as many as fit `bytes` of partial sums; a
+// plan holds the sums of up to 64 (room for 256, and whole 64 x 64 tiles, gained nothing: 38 us per random block of 2048 x 19, 36 of
+// 8192 x 16 either way)
+int pg_splits(int n_cu, int64_t d, int n, size_t bytes) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>({n_cu / pg_tiles(n), (d + PG_K - 1) / PG_K, (int64_t)(bytes / pg_bytes(n))}));
+}
+size_t pg_need(int n_cu, int64_t d, int n) { return n > 0 ? pg_splits(n_cu, d, n, 64 * pg_bytes(n)) * pg_bytes(n) : 0; }
 
 struct FitWs {
   size_t G, V, Y, W64, X64, Rinv, lam, Z, S, T, slabs, slab_bytes, gram, total;
@@ -1085,11 +1097,7 @@ FitWs plan_fit(int64_t d, int k, int r, const prac_fit_opts& o, int n_cu, bool n
   w.Z = p.take((size_t)bb * (k > 0 ? k : 1) * 4);
   w.S = p.take((size_t)d * (rf > 0 ? rf : 1) * 4);
   w.T = p.take((size_t)(k > 0 ? k : 1) * (rf > 0 ? rf : 1) * 4);
-  const int tiles = ((bb + 63) / 64) * ((bb + 63) / 64);
-  int s = (2 * n_cu + tiles - 1) / tiles;
-  if (s > d / 64) s = (int)(d / 64);
-  if (s < 1) s = 1;
-  if (s > 64) s = 64;
+  const int s = panel_splits(n_cu, d, bb);
   w.splits_bb = s;
   // G V (d x b, fp32): split the sum over k until the tiles fill the chip
   const int tiles_gv = (int)((d + 63) / 64) * ((b + 63) / 64);
@@ -1103,8 +1111,8 @@ FitWs plan_fit(int64_t d, int k, int r, const prac_fit_opts& o, int n_cu, bool n
   const size_t slab_bb = (size_t)s * bb * bb * 8, slab_gv = sg > 1 ? (size_t)sg * d * b * 4 : 0;
   const size_t slab_kr = (size_t)s * k * rf * 4;  // also the completion's Q1^T S (kq x fill)
   w.slab_bytes = std::max(slab_bb, std::max(slab_gv, slab_kr));
-  for (int n : {b, kq, k - kq, r})  // the panel Gram matrices with fp64 sums
-    if (n > 0) w.slab_bytes = std::max(w.slab_bytes, (size_t)pg_splits(n_cu, d, n) * pg_tiles(n) * PG_TILE * 8);
+  for (int n : {b, b > 0 ? kq : 0, fill, r})  // the panel Gram matrices with fp64 sums
+    w.slab_bytes = std::max(w.slab_bytes, pg_need(n_cu, d, n));
   w.slabs = p.take(w.slab_bytes);
   w.gram = p.take(gram_bytes);
   if (track) {
@@ -1138,13 +1146,13 @@ int set_dyn_smem(prac_ctx* ctx) {
 
 // src^T src for a d x n block (ld = n) with fp64 sums: the upper triangle of W64
 int panel_gram64(prac_ctx* ctx, const FitWs& w, const float* src, int64_t d, int n, double* W64) {
-  const int tiles = pg_tiles(n), splits = pg_splits(ctx->n_cu, d, n);
-  if ((size_t)splits * tiles * PG_TILE * 8 > w.slab_bytes) return PRAC_EINVAL;
+  const int tiles = pg_tiles(n), splits = pg_splits(ctx->n_cu, d, n, w.slab_bytes);
+  if (splits * pg_bytes(n) > w.slab_bytes) return PRAC_EINVAL;
   double* slabs = reinterpret_cast<double*>(ctx->ws + w.slabs);
   const int64_t per = round_up64((d + splits - 1) / splits, PG_K);
   const int used = (int)((d + per - 1) / per);
   hipLaunchKernelGGL(panel_gram64_kernel, dim3(tiles, used), dim3(256), 0, ctx->stream, src, d, n, per, slabs);
-  hipLaunchKernelGGL(panel_gram64_sum_kernel, dim3(tiles * 16), dim3(256), 0, ctx->stream, slabs, used, n, W64);
+  hipLaunchKernelGGL(panel_gram64_sum_kernel, dim3((unsigned)(pg_bytes(n) / 2048)), dim3(256), 0, ctx->stream, slabs, used, n, W64);
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
 }
@@ -1278,7 +1286,7 @@ int64_t fit_slab_margin(int n_cu, prac_dtype xdt, int64_t N, int64_t d, int k, i
   size_t need = 0;
   auto product = [&](int splits, int64_t M, int64_t Nn, size_t esz) {
     if (splits > 1) need = std::max(need, (size_t)splits * M * Nn * esz);
-    if (M == Nn) need = std::max(need, (size_t)pg_splits(n_cu, d, (int)M) * pg_tiles((int)M) * PG_TILE * 8);
+    if (M == Nn) need = std::max(need, pg_need(n_cu, d, (int)M));
   };
   if (f.do_q1) {
     const int n = L.b;  // block width of the iteration (k when tracking)

@@ -251,6 +251,10 @@ def test_workspace_bytes_matches_the_documented_scratch_of_each_call(lib):
     rnd = ws(prac.call_shape("fit_basis", N, d, k, r, refresh=2))
     assert cold > d * d * 4 and 0 < rnd < track < cold
     assert ws(prac.call_shape("gram", N, d, 0, 0)) > 0
+    # narrow bases: the partial sums of the panels' Gram matrices are no more than 64 ranges of their 16 x 16 blocks (1, 3 and 3 of them)
+    for d1, k1, r1, blocks in ((2048, 0, 1, 1), (7987, 0, 19, 3), (7987, 9, 20, 3)):
+        arrays = 3 * d1 * max(k1, r1) * 4 + 4096 * 4 + k1 * r1 * 64 * 4
+        assert ws(prac.call_shape("fit_basis", N, d1, k1, r1, refresh=2)) < arrays + 64 * blocks * 2048
     # shapes the entry points would reject
     assert ws(prac.call_shape("compress", N, d, 0, 0)) == BAD
     assert ws(prac.call_shape("weight_grad", N, d, k, r, m=[])) == BAD
