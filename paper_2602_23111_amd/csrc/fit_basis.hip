@@ -1175,8 +1175,11 @@ int panel_gram32(prac_ctx* ctx, const FitWs& w, const float* src, int64_t d, int
     g.slabs = ctx->ws + w.slabs;
     rc = launch_gemm_f32(ctx, g, splits);
     if (splits > 1) sums = reinterpret_cast<const float*>(g.slabs);
-  } else {
+  } else {  // n = 1
     g.out = M32;
+    g.splits = w.splits_bb;
+    g.slabs = ctx->ws + w.slabs;
+    g.slab_bytes = w.slab_bytes;
     rc = launch_gemm_generic(ctx, g);
   }
   if (rc) return rc;

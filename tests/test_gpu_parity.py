@@ -1021,13 +1021,33 @@ def test_fit_basis_random_block_matches_oracle_draw(ctx, d, k, r):
 @pytest.mark.parametrize("r", [1, 16, 17, 64, 65, 239, 256, 257, 300])
 def test_fit_basis_block_orthonormalisation_widths(ctx, r):
     # a purely random basis is one Gaussian block through Cholesky-QR: one row, whole and partial 16-row panels, panels
-    # of one and of several column groups (16 + 48 g), the widest matrix that stays in registers and the first past it
+    # of one and of several column groups (16 + 64 g), the widest matrix that stays in registers and the first past it
     d = 1100
     P, _, _ = ctx.fit_basis(None, 0, r, seed=3, draw=2, d=d, P=torch.zeros((d, r), dtype=torch.float32, device=DEV), pack=False)
     ctx.sync_status()
     got = si.as_f64(P)
     assert np.abs(got - orc.complement_basis(np.zeros((d, 0)), orc.gaussian_matrix(3, 2, d, r))).max() < 2e-5
     assert np.abs(got.T @ got - np.eye(r)).max() < 1e-5
+
+
+def test_fit_basis_of_one_column_runs_on_many_workgroups(ctx):
+    # the Gram matrix of a single column is a sum over d like any other: in one workgroup it took 30 times as long as two columns
+    d, us = 8192, {}
+    for r in (1, 2):
+        P = torch.zeros((d, r), dtype=torch.float32, device=DEV)
+        t = []
+        for rep in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for i in range(5):
+                ctx.fit_basis(None, 0, r, seed=i, draw=2, d=d, P=P, pack=False)
+            b.record()
+            torch.cuda.synchronize()
+            t.append(a.elapsed_time(b))
+        ctx.sync_status()
+        assert abs(np.linalg.norm(si.as_f64(P)[:, 0]) - 1.0) < 1e-5
+        us[r] = min(t)
+    assert us[1] < 4.0 * us[2]
 
 
 @pytest.mark.parametrize("r", [15, 33, 113, 128, 129, 224, 225, 240, 241, 255, 511, 513, 1000])
