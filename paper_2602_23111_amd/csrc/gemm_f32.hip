@@ -419,7 +419,10 @@ int launch_f32_sum_pt(prac_ctx* ctx, const float* P, int64_t ldp, float* slabs, 
   a.P = P; a.ldp = ldp; a.slabs = slabs; a.splits = splits; a.c = c; a.k_lo = k_lo; a.scale_hi = scale_hi;
   a.d = d; a.m = m; a.dW = dW; a.lddw = lddw; a.beta = beta;
   const int rows = (d + 127) / 128;
-  const bool narrow = (int64_t)((m + 63) / 64) * rows < ctx->n_cu;
+  // Half the columns, half the sum per workgroup, while each still has a compute unit to itself; past that the second round costs more
+  // (weight gradient, 64 columns / 32: N = 2048, d = 512, m = 1376, c = 64, 172 narrow tiles, 23.4 / 19.4 us; 2048, 1024, 1024, 64, 256
+  // of them, 16.1 / 15.0; 2048, 1024, 1088, 64, 272, 19.9 / 20.5; 4096, 1900, 700, 200, 330, 44.1 / 46.8; 512, 1536, 1024, 32, 384, 13.5 / 14.7).
+  const bool narrow = (int64_t)((m + 31) / 32) * rows <= ctx->n_cu;
   a.tiles_n = narrow ? (m + 31) / 32 : (m + 63) / 64;
   const int64_t total = (int64_t)a.tiles_n * rows;
   if (total > INT32_MAX) return PRAC_EINVAL;

@@ -733,6 +733,7 @@ F32_CASES = [
     (2049, 9, 65, 3, 2),        # Y: 128 x 64, a row and a column past whole tiles, one k past a chunk
     (2045, 133, 2045, 30, 33),  # Y: 128 x 128, partial last tiles, five k past whole chunks
     (700, 1100, 1901, 40, 33),  # dW from 64 columns a workgroup, partial last tiles (all others above: 32 columns)
+    (700, 1100, 1000, 40, 33),  # the same, fewer workgroups than compute units
 ]
 
 
