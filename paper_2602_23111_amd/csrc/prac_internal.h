@@ -265,10 +265,11 @@ int gram_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, int64_t
                 int64_t row_stride, float* G, int64_t ldg, char* scratch);
 
 // Launch on the ctx stream; when a ProfScope is open, the kernel's own begin / end time
-// stamps go into its event pair (so the measured time excludes launch gaps).
+// stamps go into its event pair (so the measured time excludes launch gaps; a launcher with two kernels in a scope hands one
+// event to each).
 #define PRAC_LAUNCH(ctx, kern, grid, block, smem, ...)                                              \
   do {                                                                                             \
-    if ((ctx)->ev_start) {                                                                         \
+    if ((ctx)->ev_start || (ctx)->ev_stop) {                                                       \
       hipExtLaunchKernelGGL(kern, grid, block, smem, (ctx)->stream, (ctx)->ev_start, (ctx)->ev_stop, 0, \
                             __VA_ARGS__);                                                          \
       (ctx)->ev_start = nullptr;                                                                   \

@@ -1585,6 +1585,9 @@ int launch_compress_ws(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d
   const size_t smem = (size_t)WS_STAGES * WS_STAGE;
   const int total = tiles * a.splits;
   const dim3 grid(((total + 7) / 8) * 8), block(512);
+  // a timed product with ranges ends with their sum: the first launch carries the start event, the second the stop
+  const hipEvent_t ev_stop = a.splits > 1 ? ctx->ev_stop : nullptr;
+  if (a.splits > 1) ctx->ev_stop = nullptr;
   static bool done_dev[PRAC_MAX_DEVICES][4] = {};  // the attribute is per device
   bool* done = done_dev[ctx->device % PRAC_MAX_DEVICES];
 #define PRAC_COMPRESS_CASE(I, FN, UA)                                     \
@@ -1604,8 +1607,9 @@ int launch_compress_ws(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d
 #undef PRAC_COMPRESS_CASE
   if (a.splits > 1) {
     const dim3 sgrid(tiles * 4 * 4 * FN * 2 / 4);
-    if (FN == 1) hipLaunchKernelGGL(compress_sum_kernel<1>, sgrid, dim3(256), 0, ctx->stream, a);
-    else hipLaunchKernelGGL(compress_sum_kernel<2>, sgrid, dim3(256), 0, ctx->stream, a);
+    ctx->ev_stop = ev_stop;
+    if (FN == 1) PRAC_LAUNCH(ctx, compress_sum_kernel<1>, sgrid, dim3(256), 0, a);
+    else PRAC_LAUNCH(ctx, compress_sum_kernel<2>, sgrid, dim3(256), 0, a);
   }
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;

@@ -1465,3 +1465,23 @@ def test_profile_hook_counts_selected_launches_only(ctx):
     ctx.compress(X, P)
     assert ctx.profile_read_each() == []
     ctx.sync_status()
+
+
+def test_profile_hook_counts_a_product_in_ranges_once(ctx):
+    # few tokens, long rows: the sum over d runs in ranges, the product and the sum of its ranges are two kernels under one event pair
+    N, d, m, c = 300, 8000, 500, 32
+    X = torch.randn(N, d, device=DEV).to(torch.bfloat16)
+    P = torch.randn(d, c, device=DEV) * d ** -0.5
+    W = torch.randn(d, m, device=DEV).to(torch.bfloat16)
+    lp = ctx.pack_basis(P)
+    ctx.profile_select(6)
+    for _ in range(4):
+        ctx.compress_fused_fwd(X, W, P, P_lp=lp)
+    ctx.compress(X, P, P_lp=lp)
+    each = ctx.profile_read_each()
+    ctx.profile_select(1)
+    ctx.compress(X, P, P_lp=lp)                             # the events of the products above are not left to it
+    one = ctx.profile_read_each()
+    ctx.profile_select(0)
+    assert len(each) == 4 and all(0.0 < ms < 100.0 for ms in each) and len(one) == 1 and 0.0 < one[0] < 100.0
+    ctx.sync_status()
