@@ -197,7 +197,8 @@ int prac_profile_read_each(prac_ctx* ctx, float* each_ms, int64_t cap, int64_t* 
  * launches); 1: as two launches with T (bf16, fragment order) in ctx scratch between them; 0 restores
  * the built-in choice (one launch for k + r > 256 and d <= 2048).  Results are bit-identical.
  * The last two keys do not concern small layers (a few thousand tokens, k + r <= 128), whose whole weight gradient is
- * one launch of another kernel unless PRAC_TUNE_CTDY_SPLITS is set; that key changes the order of the sums. */
+ * one launch of another kernel, nor shapes whose token ranges are of unequal length (output tiles that do not divide the
+ * compute units), which always run as three launches, unless PRAC_TUNE_CTDY_SPLITS is set; that key changes the order of the sums. */
 enum { PRAC_TUNE_CTDY_SPLITS = 1, PRAC_TUNE_PROFILE_STRIDE = 2, PRAC_TUNE_WGRAD_ONE_LAUNCH = 3, PRAC_TUNE_WGRAD_TAIL = 4 };
 int prac_set_tuning(prac_ctx* ctx, int key, int value);
 

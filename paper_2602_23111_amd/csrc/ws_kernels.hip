@@ -1245,7 +1245,7 @@ __device__ __forceinline__ void wgrad_tail(const CtdyWsArgs& a, unsigned char* s
 
 // MODE 0: partial slabs only; 1 / 2: the whole weight gradient (dW in fp32 / bf16).  UA: rows of dY that start on
 // any element (see frag_utils.h).  TAILS (MODE 0): token ranges of unequal length (see CtdyTails); a helper works through the
-// tails of two or three tiles one after the other, its loaders a segment ahead of the matrix waves' stores.
+// tails of a few tiles one after the other, its loaders a segment ahead of the matrix waves' stores.
 template <int MODE, bool UA, bool TAILS>
 __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
