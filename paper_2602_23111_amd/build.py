@@ -20,7 +20,7 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libprac.so")
 SOURCES = ["prac_api.hip", "gemm_bf16.hip", "hot_kernels.hip", "ws_kernels.hip", "gemm_generic.hip",
-           "gemm_f32.hip", "misc_kernels.hip", "fit_basis.hip"]
+           "gemm_f32.hip", "misc_kernels.hip", "sym_eig.hip", "fit_basis.hip"]
 NOISE = "is not a recognized feature for this target"
 
 

@@ -657,14 +657,15 @@ constexpr int JB_GS = JB_M + 1;               // pitch of the Gram matrices and 
 // with every launch full, 14 to 16; with all pairs from the ninth sweep on 14), so the ninth sweep and later ones rotate all
 // pairs and the limit lies four sweeps above the twelve that all-pair launches had.
 constexpr int JB_FULL = 5, JB_FULL_FROM = 8;
-// Sweeps before the iteration gives up.  Up to b = 256 the last four are one launch of one workgroup: they are hardly ever needed, and
-// 60 launches that return at once cost 90 us.  Wider blocks launch all of them: there a sweep in one workgroup takes too long (2016
-// pairs at b = 1024), and idle launches are few beside the work.
-constexpr int JB_SWEEPS = 16, JB_REST = 12, JB_REST_BLOCKS = 16;
+constexpr int JB_SWEEPS = 16;  // before the iteration gives up
 constexpr size_t JB_SMEM = (size_t)(JB_M * JB_CS + 4 * JB_M * JB_GS) * sizeof(double);
-// One pair of blocks; *count goes up by one if a pair of columns needed a rotation.  Returns whether it did (uniform).
-__device__ __forceinline__ bool jacobi_pair(double* H, int b, int bp, int bq, bool full, int inner_sweeps, double tol,
-                                            unsigned* count, const double* hmax) {
+// counts[sweep] goes up by one for every pair of blocks that has a pair of columns that needed a rotation
+__global__ __launch_bounds__(512) void jacobi_block_kernel(double* H, int b, int nblk_even, int step, int sweep, double tol,
+                                                           unsigned* counts, const double* hmax) {
+  if (sweep > 0 && counts[sweep - 1] == 0) return;  // converged in the previous sweep
+  int bp, bq;
+  tournament_pair(step, blockIdx.x, nblk_even, bp, bq);
+  const bool full = step % JB_FULL == 0 || sweep >= JB_FULL_FROM;
   extern __shared__ __align__(16) unsigned char jac_smem[];
   double* cols = reinterpret_cast<double*>(jac_smem);  // [JB_M][JB_CS]: one chunk of the columns
   double* gram = cols + JB_M * JB_CS;                  // [3][JB_M][JB_GS]
@@ -719,13 +720,13 @@ __device__ __forceinline__ bool jacobi_pair(double* H, int b, int bp, int bq, bo
     }
   }
   const bool any_counted = __syncthreads_or(counted);
-  if (!__syncthreads_or(rot)) return false;
-  if (any_counted && tid == 0) atomicAdd(count, 1u);
+  if (!__syncthreads_or(rot)) return;
+  if (any_counted && tid == 0) atomicAdd(&counts[sweep], 1u);
   // Inner tournament.  The 32 players sit in places, pair j in places j and 16 + j, and move on after a step.  All pairs (`full`):
   // place j -> j - 1 (0 -> 17) and 16 + j -> 16 + j + 1 (31 -> 15; 16 stays), 31 steps.  Pairs across the two blocks only: the
   // lower places stay, 16 + j -> 16 + j - 1 (16 -> 31), 16 steps.  Then everybody is home.  The matrix is kept by place, so a
   // thread's addresses never change.
-  const int steps = full ? inner_sweeps * (JB_M - 1) : JB_NB;
+  const int steps = full ? JB_M - 1 : JB_NB;
   if (wave < 4) {
     // thread (i, j): the 2 x 2 block of row pair i and column pair j.  Lane l of a row holds j = l + 4 wave (mod 16), so that the
     // rotation of row pair i = 4 wave + g is in lane g of lane row g.
@@ -821,29 +822,6 @@ __device__ __forceinline__ bool jacobi_pair(double* H, int b, int bp, int bq, bo
           const int c = ch * JB_CW + 32 * wave + 16 * ni + fi;
           if (row < b && c < b) H[(int64_t)row * b + c] = acc[mi][ni][v];
         }
-      }
-  }
-  return any_counted;
-}
-__global__ __launch_bounds__(512) void jacobi_block_kernel(double* H, int b, int nblk_even, int step, int sweep, int inner_sweeps,
-                                                           double tol, unsigned* counts, const double* hmax) {
-  if (sweep > 0 && counts[sweep - 1] == 0) return;  // converged in the previous sweep
-  int bp, bq;
-  tournament_pair(step, blockIdx.x, nblk_even, bp, bq);
-  jacobi_pair(H, b, bp, bq, step % JB_FULL == 0 || sweep >= JB_FULL_FROM, inner_sweeps, tol, &counts[sweep], hmax);
-}
-// sweeps JB_REST .. JB_SWEEPS - 1, pair after pair
-__global__ __launch_bounds__(512) void jacobi_rest_kernel(double* H, int b, int nblk_even, int inner_sweeps, double tol,
-                                                          unsigned* counts, const double* hmax) {
-  bool any = counts[JB_REST - 1] != 0;
-  for (int sweep = JB_REST; sweep < JB_SWEEPS && any; ++sweep) {
-    any = false;
-    for (int step = 0; step < nblk_even - 1; ++step)
-      for (int i = 0; i < nblk_even / 2; ++i) {
-        int bp, bq;
-        tournament_pair(step, i, nblk_even, bp, bq);
-        any |= jacobi_pair(H, b, bp, bq, true, inner_sweeps, tol, &counts[sweep], hmax);
-        __syncthreads();  // its columns are in H, its LDS is free
       }
   }
 }
@@ -1039,7 +1017,7 @@ int pg_splits(int n_cu, int64_t d, int n, size_t bytes) {
 size_t pg_need(int n_cu, int64_t d, int n) { return n > 0 ? pg_splits(n_cu, d, n, 64 * pg_bytes(n)) * pg_bytes(n) : 0; }
 
 struct FitWs {
-  size_t G, V, Y, W64, X64, Rinv, lam, Z, S, T, slabs, slab_bytes, gram, total;
+  size_t G, V, Y, W64, eig, Rinv, lam, Z, S, T, slabs, slab_bytes, gram, total;
   size_t trk_pf, trk_c, trk_slabs;  // tracking refit: V in fragment order, packed X V, slabs of (X V)^T X
   int trk_nkb, trk_ncb, trk_splits;
   int b;
@@ -1091,7 +1069,7 @@ FitWs plan_fit(int64_t d, int k, int r, const prac_fit_opts& o, int n_cu, bool n
   w.V = p.take((size_t)d * bb * 4);
   w.Y = p.take((size_t)d * bb * 4);
   w.W64 = p.take((size_t)bb * bb * 8);
-  w.X64 = p.take((size_t)bb * bb * 8);
+  w.eig = p.take(need_g ? std::max<size_t>(sym_eig_doubles(b) * 8, 256) : 0);
   w.Rinv = p.take((size_t)bb * bb * 4);
   w.lam = p.take((size_t)bb * 8);
   w.Z = p.take((size_t)bb * (k > 0 ? k : 1) * 4);
@@ -1398,34 +1376,32 @@ int fit_basis_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, in
       rc = launch_gemm_generic(ctx, g);
       if (rc) return rc;
     }
-    {
+    if (b <= SYM_EIG_MAX) {
+      rc = launch_sym_eig(ctx, H, b, k, reinterpret_cast<double*>(ctx->ws + L.eig), Z);
+      if (rc) return rc;
+    } else {
       const int nblk = (b + JB_NB - 1) / JB_NB, nblk_even = nblk + (nblk & 1);
       // columns count as orthogonal below this cosine: the Ritz vectors are re-orthonormalised in
       // fp32 afterwards, so anything far below fp32 rounding is spent effort
       constexpr double JACOBI_TOL = 1e-10;
-      unsigned* counts = reinterpret_cast<unsigned*>(ctx->ws + L.X64);
+      unsigned* counts = reinterpret_cast<unsigned*>(ctx->ws + L.eig);
       static bool smem_dev[PRAC_MAX_DEVICES] = {};
       bool& smem_set = smem_dev[ctx->device % PRAC_MAX_DEVICES];
       if (!smem_set) {
-        for (const void* kern : {reinterpret_cast<const void*>(jacobi_block_kernel), reinterpret_cast<const void*>(jacobi_rest_kernel)})
-          PRAC_HIP_TRY(ctx, hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)JB_SMEM));
+        PRAC_HIP_TRY(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(jacobi_block_kernel),
+                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)JB_SMEM));
         smem_set = true;
       }
       hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(64), 0, st, counts, JB_SWEEPS);
       double* hmax = reinterpret_cast<double*>(counts + JB_SWEEPS);
       hipLaunchKernelGGL(symmetrize64_kernel, dim3(16), dim3(1024), 0, st, H, b, hmax);
-      // one or two blocks are one workgroup's job: it sweeps twice per launch there
-      const int inner = nblk_even == 2 ? 2 : 1;
-      const bool rest = nblk_even <= JB_REST_BLOCKS;
-      for (int sweep = 0; sweep < (rest ? JB_REST : JB_SWEEPS); ++sweep)
+      for (int sweep = 0; sweep < JB_SWEEPS; ++sweep)
         for (int step = 0; step < nblk_even - 1; ++step)
-          hipLaunchKernelGGL(jacobi_block_kernel, dim3(nblk_even / 2), dim3(512), JB_SMEM, st, H, b, nblk_even, step, sweep,
-                             inner, JACOBI_TOL, counts, hmax);
-      if (rest)
-        hipLaunchKernelGGL(jacobi_rest_kernel, dim3(1), dim3(512), JB_SMEM, st, H, b, nblk_even, inner, JACOBI_TOL, counts, hmax);
+          hipLaunchKernelGGL(jacobi_block_kernel, dim3(nblk_even / 2), dim3(512), JB_SMEM, st, H, b, nblk_even, step, sweep, JACOBI_TOL,
+                             counts, hmax);
       hipLaunchKernelGGL(jacobi_finish_kernel, dim3(16), dim3(1024), 0, st, H, b, lam, counts, JB_SWEEPS - 1, ctx->d_flag);
+      hipLaunchKernelGGL(select_top_kernel, dim3((b + 3) / 4), dim3(256), 0, st, H, lam, b, k, Z);
     }
-    hipLaunchKernelGGL(select_top_kernel, dim3((b + 3) / 4), dim3(256), 0, st, H, lam, b, k, Z);
     PRAC_HIP_TRY(ctx, hipGetLastError());
     {
       GemmGenArgs g{};

@@ -250,6 +250,13 @@ int launch_sum_pt(prac_ctx* ctx, const bf16_t* Pa, int n_out, const float* const
 int launch_pack_ptfrag(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int c, int k_lo, float scale_hi,
                        int nkb, int ncb, bf16_t* out);
 
+// ---- eigenvectors of a small symmetric matrix (sym_eig.hip) ----------------------
+// Z (n x k fp32, row-major): the k eigenvectors of the symmetric part of H (n x n fp64) with the largest eigenvalues, in descending
+// order; n <= SYM_EIG_MAX.  scratch: sym_eig_doubles(n), 32-byte aligned.
+#define SYM_EIG_MAX 256
+size_t sym_eig_doubles(int n);
+int launch_sym_eig(prac_ctx* ctx, const double* H, int n, int k, double* scratch, float* Z);
+
 // ---- basis fit -----------------------------------------------------------------
 int fit_basis_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, int64_t d, int64_t ldx,
                      int k, int r, uint64_t seed, uint32_t draw, int refresh, const prac_fit_opts& o,

@@ -1097,6 +1097,27 @@ def test_fit_basis_ritz_vectors_come_out_diagonal_and_ordered(ctx, b):
     assert np.abs(H / np.sqrt(np.outer(lam, lam)) - np.eye(k)).max() < 1e-5
 
 
+@pytest.mark.parametrize("b,equal", [(1, False), (2, False), (3, True), (31, False), (64, True), (65, False), (96, False), (129, True),
+                                     (224, False), (225, False), (256, False), (256, True)])
+def test_fit_basis_small_eigenproblem_at_tile_edges(ctx, b, equal):
+    """The eigenvectors of the Ritz matrix at the edges of its tiles, halves and 64-element parts, and with eigenvalues that are equal
+    up to the data's rounding (a third of them each).  All b vectors are asked for, so Q1^T G Q1 must be diagonal with descending entries:
+    off-diagonal cosines by the basis' fp32 rounding, 2^-24 times the ratio of the extreme Ritz values' roots (4) and some roundings."""
+    N, d = 1024, 320
+    i = np.arange(d)
+    sig = np.where(i < b, 4.0 ** (-(3 * i // b) / 3.0), 0.1) if equal else np.where(i < b, 4.0 ** (-i / b), 0.1)
+    Xt = si.round_to(si.activation(N, d, 0.4, 13, exact_spectrum=True, sigma=sig)[0], "f32")
+    P, _, _ = ctx.fit_basis(Xt.to(DEV), b, 8, seed=2, draw=0, oversample=-1, pack=False)
+    ctx.sync_status()
+    P64 = si.as_f64(P)
+    assert np.abs(P64.T @ P64 - np.eye(b + 8)).max() < 1e-5
+    H = P64[:, :b].T @ orc.gram(si.as_f64(Xt)) @ P64[:, :b]
+    lam = np.diag(H)
+    assert (np.diff(lam) <= 1e-5 * lam[:-1]).all()
+    assert np.abs(H / np.sqrt(np.outer(lam, lam)) - np.eye(b)).max() < 1e-5
+    assert lam.sum() > (1 - 1e-5) * np.sum((sig[:b] * np.linalg.norm(si.as_f64(Xt)) / np.linalg.norm(sig)) ** 2)
+
+
 @pytest.mark.parametrize("b,spectrum,outliers", [(48, "power", 8), (80, "power", 0), (80, "geometric", 0), (320, "geometric", 0)])
 def test_fit_basis_settles_on_steep_spectra(ctx, b, spectrum, outliers):
     """One power iteration on singular values ~ i^-2.5 (some channels scaled up) or 0.8^i: the eigen-iteration needs more than twelve
