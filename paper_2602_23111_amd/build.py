@@ -19,7 +19,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libprac.so")
-SOURCES = ["prac_api.hip", "gemm_bf16.hip", "hot_kernels.hip", "ws_kernels.hip", "gemm_generic.hip",
+SOURCES = ["prac_api.hip", "gemm_bf16.hip", "hot_kernels.hip", "ws_kernels.hip", "tile_kernels.hip", "gemm_generic.hip",
            "gemm_f32.hip", "misc_kernels.hip", "sym_eig.hip", "fit_basis.hip"]
 NOISE = "is not a recognized feature for this target"
 

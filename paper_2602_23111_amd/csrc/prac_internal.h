@@ -147,6 +147,11 @@ int launch_cast_out(prac_ctx* ctx, const float* src, int64_t lds, void* dst, pra
 int launch_compress_ws(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d, const bf16_t* Pfrag, int ncb,
                        int c, bf16_t* C, int64_t ldc, bool packed, const bf16_t* Wfrag, int ncb_w, int m,
                        bf16_t* Y, int64_t ldy, bool any_element = false, float* part = nullptr);
+// C = X P by small tiles whose sum over d is split over a workgroup's waves (tile_kernels.hip); aligned rows only
+enum class CompressTile { NONE, T32x32, T32x64, T32x128 };
+CompressTile compress_tile(int n_cu, int N, int c);  // NONE: enough rows for compress_ws_kernel
+int launch_compress_tile(prac_ctx* ctx, CompressTile tile, const bf16_t* X, int64_t ldx, int N, int d, const bf16_t* Pfrag, int ncb, int c,
+                         bf16_t* C, int64_t ldc, bool packed);
 // out_h (N x n[h], bf16) = A (N x c bf16, row-major with lda or packed; c <= 256) B_h for up to PRAC_CTDY_MAX_OUT outputs,
 // B_h in fragment order [nkb][ncb[h]][64][8], zero past row c and column n[h]: nkb = wide_kblocks(c), ncb[h] a multiple
 // of 8 covering n[h]; recon: the reconstruction (one output).  Rows of out_h may start on any element.

@@ -1557,6 +1557,8 @@ int launch_compress_ws(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d
                        int64_t ldy, bool any_element, float* part) {
   // callers route wider pitches, and rows shorter than one 16-byte chunk that start on any element, to the strided kernels
   if (ldx > PRAC_MAX_STREAM_PITCH || (any_element && d < 8)) return PRAC_EINVAL;
+  const CompressTile small = Wfrag || any_element || part ? CompressTile::NONE : compress_tile(ctx->n_cu, N, c);
+  if (small != CompressTile::NONE) return launch_compress_tile(ctx, small, X, ldx, N, d, Pfrag, ncb, c, C, ldc, packed);
   CompressWsArgs a;
 #ifdef PRAC_WS_TIMESTAMPS
   a.stamps = g_ws_stamps;

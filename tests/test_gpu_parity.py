@@ -976,6 +976,30 @@ def test_gram_matches_oracle(ctx, dt, N, d, ldx, stride):
     assert torch.equal(G, G.t()) or rel_fro(si.as_f64(G), si.as_f64(G).T) < 1e-6
 
 
+@pytest.mark.parametrize("N,d,c", [(1, 8, 1), (31, 40, 32), (33, 31, 31), (160, 264, 33), (8192, 33, 32), (8193, 32, 32), (8192, 65, 64),
+                                   (8193, 95, 64), (4096, 300, 225), (8192, 520, 128), (8193, 257, 128), (200, 1288, 1024)])
+def test_compress_of_few_rows_at_tile_edges(ctx, N, d, c):
+    """Both sides of the lines between the tiles (32 x 32, 64, 128 columns, then the 128-row kernel), pieces of k that are
+    partial, missing for some waves or more than the ring holds; NaN behind the rows' last column.  C is the fp64 product with the bf16
+    basis rounded once (half a unit of its eight bits, 2^-8 of the element at most), plus fp32 sums (sqrt(d) 2^-24 of the row's norm, below 2^-18 here)."""
+    from paper_2602_23111_amd.prac import C_PACKED
+    g = torch.Generator(device=DEV)
+    g.manual_seed(N + d + c)
+    X = torch.full((N, (d + 15) // 8 * 8), float("nan"), dtype=torch.bfloat16, device=DEV)
+    X[:, :d] = torch.randn((N, d), generator=g, device=DEV)
+    P = torch.randn((d, c), generator=g, device=DEV)
+    lp = ctx.pack_basis(P)
+    C = ctx.compress(X[:, :d], P, P_lp=lp)
+    pk = ctx.compress(X[:, :d], P, P_lp=lp, layout=C_PACKED)
+    ctx.sync_status()
+    ref = X[:, :d].double() @ P.to(torch.bfloat16).double()
+    scale = X[:, :d].double().norm(dim=1, keepdim=True) * P.double().norm(dim=0, keepdim=True)
+    assert ((C.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2.0 ** -18 * scale).all()
+    assert torch.equal(ctx.unpack_compressed(pk, N, c), C)
+    blocks = pk.view(-1, (c + 31) // 32, 64, 8)                     # whole 16-token blocks past N are zero
+    assert not blocks[(N + 15) // 16:].any()
+
+
 # ---------------------------------------------------------------- basis fit
 def gapped_activation(N, d, k, alpha, seed, dt):
     """Exact-spectrum activation whose Gram eigenvalue ratio at k is >= 1.05."""
