@@ -235,8 +235,8 @@ struct F32SumPtArgs {
 };
 template <int WC, bool OUT_BF16>
 __global__ __launch_bounds__(256 * WC) void f32_sum_pt_kernel(F32SumPtArgs a) {
-  constexpr int TN = 32 * WC;
-  __shared__ float T[FP_K][TN];
+  constexpr int TN = 32 * WC, NBUF = WC == 1 ? 2 : 1;
+  __shared__ float T[NBUF][FP_K][TN];
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m0 = (blockIdx.x / a.tiles_n) * 128 + wave / WC * 32, n0 = (blockIdx.x % a.tiles_n) * TN, wc = wave % WC * 32;
@@ -246,70 +246,122 @@ __global__ __launch_bounds__(256 * WC) void f32_sum_pt_kernel(F32SumPtArgs a) {
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
   const int sr = tid / (TN / 4), sc = tid % (TN / 4) * 4;  // summing: rows sr, sr + 32, columns sc .. sc + 3
   const int64_t slab = (int64_t)a.c * a.m;
-  for (int k0 = 0; k0 < a.c; k0 += FP_K) {
-    f32x4_t fp[FP_K / 8];  // P[row][k0 + 8 q + 4 lh .. + 3]; requested before the sum, which they do not depend on
+  // a row's last columns are taken from its last four and moved down (m < 4: element by element)
+  const int back = a.m >= 4 ? max(n0 + sc + 4 - a.m, 0) : 0;
+  const float* const col = a.slabs + n0 + sc - back;
+  struct P64 {
+    f32x4_t x[FP_K / 8];  // P[row][k0 + 8 q + 4 lh .. + 3]
+  };
+  auto load_p = [&](P64& p, int k0) __attribute__((always_inline)) {
 #pragma unroll
     for (int q = 0; q < FP_K / 8; ++q) {
       const int k = k0 + 8 * q + 4 * lh;
       if (k + 4 <= a.c) {
-        fp[q] = *reinterpret_cast<const f32x4_el*>(prow + k);
+        p.x[q] = *reinterpret_cast<const f32x4_el*>(prow + k);
       } else {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) fp[q][s] = k + s < a.c ? prow[k + s] : 0.f;
+        for (int s = 0; s < 4; ++s) p.x[q][s] = k + s < a.c ? prow[k + s] : 0.f;
       }
     }
-    f32x4_t sum[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
-    const float* const q0 = a.slabs + (int64_t)min(k0 + sr, a.c - 1) * a.m + n0 + sc;
-    const float* const q1 = a.slabs + (int64_t)min(k0 + sr + 32, a.c - 1) * a.m + n0 + sc;
-    if (n0 + sc + 4 <= a.m) {
-      if constexpr (WC == 1) {
-        // Eight slabs in flight, the last ones too (past the end: the last again, not added).  Its registers halve the waves that
-        // fit, so where the launch fills the chip the plain loop below stays ahead (23.6 us against 30.5 with 480 workgroups).
-        for (int z0 = 0; z0 < a.splits; z0 += 8) {
-          f32x4_t x[8], y[8];
+  };
+  // the sum of rows k0 .. + 63 as T, in `to`
+  auto finish = [&](f32x4_t (&sum)[2], int k0, float (&to)[FP_K][TN]) __attribute__((always_inline)) {
 #pragma unroll
-          for (int z = 0; z < 8; ++z) {
-            const int64_t o = min(z0 + z, a.splits - 1) * slab;
-            x[z] = *reinterpret_cast<const f32x4_el*>(q0 + o);
-            y[z] = *reinterpret_cast<const f32x4_el*>(q1 + o);
-          }
+    for (int p = 0; p < 2; ++p) {
+      const int k = k0 + sr + 32 * p;
+      f32x4_t x = sum[p] * (k >= a.k_lo ? a.scale_hi : 1.f);
+      if (back > 0) {
+        const f32x4_t y = x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          x[e] = 0.f;
+#pragma unroll
+          for (int f = e + 1; f < 4; ++f) x[e] = f - e == back ? y[f] : x[e];
+        }
+      }
+      if (k >= a.c) x = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      *reinterpret_cast<f32x4_t*>(&to[sr + 32 * p][sc]) = x;
+    }
+  };
+  auto multiply = [&](const P64& p, const float (&t)[FP_K][TN]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < FP_K / 8; ++q)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(p.x[q][s], t[8 * q + 4 * lh + s][wc + li], acc, 0, 0, 0);
+  };
+  auto by_element = [&](f32x4_t (&sum)[2], int k0) __attribute__((always_inline)) {
+    for (int z = 0; z < a.splits; ++z)
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (n0 + sc + e < a.m) sum[p][e] += col[z * slab + (int64_t)min(k0 + sr + 32 * p, a.c - 1) * a.m + e];
+  };
+  if constexpr (WC == 1) {
+    // Eight slabs in flight, the last ones too (past the end: the last again, not added), and the first of the next rows of T while these
+    // are multiplied.  Its registers halve the waves that fit, so where the launch fills the chip the plain loop below stays
+    // ahead (23.6 us against 30.5 with 480 workgroups).
+    struct Batch {
+      f32x4_t x[8][2];
+    };
+    auto load = [&](Batch& b, int k0, int z0) __attribute__((always_inline)) {
+#pragma unroll
+      for (int z = 0; z < 8; ++z)
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+          b.x[z][p] = *reinterpret_cast<const f32x4_el*>(col + min(z0 + z, a.splits - 1) * slab + (int64_t)min(k0 + sr + 32 * p, a.c - 1) * a.m);
+    };
+    P64 fp, fn;
+    Batch b;
+    load_p(fp, 0);
+    if (a.m >= 4) load(b, 0, 0);
+    for (int k0 = 0, it = 0; k0 < a.c; k0 += FP_K, it ^= 1) {
+      f32x4_t sum[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
+      if (a.m >= 4) {  // uniform
+        for (int z0 = 0; z0 < a.splits; z0 += 8) {
+          if (z0 > 0) load(b, k0, z0);
 #pragma unroll
           for (int z = 0; z < 8; ++z)
             if (z0 + z < a.splits) {
-              sum[0] += x[z];
-              sum[1] += y[z];
+              sum[0] += b.x[z][0];
+              sum[1] += b.x[z][1];
             }
         }
       } else {
+        by_element(sum, k0);
+      }
+      const bool more = k0 + FP_K < a.c;  // uniform
+      if (more) {
+        load_p(fn, k0 + FP_K);
+        if (a.m >= 4) load(b, k0 + FP_K, 0);
+      }
+      finish(sum, k0, T[it]);
+      __syncthreads();  // (the buffer that is written next was multiplied before the barrier that everybody has passed)
+      multiply(fp, T[it]);
+      if (more) fp = fn;
+    }
+  } else {
+    for (int k0 = 0; k0 < a.c; k0 += FP_K) {
+      P64 fp;
+      load_p(fp, k0);  // requested before the sum, which it does not depend on
+      f32x4_t sum[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
+      if (a.m >= 4) {  // uniform
+        const float* const q0 = col + (int64_t)min(k0 + sr, a.c - 1) * a.m;
+        const float* const q1 = col + (int64_t)min(k0 + sr + 32, a.c - 1) * a.m;
 #pragma unroll 8
         for (int z = 0; z < a.splits; ++z) {  // eight slabs in flight
           sum[0] += *reinterpret_cast<const f32x4_el*>(q0 + z * slab);
           sum[1] += *reinterpret_cast<const f32x4_el*>(q1 + z * slab);
         }
+      } else {
+        by_element(sum, k0);
       }
-    } else {
-      for (int z = 0; z < a.splits; ++z)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (n0 + sc + e < a.m) {
-            sum[0][e] += q0[z * slab + e];
-            sum[1][e] += q1[z * slab + e];
-          }
+      if (k0 > 0) __syncthreads();  // the previous rows of T have been multiplied
+      finish(sum, k0, T[0]);
+      __syncthreads();
+      multiply(fp, T[0]);
     }
-    if (k0 > 0) __syncthreads();  // the previous rows of T have been multiplied
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      const int k = k0 + sr + 32 * p;
-      f32x4_t x = sum[p] * (k >= a.k_lo ? a.scale_hi : 1.f);
-      if (k >= a.c) x = f32x4_t{0.f, 0.f, 0.f, 0.f};
-      *reinterpret_cast<f32x4_t*>(&T[sr + 32 * p][sc]) = x;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < FP_K / 8; ++q)
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fp[q][s], T[8 * q + 4 * lh + s][wc + li], acc, 0, 0, 0);
   }
   if (OUT_BF16) {
     // neighbouring lanes hold neighbouring columns: of two registers (two rows) the even lane takes the first row's pair

@@ -1000,6 +1000,23 @@ def test_compress_of_few_rows_at_tile_edges(ctx, N, d, c):
     assert not blocks[(N + 15) // 16:].any()
 
 
+@pytest.mark.parametrize("m", [1, 2, 3, 4, 5, 6, 7, 33, 66, 95])
+def test_f32_weight_grad_of_ragged_columns(ctx, m):
+    """The last columns of the sum over token ranges (taken from a row's last four), one to three rows of 64 of T."""
+    for N, d, c in ((700, 200, 40), (1100, 96, 90), (520, 300, 170)):
+        g = torch.Generator(device=DEV)
+        g.manual_seed(m + N)
+        k = c // 2
+        C, dY, P = (torch.randn(s, generator=g, device=DEV) for s in ((N, c), (N, m), (d, c)))
+        dW = ctx.weight_grad(C, dY, P, k, c - k, 2.5)
+        w = torch.ones(c, dtype=torch.float64, device=DEV)
+        w[k:] = 2.5
+        ref = (P.double() * w) @ (C.double().T @ dY.double())
+        assert ((dW.double() - ref).norm() / ref.norm()).item() < 1e-5
+        acc = ctx.weight_grad(C, dY, P, k, c - k, 2.5, out=dW.clone(), beta=1.0)
+        assert ((acc.double() - 2 * ref).norm() / ref.norm()).item() < 2e-5
+
+
 # ---------------------------------------------------------------- basis fit
 def gapped_activation(N, d, k, alpha, seed, dt):
     """Exact-spectrum activation whose Gram eigenvalue ratio at k is >= 1.05."""
