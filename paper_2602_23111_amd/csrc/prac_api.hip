@@ -717,22 +717,22 @@ constexpr size_t WGRAD_ROOM = PRAC_STATIC_SCRATCH_BYTES - PRAC_SYNC_BYTES;
 
 // Token ranges of C^T dY.  As many as one round of workgroups holds (one per compute unit), or more of them (that `fits` accepts) in
 // several rounds where the cost rule favours that: a round costs its start (6 us) and 15.6 ns per token of a range (a k-block of 16 takes
-// 0.25 us), a range a write and a read of its partial sums (3 TB/s).  Where the column tiles do not divide the compute
+// 0.25 us; with the 128-row tiles of c <= 128 11.5 ns), a range a write and a read of its partial sums (3 TB/s).  Where the column tiles do not divide the compute
 // units, several short rounds fill them better than one long one.  Measured, one round against the rule's choice, per
 // weight gradient: 86 tiles, N = 32768, c = 256 (up and gate) 2 ranges 294 us, 5 ranges 282; 172 tiles, N = 16384, c = 512 one
 // range 307, 4 ranges 295 (90 MB of partial sums, past what a single gradient may use); the rule keeps 16, 5, 4 and 6 ranges for
 // 16, 48, 64 and 40 tiles (next best 3 to 30 us worse).
 struct WgradWork {
   int64_t tiles = 0, slab = 0;  // 256 x 128 tiles of T, bytes of one set of partial sums
-  WgradWork(int c, int n_out, const int64_t* m) {
+  double token_us;              // of equal ranges; unequal ones always have 256-row tiles
+  WgradWork(int c, int n_out, const int64_t* m) : token_us(c <= 128 ? 0.0115 : 0.0156) {
     for (int h = 0; h < n_out; ++h) {
       tiles += (int64_t)((c + 255) / 256) * ((m[h] + 127) / 128);
       slab += (int64_t)c * m[h] * 4;
     }
   }
-  static double round_us(double tokens) { return 6.0 + 0.0156 * tokens; }
   double equal_us(int n_cu, int64_t N, int s) const {
-    return (double)((tiles * s + n_cu - 1) / n_cu) * round_us((double)((N + s - 1) / s)) + (double)(2 * slab) * s / 3e6;
+    return (double)((tiles * s + n_cu - 1) / n_cu) * (6.0 + token_us * (double)((N + s - 1) / s)) + (double)(2 * slab) * s / 3e6;
   }
 };
 template <typename Fits>
@@ -774,7 +774,7 @@ CtdyTails wgrad_tails(int n_cu, int c, int n_out, const int64_t* m, int64_t N, i
     t.run = (int)run;
     t.helpers = (int)((w.tiles * tail + run - 1) / run);
     t.t1 = (int)w.tiles;
-    const double us = WgradWork::round_us(128.0 * (double)len) +
+    const double us = 6.0 + 0.0156 * 128.0 * (double)len +
                       (double)(2 * w.slab) * ((double)t.main + 1.0 + (double)t.helpers / (double)w.tiles) / 3e6;
     const double equal = w.equal_us(n_cu, N, splits);
     return us < 0.97 * equal && us < equal - 2.5 ? t : CtdyTails{};

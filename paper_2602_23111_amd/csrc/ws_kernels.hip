@@ -1246,7 +1246,10 @@ __device__ __forceinline__ void wgrad_tail(const CtdyWsArgs& a, unsigned char* s
 // MODE 0: partial slabs only; 1 / 2: the whole weight gradient (dW in fp32 / bf16).  UA: rows of dY that start on
 // any element (see frag_utils.h).  TAILS (MODE 0): token ranges of unequal length (see CtdyTails); a helper works through the
 // tails of a few tiles one after the other, its loaders a segment ahead of the matrix waves' stores.
-template <int MODE, bool UA, bool TAILS>
+// HALF (c <= 128, no TAILS): T's tile has 128 rows, of which a matrix wave has 64 and every other k-block; the two sums of a row
+// block meet in LDS.  With the 256-row tile two of the four waves multiplied rows that are not there: 22.4 us at N = 32768, m = 768,
+// c = 128, now 19.7 (memory bound).
+template <int MODE, bool UA, bool TAILS, bool HALF>
 __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int bid = touch_kernel_args<(MODE != 0 ? sizeof(CtdyWsArgs) : TAILS ? offsetof(CtdyWsArgs, cnt)
@@ -1409,11 +1412,14 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
     }
     } while (TAILS && next_segment());
     if constexpr (MODE == 0) return;
+    if constexpr (HALF) __syncthreads();  // the matrix waves' exchange
   } else {
   // -------------------------------------------------------------- matrix waves
   const int lane = tid & 63, li = lane & 31, lh = lane >> 5;
   do {
-  const int cb0 = rg * 8 + wave * 2;  // this wave's two 32-row blocks of T (column blocks of C)
+  const int half = HALF ? wave >> 1 : 0;                        // HALF: k-blocks half, half + 2, ...
+  // this wave's two 32-row blocks of T (column blocks of C); HALF: the second one's sums go to the wave with the other k-blocks
+  const int cb0 = HALF ? (wave & 1) * 2 + half : rg * 8 + wave * 2, cb1 = HALF ? cb0 ^ 1 : cb0 + 1;
   f32x16 acc[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i)
@@ -1425,7 +1431,7 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
     const char* cbase = reinterpret_cast<const char*>(a.Cpk);
     // column blocks past the end re-read block 0; their rows of T are never stored
     const uint32_t aoff0 = (uint32_t)((cb0 < a.ccb ? cb0 : 0) * 64 + lane) * 16u;
-    const uint32_t aoff1 = (uint32_t)((cb0 + 1 < a.ccb ? cb0 + 1 : 0) * 64 + lane) * 16u;
+    const uint32_t aoff1 = (uint32_t)((cb1 < a.ccb ? cb1 : 0) * 64 + lane) * 16u;
     const int64_t tbrow = (int64_t)a.ccb * 1024;  // bytes per 16-token block of packed C
 
     // Ring of eight k-blocks' C fragments (16 tokens each): block j multiplies with slot j % 8 and
@@ -1433,10 +1439,10 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
     // other in memory, so the request address just advances; it stops at the last token block of
     // packed C (requests past the split's end are never used).
     u32x4 rc[8][2];
-    const char* creq = cbase + (int64_t)(tok_beg / 16) * tbrow;  // uniform
+    const char* creq = cbase + (int64_t)(tok_beg / 16 + half) * tbrow;  // uniform
     const char* const clast = cbase + (int64_t)(ntb - 1) * tbrow;
     auto advance = [&]() {
-      creq += tbrow;
+      creq += HALF ? 2 * tbrow : tbrow;
       if (creq > clast) creq = clast;
     };
 #pragma unroll
@@ -1455,30 +1461,63 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
     };
 
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem_raw +
-                          (unsigned)(frag_slot(li, lh) * 16);
+                          (unsigned)(frag_slot(li, lh) * 16 + half * 4096);
     u32x4 fa[4], fb[4];
     __builtin_amdgcn_s_barrier();  // tile 0 is in LDS
     frag_read4_ct(fa, lds0);
     int stage = 0;
-    for (int kt = 0; kt < nk; ++kt) {
-      const unsigned cur = lds0 + (unsigned)stage * CW_STAGE;
-      stage = stage == CW_STAGES - 1 ? 0 : stage + 1;
-      const unsigned nxt = lds0 + (unsigned)stage * CW_STAGE;
-      kblock(PRAC_IC(4096 * 1), fa, fb, PRAC_IC(0), cur);
-      kblock(PRAC_IC(4096 * 2), fb, fa, PRAC_IC(1), cur);
-      kblock(PRAC_IC(4096 * 3), fa, fb, PRAC_IC(2), cur);
-      kblock(PRAC_IC(4096 * 4), fb, fa, PRAC_IC(3), cur);
-      kblock(PRAC_IC(4096 * 5), fa, fb, PRAC_IC(4), cur);
-      kblock(PRAC_IC(4096 * 6), fb, fa, PRAC_IC(5), cur);
-      kblock(PRAC_IC(4096 * 7), fa, fb, PRAC_IC(6), cur);
-      __builtin_amdgcn_s_barrier();
-      kblock(PRAC_IC(0), fb, fa, PRAC_IC(7), nxt);
-      if (kt == nk - 1) drain_mfma<8, 2>(acc, rc);  // inside the loop, see the compress kernel
+    if constexpr (HALF) {
+      // four k-blocks per tile, so two tiles to a turn of the ring
+      auto tile = [&](auto kc) {
+        constexpr int K = decltype(kc)::value;
+        const unsigned cur = lds0 + (unsigned)stage * CW_STAGE;
+        stage = stage == CW_STAGES - 1 ? 0 : stage + 1;
+        const unsigned nxt = lds0 + (unsigned)stage * CW_STAGE;
+        kblock(PRAC_IC(4096 * 2), fa, fb, PRAC_IC(K), cur);
+        kblock(PRAC_IC(4096 * 4), fb, fa, PRAC_IC(K + 1), cur);
+        kblock(PRAC_IC(4096 * 6), fa, fb, PRAC_IC(K + 2), cur);
+        __builtin_amdgcn_s_barrier();
+        kblock(PRAC_IC(0), fb, fa, PRAC_IC(K + 3), nxt);
+      };
+      for (int kt = 0; kt < nk; kt += 2) {
+        tile(PRAC_IC(0));
+        if (kt + 1 < nk) tile(PRAC_IC(4));
+        if (kt + 2 >= nk) drain_mfma<8, 2>(acc, rc);  // inside the loop, see the compress kernel
+      }
+    } else {
+      for (int kt = 0; kt < nk; ++kt) {
+        const unsigned cur = lds0 + (unsigned)stage * CW_STAGE;
+        stage = stage == CW_STAGES - 1 ? 0 : stage + 1;
+        const unsigned nxt = lds0 + (unsigned)stage * CW_STAGE;
+        kblock(PRAC_IC(4096 * 1), fa, fb, PRAC_IC(0), cur);
+        kblock(PRAC_IC(4096 * 2), fb, fa, PRAC_IC(1), cur);
+        kblock(PRAC_IC(4096 * 3), fa, fb, PRAC_IC(2), cur);
+        kblock(PRAC_IC(4096 * 4), fb, fa, PRAC_IC(3), cur);
+        kblock(PRAC_IC(4096 * 5), fa, fb, PRAC_IC(4), cur);
+        kblock(PRAC_IC(4096 * 6), fb, fa, PRAC_IC(5), cur);
+        kblock(PRAC_IC(4096 * 7), fa, fb, PRAC_IC(6), cur);
+        __builtin_amdgcn_s_barrier();
+        kblock(PRAC_IC(0), fb, fa, PRAC_IC(7), nxt);
+        if (kt == nk - 1) drain_mfma<8, 2>(acc, rc);  // inside the loop, see the compress kernel
+      }
     }
 #undef PRAC_IC
   }
 
-  // epilogue: acc[4 i + j], register v of lane (li, lh): T row 32 (cb0 + i) + 8*(v/4) + 4*lh + v%4,
+  f32x4_t* const ex = reinterpret_cast<f32x4_t*>(smem_raw);  // HALF: [wave][4 column blocks][4 quads][64 lanes]
+  if constexpr (HALF) {  // (LDS is free behind the last tile's barrier)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      asm volatile("" : "+a"(acc[4 + j]) : : "memory");
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        ex[(wave * 16 + 4 * j + q) * 64 + lane] =
+            f32x4_t{acc[4 + j][4 * q], acc[4 + j][4 * q + 1], acc[4 + j][4 * q + 2], acc[4 + j][4 * q + 3]};
+    }
+    __syncthreads();  // (the loader waves have exited, or wait here too)
+  }
+
+  // epilogue: acc[4 i + j], register v of lane (li, lh): T row 32 cb_i + 8*(v/4) + 4*lh + v%4,
   // column n0 + 4 li + j
   PRAC_STAMP(a, 6);
   const int sld = TAILS ? CW_BN : a.sld[hout], mh = a.m[hout];
@@ -1491,21 +1530,50 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
     out = a.slabs[hout] + (int64_t)split * a.c * sld + n;
     vec = (sld & 3) == 0 && n < mh;  // (a pitch of whole quads has room for the last one)
   }
+  // (spelled out in both forms: through a common function, or without the empty statement, the compiler merges the two ways to store into
+  // stores of three words and one, 2 % of a step)
+  if constexpr (HALF) {
+    asm volatile("" : "+a"(acc[0]), "+a"(acc[1]), "+a"(acc[2]), "+a"(acc[3]) : : "memory");
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    asm volatile("" : "+a"(acc[4 * i]), "+a"(acc[4 * i + 1]), "+a"(acc[4 * i + 2]), "+a"(acc[4 * i + 3]) : : "memory");
+    for (int q = 0; q < 4; ++q) {
+      f32x4_t x[4];  // of the other half
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int row = (cb0 + i) * 32 + 8 * (v / 4) + 4 * lh + (v % 4);
-      if (row < a.c) {
-        float* o = out + (int64_t)row * sld;
-        if (vec) {
-          *reinterpret_cast<float4*>(o) =
-              make_float4(acc[4 * i][v], acc[4 * i + 1][v], acc[4 * i + 2][v], acc[4 * i + 3][v]);
-        } else {
+      for (int j = 0; j < 4; ++j) x[j] = ex[((wave ^ 2) * 16 + 4 * j + q) * 64 + lane];
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            if (n + j < mh) o[j] = acc[4 * i + j][v];
+      for (int e = 0; e < 4; ++e) {
+        const int row = cb0 * 32 + 8 * q + 4 * lh + e;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j][e] += acc[j][4 * q + e];
+        if (row < a.c) {
+          float* o = out + (int64_t)row * sld;
+          if (vec) {
+            *reinterpret_cast<float4*>(o) = make_float4(x[0][e], x[1][e], x[2][e], x[3][e]);
+            asm volatile("" : : : "memory");
+          } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              if (n + j < mh) o[j] = x[j][e];
+          }
+        }
+      }
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      asm volatile("" : "+a"(acc[4 * i]), "+a"(acc[4 * i + 1]), "+a"(acc[4 * i + 2]), "+a"(acc[4 * i + 3]) : : "memory");
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int row = (cb0 + i) * 32 + 8 * (v / 4) + 4 * lh + (v % 4);
+        if (row < a.c) {
+          float* o = out + (int64_t)row * sld;
+          if (vec) {
+            *reinterpret_cast<float4*>(o) =
+                make_float4(acc[4 * i][v], acc[4 * i + 1][v], acc[4 * i + 2][v], acc[4 * i + 3][v]);
+          } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              if (n + j < mh) o[j] = acc[4 * i + j][v];
+          }
         }
       }
     }
@@ -1674,6 +1742,8 @@ void fill_ctdy_args(CtdyWsArgs& a, const bf16_t* Cpk, int c, int N, int n_out, c
   a.tiles_n = tiles;
   a.row_groups = (a.ccb + 7) / 8;
 }
+// equal ranges of a narrow C: the 128-row tile
+bool ctdy_half(int c) { return c <= 128; }
 }  // namespace
 
 int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, const bf16_t* const* dY,
@@ -1701,21 +1771,23 @@ int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, co
   }
   const size_t smem = (size_t)CW_STAGES * CW_STAGE;
   const int total = uneven ? (tails->t1 - tails->t0) * tails->main + tails->helpers : a.tiles_n * a.row_groups * splits;
-  static bool done_dev[PRAC_MAX_DEVICES][3] = {};
+  static bool done_dev[PRAC_MAX_DEVICES][5] = {};
   bool* done = done_dev[ctx->device % PRAC_MAX_DEVICES];
   const dim3 grid(((total + 7) / 8) * 8), block(512);
-#define PRAC_CTDY_CASE(I, UA, TAILS)                                        \
+#define PRAC_CTDY_CASE(I, UA, TAILS, HALF)                                  \
   case I: {                                                                 \
-    constexpr auto kern = ctdy_ws_kernel<0, UA, TAILS>;                     \
+    constexpr auto kern = ctdy_ws_kernel<0, UA, TAILS, HALF>;               \
     int rc = set_smem(ctx, kern, smem, done[I]);                            \
     if (rc) return rc;                                                      \
     PRAC_LAUNCH(ctx, kern, grid, block, smem, a);                           \
     break;                                                                  \
   }
-  switch (any_element ? 1 : (uneven ? 2 : 0)) {
-    PRAC_CTDY_CASE(0, false, false)
-    PRAC_CTDY_CASE(1, true, false)
-    PRAC_CTDY_CASE(2, false, true)
+  switch (uneven ? 2 : (any_element ? 1 : 0) + (ctdy_half(c) ? 3 : 0)) {
+    PRAC_CTDY_CASE(0, false, false, false)
+    PRAC_CTDY_CASE(1, true, false, false)
+    PRAC_CTDY_CASE(2, false, true, false)
+    PRAC_CTDY_CASE(3, false, false, true)
+    PRAC_CTDY_CASE(4, true, false, true)
   }
 #undef PRAC_CTDY_CASE
   PRAC_HIP_TRY(ctx, hipGetLastError());
@@ -1754,18 +1826,24 @@ int launch_wgrad_fused(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out
     a.vec_ok[h] = (reinterpret_cast<uintptr_t>(dW[h]) % 16 == 0 && lddw[h] % (out_bf16 ? 8 : 4) == 0) ? 1 : 0;
   }
   const size_t smem = std::max((size_t)CW_STAGES * CW_STAGE, (size_t)WG_SMEM);
-  static bool f1[PRAC_MAX_DEVICES] = {}, f2[PRAC_MAX_DEVICES] = {};
-  bool &s1 = f1[ctx->device % PRAC_MAX_DEVICES], &s2 = f2[ctx->device % PRAC_MAX_DEVICES];
+  static bool done_dev[PRAC_MAX_DEVICES][4] = {};
+  bool* done = done_dev[ctx->device % PRAC_MAX_DEVICES];
   const dim3 grid(8 * per_xcd), block(512);
-  if (out_bf16) {
-    int rc = set_smem(ctx, (ctdy_ws_kernel<2, false, false>), smem, s2);
-    if (rc) return rc;
-    PRAC_LAUNCH(ctx, (ctdy_ws_kernel<2, false, false>), grid, block, smem, a);
-  } else {
-    int rc = set_smem(ctx, (ctdy_ws_kernel<1, false, false>), smem, s1);
-    if (rc) return rc;
-    PRAC_LAUNCH(ctx, (ctdy_ws_kernel<1, false, false>), grid, block, smem, a);
+#define PRAC_FUSED_CASE(I, MODE, HALF)                                      \
+  case I: {                                                                 \
+    constexpr auto kern = ctdy_ws_kernel<MODE, false, false, HALF>;         \
+    int rc = set_smem(ctx, kern, smem, done[I]);                            \
+    if (rc) return rc;                                                      \
+    PRAC_LAUNCH(ctx, kern, grid, block, smem, a);                           \
+    break;                                                                  \
   }
+  switch ((out_bf16 ? 1 : 0) + (ctdy_half(c) ? 2 : 0)) {
+    PRAC_FUSED_CASE(0, 1, false)
+    PRAC_FUSED_CASE(1, 2, false)
+    PRAC_FUSED_CASE(2, 1, true)
+    PRAC_FUSED_CASE(3, 2, true)
+  }
+#undef PRAC_FUSED_CASE
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
 }

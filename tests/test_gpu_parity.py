@@ -1017,6 +1017,31 @@ def test_f32_weight_grad_of_ragged_columns(ctx, m):
         assert ((acc.double() - 2 * ref).norm() / ref.norm()).item() < 2e-5
 
 
+@pytest.mark.parametrize("N", [1, 127, 129, 257, 385, 8192])
+@pytest.mark.parametrize("c", [1, 32, 33, 65, 97, 128, 129])
+def test_weight_grad_of_narrow_c(ctx, N, c):
+    """The 128-row tile of T (and c = 129, the 256-row one): row blocks of one half alone, ranges of an even and an odd number of token
+    tiles, partial ones; rows of dY on 16-byte boundaries and on any element.  T is exact products summed in fp32 and rounded to bf16 on the
+    aligned path (2^-8 of an element each, as the operands of dW), dW in fp32."""
+    from paper_2602_23111_amd.prac import C_PACKED
+    g = torch.Generator(device=DEV)
+    g.manual_seed(N * 131 + c)
+    d, m, k = 320, 200, c // 2
+    P = torch.randn((d, c), generator=g, device=DEV)
+    X = torch.randn((N, d), generator=g, device=DEV).to(torch.bfloat16)
+    lp = ctx.pack_basis(P)
+    C = ctx.compress(X, P, P_lp=lp, layout=C_PACKED)
+    C64 = ctx.unpack_compressed(C, N, c).double()
+    w = torch.ones(c, dtype=torch.float64, device=DEV)
+    w[k:] = 1.5
+    for width in (m, m + 1):  # rows of m + 1 elements start on any element
+        dY = torch.randn((N, width), generator=g, device=DEV).to(torch.bfloat16)[:, :m] if width == m else \
+            torch.randn((N, width), generator=g, device=DEV).to(torch.bfloat16)
+        dW = ctx.weight_grad(C, dY, P, k, c - k, 1.5, P_lp=lp, layout=C_PACKED)
+        ref = (P.double() * w) @ (C64.T @ dY.double())
+        assert ((dW.double() - ref).norm() / ref.norm()).item() < 2.0 ** -8
+
+
 # ---------------------------------------------------------------- basis fit
 def gapped_activation(N, d, k, alpha, seed, dt):
     """Exact-spectrum activation whose Gram eigenvalue ratio at k is >= 1.05."""
