@@ -1000,6 +1000,24 @@ def test_compress_of_few_rows_at_tile_edges(ctx, N, d, c):
     assert not blocks[(N + 15) // 16:].any()
 
 
+@pytest.mark.parametrize("K", [1, 8, 63, 64, 65, 255, 256, 263, 320, 511, 513, 584, 1100])
+@pytest.mark.parametrize("M,n", [(33, 31), (2050, 90), (4090, 97), (3001, 201)])
+def test_f32_products_by_chunks_of_k(ctx, M, n, K):
+    """X P and C^T dY (sums over k = d and over k = tokens) with no, some and more chunks of k per wave than its ring holds, a multiple of them
+    or not, in the three tiles whose waves split k.  Every fp32 sum of K products is within (K + 2) 2^-24 of the sum of their moduli."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M + K)
+    c = min(n, K)
+    X, P = (torch.randn(s, generator=g, device=DEV) for s in ((M, K), (K, c)))
+    bound = lambda A, B: (K + 2) * 2.0 ** -24 * (A.double().abs() @ B.double().abs())
+    C = ctx.compress(X, P)
+    assert ((C.double() - X.double() @ P.double()).abs() <= bound(X, P)).all()
+    # the basis the identity: dW is T = C^T dY (its own product adds exact zeros; T's partial sums are added in fp32)
+    C, dY, one = torch.randn((K, n), generator=g, device=DEV), torch.randn((K, M // 2), generator=g, device=DEV), torch.eye(n, device=DEV)
+    dW = ctx.weight_grad(C, dY, one, n, 0, 1.0)
+    assert ((dW.double() - C.double().T @ dY.double()).abs() <= bound(C.T, dY)).all()
+
+
 @pytest.mark.parametrize("m", [1, 2, 3, 4, 5, 6, 7, 33, 66, 95])
 def test_f32_weight_grad_of_ragged_columns(ctx, m):
     """The last columns of the sum over token ranges (taken from a row's last four), one to three rows of 64 of T."""
