@@ -256,7 +256,7 @@ struct F32SumPtArgs {
   int tiles_n;
 };
 template <int WC, bool OUT_BF16>
-__global__ __launch_bounds__(256 * WC) void f32_sum_pt_kernel(F32SumPtArgs a) {
+__global__ __launch_bounds__(256 * WC, WC == 2 ? 4 : 1) void f32_sum_pt_kernel(F32SumPtArgs a) {
   constexpr int TN = 32 * WC, NBUF = WC == 1 ? 2 : 1;
   __shared__ float T[NBUF][FP_K][TN];
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
@@ -288,6 +288,9 @@ __global__ __launch_bounds__(256 * WC) void f32_sum_pt_kernel(F32SumPtArgs a) {
   };
   // the sum of rows k0 .. + 63 as T, in `to`
   auto finish = [&](f32x4_t (&sum)[2], int k0, float (&to)[FP_K][TN]) __attribute__((always_inline)) {
+    int t = threadIdx.x;  // (its indexes are formed again here: kept across the sum they cost the wide form its second workgroup per compute unit)
+    asm("" : "+v"(t));
+    const int sr = t / (TN / 4), sc = t % (TN / 4) * 4, back = a.m >= 4 ? max(n0 + sc + 4 - a.m, 0) : 0;
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
       const int k = k0 + sr + 32 * p;
