@@ -103,23 +103,17 @@ struct Operand {
 };
 
 // Where k is split a wave has few chunks, and the requests past its last one would be a large part of all.  Each kernel leaves them out in the
-// way that costs it less: 64 x 64 tiles by a test per chunk (us without / with it and three waves per SIMD, which keep the sums out of the
-// accumulation registers: C^T dY of 4096 x 128 and 1024 in 16 ranges 17.2 / 14.7, 8192 x 256 and 2048 in four 87 / 79, X P of 8192 x 2048 -> 256 85.5 / 83.8),
-// 32 x 32 ones by a second body for the last turn of the ring (of 2048 x 64 and 1376 in eight 11.2 / 9.7, a test 9.8; X P of 2048 x 512 -> 64
-// 6.2 / 5.5, a test 6.4), 32 x 64 ones by a test if A's k runs along memory (4096 x 1024 -> 128 16.2 / 14.9), else not (registers spill: twice the time).
+// way that costs it less.  TEST, one per chunk: 64 x 64 tiles (us without / with it and three waves per SIMD, which keep the sums out of the
+// accumulation registers: C^T dY of 4096 x 128 and 1024 in 16 ranges 17.2 / 14.7, 8192 x 256 and 2048 in four 87 / 79, X P of 8192 x 2048 -> 256 85.5 /
+// 83.8), and one round of 32 x 64 tiles if A's k runs along memory (X P of 4096 x 1024 -> 128 16.2 / 14.9; in two rounds its registers cost more, 3001 x
+// 1501 -> 201 34.0 / 36.6; otherwise they spill: twice the time).  SECOND_BODY for the ring's last turn: 32 x 32 tiles (C^T dY of 2048 x 64 and
+// 1376 in eight ranges 11.2 / 9.7, a test 9.8; X P of 2048 x 512 -> 64 6.2 / 5.5, a test 6.4).
 enum class Turn { ALL, SECOND_BODY, TEST };
-template <bool AKF, int RM, int RN, int SK>
-constexpr Turn f32_turn() {
-  if (SK == 1) return Turn::ALL;
-  if (RM * RN == 1) return Turn::SECOND_BODY;
-  return RM * RN == 4 || AKF ? Turn::TEST : Turn::ALL;
-}
 
 // Tile (32 RM WM) x (32 RN WN) per workgroup of WM x WN x SK waves; SK waves share a wave tile and split its chunks.
-template <bool AKF, bool BKF, int RM, int RN, int WM, int WN, int SK>
+template <bool AKF, bool BKF, int RM, int RN, int WM, int WN, int SK, Turn TURN>
 __global__ __launch_bounds__(64 * WM * WN * SK, SK == 8 ? 4 : (SK > 1 ? 3 : 1)) void gemm_f32_kernel(F32Args a) {
   constexpr int D = 4;  // chunks in flight
-  constexpr Turn TURN = f32_turn<AKF, RM, RN, SK>();
   constexpr int NREG = RM * RN * 16;
   static_assert(RN <= 2, "the epilogue stores single columns or pairs");
   static_assert(SK == 1 || (WM == 1 && WN == 1 && NREG % (RN * SK) == 0), "one wave tile per workgroup when k is split");
@@ -435,22 +429,29 @@ void launch_gemm_f32_ops(prac_ctx* ctx, F32Args& a) {
     const size_t smem = split_k > 1 ? (size_t)split_k * tm * tn * sizeof(float) : 0;  // at most 64 KB
     PRAC_LAUNCH(ctx, kern, dim3((unsigned)((int64_t)((a.M + tm - 1) / tm) * a.tiles_n), 1, a.splits), dim3(threads), smem, a);
   };
-  // 32 x 32 tiles in place of 32 x 64 or 64 x 64 where they take no more rounds of one workgroup per compute unit than 32 x 64 ones: a
-  // workgroup's waves share four SIMDs however many compute units idle, so each round costs 7 us per 1000 k instead of 11 (64 x 64: 20).
-  // us with 32 x 64 / 32 x 32 (same bits): X P of 2048 x 512 -> 64, 128 small tiles, 8.7 / 5.5; 1500 x 1000 -> 100, 188, 13.7 / 10.1; 1024 x 2048 -> 256,
-  // 256, 24.4 / 15.8; 8192 x 1024 -> 32, 256, 16.1 / 11.4; 5000 x 700 -> 90, 471, 17.8 / 14.9; one round more: 4096 x 1024 -> 128, 512, 14.9 / 17.4; C^T dY
-  // of 700 x 40 and 300 in two ranges, 40, 6.8 / 4.9; of 2048 x 64 and 1376 in five, 430, 8.4 / 9.2.  Sixteen waves, or eight chunks in flight, are 0.5 to 2 us behind.
+  // 32 x 32 tiles in place of 32 x 64 ones (same bits) or 64 x 64 ones.  A workgroup's waves share four SIMDs however many compute units idle, so
+  // what counts is rounds of one workgroup per compute unit: 7 us of one per 1000 k instead of 11 (64 x 64: 20).  If A's k runs along memory,
+  // more workgroups per compute unit wait for L1 (a load touches 32 lines): only without a round more.
+  // us with 32 x 64 / 32 x 32: X P of 2048 x 512 -> 64, 128 small tiles, 8.7 / 5.5; 1500 x 1000 -> 100, 188, 13.7 / 10.1; 1024 x 2048 -> 256, 256, 24.4 / 15.8;
+  // 8192 x 1024 -> 32, 256, 16.1 / 11.4; 5000 x 700 -> 90, 471, 17.8 / 14.9; a round more: 4096 x 1024 -> 128, 512, 14.9 / 17.4; 3001 x 1501 -> 201, 658,
+  // 34.0 / 43.8.  C^T dY of 700 x 40 and 300 in two ranges, 40, 6.8 / 4.9; 2048 x 64 and 1376 in eight, 688, 11.4 / 9.7, in five, 430, 8.4 / 9.2; 1500 x 100
+  // and 1000 in five, 640, 11.2 / 10.6; 8192 x 64 and 512 in 32, 1024, 11.9 / 11.6; 3001 x 201 and 1501 in five, 1645, 31.8 / 36.3.  Sixteen waves, or eight
+  // chunks in flight, are 0.5 to 2 us behind.
   const F32Tile tile = f32_tile(ctx->n_cu, a.M, a.N, a.K, a.splits);
   auto rounds = [&](int tn) { return ((int64_t)((a.M + 31) / 32) * ((a.N + tn - 1) / tn) * a.splits + ctx->n_cu - 1) / ctx->n_cu; };
-  if ((tile == F32Tile::T32x64 || tile == F32Tile::T64x64) && rounds(32) == rounds(64)) {
-    launch(gemm_f32_kernel<AKF, BKF, 1, 1, 1, 1, 8>, 32, 32, 512, 8);
+  const bool one_more = !AKF && tile == F32Tile::T32x64 && 7 * rounds(32) < 11 * rounds(64);
+  if ((tile == F32Tile::T32x64 || tile == F32Tile::T64x64) && (rounds(32) == rounds(64) || one_more)) {
+    launch(gemm_f32_kernel<AKF, BKF, 1, 1, 1, 1, 8, Turn::SECOND_BODY>, 32, 32, 512, 8);
     return;
   }
   switch (tile) {
-    case F32Tile::T128x128: launch(gemm_f32_kernel<AKF, BKF, 2, 2, 2, 2, 1>, 128, 128, 256); break;
-    case F32Tile::T128x64: launch(gemm_f32_kernel<AKF, BKF, 1, 2, 4, 1, 1>, 128, 64, 256); break;
-    case F32Tile::T64x64: launch(gemm_f32_kernel<AKF, BKF, 2, 2, 1, 1, 4>, 64, 64, 256, 4); break;
-    case F32Tile::T32x64: launch(gemm_f32_kernel<AKF, BKF, 1, 2, 1, 1, 8>, 32, 64, 512, 8); break;
+    case F32Tile::T128x128: launch(gemm_f32_kernel<AKF, BKF, 2, 2, 2, 2, 1, Turn::ALL>, 128, 128, 256); break;
+    case F32Tile::T128x64: launch(gemm_f32_kernel<AKF, BKF, 1, 2, 4, 1, 1, Turn::ALL>, 128, 64, 256); break;
+    case F32Tile::T64x64: launch(gemm_f32_kernel<AKF, BKF, 2, 2, 1, 1, 4, Turn::TEST>, 64, 64, 256, 4); break;
+    case F32Tile::T32x64:
+      if (AKF && rounds(64) == 1) launch(gemm_f32_kernel<AKF, BKF, 1, 2, 1, 1, 8, AKF ? Turn::TEST : Turn::ALL>, 32, 64, 512, 8);
+      else launch(gemm_f32_kernel<AKF, BKF, 1, 2, 1, 1, 8, Turn::ALL>, 32, 64, 512, 8);
+      break;
   }
 }
 
@@ -467,7 +468,7 @@ F32Tile f32_tile(int n_cu, int M, int N, int64_t K, int splits) {
   auto cost = [&](int tm, int tn, int rm, int rn, int waves, int sk) {
     const int64_t tiles = (int64_t)((M + tm - 1) / tm) * ((N + tn - 1) / tn) * splits;
     const double chunks = std::ceil((double)k / 8 / sk);
-    const double per_simd = std::ceil((double)tiles / n_cu) * (waves / 4);  // a workgroup stays on its compute unit
+    const double per_simd = std::ceil((double)tiles * waves / (4.0 * n_cu));
     const double bytes = (double)tiles * (tm + tn) * 4 * k;
     return std::max({per_simd * chunks * 256 * rm * rn, std::ceil(chunks / 4) * 2400, bytes / 8192}) +
            (sk > 1 ? 1500 : per_simd * rm * rn * 700);

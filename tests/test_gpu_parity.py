@@ -1001,7 +1001,7 @@ def test_compress_of_few_rows_at_tile_edges(ctx, N, d, c):
 
 
 @pytest.mark.parametrize("K", [1, 8, 63, 64, 65, 255, 256, 263, 320, 511, 513, 584, 1100])
-@pytest.mark.parametrize("M,n", [(33, 31), (2050, 90), (4090, 97), (3001, 201)])
+@pytest.mark.parametrize("M,n", [(33, 31), (2050, 90), (4090, 97), (3001, 201), (4090, 250), (8190, 250)])
 def test_f32_products_by_chunks_of_k(ctx, M, n, K):
     """X P and C^T dY (sums over k = d and over k = tokens) with no, some and more chunks of k per wave than its ring holds, a multiple of them
     or not, in the three tiles whose waves split k.  Every fp32 sum of K products is within (K + 2) 2^-24 of the sum of their moduli."""
