@@ -3,7 +3,7 @@
 // Q1: the paper takes the top-r_1 right singular vectors of X "via SVD".  They are
 // the dominant eigenvectors of G = X^T X, found here by block power iteration
 // V <- orth(G V) on a block of b = k + oversample columns, followed by a
-// Rayleigh-Ritz step (eigenvectors of the small matrix V^T G V, by one-sided Jacobi).
+// Rayleigh-Ritz step (eigenvectors of the small matrix V^T G V: sym_eig.hip up to 256 columns, one-sided Jacobi above).
 // Q2: S is drawn from the counter-based Gaussian generator, projected twice onto the
 // complement of Q1 and orthonormalised.  orth() is Cholesky-QR with an fp64 Gram
 // matrix, which yields the thin-QR factor with a positive-diagonal R, i.e. the
@@ -550,7 +550,7 @@ __global__ __launch_bounds__(64 * TR_W) void trsm_right_upper_kernel(const float
   }
 }
 
-// ------------------------------------------------------- symmetric eigen (Jacobi)
+// ------------------------------------------------------- symmetric eigen (Jacobi; more than 256 columns)
 // One-sided (Hestenes) Jacobi on the columns of the symmetric PSD matrix H, held
 // row-major so that "column" p is the contiguous row p (H is symmetric).  Rotating
 // column pairs until all are mutually orthogonal gives H J = B with B's columns
