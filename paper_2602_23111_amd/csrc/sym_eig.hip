@@ -4,8 +4,14 @@
 // Why not rotations: a sweep of one-sided Jacobi is a chain of n - 1 dependent steps and takes seven sweeps, the reduction is one
 // such chain.  At n = 256, k = 128 the rotations took 1.72 ms.
 // Accuracy: columns are reduced from the front, where the power iteration has put the large directions, so that a step's rounding is
-// relative to what is left of a graded matrix.  Vectors of eigenvalues closer than rounding come out independent (random start
-// vectors), not orthogonal; the caller orthonormalises what it makes of them.
+// relative to what is left of a graded matrix.
+// Equal eigenvalues: inverse iteration tells eigenvectors apart by their eigenvalues, and eigenvalues equal to fp64 rounding gave the same vector
+// twice (batches of low rank, whose Ritz values are zero up to rounding; an exactly diagonal H).  So T's diagonal is moved by up to 2^-33 of each
+// entry, by another fraction in every row: the eigenvalues come apart by some 1e-13, and their vectors come out orthogonal to 1e-3 or, now and
+// then, two or three of them to a few tenths, which the caller's orthonormalisation mends.  2^-33 is below what fp32 rounding of V and G V does to
+// H, and as much as the cosine at which the rotations of wider blocks stop.  775 matrices of 1 to 256 rows with equal, zero, nearly equal
+// and graded eigenvalues in random directions and along the axes: the smallest singular value of the k vectors (fp32) was below 0.3 for 262 of
+// them and below 1e-7, a lost vector, for many; now it is below 0.3 for 9 and 0.03 at least.
 #include <algorithm>
 #include <type_traits>
 
@@ -260,7 +266,7 @@ __global__ __launch_bounds__(64 * TD_W) void tridiag_kernel(const double* __rest
 #pragma unroll
     for (int q = 1; q < M; ++q) sq = fma(x[q], x[q], sq);
     const double nn = wave_sum_f64(sq);
-    const bool some = nn > 1e-280;  // (a NaN: no reflector)
+    const bool some = nn > 1e-140;  // (tau^2 is formed; a NaN: no reflector)
     const double rn = rsqrt_f64(some ? nn : 1.0), nrm = nn * rn;
     const double norm = fma(fma(-nrm, nrm, nn), 0.5 * rn, nrm);
     const double beta = some ? -copysign(norm, alpha) : 0.0, t = some ? recip_f64(fma(fabs(alpha), norm, nn)) : 0.0;
@@ -336,10 +342,12 @@ __global__ __launch_bounds__(64 * TD_W) void tridiag_kernel(const double* __rest
     v0 = next;
   }
   for (int i = threadIdx.x; i < n; i += 64 * TD_W) {
-    const double e = s.e[i];
-    out.a[i] = s.a[i];
+    const double e = s.e[i], a = s.a[i];
+    // multiples of the golden section: any run of rows has its fractions spread out evenly; zero rows are moved too
+    const double u = (double)i * 0.6180339887498949, spread = u - floor(u);
+    out.a[i] = fma(spread, fma(0x1p-33, fabs(a), 1e-34), a);
     out.e[i] = e;
-    out.e2[i] = fmax(e * e, 1e-60);
+    out.e2[i] = fmax(e * e, 1e-80);
     out.tau[i] = s.tau[i];
     out.vv[i] = i > 0 && i + 1 < n ? s.vv[i] : 0.0;
   }
@@ -453,8 +461,10 @@ __global__ __launch_bounds__(64 * IV_V) void tridiag_vectors_kernel(TriOut in, c
   }
   __syncthreads();
   if (tid < 2 * IV_V) {
-    const double lm = lam[min((int)blockIdx.x * IV_V + tid % IV_V, k - 1)];
-    const double tiny = 1e-30;  // (H's largest diagonal entry is one)
+    // a little off the eigenvalue: where two agree to the last bits all the same, both shifts leave both vectors in, and the start vectors tell
+    // them apart
+    const double lm = lam[min((int)blockIdx.x * IV_V + tid % IV_V, k - 1)] * (1.0 + 0x1p-50);
+    const double tiny = 1e-60;  // (H's largest diagonal entry is one)
     auto off_zero = [&](double x) __attribute__((always_inline)) { return fabs(x) < tiny ? tiny : x; };
     auto other = [](double x) __attribute__((always_inline)) { return dpp_f64<0x128>(x); };  // the other half's
     // row r of a half: diagonal ap[r da], coupling with row r + 1 ep[r da]
@@ -487,8 +497,11 @@ __global__ __launch_bounds__(64 * IV_V) void tridiag_vectors_kernel(TriOut in, c
       for (int u = 0; u < IV_U; ++u) eliminate(r0 + u, an[u], en[u]);
     }
     for (; r0 < h - 1; ++r0) eliminate(r0, ap[(r0 + 1) * da], ep[(r0 + 1) * da]);
-    // what is left: d x + sup x' = r, x' the other half's last element
-    const double od = other(d), os = other(sup), det = recip_f64(off_zero(fma(d, od, -(sup * os))));
+    // what is left: d x + sup x' = r, x' the other half's last element.  A pivot and the determinant are kept off zero each on its own
+    // scale: without a coupling x is r / d as in every other row, however small both pivots are.
+    d = off_zero(d);
+    const double od = other(d), os = other(sup), size = fma(fabs(d), fabs(od), fabs(sup * os)), least = 0x1p-60 * size;
+    const double dd = fma(d, od, -(sup * os)), det = recip_f64(fabs(dd) < least ? least : dd);
     double f = 1.0, big = 0.0;
     for (int solve = 0; solve < 2; ++solve) {
       double cur = s.x[0][tid] * f;
@@ -541,7 +554,7 @@ __global__ __launch_bounds__(64 * IV_V) void tridiag_vectors_kernel(TriOut in, c
       }
       for (; r >= 0; --r) backward(r, s.x[r][tid], s.inv[r][tid], s.u1[r][tid], s.u2[r][tid]);
       big = fmax(big, other(big));
-      f = recip_f64(big);
+      f = big > 0.0 ? recip_f64(big) : 1.0;  // (all zero: flagged below)
     }
     if (tid < IV_V) s.f[tid] = f;
   }

@@ -1202,6 +1202,57 @@ def test_fit_basis_small_eigenproblem_at_tile_edges(ctx, b, equal):
     assert lam.sum() > (1 - 1e-5) * np.sum((sig[:b] * np.linalg.norm(si.as_f64(Xt)) / np.linalg.norm(sig)) ** 2)
 
 
+@pytest.mark.parametrize("b", [1, 2, 7, 8, 31, 64, 65, 128, 255, 256])
+@pytest.mark.parametrize("kind", ["equal", "two", "steps", "pairs"])
+def test_fit_basis_equal_ritz_values(ctx, b, kind):
+    """A Ritz matrix whose eigenvalues repeat exactly: G is diagonal (or of equal 2 x 2 blocks, "pairs") and the block starts as columns of the
+    identity, so that H is G's corner to the last bit.  Any orthonormal basis of an eigenspace will do, but one it has to be: all b vectors are
+    asked for, and the iteration cannot leave the first b coordinates.  Powers of two throughout: what rounds is the basis, 2^-24 an element."""
+    d, i = 320, np.arange(320)
+    root = np.diag({"equal": np.ones(d), "two": np.where(i % 3 == 0, 2.0, 1.0), "steps": 2.0 ** -(i // 40),
+                    "pairs": np.ones(d)}[kind])
+    if kind == "pairs":
+        for j in range(0, d, 2):
+            root[j:j + 2, j:j + 2] = [[1.25, 0.75], [0.75, 1.25]]
+    Xt = torch.from_numpy(np.concatenate([root, root]).astype(np.float32))
+    P = torch.zeros((d, b + 8), dtype=torch.float32, device=DEV)
+    P[:b, :b] = torch.eye(b, device=DEV)
+    ctx.fit_basis(Xt.to(DEV), b, 8, seed=2, draw=0, P=P, oversample=-1, warm_start=True, pack=False)
+    ctx.sync_status()
+    P64 = si.as_f64(P)
+    assert np.abs(P64.T @ P64 - np.eye(b + 8)).max() < 1e-5
+    H = P64[:, :b].T @ orc.gram(si.as_f64(Xt)) @ P64[:, :b]
+    assert (np.diff(np.diag(H)) <= 1e-5 * H[0, 0]).all()
+    assert np.abs(H - np.diag(np.diag(H))).max() < 1e-5 * H[0, 0]
+    if kind != "pairs":
+        assert np.abs(np.diag(H) - np.sort(np.diag(2.0 * root * root)[:b])[::-1]).max() < 1e-5 * H[0, 0]
+
+
+LOW_RANK = [("f32", 5, False), ("f32", 16, False), ("f32", 40, False), ("f32", 40, True), ("bf16", 1, False), ("bf16", 16, False)]
+
+
+@pytest.mark.parametrize("dt,rank,warm", LOW_RANK)
+def test_fit_basis_of_low_rank_batches(ctx, dt, rank, warm):
+    """More directions asked for than the batch has: the surplus Ritz values are zero up to rounding.  All of the energy is in Q1 (to the
+    Gram matrix' tolerance, 2e-5), the surplus columns complete it to an orthonormal basis."""
+    for d in (256, 520):
+        for seed in range(2):
+            g = torch.Generator(device=DEV)
+            g.manual_seed(100 * seed + rank)
+            X = (torch.randn((1024, rank), generator=g, device=DEV) @ torch.randn((rank, d), generator=g, device=DEV))
+            X = X.to(torch.bfloat16 if dt == "bf16" else torch.float32)
+            G = X.double().T @ X.double()
+            for k, oversample in ((8, -1), (16, -1), (64, -1), (100, -1), (16, 0), (64, 0)):
+                P = torch.zeros((d, k + 8), dtype=torch.float32, device=DEV)
+                P[:k, :k] = torch.eye(k, device=DEV)
+                ctx.fit_basis(X, k, 8, seed=seed, draw=0, P=P, oversample=oversample, warm_start=warm, pack=False)
+                ctx.sync_status()
+                P64 = P.double()
+                assert (P64.T @ P64 - torch.eye(k + 8, dtype=torch.float64, device=DEV)).abs().max() < 1e-5, (d, seed, k, oversample)
+                lost = 1.0 - torch.trace(P64[:, :k].T @ G @ P64[:, :k]) / torch.trace(G)
+                assert lost < (2e-5 if dt == "f32" else 1e-2) or k < rank, (d, seed, k, oversample)
+
+
 @pytest.mark.parametrize("b,spectrum,outliers", [(48, "power", 8), (80, "power", 0), (80, "geometric", 0), (320, "geometric", 0)])
 def test_fit_basis_settles_on_steep_spectra(ctx, b, spectrum, outliers):
     """One power iteration on singular values ~ i^-2.5 (some channels scaled up) or 0.8^i: the eigen-iteration needs more than twelve
