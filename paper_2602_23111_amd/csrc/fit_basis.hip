@@ -153,14 +153,24 @@ __device__ __forceinline__ void chol_panel_group(double* panel, int ldp, int wpa
   }
 }
 
-// Both kernels below: in place on the row-major b x b fp64 matrix W, the upper triangle of W = R^T R (`shift_rel` * max diag(W) is
-// added to its diagonal first) becomes R, with the inverse of every 16 x 16 diagonal block of R in that block's place.
+// Both kernels below: in place on the row-major b x b fp64 matrix W, the upper triangle of W = R^T R (after `shift_rel` of
+// its entry, of the largest entry in the second kernel, is added to each diagonal entry) becomes R, with the inverse of every 16 x 16 diagonal block of R in that block's place.
 // One workgroup of 1024 threads, the columns padded to a multiple of 16 with the identity; products and updates are 16 x 16 tiles
 // on v_mfma_f64_16x16x4_f64.
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
 constexpr int CH_NB = 16;  // panel height = block size of the fp64 matrix instruction
 constexpr int CH_TB = 4;   // trailing tiles a wave has in flight
 constexpr int CH_MAX = 1024;
+// What is added to a diagonal entry: a pivot's rounding is a few 1e-16 of its own column's square, so a share of that keeps it positive, and
+// a short column (a direction that the batch has only as rounding noise) comes out as long as the others.  A share of the largest entry leaves
+// such columns short by 1e9 and more after three passes, past what the rest of the fit mends (rank 1 to 5, fp32, 24 to 100 columns asked
+// for: half of the fits refused, now none).  Blocks wider than 256 columns keep that share: the rotations that follow there do not wait for
+// columns below 1e-13 to settle, and full-length noise does not settle in their sixteen sweeps.  `least`: a column of zeros stays one.
+struct CholShift {
+  double rel, least;
+  __device__ __forceinline__ CholShift(double rel_, double mx) : rel(rel_), least(1e-13 * rel_ * mx) {}
+  __device__ __forceinline__ double of(double x) const { return fmax(rel * x, least); }
+};
 
 // b <= 256: the whole matrix stays in registers as 16 x 16 upper-triangular tiles.  Wave 0 eliminates the diagonal blocks, with
 // the identity beside them, which leaves R_jj^-T; the other 15 waves hold the tiles (round robin, nine at most: both fit the 128
@@ -207,11 +217,11 @@ __device__ __forceinline__ f64x4_t chol_load_tile(const double* W, int b, int I,
     t[v] = *reinterpret_cast<const double*>(base + 8u * (unsigned)(min(CH_NB * I + 4 * v + fk, b - 1) * b + c));
   return t;
 }
-__device__ __forceinline__ void chol_border(f64x4_t& t, int b, double shift, int I, int J) {
+__device__ __forceinline__ void chol_border(f64x4_t& t, int b, CholShift shift, int I, int J) {
   const int fi = threadIdx.x & 15, fk = (threadIdx.x & 63) >> 4, c = CH_NB * J + fi;
   if (I == J) {  // uniform
 #pragma unroll
-    for (int v = 0; v < 4; ++v) t[v] += 4 * v + fk == fi ? shift : 0.0;
+    for (int v = 0; v < 4; ++v) t[v] += 4 * v + fk == fi ? shift.of(t[v]) : 0.0;
   }
   if (CH_NB * (J + 1) > b) {  // uniform
 #pragma unroll
@@ -228,7 +238,7 @@ __device__ __forceinline__ void chol_wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ void chol_pivot_wave(CholRegLds& s, const double* W, int b, double shift, double tiny, int* flag) {
+__device__ __forceinline__ void chol_pivot_wave(CholRegLds& s, const double* W, int b, CholShift shift, double tiny, int* flag) {
   const int lane = threadIdx.x & 63, fi = lane & 15, fk = lane >> 4;
   const int nb = (b + CH_NB - 1) / CH_NB;
   bool bad = false;
@@ -269,7 +279,7 @@ __device__ __forceinline__ void chol_pivot_wave(CholRegLds& s, const double* W, 
   if (bad && lane == 0) atomicOr(flag, 1);
 }
 
-__device__ __forceinline__ void chol_tile_wave(CholRegLds& s, double* W, int b, double shift, int wave) {
+__device__ __forceinline__ void chol_tile_wave(CholRegLds& s, double* W, int b, CholShift shift, int wave) {
   const int lane = threadIdx.x & 63, fi = lane & 15, fk = lane >> 4;
   const int nb = (b + CH_NB - 1) / CH_NB, ntiles = nb * (nb + 1) / 2;
   f64x4_t acc[CHR_UT];
@@ -359,7 +369,8 @@ __global__ __launch_bounds__(1024) void chol_upper_reg_kernel(double* W, int b, 
   __shared__ CholRegLds s;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const double mx = chol_diag_max(W, b, s.red);
-  const double shift = shift_rel * mx, tiny = 1e-300 + 1e-30 * mx;
+  const CholShift shift{shift_rel, mx};
+  const double tiny = 1e-300 + 1e-30 * mx;
   if (wave == 0) chol_pivot_wave(s, W, b, shift, tiny, flag);
   else chol_tile_wave(s, W, b, shift, wave);
 }

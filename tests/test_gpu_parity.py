@@ -1228,7 +1228,7 @@ def test_fit_basis_equal_ritz_values(ctx, b, kind):
         assert np.abs(np.diag(H) - np.sort(np.diag(2.0 * root * root)[:b])[::-1]).max() < 1e-5 * H[0, 0]
 
 
-LOW_RANK = [("f32", 5, False), ("f32", 16, False), ("f32", 40, False), ("f32", 40, True), ("bf16", 1, False), ("bf16", 16, False)]
+LOW_RANK = [(dt, rank, warm) for dt in ("f32", "bf16") for rank in (1, 2, 5, 16, 40) for warm in (False, True)]
 
 
 @pytest.mark.parametrize("dt,rank,warm", LOW_RANK)
