@@ -1,5 +1,6 @@
 // Small streaming kernels: the counter-based Gaussian generator, basis packing,
 // split-reduction epilogues and element-wise helpers.
+#include "philox.h"
 #include "prac_internal.h"
 
 namespace {
@@ -12,28 +13,9 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) {
 }
 __device__ __forceinline__ float bf16_to_f32(bf16_t v) { return __uint_as_float(((uint32_t)v) << 16); }
 
-// ---- Philox4x32-10 (Salmon et al., SC'11) ------------------------------------------
+// ---- Gaussian draw ------------------------------------------------------------------
 // Stream layout: word i of (seed, draw, stream) is output i%4 of the block whose counter
 // is (i/4 low, i/4 high, stream, draw) under key (seed low, seed high).
-struct U4 { uint32_t x, y, z, w; };
-
-__device__ __forceinline__ U4 philox4x32_10(U4 c, uint32_t k0, uint32_t k1) {
-#pragma unroll
-  for (int r = 0; r < 10; ++r) {
-    const uint32_t hi0 = __umulhi(0xD2511F53u, c.x), lo0 = 0xD2511F53u * c.x;
-    const uint32_t hi1 = __umulhi(0xCD9E8D57u, c.z), lo1 = 0xCD9E8D57u * c.z;
-    U4 n;
-    n.x = hi1 ^ c.y ^ k0;
-    n.y = lo1;
-    n.z = hi0 ^ c.w ^ k1;
-    n.w = lo0;
-    c = n;
-    k0 += 0x9E3779B9u;
-    k1 += 0xBB67AE85u;
-  }
-  return c;
-}
-
 __device__ __forceinline__ float word_to_uniform(uint32_t w) {
   // ((w >> 9) + 1/2) * 2^-23: an odd multiple of 2^-24, exact in fp32, inside (0, 1)
   return ((float)(w >> 9) + 0.5f) * 1.1920928955078125e-07f;

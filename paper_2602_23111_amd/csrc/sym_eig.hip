@@ -16,6 +16,7 @@
 #include <type_traits>
 
 #include "frag_utils.h"
+#include "philox.h"
 
 namespace {
 
@@ -434,13 +435,6 @@ struct IvLds {  // [row, counted from the end][lane]: lanes 0 - 7 from the front
   double tau[TD_MAX], vv[TD_MAX];
   double f[IV_V];
 };
-__device__ __forceinline__ double iv_start(unsigned i, unsigned t) {  // in (-1, 1), another one for every element
-  unsigned h = i * 0x9E3779B9u + t * 0x85EBCA6Bu + 0x165667B1u;
-  h = (h ^ h >> 15) * 0x2C1B3C6Du;
-  h = (h ^ h >> 12) * 0x297A2D39u;
-  h ^= h >> 15;
-  return ((double)h + 0.5) * 0x1p-31 - 1.0;
-}
 __global__ __launch_bounds__(64 * IV_V) void tridiag_vectors_kernel(TriOut in, const double* __restrict__ lam, int n, int k, float* Z,
                                                                     int* flag) {
   extern __shared__ __align__(16) unsigned char iv_smem[];
@@ -455,9 +449,17 @@ __global__ __launch_bounds__(64 * IV_V) void tridiag_vectors_kernel(TriOut in, c
       s.vv[i] = i > 0 && i < n ? in.vv[i] : 0.0;
     }
   }
-  for (int i = tid; i < IV_H * 2 * IV_V; i += 64 * IV_V) {
-    const int half = i / IV_V % 2, r = i / (2 * IV_V), g = half ? 2 * h - 1 - r : r;
-    s.x[r][i % (2 * IV_V)] = r < h && g < n ? iv_start(g, blockIdx.x * IV_V + i % IV_V) : 0.0;
+  {  // start vectors, in (-1, 1): four rows of a half from one counter
+    constexpr int RW = 64 * IV_V / (2 * IV_V);  // rows that the workgroup fills at a time
+    static_assert(IV_H == 4 * RW, "one word per row");
+    const int half = tid / IV_V % 2, r0 = tid / (2 * IV_V);
+    const U4 u = philox4x32_10({(uint32_t)(half * RW + r0), blockIdx.x * IV_V + tid % IV_V, 3u, 0u}, 0u, 0u);  // (streams 0 - 2 are the fit's draws)
+    const uint32_t word[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = r0 + q * RW, g = half ? 2 * h - 1 - r : r;
+      s.x[r][tid % (2 * IV_V)] = r < h && g < n ? fma((double)word[q], 0x1p-31, 0x1p-32 - 1.0) : 0.0;
+    }
   }
   __syncthreads();
   if (tid < 2 * IV_V) {
