@@ -44,10 +44,9 @@ __global__ __launch_bounds__(64 * CT_W) void compress_tile_kernel(CompressTileAr
   const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
-  // rows past N repeat the last one (a tile may lie in the padding of packed C altogether); they are not stored
-  const int mb = min(m0, a.N - 1);
-  const char* const xbase = reinterpret_cast<const char*>(a.X + (int64_t)mb * a.ldx);
-  const uint32_t xrow = (uint32_t)(min(m0 + li, a.N - 1) - mb) * (uint32_t)a.ldx * 2u, xoff = xrow + lh * 32u;
+  // rows past N repeat the last one; they are not stored
+  const char* const xbase = reinterpret_cast<const char*>(a.X + (int64_t)m0 * a.ldx);
+  const uint32_t xrow = (uint32_t)min(li, a.N - 1 - m0) * (uint32_t)a.ldx * 2u, xoff = xrow + lh * 32u;
   const int64_t brow = (int64_t)a.ncb * 1024;  // bytes per k-block of fragments
   const uint32_t poff = (uint32_t)lh * (uint32_t)brow + (uint32_t)(cb0 * 64 + li) * 16u;
   const char* const pbase = reinterpret_cast<const char*>(a.Pfrag);
@@ -114,6 +113,13 @@ __global__ __launch_bounds__(64 * CT_W) void compress_tile_kernel(CompressTileAr
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       red[((wave * RN + j) * 4 + q) * 64 + lane] = f32x4_t{acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]};
+  if (a.packed && tm == a.tiles_m - 1) {  // the padding of packed C behind the last row tile: whole 128-token tiles, zeros
+    const int tb0 = m0 / 16 + 2, n_pad = (a.N + 127) / 128 * 8 - tb0;
+    for (int i = wave; i < n_pad * RN; i += CT_W) {
+      const int cb = cb0 + i % RN;
+      if (cb < a.ccb) stream_store(reinterpret_cast<u32x4*>(a.C) + ((int64_t)(tb0 + i / RN) * a.ccb + cb) * 64 + lane, u32x4{0u, 0u, 0u, 0u});
+    }
+  }
   __syncthreads();
   // a wave finishes whole 16-token blocks of a column block (two quads), or single quads where there are fewer blocks than waves
   constexpr int Q = RN >= 4 ? 2 : 1, UNITS = RN * 4 / Q;
@@ -177,7 +183,7 @@ int launch_compress_tile(prac_ctx* ctx, CompressTile tile, const bf16_t* X, int6
   CompressTileArgs a;
   a.X = X; a.ldx = ldx; a.N = N; a.d = d; a.Pfrag = Pfrag; a.ncb = ncb; a.c = c; a.C = C; a.ldc = ldc;
   a.ccb = (c + 31) / 32; a.packed = packed ? 1 : 0;
-  a.tiles_m = (int)(((packed ? round_up64(N, 128) : (int64_t)N) + 31) / 32);  // packed C is padded to whole 128-token tiles, which are written
+  a.tiles_m = (int)(((int64_t)N + 31) / 32);  // as compress_tile counts them
   auto launch = [&](auto rnc, auto dc) -> int {
     constexpr int RN = decltype(rnc)::value;
     constexpr auto kern = compress_tile_kernel<RN, decltype(dc)::value>;

@@ -1000,6 +1000,30 @@ def test_compress_of_few_rows_at_tile_edges(ctx, N, d, c):
     assert not blocks[(N + 15) // 16:].any()
 
 
+@pytest.mark.parametrize("N,d,c", [(2720, 4096, 384), (2720, 4096, 192), (2720, 4096, 96)])
+def test_packed_compress_of_few_rows_takes_one_round(ctx, N, d, c):
+    """85 row tiles, 255 workgroups of 32 x 128, 32 x 64 and 32 x 32 elements: the padding of packed C to 128 tokens adds none, so that the call
+    costs what a batch of whole 128-token tiles does (with row tiles in the padding, a second round: 1.5 to 1.8 times that)."""
+    from paper_2602_23111_amd.prac import C_PACKED
+    P = torch.randn((d, c), device=DEV)
+    lp = ctx.pack_basis(P)
+
+    def us(n):
+        X = torch.randn((n, d), device=DEV).to(torch.bfloat16)
+        out = torch.empty(ctx.compressed_bytes(n, c) // 2, dtype=torch.bfloat16, device=DEV)
+        best = float("inf")
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(40):
+                ctx.compress(X, P, P_lp=lp, out=out, layout=C_PACKED)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+    assert us(N) < 1.25 * us(N // 128 * 128)
+
+
 @pytest.mark.parametrize("K", [1, 8, 63, 64, 65, 255, 256, 263, 320, 511, 513, 584, 1100])
 @pytest.mark.parametrize("M,n", [(33, 31), (2050, 90), (4090, 97), (3001, 201), (4090, 250), (8190, 250)])
 def test_f32_products_by_chunks_of_k(ctx, M, n, K):
