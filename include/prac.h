@@ -154,8 +154,9 @@ int64_t prac_debug_fit_slab_margin(const prac_call_shape* shape /* [host] */);
 int prac_debug_gram_rows(const void* X, int dt, int64_t N, int64_t d, int64_t ldx, int64_t row_stride);
 
 /* Test hook [host]: the tile (rows * 1000 + columns) that a workgroup of the fp32 product kernel takes for an M x N product over
- * K in `splits` ranges on 256 compute units, by the cost rule (a launch may put 32 x 32 tiles in place of 32 x 64 or 64 x 64 ones). */
-int prac_debug_f32_tile(int M, int N, int64_t K, int splits);
+ * K in `splits` ranges on 256 compute units; a_k_fast: 1 if k is the contiguous index of the left operand (X P), 0 if not (C^T dY).
+ * 1000000 more for the form of the 32 x 64 tile that a single round of workgroups takes. */
+int prac_debug_f32_tile(int M, int N, int64_t K, int splits, int a_k_fast);
 
 /* ---- per-kernel timing hook (for benchmarks) ---------------------------- */
 /* While a kind other than PRAC_KERNEL_NONE is selected, every launch of that

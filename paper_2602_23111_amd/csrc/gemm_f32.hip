@@ -429,29 +429,13 @@ void launch_gemm_f32_ops(prac_ctx* ctx, F32Args& a) {
     const size_t smem = split_k > 1 ? (size_t)split_k * tm * tn * sizeof(float) : 0;  // at most 64 KB
     PRAC_LAUNCH(ctx, kern, dim3((unsigned)((int64_t)((a.M + tm - 1) / tm) * a.tiles_n), 1, a.splits), dim3(threads), smem, a);
   };
-  // 32 x 32 tiles in place of 32 x 64 ones (same bits) or 64 x 64 ones.  A workgroup's waves share four SIMDs however many compute units idle, so
-  // what counts is rounds of one workgroup per compute unit: 7 us of one per 1000 k instead of 11 (64 x 64: 20).  If A's k runs along memory,
-  // more workgroups per compute unit wait for L1 (a load touches 32 lines): only without a round more.
-  // us with 32 x 64 / 32 x 32: X P of 2048 x 512 -> 64, 128 small tiles, 8.7 / 5.5; 1500 x 1000 -> 100, 188, 13.7 / 10.1; 1024 x 2048 -> 256, 256, 24.4 / 15.8;
-  // 8192 x 1024 -> 32, 256, 16.1 / 11.4; 5000 x 700 -> 90, 471, 17.8 / 14.9; a round more: 4096 x 1024 -> 128, 512, 14.9 / 17.4; 3001 x 1501 -> 201, 658,
-  // 34.0 / 43.8.  C^T dY of 700 x 40 and 300 in two ranges, 40, 6.8 / 4.9; 2048 x 64 and 1376 in eight, 688, 11.4 / 9.7, in five, 430, 8.4 / 9.2; 1500 x 100
-  // and 1000 in five, 640, 11.2 / 10.6; 8192 x 64 and 512 in 32, 1024, 11.9 / 11.6; 3001 x 201 and 1501 in five, 1645, 31.8 / 36.3.  Sixteen waves, or eight
-  // chunks in flight, are 0.5 to 2 us behind.
-  const F32Tile tile = f32_tile(ctx->n_cu, a.M, a.N, a.K, a.splits);
-  auto rounds = [&](int tn) { return ((int64_t)((a.M + 31) / 32) * ((a.N + tn - 1) / tn) * a.splits + ctx->n_cu - 1) / ctx->n_cu; };
-  const bool one_more = !AKF && tile == F32Tile::T32x64 && 7 * rounds(32) < 11 * rounds(64);
-  if ((tile == F32Tile::T32x64 || tile == F32Tile::T64x64) && (rounds(32) == rounds(64) || one_more)) {
-    launch(gemm_f32_kernel<AKF, BKF, 1, 1, 1, 1, 8, Turn::SECOND_BODY>, 32, 32, 512, 8);
-    return;
-  }
-  switch (tile) {
+  switch (f32_tile(ctx->n_cu, a.M, a.N, a.K, a.splits, AKF)) {
     case F32Tile::T128x128: launch(gemm_f32_kernel<AKF, BKF, 2, 2, 2, 2, 1, Turn::ALL>, 128, 128, 256); break;
     case F32Tile::T128x64: launch(gemm_f32_kernel<AKF, BKF, 1, 2, 4, 1, 1, Turn::ALL>, 128, 64, 256); break;
     case F32Tile::T64x64: launch(gemm_f32_kernel<AKF, BKF, 2, 2, 1, 1, 4, Turn::TEST>, 64, 64, 256, 4); break;
-    case F32Tile::T32x64:
-      if (AKF && rounds(64) == 1) launch(gemm_f32_kernel<AKF, BKF, 1, 2, 1, 1, 8, AKF ? Turn::TEST : Turn::ALL>, 32, 64, 512, 8);
-      else launch(gemm_f32_kernel<AKF, BKF, 1, 2, 1, 1, 8, Turn::ALL>, 32, 64, 512, 8);
-      break;
+    case F32Tile::T32x64_ONE_ROUND: launch(gemm_f32_kernel<AKF, BKF, 1, 2, 1, 1, 8, AKF ? Turn::TEST : Turn::ALL>, 32, 64, 512, 8); break;  // (AKF only)
+    case F32Tile::T32x64: launch(gemm_f32_kernel<AKF, BKF, 1, 2, 1, 1, 8, Turn::ALL>, 32, 64, 512, 8); break;
+    case F32Tile::T32x32: launch(gemm_f32_kernel<AKF, BKF, 1, 1, 1, 1, 8, Turn::SECOND_BODY>, 32, 32, 512, 8); break;
   }
 }
 
@@ -463,7 +447,7 @@ void launch_gemm_f32_ops(prac_ctx* ctx, F32Args& a) {
 // or the exchange of the partial tiles where k is split.  Measured at the ends of the range: 2048 x 64
 // over 512 runs 9 us with 32 x 64 tiles and k split over eight waves against 17 - 23 us with 64 x 64 tiles through
 // LDS; 8192 x 256 over 2048 takes 84 us (102 TFLOP/s) with 64 x 64 tiles against 143 us.
-F32Tile f32_tile(int n_cu, int M, int N, int64_t K, int splits) {
+F32Tile f32_tile(int n_cu, int M, int N, int64_t K, int splits, bool a_k_fast) {
   const int64_t k = std::min(K, f32_k_per_split(K, splits));
   auto cost = [&](int tm, int tn, int rm, int rn, int waves, int sk) {
     const int64_t tiles = (int64_t)((M + tm - 1) / tm) * ((N + tn - 1) / tn) * splits;
@@ -476,7 +460,21 @@ F32Tile f32_tile(int n_cu, int M, int N, int64_t K, int splits) {
   const double big = cost(128, 128, 2, 2, 4, 1), mid = cost(64, 64, 2, 2, 4, 4), small = cost(32, 64, 1, 2, 8, 8),
                flat = cost(128, 64, 1, 2, 4, 1);
   const double best = std::min({big, mid, small, flat});
-  return big == best ? F32Tile::T128x128 : (flat == best ? F32Tile::T128x64 : (mid == best ? F32Tile::T64x64 : F32Tile::T32x64));
+  if (big == best) return F32Tile::T128x128;
+  if (flat == best) return F32Tile::T128x64;
+  // 32 x 32 tiles in place of 32 x 64 ones (same bits) or 64 x 64 ones.  A workgroup's waves share four SIMDs however many compute units idle, so
+  // what counts is rounds of one workgroup per compute unit: 7 us of one per 1000 k instead of 11 (64 x 64: 20).  If A's k runs along memory,
+  // more workgroups per compute unit wait for L1 (a load touches 32 lines): only without a round more.
+  // us with 32 x 64 / 32 x 32: X P of 2048 x 512 -> 64, 128 small tiles, 8.7 / 5.5; 1500 x 1000 -> 100, 188, 13.7 / 10.1; 1024 x 2048 -> 256, 256, 24.4 / 15.8;
+  // 8192 x 1024 -> 32, 256, 16.1 / 11.4; 5000 x 700 -> 90, 471, 17.8 / 14.9; a round more: 4096 x 1024 -> 128, 512, 14.9 / 17.4; 3001 x 1501 -> 201, 658,
+  // 34.0 / 43.8.  C^T dY of 700 x 40 and 300 in two ranges, 40, 6.8 / 4.9; 2048 x 64 and 1376 in eight, 688, 11.4 / 9.7, in five, 430, 8.4 / 9.2; 1500 x 100
+  // and 1000 in five, 640, 11.2 / 10.6; 8192 x 64 and 512 in 32, 1024, 11.9 / 11.6; 3001 x 201 and 1501 in five, 1645, 31.8 / 36.3.  Sixteen waves, or eight
+  // chunks in flight, are 0.5 to 2 us behind.
+  auto rounds = [&](int tn) { return ((int64_t)((M + 31) / 32) * ((N + tn - 1) / tn) * splits + n_cu - 1) / n_cu; };
+  const bool one_more = !a_k_fast && mid != best && 7 * rounds(32) < 11 * rounds(64);
+  if (rounds(32) == rounds(64) || one_more) return F32Tile::T32x32;
+  if (mid == best) return F32Tile::T64x64;
+  return a_k_fast && rounds(64) == 1 ? F32Tile::T32x64_ONE_ROUND : F32Tile::T32x64;
 }
 
 bool gemm_f32_takes(const GemmGenArgs& g) {

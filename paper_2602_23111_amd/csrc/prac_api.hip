@@ -1345,9 +1345,9 @@ int prac_debug_gram_rows(const void* X, int dt, int64_t N, int64_t d, int64_t ld
   return (int)gram_rows(X, (prac_dtype)dt, (N + row_stride - 1) / row_stride, d, ldx, row_stride);
 }
 
-int prac_debug_f32_tile(int M, int N, int64_t K, int splits) {
-  if (M < 2 || N < 2 || K < 1 || splits < 1) return -1;
-  return (int)f32_tile(256, M, N, K, splits);
+int prac_debug_f32_tile(int M, int N, int64_t K, int splits, int a_k_fast) {
+  if (M < 2 || N < 2 || K < 1 || splits < 1 || a_k_fast < 0 || a_k_fast > 1) return -1;
+  return (int)f32_tile(256, M, N, K, splits, a_k_fast != 0);
 }
 
 int64_t prac_debug_fit_slab_margin(const prac_call_shape* sh) {

@@ -119,8 +119,10 @@ int launch_gemm_generic(prac_ctx* ctx, const GemmGenArgs& a);
 // Products launch_gemm_generic hands to gemm_f32.hip; with splits > 1 that leaves the partial sums in a.slabs.
 bool gemm_f32_takes(const GemmGenArgs& a);
 int launch_gemm_f32(prac_ctx* ctx, const GemmGenArgs& a, int splits);
-enum class F32Tile { T128x128 = 128128, T128x64 = 128064, T64x64 = 64064, T32x64 = 32064 };
-F32Tile f32_tile(int n_cu, int M, int N, int64_t K, int splits);  // tile of a workgroup for an M x N product over K
+// T32x64_ONE_ROUND: 32 x 64 in the form for a single round of workgroups
+enum class F32Tile { T128x128 = 128128, T128x64 = 128064, T64x64 = 64064, T32x64 = 32064, T32x64_ONE_ROUND = 1032064, T32x32 = 32032 };
+// tile of a workgroup for an M x N product over K in `splits` ranges; a_k_fast: A's k runs along memory
+F32Tile f32_tile(int n_cu, int M, int N, int64_t K, int splits, bool a_k_fast);
 // dW (d x m, fp32 or bf16) = P (sum of the slabs [splits][c][m], rows >= k_lo times scale_hi) (+ beta dW), all in fp32;
 // the slabs may be overwritten
 int launch_f32_sum_pt(prac_ctx* ctx, const float* P, int64_t ldp, float* slabs, int splits, int c, int k_lo,

@@ -109,7 +109,7 @@ def load_library() -> C.CDLL:
         "prac_reserve_workspace": (i32, [vp, C.c_size_t]),
         "prac_debug_fit_slab_margin": (i64, [C.POINTER(CallShape)]),
         "prac_debug_gram_rows": (i32, [vp, i32, i64, i64, i64, i64]),
-        "prac_debug_f32_tile": (i32, [i32, i32, i64, i32]),
+        "prac_debug_f32_tile": (i32, [i32, i32, i64, i32, i32]),
         "prac_weight_grad_shared": (i32, [vp, vp, i32, i64, i64, i32, i32, C.POINTER(vp), C.POINTER(i64),
                                           C.POINTER(i64), vp, vp, i64, i64, i32, i32, f32, C.POINTER(vp), i32,
                                           C.POINTER(i64), f32]),

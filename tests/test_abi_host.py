@@ -305,7 +305,7 @@ def test_fp32_cases_reach_every_tile(lib):
     not take one out of the tests."""
     from test_gpu_parity import F32_CASES, GRAM_CASES
 
-    tile = lambda M, N, K: lib.prac_debug_f32_tile(M, N, K, 1)
-    assert {tile(N, m, d) for N, d, m, _, _ in F32_CASES} == {128128, 128064, 64064, 32064}             # Y, either layout of W
-    assert 128128 in {tile(d, d, N) for dt, N, d, _, stride in GRAM_CASES if dt == "f32" and stride == 1}
-    assert tile(1, 8, 8) == -1 and lib.prac_debug_f32_tile(8, 8, 8, 0) == -1
+    tile = lambda M, N, K, a_k_fast=1: lib.prac_debug_f32_tile(M, N, K, 1, a_k_fast)
+    assert {tile(N, m, d) for N, d, m, _, _ in F32_CASES} == {128128, 128064, 64064, 32064, 1032064, 32032}  # Y, either layout of W
+    assert 128128 in {tile(d, d, N, 0) for dt, N, d, _, stride in GRAM_CASES if dt == "f32" and stride == 1}
+    assert tile(1, 8, 8) == -1 and lib.prac_debug_f32_tile(8, 8, 8, 0, 1) == -1 and tile(8, 8, 8, 2) == -1

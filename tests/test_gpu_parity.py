@@ -727,12 +727,13 @@ F32_CASES = [
     (2, 2, 2, 1, 1),            # the smallest the matrix-core kernel takes, less than one 8-k chunk
     (33, 9, 65, 3, 2),          # one row / column more than a 32-wide block, 64-wide tile; one k more than a chunk
     (65, 71, 63, 17, 16),       # odd widths (a pair of columns that starts early), seven k in the tail
-    (129, 72, 127, 30, 33),     # more chunks than waves that split them, by one
+    (129, 72, 127, 30, 33),     # more chunks than waves that split them, by one (32 x 32 tiles, as for most of these products)
+    (4090, 1100, 97, 40, 33),   # Y: one round of 32 x 64 tiles (two of 32 x 32)
     (2049, 130, 193, 40, 25),   # token ranges of C^T dY with a ragged last one
     (4097, 24, 1025, 8, 8),     # 64 x 64 tiles of Y, more than compute units
     (2049, 9, 65, 3, 2),        # Y: 128 x 64, a row and a column past whole tiles, one k past a chunk
     (2045, 133, 2045, 30, 33),  # Y: 128 x 128, partial last tiles, five k past whole chunks
-    (700, 1100, 1901, 40, 33),  # dW from 64 columns a workgroup, partial last tiles (all others above: 32 columns)
+    (700, 1100, 1901, 40, 33),  # Y: 32 x 64 in three rounds; dW from 64 columns a workgroup, partial last tiles (all others above: 32 columns)
     (700, 1100, 1000, 40, 33),  # the same, fewer workgroups than compute units
 ]
 
@@ -977,10 +978,12 @@ def test_gram_matches_oracle(ctx, dt, N, d, ldx, stride):
 
 
 @pytest.mark.parametrize("N,d,c", [(1, 8, 1), (31, 40, 32), (33, 31, 31), (160, 264, 33), (8192, 33, 32), (8193, 32, 32), (8192, 65, 64),
-                                   (8193, 95, 64), (4096, 300, 225), (8192, 520, 128), (8193, 257, 128), (200, 1288, 1024)])
+                                   (8193, 95, 64), (4096, 300, 225), (8192, 520, 128), (8193, 257, 128), (200, 1288, 1024),
+                                   (4090, 1000, 128), (4096, 1320, 128), (2048, 2088, 225),                    # 32 x 64: 3 to 9 pieces a wave, ring of 4
+                                   (8190, 744, 128), (8190, 1000, 128), (4096, 1320, 256), (4090, 1832, 256)])  # 32 x 128: 2 to 8 pieces, ring of 3
 def test_compress_of_few_rows_at_tile_edges(ctx, N, d, c):
     """Both sides of the lines between the tiles (32 x 32, 64, 128 columns, then the 128-row kernel), pieces of k that are
-    partial, missing for some waves or more than the ring holds; NaN behind the rows' last column.  C is the fp64 product with the bf16
+    partial, missing for some waves, and in every tile fewer, as many and more than the ring holds, with a remainder; NaN behind the rows' last column.  C is the fp64 product with the bf16
     basis rounded once (half a unit of its eight bits, 2^-8 of the element at most), plus fp32 sums (sqrt(d) 2^-24 of the row's norm, below 2^-18 here)."""
     from paper_2602_23111_amd.prac import C_PACKED
     g = torch.Generator(device=DEV)
