@@ -1191,10 +1191,10 @@ def test_fit_basis_ritz_block_widths(ctx, b):
     assert np.abs(np.abs(np.sum(si.as_f64(P)[:, :k] * Q1, axis=0)) - 1.0).max() < 5e-7
 
 
-@pytest.mark.parametrize("b", [64, 97, 160, 512])
+@pytest.mark.parametrize("b", [64, 97, 160, 257, 305, 512])
 def test_fit_basis_ritz_vectors_come_out_diagonal_and_ordered(ctx, b):
-    # the eigen-iteration where a sweep holds launches of both kinds (all pairs; pairs across two blocks), on a spectrum without
-    # gaps: Q1^T G Q1 must be diagonal with descending entries.  Off-diagonal cosines: the rotation's 1e-10, the basis' fp32
+    # the reduction to tridiagonal form (up to 256), and the rotations, where a sweep holds launches of both kinds (all pairs; pairs across
+    # two blocks), an odd number of blocks and a partial last one, on a spectrum without gaps: Q1^T G Q1 must be diagonal with descending entries.  Off-diagonal cosines: the rotation's 1e-10, the basis' fp32
     # rounding 2^-24 times the ratio of the extreme Ritz values' roots (here below 9), some roundings: below 1e-5
     N, d = 2048, 640
     k = b // 2
@@ -1280,10 +1280,11 @@ def test_fit_basis_of_low_rank_batches(ctx, dt, rank, warm):
                 assert lost < (2e-5 if dt == "f32" else 1e-2) or k < rank, (d, seed, k, oversample)
 
 
-@pytest.mark.parametrize("b,spectrum,outliers", [(48, "power", 8), (80, "power", 0), (80, "geometric", 0), (320, "geometric", 0)])
+@pytest.mark.parametrize("b,spectrum,outliers", [(48, "power", 8), (80, "power", 0), (80, "geometric", 0), (272, "power", 8), (320, "power", 0),
+                                                 (320, "geometric", 0)])
 def test_fit_basis_settles_on_steep_spectra(ctx, b, spectrum, outliers):
-    """One power iteration on singular values ~ i^-2.5 (some channels scaled up) or 0.8^i: the eigen-iteration needs more than twelve
-    sweeps with launches of both kinds, which is no failure.  Q1^T G Q1 diagonal to the Gram matrix' tolerance, 2e-5 lambda_1, and the
+    """One power iteration on singular values ~ i^-2.5 (some channels scaled up) or 0.8^i: above 256 columns the rotations need more than
+    twelve sweeps with launches of both kinds, which is no failure.  Q1^T G Q1 diagonal to the Gram matrix' tolerance, 2e-5 lambda_1, and the
     fp32 rounding of the basis (below 1e-6 lambda_1 each side)."""
     N, d, k = 2048, 512, b // 2
     i = np.arange(1, d + 1.0)
