@@ -163,8 +163,8 @@ constexpr int CH_TB = 4;   // trailing tiles a wave has in flight
 constexpr int CH_MAX = 1024;
 // What is added to a diagonal entry: a pivot's rounding is a few 1e-16 of its own column's square, so a share of that keeps it positive, and
 // a short column (a direction that the batch has only as rounding noise) comes out as long as the others.  A share of the largest entry leaves
-// such columns short by 1e9 and more after three passes, past what the rest of the fit mends (rank 1 to 5, fp32, 24 to 100 columns asked
-// for: half of the fits refused, now none).  Blocks wider than 256 columns keep that share: the rotations that follow there do not wait for
+// such columns short by 1e9 and more after three passes, past what the rest of the fit mends (fp32 batches of rank 1 to 5, 8 to 100
+// columns asked for: 170 of 288 fits refused, now none).  Blocks wider than 256 columns keep that share: the rotations that follow there do not wait for
 // columns below 1e-13 to settle, and full-length noise does not settle in their sixteen sweeps.  `least`: a column of zeros stays one.
 struct CholShift {
   double rel, least;
@@ -656,16 +656,16 @@ __device__ __forceinline__ double row_shift_f64(double x, double edge) {
 // 8 waves: 0 - 3 rotate the Gram matrix in LDS (a step reads one buffer and writes the other: one barrier), 4 - 7 the
 // accumulated rotation in registers.  What bounds it is the issue of a step's instructions (two waves per SIMD) and one round trip
 // through LDS, so no address is computed in it, and a row of 16 lanes passes its rotations on by DPP.
-// At b = 256: 21 us per launch with all pairs, 16 us across the blocks, 7 us without a rotation (29 us before, with every address and
-// every thread's rotations computed in the step); 1.7 ms for the seven sweeps of the first step's fit, 2.7 before.
+// At b = 320: 29 us per launch with all pairs, 25 us across the blocks, 12 us where no pair needs a rotation, 3.4 ms for a cold fit's seven
+// sweeps; at b = 512 31, 27, 12 us and 6.5 ms.  (With every address and every thread's rotations computed in the step 29 us instead of 21 at b = 256.)
 constexpr int JB_NB = 16, JB_M = 2 * JB_NB;   // columns per block and per workgroup
 constexpr int JB_CW = 256, JB_CS = JB_CW + 4; // elements of each column in LDS at a time, their pitch
 constexpr int JB_GS = JB_M + 1;               // pitch of the Gram matrices and of J
 // Every fifth launch of a sweep rotates all pairs of its 32 columns, the others those across the two blocks: half the inner steps.
-// (Simulated on three spectra of the cases at b = 256, launches weighted by their times: every launch full 1.67 - 1.81 ms in six to seven
-// sweeps, every third 1.38 - 1.52, every fifth 1.32 - 1.47, the first of a sweep only 1.61 in eight.)  Steep spectra with few power
-// iterations take up to four sweeps more that way (singular values ~ i^-2.5, some channels 100 times the others, one iteration, b = 80: 12
-// with every launch full, 14 to 16; with all pairs from the ninth sweep on 14), so the ninth sweep and later ones rotate all
+// (Chosen by a simulation of three spectra at b = 256, launches weighted by their times there: every launch full 1.67 - 1.81 ms in six to
+// seven sweeps, every third 1.38 - 1.52, every fifth 1.32 - 1.47, the first of a sweep only 1.61 in eight.)  Steep spectra with few power
+// iterations take up to four sweeps more that way (simulated at b = 80, singular values ~ i^-2.5, some channels 100 times the others, one
+// iteration: 12 with every launch full, 14 to 16; with all pairs from the ninth sweep on 14), so the ninth sweep and later ones rotate all
 // pairs and the limit lies four sweeps above the twelve that all-pair launches had.
 constexpr int JB_FULL = 5, JB_FULL_FROM = 8;
 constexpr int JB_SWEEPS = 16;  // before the iteration gives up

@@ -6,9 +6,11 @@
 // k order is free as long as both operands use the same: lane half h of block b holds k = 32 g + 16 h + 8 b .. + 7, which are the
 // neighbouring 16-byte halves of a lane's 32 bytes of X and half b of k-block 2 g + h of P.
 // The waves' sums meet in LDS at the end and are added in wave order.
-// What bounds it is the bytes out of L2, (32 RM + 32 RN) d 2 per tile (21 TB/s at 4096 x 2048 -> 256), behind that the start: 3 us.
-// us per launch, compress_ws_kernel / here: 1024 x 256 -> 32 4.8 / 3.7, 2048 x 768 -> 128 9.4 / 4.3, 4096 x 2048 -> 64 19.2 / 9.1, 4096 x 2048 -> 256
-// 18.4 / 11.6, 512 x 8192 -> 1024 59.7 / 28.8, 1018 x 5376 -> 836 40.9 / 26.3.
+// What bounds it, with X in the caches (the same X again), is the bytes out of L2, 64 (1 + RN) d per tile (21 TB/s at 4096 x 2048 -> 256); with an X
+// from memory (another one on each call, 640 MB of them) how much of it is requested at a time: 8192 x 8192 arrives at 2.4 to 3.6 TB/s.
+// us per launch, compress_ws_kernel / here, X from memory and in brackets from the caches: 1024 x 256 -> 32 5.3 / 4.2 (5.3 / 4.2), 2048 x 768 -> 128
+// 8.0 / 4.7 (9.1 / 4.5), 4096 x 2048 -> 64 18.9 / 11.3 (18.3 / 9.1), 4096 x 2048 -> 256 18.8 / 14.6 (18.2 / 10.7), 512 x 8192 -> 1024 59.7 / 32.2
+// (59.0 / 29.7), 1018 x 5376 -> 836 41.3 / 32.3 (40.9 / 26.8), 8192 x 1024 -> 32 11.9 / 9.7 (10.6 / 6.3), 8192 x 8192 -> 128 68.7 / 54.9 (68.0 / 38.5).
 #include <algorithm>
 #include <type_traits>
 
@@ -166,7 +168,7 @@ __global__ __launch_bounds__(64 * CT_W) void compress_tile_kernel(CompressTileAr
 }  // namespace
 
 // The smallest tile whose workgroups each have a compute unit to themselves: a second round of them costs more than the larger tiles
-// (4096 x 2048 -> 256: 32 x 32 27.2 us, 32 x 64 18.7, 32 x 128 11.6), and past one round of the largest one compress_ws_kernel, which reads P a
+// (X in the caches: 4096 x 2048 -> 256: 32 x 32 27.2 us, 32 x 64 18.7, 32 x 128 11.6), and past one round of the largest one compress_ws_kernel, which reads P a
 // quarter as often, is ahead (8192 x 2048 -> 128 in one round 15.9, compress_ws_kernel 20.0; 8192 x 2048 -> 256 in two 27.4, 19.7).  Tiles of 64 rows
 // never were the best (64 x 64 within 0.7 us of 32 x 128 at d = 768 and below, 4 us behind at 2048).
 CompressTile compress_tile(int n_cu, int N, int c) {

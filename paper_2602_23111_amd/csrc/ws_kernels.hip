@@ -1607,9 +1607,9 @@ int set_smem(prac_ctx* ctx, K kern, size_t bytes, bool& done) {
 // each, fit the ctx's block of 128 KiB per compute unit.  Whole call, one range against these (N, d, c):
 // step 7463, 8025 on any element, 35 233 / 132 us; fused forward 905, 6848, 63 with m = 2304 103 / 68; 532, 1344, 48 with m = 547
 // 27.3 / 17.4; a refit's product 4096, 4096, 256 34 / 23 alone.
-// Only for calls that work in the ctx's scratch anyway (`part`): a compress of aligned rows with a packed basis keeps nothing in the
-// ctx, so that calls on several streams, and replays of graphs beside them, may overlap; it stays one launch (with ranges, a step of
-// 1018, 5376, 836 took 87 us instead of 106, of 4812, 4800, 24 54 instead of 78).
+// Only for calls that work in the ctx's scratch anyway (`part`): rows on any element, the fused forward, a refit's
+// product.  A compress of aligned rows with a packed basis keeps nothing in the ctx, so that calls on several
+// streams, and replays of graphs beside them, may overlap; it stays one launch (of few rows compress_tile_kernel's).
 static void compress_ranges(int n_cu, int tiles, int nk, int fn, bool parts, int& splits, int& kt_per) {
   const double tile_us = (fn == 2 ? 3.4 : 2.2) * (parts ? WS_SPLIT : 1), part_us = 2.0 * tiles * fn * 65536.0 / 3e6;
   auto cost = [&](int s) { return tile_us * ((nk + s - 1) / s) + (s > 1 ? 5.0 + part_us * s : 0.0); };
@@ -1635,8 +1635,8 @@ int launch_compress_ws(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d
   a.C = C; a.ldc = ldc; a.ccb = (c + 31) / 32; a.packed = packed ? 1 : 0;
   a.tiles_m = (N + WS_BM - 1) / WS_BM;
   // with a forward output the wide (64-column) wave tile is used throughout; without one the narrow
-  // tile also serves launches whose wide tiles would leave half of the CUs idle (few token rows):
-  // twice the workgroups, each with half the multiplications, X reaching the second of a pair from L2
+  // tile also serves launches whose wide tiles would leave half of the CUs idle (few token rows that compress_tile does
+  // not take: past its largest tile, rows on any element, ranges of d): twice the workgroups, each with half the multiplications, X reaching the second of a pair from L2
   const int wide_groups = (a.ccb + 7) / 8;
   const int FN = (!Wfrag && (c <= 128 || (int64_t)a.tiles_m * wide_groups * 2 <= ctx->n_cu)) ? 1 : 2;
   // Pfrag == nullptr (only with a forward output): no C part, the launch is a plain Y = X W
