@@ -669,6 +669,40 @@ def test_reconstruct_matches_oracle(ctx, dt, N, d, k, r, ldc, ldxh):
     assert rel_fro(si.as_f64(out), orc.reconstruct(si.as_f64(Ct), P64, k, scale)) < TOL[dt]
 
 
+@pytest.mark.parametrize("N,d,c,ld,packed", [
+    (256, 2048, 256, 2048, True),     # whole strips on whole lines
+    (300, 1984, 256, 1984, True),     # 31 strips for eight waves, a ragged row tile
+    (128, 2048, 200, 2053, False),   # whole strips, rows on any element
+    (1000, 1163, 130, 1163, False),  # the last strip 11 columns wide
+    (129, 70, 17, 72, True),          # two strips, eight k-blocks
+    (64, 512, 128, 512, False),      # one strip per wave
+])
+def test_reconstruct_strips(ctx, N, d, c, ld, packed):
+    """Every element against the product of the same bf16 operands (fp32 sums of c products: c 2^-24 of the sum of their
+    magnitudes; one rounding, 2^-9), and nothing written beside the rows."""
+    from paper_2602_23111_amd.prac import C_PACKED, C_ROWMAJOR
+    layout = C_PACKED if packed else C_ROWMAJOR
+    k = c // 2
+    s = (d - k) / (c - k)
+    g = torch.Generator(device=DEV).manual_seed(N + d)
+    X = torch.randn((N, d), generator=g, device=DEV).bfloat16()
+    P = torch.randn((d, c), generator=g, device=DEV) * d ** -0.5
+    lp = ctx.pack_basis(P)
+    Xa = torch.zeros((N, (d + 7) // 8 * 8), dtype=torch.bfloat16, device=DEV)[:, :d].copy_(X)
+    rows = None if packed else torch.zeros((N, (c + 7) // 8 * 8), dtype=torch.bfloat16, device=DEV)[:, :c]
+    C = ctx.compress(Xa, P, P_lp=lp, out=rows, layout=layout)
+    Cr = ctx.unpack_compressed(C, N, c) if packed else C
+    buf = torch.full((N + 1, ld), 7.0, dtype=torch.bfloat16, device=DEV)
+    ctx.reconstruct(C, P, k, c - k, s, N=N, out=buf[:N, :d], layout=layout)
+    ctx.sync_status()
+    w = torch.ones(c, device=DEV)
+    w[k:] = s
+    Ps = (P * w).bfloat16().double()
+    ref, mag = Cr.double() @ Ps.t().contiguous(), Cr.double().abs() @ Ps.abs().t().contiguous()
+    assert ((buf[:N, :d].double() - ref).abs() <= 2.0 ** -8 * ref.abs() + c * 2.0 ** -24 * mag).all()
+    assert (buf[N:] == 7.0).all() and (buf[:, d:] == 7.0).all()
+
+
 def test_reconstruct_packed_equals_rowmajor(ctx):
     from paper_2602_23111_amd.prac import C_PACKED
     N, d, k, r = 515, 384, 48, 24
