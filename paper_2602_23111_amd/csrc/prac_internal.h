@@ -132,6 +132,9 @@ int launch_f32_sum_pt(prac_ctx* ctx, const float* P, int64_t ldp, float* slabs, 
 // out[i] = alpha * sum_s part[s*stride + i] + beta * out[i], i < n (fp32)
 int launch_reduce_slabs(prac_ctx* ctx, const float* part, int splits, int64_t stride, float* out,
                         int64_t n, float alpha, float beta);
+// out (n x n, ldo) = sum of the symmetric partial sums part[splits][n][n], of which only 64 x 64 blocks on and above the diagonal
+// are read; with one of them out may be part (ldo = n)
+int launch_reduce_symmetric(prac_ctx* ctx, const float* part, int splits, int n, float* out, int64_t ldo);
 // out (N x M fp32, ld = ldo) = transpose of sum_s part[s][j][n], j < M
 int launch_reduce_transpose_f32(prac_ctx* ctx, const float* part, int splits, int M, int N, float* out, int64_t ldo);
 int launch_philox(prac_ctx* ctx, uint64_t seed, uint32_t draw, uint32_t stream, void* out, int64_t n,
@@ -205,10 +208,15 @@ static inline int ctdy_tail_blocks(const CtdyTails& p, int t0, int t1) {
 // dY_h may start on any element, and a row owns nothing past its last column (then m[h] >= 8); otherwise they are 16-byte
 // aligned and own whole 16-byte chunks (the caller says which: where the rows are a sample of a matrix, their pitch does not).
 // tails with main > 0: unequal ranges instead (slabs, splits and sld are not looked at).
+// upper (one output, m = c, the same matrix as C and dY): the slabs hold only the tiles on and above the diagonal.
 #define PRAC_CTDY_MAX_OUT 4
 int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, const bf16_t* const* dY,
                    const int64_t* lddy, const int* m, float* const* slabs, int splits, bool any_element,
-                   int range_tokens = 0, const int* sld = nullptr, const CtdyTails* tails = nullptr);
+                   int range_tokens = 0, const int* sld = nullptr, const CtdyTails* tails = nullptr, bool upper = false);
+// tiles (256 rows x 128 columns) of a square matrix that hold an element on or above its diagonal
+static inline __host__ __device__ int ctdy_upper_tiles(int tiles_n, int row_groups) {
+  return row_groups * tiles_n - row_groups * (row_groups - 1);
+}
 // tokens of a range (whole 128-token tiles; the last ranges may be short or empty); launch_ctdy_ws takes another value for a
 // part of the ranges of a longer product
 inline int64_t ctdy_range_tokens(int64_t N, int splits) { return ((N + 127) / 128 + splits - 1) / splits * 128; }

@@ -876,6 +876,7 @@ struct CtdyWsArgs {
   int tok_per_split;   // multiple of 128
   int tiles_n;         // column tiles of 128 over all outputs
   int row_groups;      // groups of 8 column blocks (256 rows of T) over c
+  int upper;           // T is symmetric (C and dY hold the same matrix): only tiles that reach its diagonal or lie above it
   CtdyTails tails;     // TAILS
   int groups_per_xcd;  // MODE > 0: column tiles per XCD
   // ---- whole weight gradient in this launch (MODE > 0): the workgroups of one column tile sum their
@@ -1263,7 +1264,9 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
   int tn = 0, rg = 0, split = 0;
   int run_beg = 0, run_end = -1;  // helpers: units of the tails of all tiles
   if constexpr (MODE == 0) {
-    const int per_split = TAILS ? a.tails.t1 - a.tails.t0 : a.tiles_n * a.row_groups;
+    const int per_split = TAILS     ? a.tails.t1 - a.tails.t0
+                          : a.upper ? ctdy_upper_tiles(a.tiles_n, a.row_groups)
+                                    : a.tiles_n * a.row_groups;
     const int mains = per_split * (TAILS ? a.tails.main : a.splits);
     const int total = mains + (TAILS ? a.tails.helpers : 0);
     const int per_xcd = (total + 7) / 8;
@@ -1276,8 +1279,14 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
       run_beg = max(run_beg, a.tails.t0 * a.tails.tail);
     } else {
       const int t = (TAILS ? a.tails.t0 : 0) + logical % per_split;
-      tn = t % a.tiles_n;
-      rg = t / a.tiles_n;
+      if (!TAILS && a.upper) {
+        tn = t;
+        for (int left = a.tiles_n; tn >= left; left -= 2, ++rg) tn -= left;  // row group rg: column tiles 2 rg ..
+        tn += 2 * rg;
+      } else {
+        tn = t % a.tiles_n;
+        rg = t / a.tiles_n;
+      }
       split = logical / per_split;
     }
   } else {
@@ -1753,7 +1762,7 @@ bool ctdy_half(int c) { return c <= 128; }
 
 int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, const bf16_t* const* dY,
                    const int64_t* lddy, const int* m, float* const* slabs, int splits, bool any_element, int range_tokens,
-                   const int* sld, const CtdyTails* tails) {
+                   const int* sld, const CtdyTails* tails, bool upper) {
   if (n_out < 1 || n_out > PRAC_CTDY_MAX_OUT) return PRAC_EINVAL;
   for (int h = 0; h < n_out; ++h) {
     if (lddy[h] > PRAC_MAX_STREAM_PITCH) return PRAC_EINVAL;
@@ -1764,6 +1773,8 @@ int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, co
   fill_ctdy_args(a, Cpk, c, N, n_out, dY, lddy, m, slabs, splits, sld);
   if (range_tokens > 0) a.tok_per_split = range_tokens;
   const bool uneven = tails && tails->main > 0;
+  a.upper = upper ? 1 : 0;
+  if (upper && (uneven || n_out != 1 || m[0] != c)) return PRAC_EINVAL;
   if (uneven) {
     // every token of every tile belongs to one main range or to a tail, every tile of the launch has its blocks
     const int64_t tiles = (int64_t)a.tiles_n * a.row_groups;
@@ -1775,7 +1786,8 @@ int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, co
     a.tails = *tails;
   }
   const size_t smem = (size_t)CW_STAGES * CW_STAGE;
-  const int total = uneven ? (tails->t1 - tails->t0) * tails->main + tails->helpers : a.tiles_n * a.row_groups * splits;
+  const int total = uneven ? (tails->t1 - tails->t0) * tails->main + tails->helpers
+                           : (upper ? ctdy_upper_tiles(a.tiles_n, a.row_groups) : a.tiles_n * a.row_groups) * splits;
   static bool done_dev[PRAC_MAX_DEVICES][5] = {};
   bool* done = done_dev[ctx->device % PRAC_MAX_DEVICES];
   const dim3 grid(((total + 7) / 8) * 8), block(512);

@@ -1011,6 +1011,23 @@ def test_gram_matches_oracle(ctx, dt, N, d, ldx, stride):
     assert torch.equal(G, G.t()) or rel_fro(si.as_f64(G), si.as_f64(G).T) < 1e-6
 
 
+@pytest.mark.parametrize("N,d,ldg", [(2048, 256, 256), (2100, 257, 260), (2048, 384, 384), (3000, 385, 385), (2048, 640, 645),
+                                     (4096, 1031, 1031), (2048, 4161, 4161)])  # the last: a single token range, mirrored in place
+def test_gram_from_its_upper_tiles(ctx, N, d, ldg):
+    """Edges of the 256 x 128 tiles that reach the diagonal and of the 64 x 64 blocks of their sum, both triangles the same bits;
+    fp32 sums of N products (a few N^1/2 2^-24 of the column norms' product, below 2e-5)."""
+    g = torch.Generator(device=DEV).manual_seed(d)
+    X = torch.zeros((N, (d + 7) // 8 * 8), dtype=torch.bfloat16, device=DEV)[:, :d]
+    X.copy_(torch.randn((N, d), generator=g, device=DEV))
+    buf = torch.full((d + 1, ldg), 7.0, device=DEV)
+    ctx.gram(X, out=buf[:d, :d])
+    ctx.sync_status()
+    G, X64 = buf[:d, :d], X.double()
+    cn = X64.norm(dim=0)
+    assert ((G.double() - X64.t().contiguous() @ X64).abs() <= 2e-5 * cn[:, None] * cn[None, :]).all()
+    assert torch.equal(G, G.t()) and (buf[d:] == 7.0).all() and (buf[:, d:] == 7.0).all()
+
+
 @pytest.mark.parametrize("N,d,c", [(1, 8, 1), (31, 40, 32), (33, 31, 31), (160, 264, 33), (8192, 33, 32), (8193, 32, 32), (8192, 65, 64),
                                    (8193, 95, 64), (4096, 300, 225), (8192, 520, 128), (8193, 257, 128), (200, 1288, 1024),
                                    (4090, 1000, 128), (4096, 1320, 128), (2048, 2088, 225),                    # 32 x 64: 3 to 9 pieces a wave, ring of 4
