@@ -447,6 +447,23 @@ __global__ __launch_bounds__(1024) void chol_upper_kernel(double* W, int b, doub
   }
 }
 
+// eight numbers as three bf16 parts each
+__device__ __forceinline__ void split3(const float (&x)[8], u32x4 (&part)[3]) {
+  float r[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) r[e] = x[e];
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+      const uint32_t w = pack2_hw(r[e], r[e + 1]);
+      part[p][e / 2] = w;
+      r[e] -= __uint_as_float(w << 16);
+      r[e + 1] -= __uint_as_float(w & 0xFFFF0000u);
+    }
+  }
+}
+
 // dst (rows x n fp32, pitch ldd) = src * R^-1 (src pitch n; dst may be src: a workgroup reads its rows before it writes them)
 // for the upper-triangular R (row-major n x n fp64, its 16 x 16 diagonal blocks inverted),
 // in fp64 on the matrix cores.  A workgroup of eight waves solves 16 rows, as the transpose R^-T src^T: wave w holds the column
@@ -457,10 +474,11 @@ __global__ __launch_bounds__(1024) void chol_upper_kernel(double* W, int b, doub
 // column 4 b + a: a lane then holds four neighbouring columns of its row.
 // 18.5 us at 2048 x 256, 9 us at 2048 x 128 (42 / 16.5 us in fp32 on the vector units, columns of R staged through LDS); R's lines not
 // requested ahead 64 us.
+// PARTS (n <= 256): also the result as three bf16 parts for gram_times_block_kernel (its 16 rows are one k-block).
 constexpr int TR_ROWS = 16, TR_W = 8;
-template <int NT>
+template <int NT, bool PARTS>
 __global__ __launch_bounds__(64 * TR_W) void trsm_right_upper_kernel(const float* src, const double* __restrict__ R, float* dst,
-                                                                     int64_t ldd, int64_t rows, int n) {
+                                                                     int64_t ldd, int64_t rows, int n, u32x4* parts, int ncb) {
   __shared__ double s_x[2][256];
   const int lane = threadIdx.x & 63, fi = lane & 15, fk = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -542,6 +560,27 @@ __global__ __launch_bounds__(64 * TR_W) void trsm_right_upper_kernel(const float
     }
   });
   asm volatile("" : : "v"(touched));
+  if constexpr (PARTS) {
+    __shared__ float tile[TR_ROWS][260];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int c = 16 * (wave + TR_W * t) + 4 * fk + q;
+        tile[fi][c] = row < rows && c < n ? (float)z[t][q] : 0.f;
+      }
+    __syncthreads();
+    const int c = threadIdx.x & 255, h = threadIdx.x >> 8;
+    if (c < 32 * ncb) {
+      float x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = c < 128 * NT ? tile[8 * h + e][c] : 0.f;
+      u32x4 part[3];
+      split3(x, part);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) parts[(((int64_t)blockIdx.x * ncb + (c >> 5)) * 3 + p) * 64 + 32 * h + (c & 31)] = part[p];
+    }
+  }
   if (row < rows) {
     float* const drow = dst + row * ldd;
 #pragma unroll
@@ -884,6 +923,126 @@ __global__ __launch_bounds__(256) void copy_cols_kernel(const float* __restrict_
     dst[(i / cols) * ldd + i % cols] = src[(i / cols) * lds + i % cols];
 }
 
+// ------------------------------------------------------- G V
+// Y = G V for the iteration (G symmetric d x d, V d x b, both fp32), on the bf16 matrix instructions: every number as three bf16 parts
+// that add up to it exactly (8 significant bits each, rounded to nearest), and of the nine products the six down to
+// 2^-17 of the largest; the other three come to less than 2^-24 of a product.  The sums are fp32 as before, a sixteenth as many.
+// Parts lie in fragment order, a 32 x 16 piece of an operand as 3 x [64 lanes][8]: G as [row blocks][k-blocks], split once per fit, V as
+// [k-blocks][column blocks], written by the triangular solve that makes it.
+// A workgroup has 32 rows and 64 columns, its eight waves every eighth k-block; their sums meet in LDS, in wave order.  Bound by L2
+// (9 KB per twelve matrix instructions of a wave, 302 MB per launch at d = 2048, b = 256); a larger tile would leave compute units idle or
+// need ranges of k and their sum.  16.8 us there, where fp32 instructions took 27 and the sum of two ranges 5.  |Y - G V| against 64 bits: 0.4 to
+// 0.9 of theirs in six shapes of d 256 to 2048, b 2 to 256 (1.3e-7 of |Y| against 3.0e-7 at d = 2048, b = 256).
+constexpr int GV_W = 8, GV_D = 4;  // waves, k-blocks in flight
+static inline int gv_kblocks(int64_t d) { return (int)(round_up64(d, 16 * GV_W) / 16); }
+static inline size_t gv_g_bytes(int64_t d) { return (size_t)((d + 31) / 32) * gv_kblocks(d) * 3072; }
+static inline int gv_col_blocks(int b) { return (b + 63) / 64 * 2; }
+static inline size_t gv_v_bytes(int64_t d, int b) { return (size_t)gv_kblocks(d) * gv_col_blocks(b) * 3072; }
+
+// KF: line i, element k at src[i ld + k], pieces [line blocks][k-blocks]; otherwise at src[k ld + i], pieces [k-blocks][line blocks].
+// Zeros outside lines x K.
+template <bool KF>
+__global__ __launch_bounds__(256) void split_parts_kernel(const float* __restrict__ src, int64_t ld, int lines, int64_t K, int nlb,
+                                                          int nkb, u32x4* __restrict__ out) {
+  const int64_t piece = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (piece >= (int64_t)nlb * nkb) return;
+  const int lane = threadIdx.x & 63;
+  const int64_t lb = KF ? piece / nkb : piece % nlb, kb = KF ? piece % nkb : piece / nlb;
+  const int64_t line = 32 * lb + (lane & 31), k = 16 * kb + 8 * (lane >> 5);
+  float x[8];
+  if (line < lines && k + 8 <= K) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = KF ? src[line * ld + k + e] : src[(k + e) * ld + line];
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = line < lines && k + e < K ? (KF ? src[line * ld + k + e] : src[(k + e) * ld + line]) : 0.f;
+  }
+  u32x4 part[3];
+  split3(x, part);
+#pragma unroll
+  for (int p = 0; p < 3; ++p) out[(piece * 3 + p) * 64 + lane] = part[p];
+}
+
+__global__ __launch_bounds__(64 * GV_W, 2) void gram_times_block_kernel(const u32x4* __restrict__ Gf, const u32x4* __restrict__ Vf, int d,
+                                                                        int b, int nkb, int ncb, float* __restrict__ Y) {
+  extern __shared__ float gv_red[];  // [GV_W][32][64]
+  // the column tiles of a few row blocks sit next to each other on one XCD
+  const int tiles_n = ncb / 2, total = (d + 31) / 32 * tiles_n, per_xcd = (total + 7) / 8;
+  const int slot = blockIdx.x >> 3, logical = (blockIdx.x & 7) * per_xcd + slot;
+  if (slot >= per_xcd || logical >= total) return;
+  const int tm = logical / tiles_n, tn = logical % tiles_n;
+  const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const u32x4* const pg = Gf + (int64_t)tm * nkb * 192 + lane;
+  const u32x4* const pv = Vf + (int64_t)tn * 384 + lane;
+  const int64_t vrow = (int64_t)ncb * 192;
+  struct Step {
+    u32x4 g[3], v[2][3];
+  };
+  auto load = [&](Step& s, int kb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) s.g[p] = pg[(int64_t)kb * 192 + p * 64];
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int p = 0; p < 3; ++p) s.v[c][p] = pv[kb * vrow + (c * 3 + p) * 64];
+  };
+  // the products of the high parts and the other five, which are 2^-8 of them at most, have sums of their own: six roundings per
+  // k-block at the size of the sum would put Y further off than the fp32 instructions do
+  f32x16 acc[2], low[2];
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[c][v] = low[c][v] = 0.f;
+  auto mul = [&](const Step& s) __attribute__((always_inline)) {
+    constexpr int PG[5] = {2, 0, 1, 1, 0}, PV[5] = {0, 2, 1, 0, 1};
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+      acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(s.g[0]), as_frag(s.v[c][0]), acc[c], 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < 5; ++t)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        low[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(s.g[PG[t]]), as_frag(s.v[c][PV[t]]), low[c], 0, 0, 0);
+  };
+  const int n = nkb / GV_W;  // (a multiple)
+  Step st[GV_D];
+#pragma unroll
+  for (int u = 0; u < GV_D; ++u)
+    load(st[u], wave + GV_W * min(u, n - 1));
+  int t = 0;
+  for (; t + 2 * GV_D <= n; t += GV_D) {  // (no test per request here: behind one the compiler waits for all of them)
+#pragma unroll
+    for (int u = 0; u < GV_D; ++u) {
+      mul(st[u]);
+      load(st[u], wave + GV_W * (t + GV_D + u));
+      __builtin_amdgcn_sched_barrier(0);  // (requests stay where they are, or all of them end up behind the products)
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < GV_D; ++u) {
+    if (t + u < n) mul(st[u]);
+    if (t + GV_D + u < n) load(st[u], wave + GV_W * (t + GV_D + u));
+  }
+#pragma unroll
+  for (int u = 0; u < GV_D - 1; ++u)
+    if (t + GV_D + u < n) mul(st[u]);
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) gv_red[(wave * 32 + c * 16 + v) * 64 + lane] = acc[c][v] + low[c][v];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int r = wave * 4 + u, v = r & 15;
+    float x = 0.f;
+#pragma unroll
+    for (int w = 0; w < GV_W; ++w) x += gv_red[(w * 32 + r) * 64 + lane];
+    const int row = 32 * tm + 8 * (v / 4) + 4 * lh + v % 4, col = 64 * tn + 32 * (r >> 4) + li;
+    if (row < d && col < b) Y[(int64_t)row * b + col] = x;
+  }
+}
+
 // ------------------------------------------------------- Gram matrices of the panels
 // src^T src for a d x n fp32 block (pitch n) with fp64 sums on the matrix cores: the 64 x 64 tiles of the upper triangle (all that the
 // factorisation reads) times ranges of rows, as many as fill the chip; 32 x 32 per wave, 32 rows per step, the next step's
@@ -1029,12 +1188,12 @@ size_t pg_need(int n_cu, int64_t d, int n) { return n > 0 ? pg_splits(n_cu, d, n
 
 struct FitWs {
   size_t G, V, Y, W64, eig, Rinv, lam, Z, S, T, slabs, slab_bytes, gram, total;
+  size_t gv_g, gv_v;  // parts of G and of the iteration's block
   size_t trk_pf, trk_c, trk_slabs;  // tracking refit: V in fragment order, packed X V, slabs of (X V)^T X
   int trk_nkb, trk_ncb, trk_splits;
   int b;
   int kq;         // principal columns the iteration computes (see principal_rank); the other k - kq are drawn
   int splits_bb;  // split count of the b x b fp64 Gram products
-  int splits_gv;  // split count of G V
 };
 
 int block_width(int64_t d, int k, const prac_fit_opts& o) {
@@ -1088,22 +1247,17 @@ FitWs plan_fit(int64_t d, int k, int r, const prac_fit_opts& o, int n_cu, bool n
   w.T = p.take((size_t)(k > 0 ? k : 1) * (rf > 0 ? rf : 1) * 4);
   const int s = panel_splits(n_cu, d, bb);
   w.splits_bb = s;
-  // G V (d x b, fp32): split the sum over k until the tiles fill the chip
-  const int tiles_gv = (int)((d + 63) / 64) * ((b + 63) / 64);
-  int sg = need_g ? (n_cu + tiles_gv - 1) / tiles_gv : 1;
-  if (sg > d / 256) sg = (int)(d / 256);
-  if (sg < 1) sg = 1;
-  if (sg > 16) sg = 16;
-  w.splits_gv = sg;
-  // the slab block serves every split product of the fit: the bb x bb panel Gram matrices (fp64), G V
-  // (d x b, fp32) and Q1^T S (k x r, fp32; wider than a panel Gram when k > 2 r and Q1 is not refreshed)
-  const size_t slab_bb = (size_t)s * bb * bb * 8, slab_gv = sg > 1 ? (size_t)sg * d * b * 4 : 0;
+  // the slab block serves every split product of the fit: the bb x bb panel Gram matrices (fp64)
+  // and Q1^T S (k x r, fp32; wider than a panel Gram when k > 2 r and Q1 is not refreshed)
+  const size_t slab_bb = (size_t)s * bb * bb * 8;
   const size_t slab_kr = (size_t)s * k * rf * 4;  // also the completion's Q1^T S (kq x fill)
-  w.slab_bytes = std::max(slab_bb, std::max(slab_gv, slab_kr));
+  w.slab_bytes = std::max(slab_bb, slab_kr);
   for (int n : {b, b > 0 ? kq : 0, fill, r})  // the panel Gram matrices with fp64 sums
     w.slab_bytes = std::max(w.slab_bytes, pg_need(n_cu, d, n));
   w.slabs = p.take(w.slab_bytes);
   w.gram = p.take(gram_bytes);
+  w.gv_g = p.take(need_g ? gv_g_bytes(d) : 0);
+  w.gv_v = p.take(need_g ? gv_v_bytes(d, b) : 0);
   if (track) {
     w.trk_nkb = (int)(round_up64(d, 256) / 16);
     w.trk_ncb = (int)round_up64((k + 31) / 32, 8);
@@ -1178,8 +1332,19 @@ int panel_gram32(prac_ctx* ctx, const FitWs& w, const float* src, int64_t d, int
   return PRAC_OK;
 }
 
-// dst (pitch ldd; may be src) = src R^-1 with R^T R = src^T src (+ shift): one Cholesky-QR pass
-int cholqr_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int64_t ldd, int64_t d, int n, double shift, bool gram64) {
+// V (d x n, pitch n) as parts for G V
+int split_block(prac_ctx* ctx, const float* V, int64_t d, int n, u32x4* parts) {
+  const int nkb = gv_kblocks(d), ncb = gv_col_blocks(n);
+  hipLaunchKernelGGL(split_parts_kernel<false>, dim3((unsigned)(((int64_t)nkb * ncb + 3) / 4)), dim3(256), 0, ctx->stream, V, (int64_t)n, n,
+                     d, ncb, nkb, parts);
+  PRAC_HIP_TRY(ctx, hipGetLastError());
+  return PRAC_OK;
+}
+
+// dst (pitch ldd; may be src) = src R^-1 with R^T R = src^T src (+ shift): one Cholesky-QR pass.  parts: the result also as parts for G V
+// (their padding past d is there already)
+int cholqr_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int64_t ldd, int64_t d, int n, double shift, bool gram64,
+                u32x4* parts) {
   double* W64 = reinterpret_cast<double*>(ctx->ws + w.W64);
   int rc = gram64 ? panel_gram64(ctx, w, src, d, n, W64) : panel_gram32(ctx, w, src, d, n, W64, nullptr, 0.f);
   if (rc) return rc;
@@ -1192,12 +1357,18 @@ int cholqr_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int
     hipLaunchKernelGGL(chol_upper_kernel, dim3(1), dim3(1024),
                        (size_t)CH_NB * (round_up64(n, CH_NB) + 2) * sizeof(double), ctx->stream, W64, n, shift, ctx->d_flag);
   const dim3 tgrid((unsigned)((d + TR_ROWS - 1) / TR_ROWS)), tblock(64 * TR_W);
-  if (n <= 128) hipLaunchKernelGGL(trsm_right_upper_kernel<1>, tgrid, tblock, 0, ctx->stream, src, W64, dst, ldd, d, n);
-  else if (n <= 256) hipLaunchKernelGGL(trsm_right_upper_kernel<2>, tgrid, tblock, 0, ctx->stream, src, W64, dst, ldd, d, n);
-  else if (n <= 512) hipLaunchKernelGGL(trsm_right_upper_kernel<4>, tgrid, tblock, 0, ctx->stream, src, W64, dst, ldd, d, n);
-  else hipLaunchKernelGGL(trsm_right_upper_kernel<8>, tgrid, tblock, 0, ctx->stream, src, W64, dst, ldd, d, n);
+  const int ncb = gv_col_blocks(n);
+  auto solve = [&](auto kern, u32x4* p) {
+    hipLaunchKernelGGL(kern, tgrid, tblock, 0, ctx->stream, src, W64, dst, ldd, d, n, p, ncb);
+  };
+  if (parts && n <= 128) solve(trsm_right_upper_kernel<1, true>, parts);
+  else if (parts && n <= 256) solve(trsm_right_upper_kernel<2, true>, parts);
+  else if (n <= 128) solve(trsm_right_upper_kernel<1, false>, nullptr);
+  else if (n <= 256) solve(trsm_right_upper_kernel<2, false>, nullptr);
+  else if (n <= 512) solve(trsm_right_upper_kernel<4, false>, nullptr);
+  else solve(trsm_right_upper_kernel<8, false>, nullptr);
   PRAC_HIP_TRY(ctx, hipGetLastError());
-  return PRAC_OK;
+  return parts && n > 256 ? split_block(ctx, dst, d, n, parts) : PRAC_OK;
 }
 
 // dst (pitch ldd) = src (1.5 I - 0.5 src^T src): one Newton-Schulz step towards orthonormal columns.  For a block
@@ -1217,9 +1388,10 @@ int polish_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int
 
 // out (d x n fp32, pitch ldo) <- orth(Y): `passes` rounds of Cholesky-QR (the first one shifted), then
 // `polish` Newton-Schulz steps.  Y is overwritten, and so is the work space V; out may be V or somewhere else.
-// gram64_first = false: the first Gram matrix is summed in fp32 (well-conditioned blocks only).
+// gram64_first = false: the first Gram matrix is summed in fp32 (well-conditioned blocks only).  parts (no polish, ldo = n): the result also
+// as parts for G V.
 int cholqr(prac_ctx* ctx, const FitWs& w, float* Y, float* V, int64_t d, int n, int passes, double first_shift, float* out,
-           int64_t ldo, int polish = 0, bool gram64_first = true) {
+           int64_t ldo, int polish = 0, bool gram64_first = true, u32x4* parts = nullptr) {
   float* src = Y;
   for (int pass = 0; pass < passes + polish; ++pass) {
     const bool last = pass == passes + polish - 1;
@@ -1232,7 +1404,8 @@ int cholqr(prac_ctx* ctx, const FitWs& w, float* Y, float* V, int64_t d, int n, 
     // (a few 1e-16), and the shift has to be safely above that for the pivot to stay positive.
     // the last Newton-Schulz step must start within 3e-3 of orthonormal to end below 1e-5 (0.75 e^2); earlier
     // ones may start anywhere inside the step's region of convergence
-    int rc = pass < passes ? cholqr_pass(ctx, w, src, dst, ldd, d, n, pass == 0 ? first_shift : 1e-13, pass > 0 || gram64_first)
+    int rc = pass < passes ? cholqr_pass(ctx, w, src, dst, ldd, d, n, pass == 0 ? first_shift : 1e-13, pass > 0 || gram64_first,
+                                         last ? parts : nullptr)
                            : polish_pass(ctx, w, src, dst, ldd, d, n, last ? 3e-3f : 0.5f);
     if (rc) return rc;
     src = dst;
@@ -1283,7 +1456,6 @@ int64_t fit_slab_margin(int n_cu, prac_dtype xdt, int64_t N, int64_t d, int k, i
   if (f.do_q1) {
     const int n = L.b;  // block width of the iteration (k when tracking)
     product(L.splits_bb, n, n, 8);                    // panel Gram matrices of orth(), Rayleigh-Ritz
-    if (!f.track) product(L.splits_gv, d, n, 4);      // G V
     product(L.splits_bb, L.kq, L.kq, 8);              // tidy passes on Q1
     const int fill = k - L.kq;
     if (fill > 0) {
@@ -1355,22 +1527,27 @@ int fit_basis_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, in
       hipLaunchKernelGGL(copy_cols_kernel, dim3(ctx->n_cu * 4), dim3(256), 0, st, P, ldp, V, (int64_t)b, d, k);
       PRAC_HIP_TRY(ctx, hipGetLastError());
     }
+    u32x4* const Gf = reinterpret_cast<u32x4*>(ctx->ws + L.gv_g);
+    u32x4* const Vf = reinterpret_cast<u32x4*>(ctx->ws + L.gv_v);
+    {
+      const int nkb = gv_kblocks(d), nrb = (int)((d + 31) / 32);
+      hipLaunchKernelGGL(split_parts_kernel<true>, dim3((unsigned)(((int64_t)nrb * nkb + 3) / 4)), dim3(256), 0, st, G, d, (int)d, d, nrb,
+                         nkb, Gf);
+      PRAC_HIP_TRY(ctx, hipGetLastError());
+    }
+    rc = split_block(ctx, V, d, b, Vf);
+    if (rc) return rc;
     // The start block goes into the first product as it is: a Gaussian block and the previous
     // (orthonormal) Q1 are both well conditioned, and every product is orthonormalised anyway.
     for (int it = 0; it <= o.iters; ++it) {
       // Y = G V
-      GemmGenArgs g{};
-      g.A = G; g.B = V; g.adt = PRAC_F32; g.bdt = PRAC_F32;
-      g.a_rs = 1; g.a_cs = d; g.b_rs = b; g.b_cs = 1;  // G(m, k) read as G[k][m]: G is symmetric
-      g.M = (int)d; g.N = b; g.K = d; g.k_stride = 1;
-      g.splits = L.splits_gv; g.slabs = ctx->ws + L.slabs; g.slab_bytes = L.slab_bytes;
-      g.out = Y; g.ldo = b; g.alpha = 1.f; g.beta = 0.f; g.acc64 = false; g.out64 = nullptr;
-      rc = launch_gemm_generic(ctx, g);
-      if (rc) return rc;
+      hipLaunchKernelGGL(gram_times_block_kernel, dim3(((d + 31) / 32 * (gv_col_blocks(b) / 2) + 7) / 8 * 8), dim3(64 * GV_W),
+                         GV_W * 32 * 64 * sizeof(float), st, Gf, Vf, (int)d, b, gv_kblocks(d), gv_col_blocks(b), Y);
+      PRAC_HIP_TRY(ctx, hipGetLastError());
       if (it == o.iters) break;  // the last product feeds Rayleigh-Ritz
       // one shifted pass keeps the block well conditioned; the last iteration orthonormalises fully
       // (two passes: the second starts from a block whose condition number is already near one)
-      rc = cholqr(ctx, L, Y, V, d, b, it == o.iters - 1 ? 2 : 1, 1e-11, V, b);
+      rc = cholqr(ctx, L, Y, V, d, b, it == o.iters - 1 ? 2 : 1, 1e-11, V, b, 0, true, Vf);
       if (rc) return rc;
     }
     // Rayleigh-Ritz: H = V^T (G V), eigenvectors of H, Q1 = V Z[:, :k]

@@ -640,6 +640,24 @@ def test_static_weight_grad_takes_narrow_outputs_of_many_tokens(ctx, N, d, c, m,
     assert torch.equal(*outs) and not torch.equal(outs[0], old)
 
 
+@pytest.mark.parametrize("dt,N,d,k", [("bf16", 900, 129, 32), ("bf16", 900, 127, 33), ("bf16", 1000, 256, 16), ("bf16", 2100, 257, 65),
+                                      ("f32", 700, 33, 3), ("f32", 1200, 385, 128), ("bf16", 2048, 640, 129), ("f32", 600, 1030, 31)])
+def test_cold_fit_at_edges_of_the_products_tiles(ctx, dt, N, d, k):
+    """Block widths 2 k and feature counts around the 32 x 64 tiles and the 128 k of a turn of the waves in G V, and blocks
+    of up to 128, 256 and more columns (whose parts are written by the solve or by a kernel of their own).  k directions ten times the
+    noise: the projector is defined to far below 1e-3, and eight iterations reach it."""
+    g = torch.Generator().manual_seed(d + k)
+    X = torch.randn((N, k), generator=g) @ torch.randn((k, d), generator=g) * 10.0 / k ** 0.5 + torch.randn((N, d), generator=g)
+    Xd = dev_padded(X.to(TORCH_DT[dt]), (d + 7) // 8 * 8)
+    P, _, _ = ctx.fit_basis(Xd, k, 2, seed=5, draw=1)
+    ctx.sync_status()
+    Q1, lam = orc.principal_subspace(orc.gram(si.as_f64(Xd)), k)
+    assert lam[k - 1] / lam[k] >= 1.5
+    P64 = si.as_f64(P)
+    assert np.abs(P64[:, :k] @ P64[:, :k].T - Q1 @ Q1.T).max() < 1e-3
+    assert np.abs(P64.T @ P64 - np.eye(k + 2)).max() < 1e-5
+
+
 # ------------------------------------------------------------- reconstruction
 RECON_CASES = [
     # dtype, N, d, k, r, ldc, ldxh
