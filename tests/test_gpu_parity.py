@@ -274,6 +274,65 @@ def test_rows_that_start_on_any_element_meet_the_fp32_basis(ctx, d, c):
         assert ((C.double().cpu() - ref).abs() <= bound).all()
 
 
+@pytest.mark.parametrize("what", ["plain", "late", "zero_first", "tiny", "huge", "wide_range", "p_small", "p_large", "p_mixed", "p_zero_columns"])
+@pytest.mark.parametrize("N,d,c,packed", [(300, 2049, 40, False), (140, 2303, 200, True), (2000, 4099, 130, False)])  # the last: ranges of d
+def test_rows_on_any_element_with_two_parts_of_the_basis(ctx, N, d, c, packed, what):
+    """From 2048 features on the basis goes in as two f16 parts, and three bf16 parts take over per tile where those do not hold X's rows or P's
+    columns: elements far above a row's first ones, rows that start with zeros, numbers at the ends of the range.  C against the
+    fp64 product: one rounding (2^-8 of the element), 2^-22 per element of P, fp32 sums (sqrt(d) 2^-24 of the norms, below 2^-18), of which what X's
+    numbers below 2^-28 of their row's largest may lose is a part."""
+    from paper_2602_23111_amd.prac import C_PACKED, C_ROWMAJOR
+    g = torch.Generator(device=DEV).manual_seed(d)
+    X = torch.randn((N, d), generator=g, device=DEV)
+    P = torch.linalg.qr(torch.randn((d, c), generator=g, device=DEV))[0].contiguous()
+    if what == "late":
+        X[3, 700:] *= 1e5
+        X[130, 2048] = 3e9
+    elif what == "zero_first":
+        X[7] = 0.0
+        X[5, :256] = 0.0
+        X[129:137, :600] = 0.0
+        X *= 1e-4
+    elif what in ("tiny", "huge"):
+        X *= 1e-34 if what == "tiny" else 1e30
+    elif what == "wide_range":
+        X *= torch.exp(5.0 * torch.randn((N, d), generator=g, device=DEV))
+    elif what in ("p_small", "p_large"):
+        P *= 1e-9 if what == "p_small" else 1e5
+    elif what == "p_mixed":
+        P *= torch.logspace(-6, 4, c, device=DEV)
+    elif what == "p_zero_columns":
+        P[:, ::3] = 0.0
+    X = X.bfloat16()
+    C = ctx.compress(rows_on_any_element(X.cpu(), d, True), P, layout=C_PACKED if packed else C_ROWMAJOR)
+    if packed:
+        C = ctx.unpack_compressed(C, N, c)
+    ctx.sync_status()
+    X64, P64 = X.double(), P.double()
+    ref = X64 @ P64
+    scale = X64.norm(dim=1, keepdim=True) * P64.norm(dim=0, keepdim=True)
+    assert ((C.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2.0 ** -18 * scale).all()
+
+
+def test_infinities_with_two_parts_of_the_basis(ctx):
+    """Infinities and NaN in X and in P, from 2048 features on: as in the plain product, rows and columns beside them untouched."""
+    N, d, c = 300, 2051, 40
+    g = torch.Generator().manual_seed(3)
+    P = torch.randn((d, c), generator=g)
+    X = torch.rand((N, d), generator=g).bfloat16() + 1
+    X[4, 2050], X[133, 3], X[134, 700] = float("inf"), -float("inf"), float("nan")
+    P[5, 39] = float("inf")
+    P[9, 38] = float("nan")
+    C = ctx.compress(rows_on_any_element(X, d, True), P.to(DEV))
+    torch.cuda.synchronize()
+    C = C.float().cpu()
+    rest = torch.ones(N, dtype=torch.bool)
+    rest[[4, 133, 134]] = False
+    assert torch.equal(C[4, :38], torch.sign(P[2050, :38]) * float("inf")) and torch.equal(C[133, :38], -torch.sign(P[3, :38]) * float("inf"))
+    assert C[134].isnan().all() and C[:, 38].isnan().all() and (C[rest, 39] == float("inf")).all()
+    assert C[rest, :38].isfinite().all()
+
+
 def test_infinity_in_rows_that_start_on_any_element(ctx):
     """An infinite element of X makes its row of C infinite with the signs of the basis, whatever the bits of P (one, some and
     all of its bf16 parts would be zero), and leaves the other rows alone; a zero of P makes it NaN."""
