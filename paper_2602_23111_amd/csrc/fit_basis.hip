@@ -933,6 +933,10 @@ __global__ __launch_bounds__(256) void copy_cols_kernel(const float* __restrict_
 // (9 KB per twelve matrix instructions of a wave, 302 MB per launch at d = 2048, b = 256); a larger tile would leave compute units idle or
 // need ranges of k and their sum.  16.8 us there, where fp32 instructions took 27 and the sum of two ranges 5.  |Y - G V| against 64 bits: 0.4 to
 // 0.9 of theirs in six shapes of d 256 to 2048, b 2 to 256 (1.3e-7 of |Y| against 3.0e-7 at d = 2048, b = 256).
+// Blocks of more than GV_MAX columns keep the fp32 instructions: their factorisation is shifted by a share of the largest diagonal entry
+// (see CholShift), and of batches of lower rank than the block the noise that rounding leaves in the surplus columns has to be above that.
+// With less of it 4 of 92 such fits of 240 drawn ones that were accepted were refused.
+constexpr int GV_MAX = 256;
 constexpr int GV_W = 8, GV_D = 4;  // waves, k-blocks in flight
 static inline int gv_kblocks(int64_t d) { return (int)(round_up64(d, 16 * GV_W) / 16); }
 static inline size_t gv_g_bytes(int64_t d) { return (size_t)((d + 31) / 32) * gv_kblocks(d) * 3072; }
@@ -1194,6 +1198,7 @@ struct FitWs {
   int b;
   int kq;         // principal columns the iteration computes (see principal_rank); the other k - kq are drawn
   int splits_bb;  // split count of the b x b fp64 Gram products
+  int splits_gv;  // split count of G V for b > GV_MAX
 };
 
 int block_width(int64_t d, int k, const prac_fit_opts& o) {
@@ -1247,17 +1252,25 @@ FitWs plan_fit(int64_t d, int k, int r, const prac_fit_opts& o, int n_cu, bool n
   w.T = p.take((size_t)(k > 0 ? k : 1) * (rf > 0 ? rf : 1) * 4);
   const int s = panel_splits(n_cu, d, bb);
   w.splits_bb = s;
-  // the slab block serves every split product of the fit: the bb x bb panel Gram matrices (fp64)
-  // and Q1^T S (k x r, fp32; wider than a panel Gram when k > 2 r and Q1 is not refreshed)
-  const size_t slab_bb = (size_t)s * bb * bb * 8;
+  // G V (d x b, fp32): split the sum over k until the tiles fill the chip
+  const bool gv_f32 = need_g && b > GV_MAX;
+  const int tiles_gv = (int)((d + 63) / 64) * ((b + 63) / 64);
+  int sg = gv_f32 ? (n_cu + tiles_gv - 1) / tiles_gv : 1;
+  if (sg > d / 256) sg = (int)(d / 256);
+  if (sg < 1) sg = 1;
+  if (sg > 16) sg = 16;
+  w.splits_gv = sg;
+  // the slab block serves every split product of the fit: the bb x bb panel Gram matrices (fp64), G V
+  // (d x b, fp32) and Q1^T S (k x r, fp32; wider than a panel Gram when k > 2 r and Q1 is not refreshed)
+  const size_t slab_bb = (size_t)s * bb * bb * 8, slab_gv = sg > 1 ? (size_t)sg * d * b * 4 : 0;
   const size_t slab_kr = (size_t)s * k * rf * 4;  // also the completion's Q1^T S (kq x fill)
-  w.slab_bytes = std::max(slab_bb, slab_kr);
+  w.slab_bytes = std::max(slab_bb, std::max(slab_gv, slab_kr));
   for (int n : {b, b > 0 ? kq : 0, fill, r})  // the panel Gram matrices with fp64 sums
     w.slab_bytes = std::max(w.slab_bytes, pg_need(n_cu, d, n));
   w.slabs = p.take(w.slab_bytes);
   w.gram = p.take(gram_bytes);
-  w.gv_g = p.take(need_g ? gv_g_bytes(d) : 0);
-  w.gv_v = p.take(need_g ? gv_v_bytes(d, b) : 0);
+  w.gv_g = p.take(need_g && !gv_f32 ? gv_g_bytes(d) : 0);
+  w.gv_v = p.take(need_g && !gv_f32 ? gv_v_bytes(d, b) : 0);
   if (track) {
     w.trk_nkb = (int)(round_up64(d, 256) / 16);
     w.trk_ncb = (int)round_up64((k + 31) / 32, 8);
@@ -1361,14 +1374,15 @@ int cholqr_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int
   auto solve = [&](auto kern, u32x4* p) {
     hipLaunchKernelGGL(kern, tgrid, tblock, 0, ctx->stream, src, W64, dst, ldd, d, n, p, ncb);
   };
+  if (parts && n > GV_MAX) return PRAC_EINVAL;
   if (parts && n <= 128) solve(trsm_right_upper_kernel<1, true>, parts);
-  else if (parts && n <= 256) solve(trsm_right_upper_kernel<2, true>, parts);
+  else if (parts) solve(trsm_right_upper_kernel<2, true>, parts);
   else if (n <= 128) solve(trsm_right_upper_kernel<1, false>, nullptr);
   else if (n <= 256) solve(trsm_right_upper_kernel<2, false>, nullptr);
   else if (n <= 512) solve(trsm_right_upper_kernel<4, false>, nullptr);
   else solve(trsm_right_upper_kernel<8, false>, nullptr);
   PRAC_HIP_TRY(ctx, hipGetLastError());
-  return parts && n > 256 ? split_block(ctx, dst, d, n, parts) : PRAC_OK;
+  return PRAC_OK;
 }
 
 // dst (pitch ldd) = src (1.5 I - 0.5 src^T src): one Newton-Schulz step towards orthonormal columns.  For a block
@@ -1456,6 +1470,7 @@ int64_t fit_slab_margin(int n_cu, prac_dtype xdt, int64_t N, int64_t d, int k, i
   if (f.do_q1) {
     const int n = L.b;  // block width of the iteration (k when tracking)
     product(L.splits_bb, n, n, 8);                    // panel Gram matrices of orth(), Rayleigh-Ritz
+    if (!f.track) product(L.splits_gv, d, n, 4);      // G V
     product(L.splits_bb, L.kq, L.kq, 8);              // tidy passes on Q1
     const int fill = k - L.kq;
     if (fill > 0) {
@@ -1528,21 +1543,32 @@ int fit_basis_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, in
       PRAC_HIP_TRY(ctx, hipGetLastError());
     }
     u32x4* const Gf = reinterpret_cast<u32x4*>(ctx->ws + L.gv_g);
-    u32x4* const Vf = reinterpret_cast<u32x4*>(ctx->ws + L.gv_v);
-    {
+    u32x4* const Vf = b <= GV_MAX ? reinterpret_cast<u32x4*>(ctx->ws + L.gv_v) : nullptr;
+    if (Vf) {
       const int nkb = gv_kblocks(d), nrb = (int)((d + 31) / 32);
       hipLaunchKernelGGL(split_parts_kernel<true>, dim3((unsigned)(((int64_t)nrb * nkb + 3) / 4)), dim3(256), 0, st, G, d, (int)d, d, nrb,
                          nkb, Gf);
       PRAC_HIP_TRY(ctx, hipGetLastError());
+      rc = split_block(ctx, V, d, b, Vf);
+      if (rc) return rc;
     }
-    rc = split_block(ctx, V, d, b, Vf);
-    if (rc) return rc;
     // The start block goes into the first product as it is: a Gaussian block and the previous
     // (orthonormal) Q1 are both well conditioned, and every product is orthonormalised anyway.
     for (int it = 0; it <= o.iters; ++it) {
       // Y = G V
-      hipLaunchKernelGGL(gram_times_block_kernel, dim3(((d + 31) / 32 * (gv_col_blocks(b) / 2) + 7) / 8 * 8), dim3(64 * GV_W),
-                         GV_W * 32 * 64 * sizeof(float), st, Gf, Vf, (int)d, b, gv_kblocks(d), gv_col_blocks(b), Y);
+      if (!Vf) {
+        GemmGenArgs g{};
+        g.A = G; g.B = V; g.adt = PRAC_F32; g.bdt = PRAC_F32;
+        g.a_rs = 1; g.a_cs = d; g.b_rs = b; g.b_cs = 1;  // G(m, k) read as G[k][m]: G is symmetric
+        g.M = (int)d; g.N = b; g.K = d; g.k_stride = 1;
+        g.splits = L.splits_gv; g.slabs = ctx->ws + L.slabs; g.slab_bytes = L.slab_bytes;
+        g.out = Y; g.ldo = b; g.alpha = 1.f; g.beta = 0.f; g.acc64 = false; g.out64 = nullptr;
+        rc = launch_gemm_generic(ctx, g);
+        if (rc) return rc;
+      } else {
+        hipLaunchKernelGGL(gram_times_block_kernel, dim3(((d + 31) / 32 * (gv_col_blocks(b) / 2) + 7) / 8 * 8), dim3(64 * GV_W),
+                           GV_W * 32 * 64 * sizeof(float), st, Gf, Vf, (int)d, b, gv_kblocks(d), gv_col_blocks(b), Y);
+      }
       PRAC_HIP_TRY(ctx, hipGetLastError());
       if (it == o.iters) break;  // the last product feeds Rayleigh-Ritz
       // one shifted pass keeps the block well conditioned; the last iteration orthonormalises fully
