@@ -365,8 +365,10 @@ __device__ __forceinline__ void chol_tile_wave(CholRegLds& s, double* W, int b, 
   }
 }
 
-__global__ __launch_bounds__(1024) void chol_upper_reg_kernel(double* W, int b, double shift_rel, int* flag) {
+// far != nullptr and zero: W is so close to the identity that the solve behind does without a factor (see there)
+__global__ __launch_bounds__(1024) void chol_upper_reg_kernel(double* W, int b, double shift_rel, int* flag, const int* far) {
   __shared__ CholRegLds s;
+  if (far && *far == 0) return;  // uniform
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const double mx = chol_diag_max(W, b, s.red);
   const CholShift shift{shift_rel, mx};
@@ -474,12 +476,16 @@ __device__ __forceinline__ void split3(const float (&x)[8], u32x4 (&part)[3]) {
 // column 4 b + a: a lane then holds four neighbouring columns of its row.
 // 18.5 us at 2048 x 256, 9 us at 2048 x 128 (42 / 16.5 us in fp32 on the vector units, columns of R staged through LDS); R's lines not
 // requested ahead 64 us.
+// far != nullptr and zero (n <= 256): R holds src^T src instead, both triangles, which is within PANEL_NEAR of the identity, and dst is
+// src (1.5 I - 0.5 src^T src), a Newton-Schulz step, also in fp64: no factorisation (57 us at n = 256).
 // PARTS (n <= 256): also the result as three bf16 parts for gram_times_block_kernel (its 16 rows are one k-block).
 constexpr int TR_ROWS = 16, TR_W = 8;
 template <int NT, bool PARTS>
 __global__ __launch_bounds__(64 * TR_W) void trsm_right_upper_kernel(const float* src, const double* __restrict__ R, float* dst,
-                                                                     int64_t ldd, int64_t rows, int n, u32x4* parts, int ncb) {
-  __shared__ double s_x[2][256];
+                                                                     int64_t ldd, int64_t rows, int n, u32x4* parts, int ncb,
+                                                                     const int* far) {
+  __shared__ double s_x[NT <= 2 ? TR_W * NT : 2][256];
+  const bool near = NT <= 2 && far && *far == 0;  // uniform
   const int lane = threadIdx.x & 63, fi = lane & 15, fk = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nb = (n + 15) / 16;
@@ -519,6 +525,44 @@ __global__ __launch_bounds__(64 * TR_W) void trsm_right_upper_kernel(const float
     for (int v = 0; v < 4; ++v) s_x[j & 1][64 * v + lane] = -x[v];
   };
   const f64x4_t zero = {0.0, 0.0, 0.0, 0.0};
+  if (near) {
+    if constexpr (NT <= 2) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) s_x[wave + TR_W * t][64 * v + lane] = z[t][v];
+      __syncthreads();
+      // four blocks at a time, the next four requested before these are multiplied (past the last one: others again, times zeros)
+      constexpr int BATCHES = 2 * NT * NT;
+      f64x4_t m[2][4], a = zero;
+      auto request = [&](auto bc) __attribute__((always_inline)) {
+        constexpr int B = decltype(bc)::value;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) m[B & 1][u] = load_r(4 * (B % (2 * NT)) + u, wave + TR_W * (B / (2 * NT)));
+      };
+      request(std::integral_constant<int, 0>{});
+      chol_static_for<BATCHES>([&](auto bc) __attribute__((always_inline)) {
+        constexpr int B = decltype(bc)::value, t = B / (2 * NT), I0 = 4 * (B % (2 * NT));
+        if constexpr (B + 1 < BATCHES) request(std::integral_constant<int, B + 1>{});
+        __builtin_amdgcn_sched_barrier(0);
+        const int c = 16 * (wave + TR_W * t) + pfi;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          f64x4_t x;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            x[v] = s_x[I0 + u][64 * v + lane];
+            m[B & 1][u][v] = (16 * (I0 + u) + 4 * fk + v == c ? 1.5 : 0.0) - 0.5 * m[B & 1][u][v];
+          }
+          a = chol_mul(m[B & 1][u], x, a);
+        }
+        if constexpr (I0 + 4 == 8 * NT) {
+          z[t] = a;
+          a = zero;
+        }
+      });
+    }
+  } else {
   if (wave == 0) {
     z[0] = chol_mul(load_r(0, 0), z[0], zero);
     put(0, z[0]);
@@ -559,6 +603,7 @@ __global__ __launch_bounds__(64 * TR_W) void trsm_right_upper_kernel(const float
       chol_static_for<NT - T>([&](auto uc) { step(std::integral_constant<int, T + decltype(uc)::value>{}); });
     }
   });
+  }
   asm volatile("" : : "v"(touched));
   if constexpr (PARTS) {
     __shared__ float tile[TR_ROWS][260];
@@ -1058,7 +1103,8 @@ constexpr int PG_K = 32;
 static inline int pg_tiles(int n) { return ((n + 63) / 64) * ((n + 63) / 64 + 1) / 2; }
 static inline size_t pg_bytes(int n) { return (size_t)(((n + 15) / 16) * ((n + 15) / 16 + 1) / 2) * 256 * 8; }  // of one range
 __global__ __launch_bounds__(256) void panel_gram64_kernel(const float* __restrict__ src, int64_t d, int n, int64_t rows_per_split,
-                                                           double* __restrict__ slabs) {
+                                                           double* __restrict__ slabs, int* far) {
+  if (far && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *far = 0;
   const int lane = threadIdx.x & 63, fi = lane & 15, fk = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nb = (n + 63) / 64;
@@ -1136,9 +1182,12 @@ __global__ __launch_bounds__(256) void panel_gram64_kernel(const float* __restri
     }
 }
 
-// W (n x n) = sum over the ranges, a workgroup per block of the upper triangle
+// W (n x n) = sum over the ranges, a workgroup per block of the upper triangle (with far both triangles).  far (zero before): set where an entry of W is further than
+// PANEL_NEAR from the identity's, or not finite.  A Newton-Schulz step leaves 0.75 e^2 of a distance e (in norm: up to n PANEL_NEAR, as a
+// rule a few times PANEL_NEAR), so it ends below fp32 rounding from there, or at 2e-6 at the very worst.
+constexpr double PANEL_NEAR = 6e-6;
 __global__ __launch_bounds__(256) void panel_gram64_sum_kernel(const double* __restrict__ slabs, int splits, int n,
-                                                               double* __restrict__ W) {
+                                                               double* __restrict__ W, int* far) {
   const int nb16 = (n + 15) / 16, lane = threadIdx.x & 63;
   int J = blockIdx.x, I = 0;
   while (J >= nb16 - I) {
@@ -1151,7 +1200,11 @@ __global__ __launch_bounds__(256) void panel_gram64_sum_kernel(const double* __r
   const double* p = slabs + (int64_t)blockIdx.x * 256 + threadIdx.x;
 #pragma unroll 8
   for (int z = 0; z < splits; ++z) s += p[(int64_t)z * gridDim.x * 256];
-  if (row < n && c < n) W[(int64_t)row * n + c] = s;
+  if (row < n && c < n) {
+    W[(int64_t)row * n + c] = s;
+    if (row < c && far) W[(int64_t)c * n + row] = s;
+  }
+  if (far && __any(row < n && c < n && row <= c && !(fabs(s - (row == c ? 1.0 : 0.0)) <= PANEL_NEAR)) && lane == 0) atomicOr(far, 1);
 }
 
 // The sum of the fp32 partial Gram matrices of a block, as fp64 (W64 != nullptr) or as the factor 1.5 I - 0.5 W of a Newton-Schulz step.
@@ -1193,6 +1246,7 @@ size_t pg_need(int n_cu, int64_t d, int n) { return n > 0 ? pg_splits(n_cu, d, n
 struct FitWs {
   size_t G, V, Y, W64, eig, Rinv, lam, Z, S, T, slabs, slab_bytes, gram, total;
   size_t gv_g, gv_v;  // parts of G and of the iteration's block
+  size_t far;         // whether a panel's Gram matrix is not near the identity
   size_t trk_pf, trk_c, trk_slabs;  // tracking refit: V in fragment order, packed X V, slabs of (X V)^T X
   int trk_nkb, trk_ncb, trk_splits;
   int b;
@@ -1247,6 +1301,7 @@ FitWs plan_fit(int64_t d, int k, int r, const prac_fit_opts& o, int n_cu, bool n
   w.eig = p.take(need_g ? std::max<size_t>(sym_eig_doubles(b) * 8, 256) : 0);
   w.Rinv = p.take((size_t)bb * bb * 4);
   w.lam = p.take((size_t)bb * 8);
+  w.far = p.take(sizeof(int));
   w.Z = p.take((size_t)bb * (k > 0 ? k : 1) * 4);
   w.S = p.take((size_t)d * (rf > 0 ? rf : 1) * 4);
   w.T = p.take((size_t)(k > 0 ? k : 1) * (rf > 0 ? rf : 1) * 4);
@@ -1301,14 +1356,15 @@ int set_dyn_smem(prac_ctx* ctx) {
 }
 
 // src^T src for a d x n block (ld = n) with fp64 sums: the upper triangle of W64
-int panel_gram64(prac_ctx* ctx, const FitWs& w, const float* src, int64_t d, int n, double* W64) {
+int panel_gram64(prac_ctx* ctx, const FitWs& w, const float* src, int64_t d, int n, double* W64, int* far) {
   const int tiles = pg_tiles(n), splits = pg_splits(ctx->n_cu, d, n, w.slab_bytes);
   if (splits * pg_bytes(n) > w.slab_bytes) return PRAC_EINVAL;
   double* slabs = reinterpret_cast<double*>(ctx->ws + w.slabs);
   const int64_t per = round_up64((d + splits - 1) / splits, PG_K);
   const int used = (int)((d + per - 1) / per);
-  hipLaunchKernelGGL(panel_gram64_kernel, dim3(tiles, used), dim3(256), 0, ctx->stream, src, d, n, per, slabs);
-  hipLaunchKernelGGL(panel_gram64_sum_kernel, dim3((unsigned)(pg_bytes(n) / 2048)), dim3(256), 0, ctx->stream, slabs, used, n, W64);
+  hipLaunchKernelGGL(panel_gram64_kernel, dim3(tiles, used), dim3(256), 0, ctx->stream, src, d, n, per, slabs, far);
+  hipLaunchKernelGGL(panel_gram64_sum_kernel, dim3((unsigned)(pg_bytes(n) / 2048)), dim3(256), 0, ctx->stream, slabs, used, n, W64,
+                     far);
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
 }
@@ -1355,24 +1411,26 @@ int split_block(prac_ctx* ctx, const float* V, int64_t d, int n, u32x4* parts) {
 }
 
 // dst (pitch ldd; may be src) = src R^-1 with R^T R = src^T src (+ shift): one Cholesky-QR pass.  parts: the result also as parts for G V
-// (their padding past d is there already)
+// (their padding past d is there already).  any_basis: of src's span any orthonormal basis will do, so a block that is orthonormal but for
+// PANEL_NEAR gets a Newton-Schulz step instead (decided on the device).
 int cholqr_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int64_t ldd, int64_t d, int n, double shift, bool gram64,
-                u32x4* parts) {
+                u32x4* parts, bool any_basis) {
   double* W64 = reinterpret_cast<double*>(ctx->ws + w.W64);
-  int rc = gram64 ? panel_gram64(ctx, w, src, d, n, W64) : panel_gram32(ctx, w, src, d, n, W64, nullptr, 0.f);
+  int* far = any_basis && gram64 && n <= CHR_MAX ? reinterpret_cast<int*>(ctx->ws + w.far) : nullptr;
+  int rc = gram64 ? panel_gram64(ctx, w, src, d, n, W64, far) : panel_gram32(ctx, w, src, d, n, W64, nullptr, 0.f);
   if (rc) return rc;
   rc = set_dyn_smem(ctx);
   if (rc) return rc;
   if (n > CH_MAX) return PRAC_EUNSUPPORTED;
   if (n <= CHR_MAX)
-    hipLaunchKernelGGL(chol_upper_reg_kernel, dim3(1), dim3(1024), 0, ctx->stream, W64, n, shift, ctx->d_flag);
+    hipLaunchKernelGGL(chol_upper_reg_kernel, dim3(1), dim3(1024), 0, ctx->stream, W64, n, shift, ctx->d_flag, far);
   else
     hipLaunchKernelGGL(chol_upper_kernel, dim3(1), dim3(1024),
                        (size_t)CH_NB * (round_up64(n, CH_NB) + 2) * sizeof(double), ctx->stream, W64, n, shift, ctx->d_flag);
   const dim3 tgrid((unsigned)((d + TR_ROWS - 1) / TR_ROWS)), tblock(64 * TR_W);
   const int ncb = gv_col_blocks(n);
   auto solve = [&](auto kern, u32x4* p) {
-    hipLaunchKernelGGL(kern, tgrid, tblock, 0, ctx->stream, src, W64, dst, ldd, d, n, p, ncb);
+    hipLaunchKernelGGL(kern, tgrid, tblock, 0, ctx->stream, src, W64, dst, ldd, d, n, p, ncb, far);
   };
   if (parts && n > GV_MAX) return PRAC_EINVAL;
   if (parts && n <= 128) solve(trsm_right_upper_kernel<1, true>, parts);
@@ -1403,9 +1461,10 @@ int polish_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int
 // out (d x n fp32, pitch ldo) <- orth(Y): `passes` rounds of Cholesky-QR (the first one shifted), then
 // `polish` Newton-Schulz steps.  Y is overwritten, and so is the work space V; out may be V or somewhere else.
 // gram64_first = false: the first Gram matrix is summed in fp32 (well-conditioned blocks only).  parts (no polish, ldo = n): the result also
-// as parts for G V.
+// as parts for G V.  Passes from any_basis_from on may give another basis of the same span.
 int cholqr(prac_ctx* ctx, const FitWs& w, float* Y, float* V, int64_t d, int n, int passes, double first_shift, float* out,
-           int64_t ldo, int polish = 0, bool gram64_first = true, u32x4* parts = nullptr) {
+           int64_t ldo, int polish = 0, bool gram64_first = true, u32x4* parts = nullptr,
+           int any_basis_from = 1 << 30) {
   float* src = Y;
   for (int pass = 0; pass < passes + polish; ++pass) {
     const bool last = pass == passes + polish - 1;
@@ -1419,7 +1478,7 @@ int cholqr(prac_ctx* ctx, const FitWs& w, float* Y, float* V, int64_t d, int n, 
     // the last Newton-Schulz step must start within 3e-3 of orthonormal to end below 1e-5 (0.75 e^2); earlier
     // ones may start anywhere inside the step's region of convergence
     int rc = pass < passes ? cholqr_pass(ctx, w, src, dst, ldd, d, n, pass == 0 ? first_shift : 1e-13, pass > 0 || gram64_first,
-                                         last ? parts : nullptr)
+                                         last ? parts : nullptr, pass >= any_basis_from)
                            : polish_pass(ctx, w, src, dst, ldd, d, n, last ? 3e-3f : 0.5f);
     if (rc) return rc;
     src = dst;
@@ -1573,7 +1632,7 @@ int fit_basis_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, in
       if (it == o.iters) break;  // the last product feeds Rayleigh-Ritz
       // one shifted pass keeps the block well conditioned; the last iteration orthonormalises fully
       // (two passes: the second starts from a block whose condition number is already near one)
-      rc = cholqr(ctx, L, Y, V, d, b, it == o.iters - 1 ? 2 : 1, 1e-11, V, b, 0, true, Vf);
+      rc = cholqr(ctx, L, Y, V, d, b, it == o.iters - 1 ? 2 : 1, 1e-11, V, b, 0, true, Vf, 1);
       if (rc) return rc;
     }
     // Rayleigh-Ritz: H = V^T (G V), eigenvectors of H, Q1 = V Z[:, :k]
@@ -1629,7 +1688,7 @@ int fit_basis_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, in
     // tidy the rounding of the last product (two Cholesky-QR passes and a Newton-Schulz step: with more
     // Ritz vectors asked for than the data has rank, the surplus ones are rounding noise, far from
     // orthogonal to each other, and one pass leaves 1e-4 or more), then store Q1 into P[:, :k]
-    rc = cholqr(ctx, L, Y, V, d, k, 2, 1e-13, P, ldp, 1);
+    rc = cholqr(ctx, L, Y, V, d, k, 2, 1e-13, P, ldp, 1, true, nullptr, 0);
     if (rc) return rc;
   }
 
