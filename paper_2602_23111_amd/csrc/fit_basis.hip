@@ -466,7 +466,7 @@ __device__ __forceinline__ void split3(const float (&x)[8], u32x4 (&part)[3]) {
   }
 }
 
-// dst (rows x n fp32, pitch ldd) = src * R^-1 (src pitch n; dst may be src: a workgroup reads its rows before it writes them)
+// dst (rows x n fp32, pitch ldd) = src * R^-1 (src pitch lds; dst may be src: a workgroup reads its rows before it writes them)
 // for the upper-triangular R (row-major n x n fp64, its 16 x 16 diagonal blocks inverted),
 // in fp64 on the matrix cores.  A workgroup of eight waves solves 16 rows, as the transpose R^-T src^T: wave w holds the column
 // tiles w, w + 8, ... of its rows as 16 x 16 accumulators Z_J (a result's registers are its operand layout, see above).  Step j:
@@ -478,19 +478,21 @@ __device__ __forceinline__ void split3(const float (&x)[8], u32x4 (&part)[3]) {
 // requested ahead 64 us.
 // far != nullptr and zero (n <= 256): R holds src^T src instead, both triangles, which is within PANEL_NEAR of the identity, and dst is
 // src (1.5 I - 0.5 src^T src), a Newton-Schulz step, also in fp64: no factorisation (57 us at n = 256).
+// gate != nullptr and zero: nothing to do.
 // PARTS (n <= 256): also the result as three bf16 parts for gram_times_block_kernel (its 16 rows are one k-block).
 constexpr int TR_ROWS = 16, TR_W = 8;
 template <int NT, bool PARTS>
-__global__ __launch_bounds__(64 * TR_W) void trsm_right_upper_kernel(const float* src, const double* __restrict__ R, float* dst,
-                                                                     int64_t ldd, int64_t rows, int n, u32x4* parts, int ncb,
-                                                                     const int* far) {
+__global__ __launch_bounds__(64 * TR_W) void trsm_right_upper_kernel(const float* src, int64_t lds, const double* __restrict__ R,
+                                                                     float* dst, int64_t ldd, int64_t rows, int n, u32x4* parts, int ncb,
+                                                                     const int* far, const int* gate) {
+  if (gate && *gate == 0) return;  // uniform
   __shared__ double s_x[NT <= 2 ? TR_W * NT : 2][256];
   const bool near = NT <= 2 && far && *far == 0;  // uniform
   const int lane = threadIdx.x & 63, fi = lane & 15, fk = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nb = (n + 15) / 16;
   const int64_t row = (int64_t)blockIdx.x * TR_ROWS + fi;
-  const float* const srow = src + (row < rows ? row : rows - 1) * n;
+  const float* const srow = src + (row < rows ? row : rows - 1) * lds;
   // R was written by one compute unit a moment ago and is in no L2 but perhaps its own: ask for every line of its upper half at once,
   // instead of meeting a trip to memory at every step
   double touched = 0.0;
@@ -1102,9 +1104,11 @@ __global__ __launch_bounds__(64 * GV_W, 2) void gram_times_block_kernel(const u3
 constexpr int PG_K = 32;
 static inline int pg_tiles(int n) { return ((n + 63) / 64) * ((n + 63) / 64 + 1) / 2; }
 static inline size_t pg_bytes(int n) { return (size_t)(((n + 15) / 16) * ((n + 15) / 16 + 1) / 2) * 256 * 8; }  // of one range
-__global__ __launch_bounds__(256) void panel_gram64_kernel(const float* __restrict__ src, int64_t d, int n, int64_t rows_per_split,
-                                                           double* __restrict__ slabs, int* far) {
-  if (far && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *far = 0;
+// (*far and, without a gate, the word behind it are zeroed for the kernels that follow; gate != nullptr and zero: nothing to do)
+__global__ __launch_bounds__(256) void panel_gram64_kernel(const float* __restrict__ src, int64_t lds, int64_t d, int n,
+                                                           int64_t rows_per_split, double* __restrict__ slabs, int* far, const int* gate) {
+  if (gate && *gate == 0) return;  // uniform
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < (gate ? 1 : 2)) far[threadIdx.x] = 0;
   const int lane = threadIdx.x & 63, fi = lane & 15, fk = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nb = (n + 63) / 64;
@@ -1129,7 +1133,7 @@ __global__ __launch_bounds__(256) void panel_gram64_kernel(const float* __restri
   auto load = [&](Step& s, int64_t k0, int64_t last) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < PG_K / 4; ++u) {
-      const int64_t o = min(k0 + 4 * u + fk, last) * n;
+      const int64_t o = min(k0 + 4 * u + fk, last) * lds;
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         s.a[u][t] = pa[t][o];
@@ -1182,12 +1186,14 @@ __global__ __launch_bounds__(256) void panel_gram64_kernel(const float* __restri
     }
 }
 
-// W (n x n) = sum over the ranges, a workgroup per block of the upper triangle (with far both triangles).  far (zero before): set where an entry of W is further than
+// W (n x n) = sum over the ranges, a workgroup per block of the upper triangle (with far or gate both triangles).  far (zero before; not with a gate): set where an entry of W is further than
 // PANEL_NEAR from the identity's, or not finite.  A Newton-Schulz step leaves 0.75 e^2 of a distance e (in norm: up to n PANEL_NEAR, as a
 // rule a few times PANEL_NEAR), so it ends below fp32 rounding from there, or at 2e-6 at the very worst.
+// gate: nullptr, or nothing to do where it is zero; then an entry further than `limit` from the identity's raises bit 1 of *flag.
 constexpr double PANEL_NEAR = 6e-6;
 __global__ __launch_bounds__(256) void panel_gram64_sum_kernel(const double* __restrict__ slabs, int splits, int n,
-                                                               double* __restrict__ W, int* far) {
+                                                               double* __restrict__ W, int* far, const int* gate, double limit, int* flag) {
+  if (gate && *gate == 0) return;  // uniform
   const int nb16 = (n + 15) / 16, lane = threadIdx.x & 63;
   int J = blockIdx.x, I = 0;
   while (J >= nb16 - I) {
@@ -1202,18 +1208,23 @@ __global__ __launch_bounds__(256) void panel_gram64_sum_kernel(const double* __r
   for (int z = 0; z < splits; ++z) s += p[(int64_t)z * gridDim.x * 256];
   if (row < n && c < n) {
     W[(int64_t)row * n + c] = s;
-    if (row < c && far) W[(int64_t)c * n + row] = s;
+    if (row < c && (far || gate)) W[(int64_t)c * n + row] = s;
   }
-  if (far && __any(row < n && c < n && row <= c && !(fabs(s - (row == c ? 1.0 : 0.0)) <= PANEL_NEAR)) && lane == 0) atomicOr(far, 1);
+  if (far || gate) {  // uniform
+    const double off = row < n && c < n && row <= c ? fabs(s - (row == c ? 1.0 : 0.0)) : 0.0;
+    if (far && __any(!(off <= PANEL_NEAR)) && lane == 0) atomicOr(far, 1);
+    if (gate && __any(!(off <= limit)) && lane == 0) atomicOr(flag, 1);
+  }
 }
 
 // The sum of the fp32 partial Gram matrices of a block, as fp64 (W64 != nullptr) or as the factor 1.5 I - 0.5 W of a Newton-Schulz step.
 // For the latter W is the Gram matrix of a block that should be close to orthonormal: an entry further than `limit` from the
 // identity (or not finite) raises bit 1 of *flag - the step that follows squares the distance, so a block that far off
-// does not come out orthonormal to fp32 rounding.  (slabs may be M32 itself)
+// does not come out orthonormal to fp32 rounding.  again (or nullptr): set where an entry is further than PANEL_NEAR.  (slabs may be M32 itself)
+constexpr float PANEL_LAST = 3e-3f;  // up to here a last step ends below 1e-5 (0.75 e^2)
 __global__ __launch_bounds__(256) void panel_gram32_sum_kernel(const float* slabs, int splits, int n, double* W64, float* M32,
-                                                               float limit, int* flag) {
-  bool off = false;
+                                                               float limit, int* flag, int* again) {
+  bool off = false, more = false;
   const int total = n * n;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
     float w = 0.f;
@@ -1224,10 +1235,12 @@ __global__ __launch_bounds__(256) void panel_gram32_sum_kernel(const float* slab
     } else {
       const float id = i / n == i % n ? 1.f : 0.f;
       off = off || !(fabsf(w - id) <= limit);
+      more = more || !(fabsf(w - id) <= (float)PANEL_NEAR);
       M32[i] = 1.5f * id - 0.5f * w;
     }
   }
   if (off) atomicOr(flag, 1);
+  if (more && again) atomicOr(again, 1);
 }
 
 // row ranges of a split panel product of width n
@@ -1246,7 +1259,7 @@ size_t pg_need(int n_cu, int64_t d, int n) { return n > 0 ? pg_splits(n_cu, d, n
 struct FitWs {
   size_t G, V, Y, W64, eig, Rinv, lam, Z, S, T, slabs, slab_bytes, gram, total;
   size_t gv_g, gv_v;  // parts of G and of the iteration's block
-  size_t far;         // whether a panel's Gram matrix is not near the identity
+  size_t far;         // two words: whether a panel's Gram matrix is not near the identity, whether a second Newton-Schulz step is needed
   size_t trk_pf, trk_c, trk_slabs;  // tracking refit: V in fragment order, packed X V, slabs of (X V)^T X
   int trk_nkb, trk_ncb, trk_splits;
   int b;
@@ -1301,7 +1314,7 @@ FitWs plan_fit(int64_t d, int k, int r, const prac_fit_opts& o, int n_cu, bool n
   w.eig = p.take(need_g ? std::max<size_t>(sym_eig_doubles(b) * 8, 256) : 0);
   w.Rinv = p.take((size_t)bb * bb * 4);
   w.lam = p.take((size_t)bb * 8);
-  w.far = p.take(sizeof(int));
+  w.far = p.take(2 * sizeof(int));
   w.Z = p.take((size_t)bb * (k > 0 ? k : 1) * 4);
   w.S = p.take((size_t)d * (rf > 0 ? rf : 1) * 4);
   w.T = p.take((size_t)(k > 0 ? k : 1) * (rf > 0 ? rf : 1) * 4);
@@ -1355,23 +1368,27 @@ int set_dyn_smem(prac_ctx* ctx) {
   return PRAC_OK;
 }
 
-// src^T src for a d x n block (ld = n) with fp64 sums: the upper triangle of W64
-int panel_gram64(prac_ctx* ctx, const FitWs& w, const float* src, int64_t d, int n, double* W64, int* far) {
+// src^T src for a d x n block with fp64 sums: the upper triangle of W64
+// (pitch lds; near: whether it is near the identity goes to the plan's first word; gate: only where it is set, and then checked against `limit`)
+int panel_gram64(prac_ctx* ctx, const FitWs& w, const float* src, int64_t lds, int64_t d, int n, double* W64, bool near,
+                 const int* gate = nullptr, double limit = 0.0) {
   const int tiles = pg_tiles(n), splits = pg_splits(ctx->n_cu, d, n, w.slab_bytes);
   if (splits * pg_bytes(n) > w.slab_bytes) return PRAC_EINVAL;
   double* slabs = reinterpret_cast<double*>(ctx->ws + w.slabs);
+  int* far = reinterpret_cast<int*>(ctx->ws + w.far);
   const int64_t per = round_up64((d + splits - 1) / splits, PG_K);
   const int used = (int)((d + per - 1) / per);
-  hipLaunchKernelGGL(panel_gram64_kernel, dim3(tiles, used), dim3(256), 0, ctx->stream, src, d, n, per, slabs, far);
+  hipLaunchKernelGGL(panel_gram64_kernel, dim3(tiles, used), dim3(256), 0, ctx->stream, src, lds, d, n, per, slabs, far, gate);
   hipLaunchKernelGGL(panel_gram64_sum_kernel, dim3((unsigned)(pg_bytes(n) / 2048)), dim3(256), 0, ctx->stream, slabs, used, n, W64,
-                     far);
+                     near ? far : nullptr, gate, limit, ctx->d_flag);
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
 }
 
 // src^T src with fp32 sums on the matrix cores (enough for a block whose condition number is small), as fp64 or as the factor
 // of a Newton-Schulz step
-int panel_gram32(prac_ctx* ctx, const FitWs& w, const float* src, int64_t d, int n, double* W64, float* factor, float limit) {
+int panel_gram32(prac_ctx* ctx, const FitWs& w, const float* src, int64_t d, int n, double* W64, float* factor, float limit,
+                 int* again = nullptr) {
   GemmGenArgs g{};
   g.A = src; g.B = src; g.adt = PRAC_F32; g.bdt = PRAC_F32;
   g.a_rs = 1; g.a_cs = n; g.b_rs = n; g.b_cs = 1;
@@ -1396,7 +1413,7 @@ int panel_gram32(prac_ctx* ctx, const FitWs& w, const float* src, int64_t d, int
   }
   if (rc) return rc;
   hipLaunchKernelGGL(panel_gram32_sum_kernel, dim3((n * n + 255) / 256), dim3(256), 0, ctx->stream, sums, splits, n, W64, factor,
-                     limit, ctx->d_flag);
+                     limit, ctx->d_flag, again);
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
 }
@@ -1417,7 +1434,7 @@ int cholqr_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int
                 u32x4* parts, bool any_basis) {
   double* W64 = reinterpret_cast<double*>(ctx->ws + w.W64);
   int* far = any_basis && gram64 && n <= CHR_MAX ? reinterpret_cast<int*>(ctx->ws + w.far) : nullptr;
-  int rc = gram64 ? panel_gram64(ctx, w, src, d, n, W64, far) : panel_gram32(ctx, w, src, d, n, W64, nullptr, 0.f);
+  int rc = gram64 ? panel_gram64(ctx, w, src, n, d, n, W64, far != nullptr) : panel_gram32(ctx, w, src, d, n, W64, nullptr, 0.f);
   if (rc) return rc;
   rc = set_dyn_smem(ctx);
   if (rc) return rc;
@@ -1430,7 +1447,7 @@ int cholqr_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int
   const dim3 tgrid((unsigned)((d + TR_ROWS - 1) / TR_ROWS)), tblock(64 * TR_W);
   const int ncb = gv_col_blocks(n);
   auto solve = [&](auto kern, u32x4* p) {
-    hipLaunchKernelGGL(kern, tgrid, tblock, 0, ctx->stream, src, W64, dst, ldd, d, n, p, ncb, far);
+    hipLaunchKernelGGL(kern, tgrid, tblock, 0, ctx->stream, src, (int64_t)n, W64, dst, ldd, d, n, p, ncb, far, nullptr);
   };
   if (parts && n > GV_MAX) return PRAC_EINVAL;
   if (parts && n <= 128) solve(trsm_right_upper_kernel<1, true>, parts);
@@ -1446,9 +1463,9 @@ int cholqr_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int
 // dst (pitch ldd) = src (1.5 I - 0.5 src^T src): one Newton-Schulz step towards orthonormal columns.  For a block
 // with ||src^T src - I|| = e the result has 0.75 e^2: the cheap second pass after a Cholesky-QR pass,
 // made of two products and no factorisation.
-int polish_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int64_t ldd, int64_t d, int n, float limit) {
+int polish_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int64_t ldd, int64_t d, int n, float limit, int* again = nullptr) {
   float* M32 = reinterpret_cast<float*>(ctx->ws + w.Rinv);
-  int rc = panel_gram32(ctx, w, src, d, n, nullptr, M32, limit);
+  int rc = panel_gram32(ctx, w, src, d, n, nullptr, M32, limit, again);
   if (rc) return rc;
   GemmGenArgs g{};
   g.A = src; g.B = M32; g.adt = PRAC_F32; g.bdt = PRAC_F32;
@@ -1456,6 +1473,26 @@ int polish_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int
   g.M = (int)d; g.N = n; g.K = n; g.k_stride = 1;
   g.out = dst; g.ldo = ldd; g.alpha = 1.f; g.beta = 0.f; g.acc64 = false; g.out64 = nullptr;
   return launch_gemm_generic(ctx, g);
+}
+
+// Two of these steps, the second (in place, in fp64) only where the first starts further than PANEL_NEAR from orthonormal, as it does where a
+// batch is steep or of low rank; decided on the device: three launches that find nothing to do take 8 us, a step 31 (4096 x 256).
+// Behind a panel_gram64 without a gate; n <= 256.
+int polish_once_or_twice(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int64_t ldd, int64_t d, int n) {
+  double* W64 = reinterpret_cast<double*>(ctx->ws + w.W64);
+  int* far = reinterpret_cast<int*>(ctx->ws + w.far);
+  int rc = polish_pass(ctx, w, src, dst, ldd, d, n, 0.5f, far + 1);
+  if (rc) return rc;
+  rc = panel_gram64(ctx, w, dst, ldd, d, n, W64, false, far + 1, PANEL_LAST);
+  if (rc) return rc;
+  auto solve = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)((d + TR_ROWS - 1) / TR_ROWS)), dim3(64 * TR_W), 0, ctx->stream, dst, ldd, W64, dst, ldd, d, n,
+                       nullptr, 0, far, far + 1);
+  };
+  if (n <= 128) solve(trsm_right_upper_kernel<1, false>);
+  else solve(trsm_right_upper_kernel<2, false>);
+  PRAC_HIP_TRY(ctx, hipGetLastError());
+  return PRAC_OK;
 }
 
 // out (d x n fp32, pitch ldo) <- orth(Y): `passes` rounds of Cholesky-QR (the first one shifted), then
@@ -1467,6 +1504,7 @@ int cholqr(prac_ctx* ctx, const FitWs& w, float* Y, float* V, int64_t d, int n, 
            int any_basis_from = 1 << 30) {
   float* src = Y;
   for (int pass = 0; pass < passes + polish; ++pass) {
+    if (pass == passes && polish == 2 && n <= CHR_MAX) return polish_once_or_twice(ctx, w, src, out, ldo, d, n);
     const bool last = pass == passes + polish - 1;
     // a solve may stay where it is, a product may not
     float* dst = last ? out : (src == Y ? V : Y);
@@ -1475,11 +1513,11 @@ int cholqr(prac_ctx* ctx, const FitWs& w, float* Y, float* V, int64_t d, int n, 
     // Later passes work on a block that is orthonormal up to the first pass's error, except in
     // directions where the input was rank deficient: there the Gram matrix is zero up to rounding
     // (a few 1e-16), and the shift has to be safely above that for the pivot to stay positive.
-    // the last Newton-Schulz step must start within 3e-3 of orthonormal to end below 1e-5 (0.75 e^2); earlier
+    // the last Newton-Schulz step must start within PANEL_LAST of orthonormal to end below 1e-5; earlier
     // ones may start anywhere inside the step's region of convergence
     int rc = pass < passes ? cholqr_pass(ctx, w, src, dst, ldd, d, n, pass == 0 ? first_shift : 1e-13, pass > 0 || gram64_first,
                                          last ? parts : nullptr, pass >= any_basis_from)
-                           : polish_pass(ctx, w, src, dst, ldd, d, n, last ? 3e-3f : 0.5f);
+                           : polish_pass(ctx, w, src, dst, ldd, d, n, last ? PANEL_LAST : 0.5f);
     if (rc) return rc;
     src = dst;
   }
