@@ -1220,8 +1220,9 @@ __global__ __launch_bounds__(256) void panel_gram64_sum_kernel(const double* __r
 // The sum of the fp32 partial Gram matrices of a block, as fp64 (W64 != nullptr) or as the factor 1.5 I - 0.5 W of a Newton-Schulz step.
 // For the latter W is the Gram matrix of a block that should be close to orthonormal: an entry further than `limit` from the
 // identity (or not finite) raises bit 1 of *flag - the step that follows squares the distance, so a block that far off
-// does not come out orthonormal to fp32 rounding.  again (or nullptr): set where an entry is further than PANEL_NEAR.  (slabs may be M32 itself)
+// does not come out orthonormal to fp32 rounding.  again (or nullptr): set where an entry is further than PANEL_ONCE.  (slabs may be M32 itself)
 constexpr float PANEL_LAST = 3e-3f;  // up to here a last step ends below 1e-5 (0.75 e^2)
+constexpr float PANEL_ONCE = 1e-4f;  // and up to here below fp32 rounding
 __global__ __launch_bounds__(256) void panel_gram32_sum_kernel(const float* slabs, int splits, int n, double* W64, float* M32,
                                                                float limit, int* flag, int* again) {
   bool off = false, more = false;
@@ -1235,7 +1236,7 @@ __global__ __launch_bounds__(256) void panel_gram32_sum_kernel(const float* slab
     } else {
       const float id = i / n == i % n ? 1.f : 0.f;
       off = off || !(fabsf(w - id) <= limit);
-      more = more || !(fabsf(w - id) <= (float)PANEL_NEAR);
+      more = more || !(fabsf(w - id) <= PANEL_ONCE);
       M32[i] = 1.5f * id - 0.5f * w;
     }
   }
@@ -1475,7 +1476,7 @@ int polish_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int
   return launch_gemm_generic(ctx, g);
 }
 
-// Two of these steps, the second (in place, in fp64) only where the first starts further than PANEL_NEAR from orthonormal, as it does where a
+// Two of these steps, the second (in place, in fp64) only where the first starts further than PANEL_ONCE from orthonormal, as it does where a
 // batch is steep or of low rank; decided on the device: three launches that find nothing to do take 8 us, a step 31 (4096 x 256).
 // Behind a panel_gram64 without a gate; n <= 256.
 int polish_once_or_twice(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int64_t ldd, int64_t d, int n) {
