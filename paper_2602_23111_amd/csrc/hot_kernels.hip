@@ -47,27 +47,28 @@ __global__ __launch_bounds__(256) void pack_pfrag_kernel(const float* __restrict
 // number have its sign, and where one would be zero the part before it is cut into halves (down to 2^-124): an infinite
 // element of X then meets what it would meet in the product with P.
 // HALVES: the f16 parts too (h = 2^12 P and l = what is left of it, each to nearest, an infinity and NaN as they are), and the largest |P| per column.
-// A workgroup has a k-tile (16 k-blocks) of one column block, four k-blocks a wave.
-template <bool HALVES>
+// A workgroup has KW k-blocks per wave of one column block; HALVES: four, a whole k-tile.
+template <bool HALVES, int KW>
 __global__ __launch_bounds__(256) void pack_pfrag_split_kernel(const float* __restrict__ P, int64_t d, int64_t ldp, int c,
                                                                int ncb, bf16_t* __restrict__ out, bf16_t* __restrict__ half,
                                                                float* __restrict__ pmax) {
   const int lane = threadIdx.x & 63, j = lane & 31, h = lane >> 5, wave = threadIdx.x >> 6;
-  const int cb = blockIdx.x % ncb;
-  const int64_t kt = blockIdx.x / ncb;
+  static_assert(!HALVES || KW == 4, "");
+  const int cb = blockIdx.x % ncb, k0 = (blockIdx.x / ncb * 4 + wave) * KW;  // its first k-block
+  const int64_t kt = k0 / 16;
   const int col = cb * 32 + j;
-  float v[4][8];
+  float v[KW][8];
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
+  for (int q = 0; q < KW; ++q)
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int64_t kk = kt * 256 + (4 * wave + q) * 16 + 8 * h + e;
+      const int64_t kk = (int64_t)(k0 + q) * 16 + 8 * h + e;
       v[q][e] = (col < c && kk < d) ? P[kk * ldp + col] : 0.f;
     }
   uint32_t top = 0;  // bits of the largest magnitude (those of a NaN are above an infinity's)
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int k = 4 * wave + q;
+  for (int q = 0; q < KW; ++q) {
+    const int k = (k0 + q) & 15;
     float part[3][8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -1105,9 +1106,9 @@ int launch_pack_pfrag(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int
 int launch_pack_pfrag_split(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int c, int nkb, int ncb, bf16_t* out, bf16_t* half,
                             float* pmax) {
   if (nkb % 16 != 0 || (half && !pmax)) return PRAC_EINVAL;
-  const dim3 grid((unsigned)(nkb / 16 * ncb)), block(256);
-  if (half) hipLaunchKernelGGL(pack_pfrag_split_kernel<true>, grid, block, 0, ctx->stream, P, d, ldp, c, ncb, out, half, pmax);
-  else hipLaunchKernelGGL(pack_pfrag_split_kernel<false>, grid, block, 0, ctx->stream, P, d, ldp, c, ncb, out, half, pmax);
+  const dim3 grid((unsigned)(nkb / (half ? 16 : 4) * ncb)), block(256);
+  if (half) hipLaunchKernelGGL((pack_pfrag_split_kernel<true, 4>), grid, block, 0, ctx->stream, P, d, ldp, c, ncb, out, half, pmax);
+  else hipLaunchKernelGGL((pack_pfrag_split_kernel<false, 1>), grid, block, 0, ctx->stream, P, d, ldp, c, ncb, out, half, pmax);
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
 }

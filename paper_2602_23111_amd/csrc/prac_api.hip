@@ -519,10 +519,7 @@ CompressPlan plan_compress(int n_cu, CompressPath path, bool fused, bool packed,
                            int c, int64_t m) {
   CompressPlan q{};
   WsPlan plan;
-  // Two f16 parts of P (up to 2^-23 of an element away from it) from d = 2048 on: the fp32 sums of three bf16 parts, a third more of them, are
-  // further off there (elements of C that round otherwise than the exact product, two / three parts, P orthonormal: d = 2049 3.0e-4 / 3.5e-4, 5461
-  // 4.8e-4 / 5.8e-4; 259 1.1e-4 / 0.9e-4), and what they save below is little.
-  q.halves = path == CompressPath::STREAM_ANY && !fused && d >= 2048;
+  q.halves = path == CompressPath::STREAM_ANY && !fused && compress_halves(n_cu, N, d, c);
   if (path != CompressPath::STRIDED) {
     const LpLayout l = lp_layout(d, c);
     if (path == CompressPath::STREAM)

@@ -155,6 +155,7 @@ int launch_compress_ws(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d
                        int c, bf16_t* C, int64_t ldc, bool packed, const bf16_t* Wfrag, int ncb_w, int m,
                        bf16_t* Y, int64_t ldy, bool any_element = false, float* part = nullptr, const bf16_t* Phalf = nullptr,
                        const float* pmax = nullptr, int* redo = nullptr);
+bool compress_halves(int n_cu, int64_t N, int64_t d, int c);  // whether it should be given them
 // workgroups of that launch at most (ints of redo)
 inline int64_t compress_ws_workgroups(int n_cu, int64_t N, int c) { return std::max<int64_t>((N + 127) / 128 * ((c + 127) / 128), n_cu); }
 // C = X P by small tiles whose sum over d is split over a workgroup's waves (tile_kernels.hip); aligned rows only

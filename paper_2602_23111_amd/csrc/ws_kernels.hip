@@ -229,7 +229,7 @@ __device__ __forceinline__ void drain_mfma(f32x16 (&acc)[NACC], u32x4 (&ring)[8]
 template <int FN, int NCH, int NIF, bool UA, bool HALVES>
 __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int bid = touch_kernel_args<sizeof(CompressWsArgs)>(blockIdx.x);
+  const int bid = touch_kernel_args<(UA ? sizeof(CompressWsArgs) : offsetof(CompressWsArgs, Phalf))>(blockIdx.x);
 
   // XCD-aware order: consecutive logical tiles (same rows, next column group) on one XCD
   const int total = a.tiles_m * a.col_groups * a.splits;
@@ -1765,6 +1765,22 @@ static void compress_ranges(int n_cu, int tiles, int nk, int fn, int parts, int&
     if (cost(s) < 0.9 * cost(1) && cost(s) < cost(best)) best = s;
   kt_per = (nk + best - 1) / best;
   splits = (nk + kt_per - 1) / kt_per;  // no empty range
+}
+
+// Two f16 parts of P instead of three bf16 ones for a compress of rows on any element: from d = 2048 on (up to 2^-23 of an element of P away
+// from it, but the fp32 sums of three parts, a third more of them, are further off there: elements of C that round otherwise than the exact
+// product, two / three parts, P orthonormal: d = 2049 3.0e-4 / 3.5e-4, 5461 4.8e-4 / 5.8e-4; 259 1.1e-4 / 0.9e-4), and where the part saved is
+// worth more than the second launch and the larger packing (7 us): 2.1 us per k-tile and round of workgroups, 0.8 with the narrow tile.
+// The step with three / two parts (N, d, c): 32768, 5461, 256 288 / 241 us; 23863, 6730, 37 172.4 / 156.9; 6754, 2132, 94 91.8 / 97.3; 9528, 2923, 74
+// 98.8 / 102.7; 970, 4111, 305 143.3 / 148.4.
+bool compress_halves(int n_cu, int64_t N, int64_t d, int c) {
+  if (d < 2048) return false;
+  const int64_t tiles_m = (N + WS_BM - 1) / WS_BM, wide = ((c + 31) / 32 + 7) / 8;
+  const int fn = c <= 128 || tiles_m * wide * 2 <= n_cu ? 1 : 2, nk = (int)((d + WS_BK - 1) / WS_BK);
+  const int64_t tiles = tiles_m * ((c + 128 * fn - 1) / (128 * fn));
+  int splits = 1, kt_per = nk;
+  if (tiles < n_cu) compress_ranges(n_cu, (int)tiles, nk, fn, WS_SPLIT, splits, kt_per);
+  return (double)((tiles * splits + n_cu - 1) / n_cu) * kt_per * (fn == 2 ? 2.1 : 0.8) > 9.0;
 }
 
 int launch_compress_ws(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d, const bf16_t* Pfrag, int ncb, int c,

@@ -274,8 +274,11 @@ def test_rows_that_start_on_any_element_meet_the_fp32_basis(ctx, d, c):
         assert ((C.double().cpu() - ref).abs() <= bound).all()
 
 
-@pytest.mark.parametrize("what", ["plain", "late", "zero_first", "tiny", "huge", "wide_range", "p_small", "p_large", "p_mixed", "p_zero_columns"])
-@pytest.mark.parametrize("N,d,c,packed", [(300, 2049, 40, False), (140, 2303, 200, True), (2000, 4099, 130, False)])  # the last: ranges of d
+@pytest.mark.parametrize("N,d,c,packed,what", [(4200, 2049, 1000, False, w) for w in (
+    "plain", "late", "zero_first", "tiny", "huge", "wide_range", "p_small", "p_large", "p_mixed", "p_zero_columns")] + [
+        (16600, 2819, 40, True, "plain"), (16600, 2819, 40, True, "late"), (16600, 2819, 40, True, "p_mixed"),      # the narrow tile
+        (12700, 9473, 33, False, "plain"), (12700, 9473, 33, False, "zero_first"),                                 # two ranges of d
+        (6754, 2132, 94, False, "plain"), (300, 2049, 40, True, "late"), (4200, 2047, 1000, False, "plain")])      # three parts by the rule
 def test_rows_on_any_element_with_two_parts_of_the_basis(ctx, N, d, c, packed, what):
     """From 2048 features on the basis goes in as two f16 parts, and three bf16 parts take over per tile where those do not hold X's rows or P's
     columns: elements far above a row's first ones, rows that start with zeros, numbers at the ends of the range.  C against the
@@ -304,7 +307,8 @@ def test_rows_on_any_element_with_two_parts_of_the_basis(ctx, N, d, c, packed, w
     elif what == "p_zero_columns":
         P[:, ::3] = 0.0
     X = X.bfloat16()
-    C = ctx.compress(rows_on_any_element(X.cpu(), d, True), P, layout=C_PACKED if packed else C_ROWMAJOR)
+    block = torch.full((N * d + 1,), float("nan"), dtype=torch.bfloat16, device=DEV)  # contiguous rows, 2 bytes past a 16-byte boundary
+    C = ctx.compress(block[1:].view(N, d).copy_(X), P, layout=C_PACKED if packed else C_ROWMAJOR)
     if packed:
         C = ctx.unpack_compressed(C, N, c)
     ctx.sync_status()
@@ -316,7 +320,7 @@ def test_rows_on_any_element_with_two_parts_of_the_basis(ctx, N, d, c, packed, w
 
 def test_infinities_with_two_parts_of_the_basis(ctx):
     """Infinities and NaN in X and in P, from 2048 features on: as in the plain product, rows and columns beside them untouched."""
-    N, d, c = 300, 2051, 40
+    N, d, c = 4200, 2051, 1000
     g = torch.Generator().manual_seed(3)
     P = torch.randn((d, c), generator=g)
     X = torch.rand((N, d), generator=g).bfloat16() + 1
@@ -330,7 +334,7 @@ def test_infinities_with_two_parts_of_the_basis(ctx):
     rest[[4, 133, 134]] = False
     assert torch.equal(C[4, :38], torch.sign(P[2050, :38]) * float("inf")) and torch.equal(C[133, :38], -torch.sign(P[3, :38]) * float("inf"))
     assert C[134].isnan().all() and C[:, 38].isnan().all() and (C[rest, 39] == float("inf")).all()
-    assert C[rest, :38].isfinite().all()
+    assert C[rest][:, [j for j in range(c) if j not in (38, 39)]].isfinite().all()
 
 
 def test_infinity_in_rows_that_start_on_any_element(ctx):
