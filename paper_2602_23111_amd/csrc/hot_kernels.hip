@@ -42,6 +42,36 @@ __global__ __launch_bounds__(256) void pack_pfrag_kernel(const float* __restrict
   }
 }
 
+// All four layouts of the packed basis from one read of P, a 32 x 32 piece per workgroup: three launches, each with a read of its own, took
+// 17.7 us at 4096 x 512 and two gaps between them, this one 7.6.
+__global__ __launch_bounds__(256) void pack_basis_kernel(const float* __restrict__ P, int64_t d, int64_t ldp, int c, PackedBasis o) {
+  __shared__ float tile[32][33];
+  const int64_t i0 = (int64_t)blockIdx.y * 32;  // feature (row of P)
+  const int j0 = blockIdx.x * 32;               // basis column
+  const int tx = threadIdx.x & 31;
+#pragma unroll
+  for (int r = threadIdx.x >> 5; r < 32; r += 8) tile[r][tx] = i0 + r < d && j0 + tx < c ? P[(i0 + r) * ldp + j0 + tx] : 0.f;
+  __syncthreads();
+  const int t = threadIdx.x & 127, lane = t & 63, q = t >> 6, x = lane & 31, h = lane >> 5;
+  auto eight = [&](auto&& at) {
+    u32x4 w;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = pack2(at(2 * e), at(2 * e + 1));
+    return w;
+  };
+  if (threadIdx.x < 128) {
+    const int r = t >> 2, ch = 8 * (t & 3);
+    if (i0 + r < d && j0 < o.ldpn) *reinterpret_cast<u32x4*>(o.Pn + (i0 + r) * o.ldpn + j0 + ch) = eight([&](int e) { return tile[r][ch + e]; });
+    reinterpret_cast<u32x4*>(o.Pf)[((i0 / 16 + q) * o.ncb + blockIdx.x) * 64 + lane] = eight([&](int e) { return tile[16 * q + 8 * h + e][x]; });
+  } else {
+    const int r = t >> 2, ch = 8 * (t & 3);
+    if (j0 + r < c && i0 < o.ldpt) *reinterpret_cast<u32x4*>(o.Pt + (j0 + r) * o.ldpt + i0 + ch) = eight([&](int e) { return tile[ch + e][r]; });
+    if ((int)blockIdx.y < o.nrb && j0 / 16 + q < o.nckb)
+      reinterpret_cast<u32x4*>(o.Pa)[((int64_t)blockIdx.y * o.nckb + j0 / 16 + q) * 64 + lane] =
+          eight([&](int e) { return tile[x][16 * q + 8 * h + e]; });
+  }
+}
+
 // The fp32 P exactly, in the same order: a tile of 16 k-blocks three times, as three bf16 parts that add up to it.  A part is
 // what is left with the low half of its bits cut off: 8 bits of the mantissa each, so the third one is exact.  The parts of a
 // number have its sign, and where one would be zero the part before it is cut into halves (down to 2^-124): an infinite
@@ -320,31 +350,6 @@ __global__ __launch_bounds__(256) void reduce_to_tfrag_kernel(Args a) {
     o.z = pack2_hw(patch[8 * hh + 4][nbl * 32 + j], patch[8 * hh + 5][nbl * 32 + j]);
     o.w = pack2_hw(patch[8 * hh + 6][nbl * 32 + j], patch[8 * hh + 7][nbl * 32 + j]);
     reinterpret_cast<u32x4*>(a.Tf[h])[((int64_t)kb * nmb + np * 2 + nbl) * 64 + lane] = o;
-  }
-}
-
-// P as an A operand in fragment order: Pa[(rb * nkb + kb) * 64 + lane][e] = bf16(P[32 rb + i][16 kb + 8 h + e]),
-// lane = 32 h + i; zero outside d x c.
-__global__ __launch_bounds__(256) void pack_pafrag_kernel(const float* __restrict__ P, int64_t d, int64_t ldp, int c,
-                                                          int nrb, int nkb, bf16_t* __restrict__ out) {
-  const int64_t total = (int64_t)nrb * nkb * 64;
-  for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < total; g += (int64_t)gridDim.x * blockDim.x) {
-    const int lane = (int)(g & 63), i = lane & 31, h = lane >> 5;
-    const int64_t blk = g >> 6;
-    const int kb = (int)(blk % nkb);
-    const int64_t row = (blk / nkb) * 32 + i;
-    float f[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int k = kb * 16 + 8 * h + e;
-      f[e] = (row < d && k < c) ? P[row * ldp + k] : 0.f;
-    }
-    u32x4 o;
-    o.x = pack2(f[0], f[1]);
-    o.y = pack2(f[2], f[3]);
-    o.z = pack2(f[4], f[5]);
-    o.w = pack2(f[6], f[7]);
-    reinterpret_cast<u32x4*>(out)[g] = o;
   }
 }
 
@@ -1165,9 +1170,10 @@ int launch_reduce_to_tfrag(prac_ctx* ctx, int n_out, const float* const* slabs, 
   return PRAC_OK;
 }
 
-int launch_pack_pafrag(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int c, int nrb, int nkb, bf16_t* out) {
-  hipLaunchKernelGGL(pack_pafrag_kernel, dim3(grid_for((int64_t)nrb * nkb * 64, ctx->n_cu)), dim3(256), 0, ctx->stream,
-                     P, d, ldp, c, nrb, nkb, out);
+int launch_pack_basis(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int c, const PackedBasis& o) {
+  if (o.nkb % 2 != 0 || (int64_t)o.nkb * 16 < std::max<int64_t>(o.ldpt, (int64_t)o.nrb * 32) || (int64_t)o.ncb * 32 < std::max<int64_t>(o.ldpn, 16 * o.nckb))
+    return PRAC_EINVAL;
+  hipLaunchKernelGGL(pack_basis_kernel, dim3((unsigned)o.ncb, (unsigned)(o.nkb / 2)), dim3(256), 0, ctx->stream, P, d, ldp, c, o);
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
 }

@@ -65,29 +65,6 @@ __global__ __launch_bounds__(256) void philox_kernel(uint32_t seed_lo, uint32_t 
   }
 }
 
-// ---- basis packing ---------------------------------------------------------------
-// Pt (c x ldpt) = bf16(P^T), Pn (d x ldpn) = bf16(P); padding columns are zero.
-__global__ __launch_bounds__(256) void pack_basis_kernel(const float* __restrict__ P, int64_t d, int64_t ldp, int c,
-                                                         bf16_t* __restrict__ Pt, int64_t ldpt,
-                                                         bf16_t* __restrict__ Pn, int64_t ldpn) {
-  __shared__ float tile[32][33];
-  const int i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;  // i: feature (row of P), j: basis column
-  const int tx = threadIdx.x % 32, ty = threadIdx.x / 32;  // 32 x 8
-  for (int r = ty; r < 32; r += 8) {
-    const int64_t i = i0 + r;
-    const int j = j0 + tx;
-    const float v = (i < d && j < c) ? P[i * ldp + j] : 0.f;
-    tile[r][tx] = v;
-    if (i < d && j < ldpn) Pn[i * ldpn + j] = f32_to_bf16(v);
-  }
-  __syncthreads();
-  for (int r = ty; r < 32; r += 8) {
-    const int j = j0 + r;
-    const int64_t i = i0 + tx;
-    if (j < c && i < ldpt) Pt[(int64_t)j * ldpt + i] = f32_to_bf16(tile[tx][r]);
-  }
-}
-
 // ---- split reductions ------------------------------------------------------------
 // (out may be the first slab: an element is read by the thread that writes it, before)
 __global__ __launch_bounds__(256) void reduce_slabs_kernel(const float* part, int splits, int64_t stride, float* out,
@@ -237,16 +214,6 @@ int launch_philox(prac_ctx* ctx, uint64_t seed, uint32_t draw, uint32_t stream, 
   const uint32_t lo = (uint32_t)(seed & 0xFFFFFFFFu), hi = (uint32_t)(seed >> 32);
   if (normal) hipLaunchKernelGGL(philox_kernel<true>, dim3(g), dim3(256), 0, ctx->stream, lo, hi, draw, stream, out, n);
   else hipLaunchKernelGGL(philox_kernel<false>, dim3(g), dim3(256), 0, ctx->stream, lo, hi, draw, stream, out, n);
-  PRAC_HIP_TRY(ctx, hipGetLastError());
-  return PRAC_OK;
-}
-
-int launch_pack_basis(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int c, bf16_t* Pt, int64_t ldpt,
-                      bf16_t* Pn, int64_t ldpn) {
-  // cover i < max(d, ldpt) and j < max(c, ldpn) so that the padding is written too
-  const int64_t ni = ldpt > d ? ldpt : d, nj = ldpn > c ? ldpn : c;
-  dim3 grid((unsigned)((nj + 31) / 32), (unsigned)((ni + 31) / 32));
-  hipLaunchKernelGGL(pack_basis_kernel, grid, dim3(256), 0, ctx->stream, P, d, ldp, c, Pt, ldpt, Pn, ldpn);
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
 }

@@ -459,12 +459,8 @@ int prac_pack_basis(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int c
   if (!ctx) return PRAC_ENOCTX;
   const LpLayout l = lp_layout(d, c);
   char* base = reinterpret_cast<char*>(P_lp);
-  int rc = launch_pack_basis(ctx, P, d, ldp, c, reinterpret_cast<bf16_t*>(base), l.ldpt,
-                             reinterpret_cast<bf16_t*>(base + l.off_pn), l.ldpn);
-  if (rc) return rc;
-  rc = launch_pack_pfrag(ctx, P, d, ldp, c, l.nkb, l.ncb, reinterpret_cast<bf16_t*>(base + l.off_pf));
-  if (rc) return rc;
-  return launch_pack_pafrag(ctx, P, d, ldp, c, l.nrb, l.nckb, reinterpret_cast<bf16_t*>(base + l.off_pa));
+  auto at = [&](size_t off) { return reinterpret_cast<bf16_t*>(base + off); };
+  return launch_pack_basis(ctx, P, d, ldp, c, {at(0), at(l.off_pn), at(l.off_pf), at(l.off_pa), l.ldpt, l.ldpn, l.nkb, l.ncb, l.nrb, l.nckb});
 }
 
 int prac_fit_basis(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, int64_t d, int64_t ldx, int k, int r,

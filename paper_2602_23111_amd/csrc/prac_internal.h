@@ -140,8 +140,15 @@ int launch_reduce_symmetric(prac_ctx* ctx, const float* part, int splits, int n,
 int launch_reduce_transpose_f32(prac_ctx* ctx, const float* part, int splits, int M, int N, float* out, int64_t ldo);
 int launch_philox(prac_ctx* ctx, uint64_t seed, uint32_t draw, uint32_t stream, void* out, int64_t n,
                   bool normal);
-int launch_pack_basis(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int c, bf16_t* Pt,
-                      int64_t ldpt, bf16_t* Pn, int64_t ldpn);
+// The packed basis, bf16 copies of P (d x c) with zeros behind its ends: Pt (c x ldpt) = P^T, Pn (d x ldpn) = P, Pf [nkb][ncb][64][8], a B operand
+// in fragment order, and Pa [nrb][nckb][64][8], P as an A operand: block (rb, kb), lane 32 h + i, element e is P[32 rb + i][16 kb + 8 h + e].
+// ldpt, ldpn multiples of 64; Pf's blocks cover all of the others.
+struct PackedBasis {
+  bf16_t *Pt, *Pn, *Pf, *Pa;
+  int64_t ldpt, ldpn;
+  int nkb, ncb, nrb, nckb;
+};
+int launch_pack_basis(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int c, const PackedBasis& o);
 int launch_cast_out(prac_ctx* ctx, const float* src, int64_t lds, void* dst, prac_dtype odt,
                     int64_t ldd, int rows, int cols, float beta);
 
@@ -251,7 +258,6 @@ int launch_pack_c(prac_ctx* ctx, const bf16_t* C, int64_t ldc, int N, int c, bf1
 // last tile with that)
 int launch_reduce_to_tfrag(prac_ctx* ctx, int n_out, const float* const* slabs, int splits, int c, const int* m, int k_lo,
                            float scale_hi, int nkb, const int* nmb, bf16_t* const* Tf, const int* sld, const CtdyTails& tails);
-int launch_pack_pafrag(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int c, int nrb, int nkb, bf16_t* out);
 // dW_h (d x m_h) = P T_h (+ beta dW_h) for n_out <= PRAC_CTDY_MAX_OUT outputs in one launch
 int launch_pt(prac_ctx* ctx, const bf16_t* Pa, int n_out, const bf16_t* const* Tf, int d, const int* m, int nkb,
               const int* nmb, void* const* dW, const int64_t* lddw, bool out_bf16, float beta);
