@@ -1009,7 +1009,6 @@ struct CtdyWsArgs {
   int tok_per_split;   // multiple of 128
   int tiles_n;         // column tiles of 128 over all outputs
   int row_groups;      // groups of 8 column blocks (256 rows of T) over c
-  int upper;           // T is symmetric (C and dY hold the same matrix): only tiles that reach its diagonal or lie above it
   CtdyTails tails;     // TAILS
   int groups_per_xcd;  // MODE > 0: column tiles per XCD
   // ---- whole weight gradient in this launch (MODE > 0): the workgroups of one column tile sum their
@@ -1382,7 +1381,8 @@ __device__ __forceinline__ void wgrad_tail(const CtdyWsArgs& a, unsigned char* s
   }
 }
 
-// MODE 0: partial slabs only; 1 / 2: the whole weight gradient (dW in fp32 / bf16).  UA: rows of dY that start on
+// MODE 0: partial slabs only; -1: those of a symmetric T (C and dY hold the same matrix), only tiles that reach its diagonal or lie above
+// it; 1 / 2: the whole weight gradient (dW in fp32 / bf16).  UA: rows of dY that start on
 // any element (see frag_utils.h).  TAILS (MODE 0): token ranges of unequal length (see CtdyTails); a helper works through the
 // tails of a few tiles one after the other, its loaders a segment ahead of the matrix waves' stores.
 // HALF (c <= 128, no TAILS): T's tile has 128 rows, of which a matrix wave has 64 and every other k-block; the two sums of a row
@@ -1391,14 +1391,14 @@ __device__ __forceinline__ void wgrad_tail(const CtdyWsArgs& a, unsigned char* s
 template <int MODE, bool UA, bool TAILS, bool HALF>
 __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int bid = touch_kernel_args<(MODE != 0 ? sizeof(CtdyWsArgs) : TAILS ? offsetof(CtdyWsArgs, cnt)
+  const int bid = touch_kernel_args<(MODE > 0 ? sizeof(CtdyWsArgs) : TAILS ? offsetof(CtdyWsArgs, cnt)
                                                                             : offsetof(CtdyWsArgs, tails))>(blockIdx.x);
 
   int tn = 0, rg = 0, split = 0;
   int run_beg = 0, run_end = -1;  // helpers: units of the tails of all tiles
-  if constexpr (MODE == 0) {
-    const int per_split = TAILS     ? a.tails.t1 - a.tails.t0
-                          : a.upper ? ctdy_upper_tiles(a.tiles_n, a.row_groups)
+  if constexpr (MODE <= 0) {
+    const int per_split = TAILS      ? a.tails.t1 - a.tails.t0
+                          : MODE < 0 ? ctdy_upper_tiles(a.tiles_n, a.row_groups)
                                     : a.tiles_n * a.row_groups;
     const int mains = per_split * (TAILS ? a.tails.main : a.splits);
     const int total = mains + (TAILS ? a.tails.helpers : 0);
@@ -1412,10 +1412,14 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
       run_beg = max(run_beg, a.tails.t0 * a.tails.tail);
     } else {
       const int t = (TAILS ? a.tails.t0 : 0) + logical % per_split;
-      if (!TAILS && a.upper) {
+      if (MODE < 0) {
         tn = t;
         for (int left = a.tiles_n; tn >= left; left -= 2, ++rg) tn -= left;  // row group rg: column tiles 2 rg ..
         tn += 2 * rg;
+      } else if (!TAILS || per_split == a.tiles_n * a.row_groups) {
+        // the row groups of a column tile next to each other on one XCD: they read the same rows of dY
+        tn = t / a.row_groups;
+        rg = t % a.row_groups;
       } else {
         tn = t % a.tiles_n;
         rg = t / a.tiles_n;
@@ -1558,7 +1562,7 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
       __syncthreads();
     }
     } while (TAILS && next_segment());
-    if constexpr (MODE == 0) return;
+    if constexpr (MODE <= 0) return;
     if constexpr (HALF) __syncthreads();  // the matrix waves' exchange
   } else {
   // -------------------------------------------------------------- matrix waves
@@ -1727,7 +1731,7 @@ __global__ __launch_bounds__(512) void ctdy_ws_kernel(CtdyWsArgs a) {
   }
   } while (TAILS && next_segment());
   }
-  if constexpr (MODE != 0) {
+  if constexpr (MODE > 0) {
     // all eight waves: the slabs of this column tile -> T -> dW (see wgrad_tail)
     const int members = a.splits * a.row_groups;
     wgrad_tail<MODE == 2>(a, smem_raw, tn, hout, n0, split * a.row_groups + rg, members);
@@ -1933,7 +1937,6 @@ int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, co
   fill_ctdy_args(a, Cpk, c, N, n_out, dY, lddy, m, slabs, splits, sld);
   if (range_tokens > 0) a.tok_per_split = range_tokens;
   const bool uneven = tails && tails->main > 0;
-  a.upper = upper ? 1 : 0;
   if (upper && (uneven || n_out != 1 || m[0] != c)) return PRAC_EINVAL;
   if (uneven) {
     // every token of every tile belongs to one main range or to a tail, every tile of the launch has its blocks
@@ -1948,23 +1951,25 @@ int launch_ctdy_ws(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out, co
   const size_t smem = (size_t)CW_STAGES * CW_STAGE;
   const int total = uneven ? (tails->t1 - tails->t0) * tails->main + tails->helpers
                            : (upper ? ctdy_upper_tiles(a.tiles_n, a.row_groups) : a.tiles_n * a.row_groups) * splits;
-  static bool done_dev[PRAC_MAX_DEVICES][5] = {};
+  static bool done_dev[PRAC_MAX_DEVICES][7] = {};
   bool* done = done_dev[ctx->device % PRAC_MAX_DEVICES];
   const dim3 grid(((total + 7) / 8) * 8), block(512);
-#define PRAC_CTDY_CASE(I, UA, TAILS, HALF)                                  \
+#define PRAC_CTDY_CASE(I, MODE, UA, TAILS, HALF)                            \
   case I: {                                                                 \
-    constexpr auto kern = ctdy_ws_kernel<0, UA, TAILS, HALF>;               \
+    constexpr auto kern = ctdy_ws_kernel<MODE, UA, TAILS, HALF>;            \
     int rc = set_smem(ctx, kern, smem, done[I]);                            \
     if (rc) return rc;                                                      \
     PRAC_LAUNCH(ctx, kern, grid, block, smem, a);                           \
     break;                                                                  \
   }
-  switch (uneven ? 2 : (any_element ? 1 : 0) + (ctdy_half(c) ? 3 : 0)) {
-    PRAC_CTDY_CASE(0, false, false, false)
-    PRAC_CTDY_CASE(1, true, false, false)
-    PRAC_CTDY_CASE(2, false, true, false)
-    PRAC_CTDY_CASE(3, false, false, true)
-    PRAC_CTDY_CASE(4, true, false, true)
+  switch (uneven ? 2 : (any_element ? 1 : 0) + (upper ? 5 : ctdy_half(c) ? 3 : 0)) {
+    PRAC_CTDY_CASE(0, 0, false, false, false)
+    PRAC_CTDY_CASE(1, 0, true, false, false)
+    PRAC_CTDY_CASE(2, 0, false, true, false)
+    PRAC_CTDY_CASE(3, 0, false, false, true)
+    PRAC_CTDY_CASE(4, 0, true, false, true)
+    PRAC_CTDY_CASE(5, -1, false, false, false)
+    PRAC_CTDY_CASE(6, -1, true, false, false)
   }
 #undef PRAC_CTDY_CASE
   PRAC_HIP_TRY(ctx, hipGetLastError());
