@@ -1622,7 +1622,7 @@ int fit_basis_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, in
       // One power step from an orthonormal block leaves a condition number of at most lambda_1 /
       // lambda_k, within reach of a Cholesky factor of the fp64 Gram matrix with a shift just above its
       // rounding (so that a rank-deficient batch still factors); the last
-      // iteration then gets two Newton-Schulz steps in place of a second factorisation.
+      // iteration then gets one or two Newton-Schulz steps in place of a second factorisation.
       const bool last = it == o.iters - 1;
       rc = cholqr(ctx, L, Y, V, d, k, 1, 1e-14, last ? P : V, last ? ldp : (int64_t)k, last ? 2 : 0);
       if (rc) return rc;
