@@ -116,27 +116,6 @@ static __device__ __forceinline__ bf16x8 as_frag(u32x4 v) {
   return c.f;
 }
 
-// two fp32 times s -> packed f16 (to nearest, an infinity where it does not fit), `lo` in the low half
-static __device__ __forceinline__ uint32_t scaled_pk_f16(float lo, float hi, float s) {
-  uint32_t r;
-  asm("v_fma_mixlo_f16 %0, %1, %2, 0 op_sel_hi:[0,0,0]" : "=v"(r) : "v"(lo), "v"(s));
-  asm("v_fma_mixhi_f16 %0, %1, %2, 0 op_sel_hi:[0,0,0]" : "+v"(r) : "v"(hi), "v"(s));
-  return r;
-}
-static __device__ __forceinline__ uint32_t max_pk_u16(uint32_t a, uint32_t b) {
-  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
-}
-// the largest of 32 lanes (0 - 31, 32 - 63), in each of them
-static __device__ __forceinline__ uint32_t max_half_wave(uint32_t x) {
-  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, true));   // lane ^ 1
-  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xf, 0xf, true));   // lane ^ 2
-  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xf, 0xf, true));  // the mirror image in eight lanes
-  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x140, 0xf, 0xf, true));  // in sixteen
-  const auto s = __builtin_amdgcn_permlane16_swap(x, x, false, false);                 // rows of sixteen change places
-  return max(s[0], s[1]);
-}
-
 // A kernel's arguments sit in memory no cache holds yet when its first waves start, and the compiler
 // fetches them where they are first used: a few dependent rounds of scalar loads, each to another
 // 64-byte line, each a full memory round trip before the first byte of data can be requested.  This

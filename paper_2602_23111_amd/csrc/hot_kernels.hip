@@ -76,72 +76,33 @@ __global__ __launch_bounds__(256) void pack_basis_kernel(const float* __restrict
 // what is left with the low half of its bits cut off: 8 bits of the mantissa each, so the third one is exact.  The parts of a
 // number have its sign, and where one would be zero the part before it is cut into halves (down to 2^-124): an infinite
 // element of X then meets what it would meet in the product with P.
-// HALVES: the f16 parts too (h = 2^12 P and l = what is left of it, each to nearest, an infinity and NaN as they are), and the largest |P| per column.
-// A workgroup has KW k-blocks per wave of one column block; HALVES: four, a whole k-tile.
-template <bool HALVES, int KW>
 __global__ __launch_bounds__(256) void pack_pfrag_split_kernel(const float* __restrict__ P, int64_t d, int64_t ldp, int c,
-                                                               int ncb, bf16_t* __restrict__ out, bf16_t* __restrict__ half,
-                                                               float* __restrict__ pmax) {
-  const int lane = threadIdx.x & 63, j = lane & 31, h = lane >> 5, wave = threadIdx.x >> 6;
-  static_assert(!HALVES || KW == 4, "");
-  const int cb = blockIdx.x % ncb, k0 = (blockIdx.x / ncb * 4 + wave) * KW;  // its first k-block
-  const int64_t kt = k0 / 16;
-  const int col = cb * 32 + j;
-  float v[KW][8];
-#pragma unroll
-  for (int q = 0; q < KW; ++q)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int64_t kk = (int64_t)(k0 + q) * 16 + 8 * h + e;
-      v[q][e] = (col < c && kk < d) ? P[kk * ldp + col] : 0.f;
-    }
-  uint32_t top = 0;  // bits of the largest magnitude (those of a NaN are above an infinity's)
-#pragma unroll
-  for (int q = 0; q < KW; ++q) {
-    const int k = (k0 + q) & 15;
+                                                               int nkb, int ncb, bf16_t* __restrict__ out) {
+  const int64_t total = (int64_t)nkb * ncb * 64;
+  for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < total; g += (int64_t)gridDim.x * blockDim.x) {
+    const int lane = (int)(g & 63), j = lane & 31, h = lane >> 5;
+    const int64_t blk = g >> 6;
+    const int cb = (int)(blk % ncb);
+    const int64_t kb = blk / ncb;
+    const int col = cb * 32 + j;
     float part[3][8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const float x = v[q][e];
-      const float hi = __uint_as_float(__float_as_uint(x) & 0xFFFF0000u), rest = x - hi;
+      const int64_t kk = kb * 16 + 8 * h + e;
+      const float v = (col < c && kk < d) ? P[kk * ldp + col] : 0.f;
+      const float hi = __uint_as_float(__float_as_uint(v) & 0xFFFF0000u), rest = v - hi;
       const float mid = __uint_as_float(__float_as_uint(rest) & 0xFFFF0000u), lo = rest - mid;
-      const bool fin = isfinite(x);
-      part[0][e] = !fin ? x : (rest == 0.f ? 0.5f * x : hi);
-      part[1][e] = !fin ? x : (rest == 0.f ? 0.25f * x : (lo == 0.f ? 0.5f * mid : mid));
-      part[2][e] = !fin ? x : (rest == 0.f ? 0.25f * x : (lo == 0.f ? 0.5f * mid : lo));
-      top = max(top, __float_as_uint(x) & 0x7FFFFFFFu);
+      const bool fin = isfinite(v);
+      part[0][e] = !fin ? v : (rest == 0.f ? 0.5f * v : hi);
+      part[1][e] = !fin ? v : (rest == 0.f ? 0.25f * v : (lo == 0.f ? 0.5f * mid : mid));
+      part[2][e] = !fin ? v : (rest == 0.f ? 0.25f * v : (lo == 0.f ? 0.5f * mid : lo));
     }
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       u32x4 w;
 #pragma unroll
       for (int e2 = 0; e2 < 4; ++e2) w[e2] = pack2(part[p][2 * e2], part[p][2 * e2 + 1]);
-      reinterpret_cast<u32x4*>(out)[((kt * 3 + p) * 16 * ncb + k * ncb + cb) * 64 + lane] = w;
-    }
-    if constexpr (HALVES) {
-      union {
-        _Float16 f[8];
-        u32x4 u;
-      } a, b;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float x = v[q][e] * 4096.f;
-        a.f[e] = (_Float16)x;
-        b.f[e] = (_Float16)(x - (float)a.f[e]);
-      }
-      u32x4* o = reinterpret_cast<u32x4*>(half) + (kt * PRAC_P_HALVES * 16 * ncb + k * ncb + cb) * 64 + lane;
-      o[0] = a.u;
-      o[(int64_t)16 * ncb * 64] = b.u;
-    }
-  }
-  if constexpr (HALVES) {
-    __shared__ uint32_t tops[8][32];
-    tops[2 * wave + h][j] = top;
-    __syncthreads();
-    if (threadIdx.x < 32) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) top = max(top, tops[i][j]);
-      pmax[kt * ncb * 32 + col] = __uint_as_float(top);
+      reinterpret_cast<u32x4*>(out)[(((kb >> 4) * 3 + p) * 16 * ncb + (kb & 15) * ncb + cb) * 64 + lane] = w;
     }
   }
 }
@@ -1108,12 +1069,9 @@ int launch_pack_pfrag(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int
   return PRAC_OK;
 }
 
-int launch_pack_pfrag_split(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int c, int nkb, int ncb, bf16_t* out, bf16_t* half,
-                            float* pmax) {
-  if (nkb % 16 != 0 || (half && !pmax)) return PRAC_EINVAL;
-  const dim3 grid((unsigned)(nkb / (half ? 16 : 4) * ncb)), block(256);
-  if (half) hipLaunchKernelGGL((pack_pfrag_split_kernel<true, 4>), grid, block, 0, ctx->stream, P, d, ldp, c, ncb, out, half, pmax);
-  else hipLaunchKernelGGL((pack_pfrag_split_kernel<false, 1>), grid, block, 0, ctx->stream, P, d, ldp, c, ncb, out, half, pmax);
+int launch_pack_pfrag_split(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int c, int nkb, int ncb, bf16_t* out) {
+  hipLaunchKernelGGL(pack_pfrag_split_kernel, dim3(grid_for((int64_t)nkb * ncb * 64, ctx->n_cu)), dim3(256), 0,
+                     ctx->stream, P, d, ldp, c, nkb, ncb, out);
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
 }

@@ -501,32 +501,25 @@ int prac_unpack_compressed(prac_ctx* ctx, const void* Cpk, int64_t N, int c, voi
 
 namespace {
 // How a compress / fused-forward call runs: STREAM, the bf16 kernels on aligned rows; STREAM_ANY, the same kernels on
-// rows that start on any element, with the fp32 P as three bf16 or two f16 parts; STRIDED, everything else (fp32 data, rows
+// rows that start on any element, with the fp32 P as three bf16 parts; STRIDED, everything else (fp32 data, rows
 // of fewer than 8 elements, pitches above PRAC_MAX_STREAM_PITCH).  At N = 32768, d = 5461 (contiguous rows), c = 256
-// STREAM_ANY takes 0.19 ms, packing included (0.23 with three parts), where the strided kernel and its cast take 2.5 ms (and STREAM with
-// padded rows 0.11 ms: half of the matrix instructions).
+// STREAM_ANY takes 0.25 ms, packing included, where the strided kernel and its cast take 2.5 ms (and STREAM with
+// padded rows 0.11 ms: a third of the matrix instructions).
 enum class CompressPath { STREAM, STREAM_ANY, STRIDED };
 struct CompressPlan {
-  size_t o_lp, o_half, o_pmax, o_redo, o_w, o_tmp, o_c, bytes;
+  size_t o_lp, o_w, o_tmp, o_c, bytes;
   int ncb_w;
-  bool halves;
 };
-CompressPlan plan_compress(int n_cu, CompressPath path, bool fused, bool packed, bool has_lp, prac_dtype xdt, int64_t N, int64_t d,
+CompressPlan plan_compress(CompressPath path, bool fused, bool packed, bool has_lp, prac_dtype xdt, int64_t N, int64_t d,
                            int c, int64_t m) {
   CompressPlan q{};
   WsPlan plan;
-  q.halves = path == CompressPath::STREAM_ANY && !fused && compress_halves(n_cu, N, d, c);
   if (path != CompressPath::STRIDED) {
     const LpLayout l = lp_layout(d, c);
     if (path == CompressPath::STREAM)
       q.o_lp = plan.take(has_lp ? 0 : l.bytes);
     else
       q.o_lp = plan.take((size_t)l.nkb * 3 * l.ncb * 64 * 8 * sizeof(bf16_t));
-    if (q.halves) {
-      q.o_half = plan.take((size_t)l.nkb * PRAC_P_HALVES * l.ncb * 64 * 8 * sizeof(bf16_t));
-      q.o_pmax = plan.take((size_t)l.nkb / 16 * l.ncb * 32 * sizeof(float));
-      q.o_redo = plan.take((size_t)compress_ws_workgroups(n_cu, N, c) * sizeof(int));
-    }
     q.ncb_w = fused ? (int)round_up64((m + 31) / 32, 8) : 0;  // whole 256-column groups
     q.o_w = plan.take(fused ? (size_t)l.nkb * q.ncb_w * 64 * 8 * sizeof(bf16_t) : 0);
   } else {
@@ -549,7 +542,7 @@ static int compress_impl(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N
   if (packed && (xdt != PRAC_BF16 || !aligned16(C))) return PRAC_EUNSUPPORTED;
   const CompressPath path = fast ? CompressPath::STREAM
                                  : (stream_any(xdt, d, ldx) ? CompressPath::STREAM_ANY : CompressPath::STRIDED);
-  const CompressPlan q = plan_compress(ctx->n_cu, path, fused, packed, P_lp != nullptr, xdt, N, d, c, m);
+  const CompressPlan q = plan_compress(path, fused, packed, P_lp != nullptr, xdt, N, d, c, m);
   if (q.bytes) {
     int rc = prac_ws_reserve(ctx, q.bytes);
     if (rc) return rc;
@@ -584,10 +577,7 @@ static int compress_impl(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N
   if (path == CompressPath::STREAM_ANY) {
     const LpLayout l = lp_layout(d, c);
     bf16_t* Ps = reinterpret_cast<bf16_t*>(ctx->ws + q.o_lp);
-    bf16_t* Ph = !q.halves ? nullptr : reinterpret_cast<bf16_t*>(ctx->ws + q.o_half);
-    float* pmax = !q.halves ? nullptr : reinterpret_cast<float*>(ctx->ws + q.o_pmax);
-    int* redo = !q.halves ? nullptr : reinterpret_cast<int*>(ctx->ws + q.o_redo);
-    int rc = launch_pack_pfrag_split(ctx, P, d, ldp, c, l.nkb, l.ncb, Ps, Ph, pmax);
+    int rc = launch_pack_pfrag_split(ctx, P, d, ldp, c, l.nkb, l.ncb, Ps);
     if (rc) return rc;
     bf16_t* Wf = nullptr;
     if (fused) {
@@ -598,7 +588,7 @@ static int compress_impl(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N
     ProfScope ps(ctx, fused ? PRAC_KERNEL_FUSED_FWD : PRAC_KERNEL_COMPRESS);
     return launch_compress_ws(ctx, reinterpret_cast<const bf16_t*>(X), ldx, (int)N, (int)d, Ps, l.ncb, c,
                               reinterpret_cast<bf16_t*>(C), ldc, packed, Wf, q.ncb_w, (int)m, reinterpret_cast<bf16_t*>(Y),
-                              ldy, true, ctx->tails, Ph, pmax, redo);
+                              ldy, true, ctx->tails);
   }
   // strided path: fp32 data (P used in fp32), and bf16 rows the streaming kernels do not take
   const bool need_tmp = xdt == PRAC_BF16;
@@ -1306,10 +1296,10 @@ size_t prac_workspace_bytes(const prac_ctx* ctx, const prac_call_shape* sh) {
       const bool fused = sh->op == PRAC_OP_FUSED_FWD;
       if (fused && (sh->n_out != 1 || sh->m[0] < 1)) return bad;
       const int64_t m = fused ? sh->m[0] : 0;
-      size_t need = plan_compress(n_cu, fast ? CompressPath::STREAM : CompressPath::STRIDED, fused, packed, sh->have_p_lp != 0, dt,
+      size_t need = plan_compress(fast ? CompressPath::STREAM : CompressPath::STRIDED, fused, packed, sh->have_p_lp != 0, dt,
                                   sh->N, sh->d, c, m).bytes;
       if (!fast && stream_any(dt, sh->d, sh->d))  // the shape does not say the pitch: enough for either path
-        need = std::max(need, plan_compress(n_cu, CompressPath::STREAM_ANY, fused, packed, sh->have_p_lp != 0, dt, sh->N, sh->d, c,
+        need = std::max(need, plan_compress(CompressPath::STREAM_ANY, fused, packed, sh->have_p_lp != 0, dt, sh->N, sh->d, c,
                                             m).bytes);
       return need;
     }

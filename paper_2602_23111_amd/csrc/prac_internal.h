@@ -7,7 +7,6 @@
 #include <stddef.h>
 #include <stdint.h>
 
-#include <algorithm>
 #include <utility>
 #include <vector>
 
@@ -156,15 +155,10 @@ int launch_cast_out(prac_ctx* ctx, const float* src, int64_t lds, void* dst, pra
 // Wfrag != nullptr: also Y (N x m, ldy) = X W, W in the fragment order of Pfrag with ncb_w column blocks
 // any_element: rows of X start on any element and own nothing past their last column (d >= 8); Pfrag then holds the fp32 P
 // as launch_pack_pfrag_split leaves it.  part: n_cu * PRAC_TAIL_BYTES of partial sums, for a product with few tiles (nullptr: one launch,
-// which writes nothing but its outputs).  Phalf, pmax (any_element, no forward output): as launch_pack_pfrag_split leaves them, with redo for
-// compress_ws_workgroups ints
+// which writes nothing but its outputs)
 int launch_compress_ws(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d, const bf16_t* Pfrag, int ncb,
                        int c, bf16_t* C, int64_t ldc, bool packed, const bf16_t* Wfrag, int ncb_w, int m,
-                       bf16_t* Y, int64_t ldy, bool any_element = false, float* part = nullptr, const bf16_t* Phalf = nullptr,
-                       const float* pmax = nullptr, int* redo = nullptr);
-bool compress_halves(int n_cu, int64_t N, int64_t d, int c);  // whether it should be given them
-// workgroups of that launch at most (ints of redo)
-inline int64_t compress_ws_workgroups(int n_cu, int64_t N, int c) { return std::max<int64_t>((N + 127) / 128 * ((c + 127) / 128), n_cu); }
+                       bf16_t* Y, int64_t ldy, bool any_element = false, float* part = nullptr);
 // C = X P by small tiles whose sum over d is split over a workgroup's waves (tile_kernels.hip); aligned rows only
 enum class CompressTile { NONE, T32x32, T32x64, T32x128 };
 CompressTile compress_tile(int n_cu, int N, int c);  // NONE: enough rows for compress_ws_kernel
@@ -246,11 +240,8 @@ int launch_wgrad_fused(prac_ctx* ctx, const bf16_t* Cpk, int c, int N, int n_out
                        int nckb, const int* nmb, bf16_t* const* Tf, const bf16_t* Pa, int d, void* const* dW,
                        const int64_t* lddw, bool out_bf16, float beta, int* cnt);
 int launch_pack_pfrag(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int c, int nkb, int ncb, bf16_t* out);
-// the fp32 P exactly, as three bf16 parts: [nkb / 16][3][16][ncb][64][8].  half: also 2^12 P as two f16 parts, [nkb / 16][2][16][ncb][64][8], and the
-// largest |P| (a NaN stays one) of every 256 rows of a column in pmax, [nkb / 16][32 ncb]
-#define PRAC_P_HALVES 2
-int launch_pack_pfrag_split(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int c, int nkb, int ncb, bf16_t* out, bf16_t* half = nullptr,
-                            float* pmax = nullptr);
+// the fp32 P exactly, as three bf16 parts: [nkb / 16][3][16][ncb][64][8]
+int launch_pack_pfrag_split(prac_ctx* ctx, const float* P, int64_t d, int64_t ldp, int c, int nkb, int ncb, bf16_t* out);
 int launch_unpack_c(prac_ctx* ctx, const bf16_t* Cpk, int N, int c, bf16_t* C, int64_t ldc);
 int launch_pack_c(prac_ctx* ctx, const bf16_t* C, int64_t ldc, int N, int c, bf16_t* Cpk);
 

@@ -80,10 +80,6 @@ struct CompressWsArgs {
   // few tiles: the sum over d in `splits` ranges of `kt_per` k-tiles, partial sums to `part` (compress_sum_kernel adds them up)
   int splits, kt_per;
   float* part;          // [splits][tiles_m][col_groups][4 waves][4 FN blocks][4 register quads][64 lanes][4]
-  // HALVES: P as two f16 parts, [nkb/16][WS_HALVES][16][ncb][64][8], and the largest |P| of every 256 rows, [nkb/16][32 ncb]
-  const bf16_t* Phalf;
-  const float* pmax;
-  int* redo;            // one per workgroup: HALVES writes it, the launch behind it works only where it is set (nullptr: everywhere)
 };
 
 constexpr int WS_BM = 128, WS_BK = 256, WS_LD = WS_BK + 8;
@@ -93,7 +89,6 @@ constexpr int WS_RB = 32 * WS_LD * 2;        // bytes between 32-row blocks of a
 constexpr int WS_KB = WS_BK / 16;            // k-blocks per tile
 constexpr int WS_NCH = 4, WS_NIF = 2;        // chunks per tile, chunks in flight
 constexpr int WS_SPLIT = 3;                  // bf16 parts of an fp32 P
-constexpr int WS_HALVES = PRAC_P_HALVES;     // or f16 parts
 
 // One k-block of a 128 x 64 wave tile: acc[2 i + j] += fa[i] * b_j, while the four A fragments
 // at byte offsets O + i * WS_RB from `lds` are read into fn.  The block also issues the two
@@ -106,64 +101,56 @@ constexpr int WS_HALVES = PRAC_P_HALVES;     // or f16 parts
 // but the VM youngest requests of this wave have arrived (the ring's distance times the
 // requests per block; b0 / b1 were requested that long ago), and n0 / n1 may only be read
 // by a later block, after that block's wait.
-#define PRAC_KBLOCK2(TYPE) \
-  asm volatile( \
-      "s_waitcnt vmcnt(%27)\n" \
-      "global_load_dwordx4 %12, %21, %22\n" \
-      "global_load_dwordx4 %13, %21, %22 offset:1024\n" \
-      "ds_read_b128 %8, %20 offset:%23\n" \
-      "v_mfma_f32_32x32x16_" TYPE " %0, %14, %18, %0\n" \
-      "ds_read_b128 %9, %20 offset:%24\n" \
-      "v_mfma_f32_32x32x16_" TYPE " %1, %14, %19, %1\n" \
-      "ds_read_b128 %10, %20 offset:%25\n" \
-      "v_mfma_f32_32x32x16_" TYPE " %2, %15, %18, %2\n" \
-      "ds_read_b128 %11, %20 offset:%26\n" \
-      "v_mfma_f32_32x32x16_" TYPE " %3, %15, %19, %3\n" \
-      "v_mfma_f32_32x32x16_" TYPE " %4, %16, %18, %4\n" \
-      "v_mfma_f32_32x32x16_" TYPE " %5, %16, %19, %5\n" \
-      "v_mfma_f32_32x32x16_" TYPE " %6, %17, %18, %6\n" \
-      "v_mfma_f32_32x32x16_" TYPE " %7, %17, %19, %7\n" \
-      "s_waitcnt lgkmcnt(0)\n" \
-      : "+a"(acc[0]), "+a"(acc[1]), "+a"(acc[2]), "+a"(acc[3]), "+a"(acc[4]), "+a"(acc[5]), "+a"(acc[6]), \
-        "+a"(acc[7]), "=&v"(fn[0]), "=&v"(fn[1]), "=&v"(fn[2]), "=&v"(fn[3]), "=&v"(n0), "=&v"(n1) \
-      : "v"(fa[0]), "v"(fa[1]), "v"(fa[2]), "v"(fa[3]), "v"(b0), "v"(b1), "v"(lds), "v"(voff), "s"(src), "n"(O), \
-        "n"(O + WS_RB), "n"(O + 2 * WS_RB), "n"(O + 3 * WS_RB), "n"(VM) \
-      : "memory")
-template <int O, int VM, bool F16>
+template <int O, int VM>
 __device__ __forceinline__ void kblock2(f32x16 (&acc)[8], const u32x4 (&fa)[4], u32x4 (&fn)[4], const u32x4& b0,
                                         const u32x4& b1, unsigned lds, u32x4& n0, u32x4& n1, uint32_t voff,
                                         const char* src) {
-  if constexpr (F16) PRAC_KBLOCK2("f16");
-  else PRAC_KBLOCK2("bf16");
+  asm volatile(
+      "s_waitcnt vmcnt(%27)\n"
+      "global_load_dwordx4 %12, %21, %22\n"
+      "global_load_dwordx4 %13, %21, %22 offset:1024\n"
+      "ds_read_b128 %8, %20 offset:%23\n"
+      "v_mfma_f32_32x32x16_bf16 %0, %14, %18, %0\n"
+      "ds_read_b128 %9, %20 offset:%24\n"
+      "v_mfma_f32_32x32x16_bf16 %1, %14, %19, %1\n"
+      "ds_read_b128 %10, %20 offset:%25\n"
+      "v_mfma_f32_32x32x16_bf16 %2, %15, %18, %2\n"
+      "ds_read_b128 %11, %20 offset:%26\n"
+      "v_mfma_f32_32x32x16_bf16 %3, %15, %19, %3\n"
+      "v_mfma_f32_32x32x16_bf16 %4, %16, %18, %4\n"
+      "v_mfma_f32_32x32x16_bf16 %5, %16, %19, %5\n"
+      "v_mfma_f32_32x32x16_bf16 %6, %17, %18, %6\n"
+      "v_mfma_f32_32x32x16_bf16 %7, %17, %19, %7\n"
+      "s_waitcnt lgkmcnt(0)\n"
+      : "+a"(acc[0]), "+a"(acc[1]), "+a"(acc[2]), "+a"(acc[3]), "+a"(acc[4]), "+a"(acc[5]), "+a"(acc[6]),
+        "+a"(acc[7]), "=&v"(fn[0]), "=&v"(fn[1]), "=&v"(fn[2]), "=&v"(fn[3]), "=&v"(n0), "=&v"(n1)
+      : "v"(fa[0]), "v"(fa[1]), "v"(fa[2]), "v"(fa[3]), "v"(b0), "v"(b1), "v"(lds), "v"(voff), "s"(src), "n"(O),
+        "n"(O + WS_RB), "n"(O + 2 * WS_RB), "n"(O + 3 * WS_RB), "n"(VM)
+      : "memory");
 }
-#undef PRAC_KBLOCK2
 
 // Same for a 128 x 32 wave tile: acc[i] += fa[i] * b, one refill request.
-#define PRAC_KBLOCK1(TYPE) \
-  asm volatile( \
-      "s_waitcnt vmcnt(%21)\n" \
-      "global_load_dwordx4 %8, %15, %16\n" \
-      "ds_read_b128 %4, %14 offset:%17\n" \
-      "ds_read_b128 %5, %14 offset:%18\n" \
-      "v_mfma_f32_32x32x16_" TYPE " %0, %9, %13, %0\n" \
-      "ds_read_b128 %6, %14 offset:%19\n" \
-      "ds_read_b128 %7, %14 offset:%20\n" \
-      "v_mfma_f32_32x32x16_" TYPE " %1, %10, %13, %1\n" \
-      "v_mfma_f32_32x32x16_" TYPE " %2, %11, %13, %2\n" \
-      "v_mfma_f32_32x32x16_" TYPE " %3, %12, %13, %3\n" \
-      "s_waitcnt lgkmcnt(0)\n" \
-      : "+a"(acc[0]), "+a"(acc[1]), "+a"(acc[2]), "+a"(acc[3]), "=&v"(fn[0]), "=&v"(fn[1]), "=&v"(fn[2]), \
-        "=&v"(fn[3]), "=&v"(n0) \
-      : "v"(fa[0]), "v"(fa[1]), "v"(fa[2]), "v"(fa[3]), "v"(b), "v"(lds), "v"(voff), "s"(src), "n"(O), \
-        "n"(O + WS_RB), "n"(O + 2 * WS_RB), "n"(O + 3 * WS_RB), "n"(VM) \
-      : "memory")
-template <int O, int VM, bool F16>
+template <int O, int VM>
 __device__ __forceinline__ void kblock1(f32x16 (&acc)[4], const u32x4 (&fa)[4], u32x4 (&fn)[4], const u32x4& b,
                                         unsigned lds, u32x4& n0, uint32_t voff, const char* src) {
-  if constexpr (F16) PRAC_KBLOCK1("f16");
-  else PRAC_KBLOCK1("bf16");
+  asm volatile(
+      "s_waitcnt vmcnt(%21)\n"
+      "global_load_dwordx4 %8, %15, %16\n"
+      "ds_read_b128 %4, %14 offset:%17\n"
+      "ds_read_b128 %5, %14 offset:%18\n"
+      "v_mfma_f32_32x32x16_bf16 %0, %9, %13, %0\n"
+      "ds_read_b128 %6, %14 offset:%19\n"
+      "ds_read_b128 %7, %14 offset:%20\n"
+      "v_mfma_f32_32x32x16_bf16 %1, %10, %13, %1\n"
+      "v_mfma_f32_32x32x16_bf16 %2, %11, %13, %2\n"
+      "v_mfma_f32_32x32x16_bf16 %3, %12, %13, %3\n"
+      "s_waitcnt lgkmcnt(0)\n"
+      : "+a"(acc[0]), "+a"(acc[1]), "+a"(acc[2]), "+a"(acc[3]), "=&v"(fn[0]), "=&v"(fn[1]), "=&v"(fn[2]),
+        "=&v"(fn[3]), "=&v"(n0)
+      : "v"(fa[0]), "v"(fa[1]), "v"(fa[2]), "v"(fa[3]), "v"(b), "v"(lds), "v"(voff), "s"(src), "n"(O),
+        "n"(O + WS_RB), "n"(O + 2 * WS_RB), "n"(O + 3 * WS_RB), "n"(VM)
+      : "memory");
 }
-#undef PRAC_KBLOCK1
 
 // One 1 KB ring request outside the k-blocks (the first fills): n <- 16 bytes at src + voff (+ OFF).
 // Issued in assembly like the blocks' own requests, so that the compiler keeps no count of
@@ -218,18 +205,10 @@ __device__ __forceinline__ void drain_mfma(f32x16 (&acc)[NACC], u32x4 (&ring)[8]
 // UA: rows of X that start on any element (see frag_utils.h), and the fp32 P instead of its bf16 copy: Pfrag then holds
 // every k-tile of P as three bf16 tiles that add up to it exactly (pack_pfrag_split), and the tile of X in LDS is
 // multiplied by each of them before the loaders move on.  W of a forward output is bf16 as it is: one step per tile.
-//
-// HALVES (UA, no forward output): two f16 parts of 2^12 P instead (22 to 24 of its bits), two thirds of the matrix instructions, which
-// bound this kernel.  A bf16 number times a power of two is an f16 number as long as it lies between 2^-17 and 65280, so the loaders
-// scale each row of X by a power of two that puts the largest element of its first k-tile between 8 and 16, and what lies below 2^-17 then is
-// off by at most 2^-28 of that; the sums are scaled back at the end.  Where that does not hold the workgroup stores nothing and marks its tile for
-// the launch behind this one, which forms it with the three bf16 parts: a later element of a row is more than 2^12 times that largest one, or not finite; a row's first
-// k-tile is zero and a later one is not, or its largest element is below 2^-111; a column of P is not zero and has its largest element outside
-// 2^-10 .. 16 (an orthonormal one of up to 2^20 rows has not).  32768 x 5461, c = 256: 171 us and 5 for the launch behind it, which finds nothing to do, against 217 to 228 with three parts.
-template <int FN, int NCH, int NIF, bool UA, bool HALVES>
+template <int FN, int NCH, int NIF, bool UA>
 __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int bid = touch_kernel_args<(UA ? sizeof(CompressWsArgs) : offsetof(CompressWsArgs, Phalf))>(blockIdx.x);
+  const int bid = touch_kernel_args<sizeof(CompressWsArgs)>(blockIdx.x);
 
   // XCD-aware order: consecutive logical tiles (same rows, next column group) on one XCD
   const int total = a.tiles_m * a.col_groups * a.splits;
@@ -237,7 +216,6 @@ __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
   const int xcd = bid & 7, slot = bid >> 3;
   const int logical = xcd * per_xcd + slot;
   if (slot >= per_xcd || logical >= total) return;
-  if (UA && !HALVES && a.redo && a.redo[logical] == 0) return;  // uniform
   int tm = logical / a.col_groups, kt0 = 0;
   const int cg = logical - tm * a.col_groups;
   if (a.splits > 1) {
@@ -258,15 +236,7 @@ __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
   // than an L2 holds and should ask for it in the same order; d = 5461, c = 256 from any element 250 against 280 us)
   const int rot = UA || a.Wfrag ? 0 : tm % nk;
   const bool fwd = cg < a.w_groups;      // this workgroup's columns belong to Y
-  const int parts = UA && !fwd ? WS_SPLIT : 1;  // steps per k-tile
-  static_assert(!HALVES || UA, "");
-  float* const row_back = reinterpret_cast<float*>(smem_raw + WS_STAGES * WS_STAGE);  // HALVES: what a row's sums are multiplied by at the end
-  int* const flags = reinterpret_cast<int*>(row_back + WS_BM);                        // one per wave, before the loop and behind it
-  auto any_flag = [&](int first, int n) {
-    int x = 0;
-    for (int i = 0; i < n; ++i) x |= flags[first + i];
-    return __builtin_amdgcn_readfirstlane(x) != 0;
-  };
+  const int reps = UA && !fwd ? WS_SPLIT : 1;  // steps per k-tile
   auto act = [&](int kt) {
     const int t = min(kt, nk - 1) + rot;
     return kt0 + (t >= nk ? t - nk : t);
@@ -306,94 +276,40 @@ __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
         ra[Q * CR + j] = __builtin_nontemporal_load(reinterpret_cast<const std::conditional_t<UA, u32x4_el, u32x4>*>(
             xbase + (live ? roff[Q * CR + j] + kb : dead_off)));
     };
-    float row_scale[HALVES ? 16 : 1];
-    uint32_t zero_rows = 0, zero_row_ends = 0;  // rows whose first tile is zero, and whether one of them is not zero behind it
-    auto to_half = [&](u32x4 x, int q) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        x[e] = scaled_pk_f16(__uint_as_float(x[e] << 16), __uint_as_float(x[e] & 0xFFFF0000u), row_scale[q]);
-      return x;
-    };
     // chunk g -> stage (g / NCH) % 2; columns past d are zeroed (only the last tile has any)
-    auto cstore = [&](int g, auto qc, auto hc) {
+    auto cstore = [&](int g, auto qc) {
       constexpr int Q = decltype(qc)::value;
-      constexpr bool H = decltype(hc)::value;
       const int kt = g / NCH;
       unsigned char* s = smem_raw + (kt & 1) * WS_STAGE + soff;
       const int nv = a.d - (act(kt) * WS_BK + ccol);
       if (nv >= 8) {
 #pragma unroll
-        for (int j = 0; j < CR; ++j) {
-          u32x4 x = ra[Q * CR + j];
-          if constexpr (H) x = to_half(x, Q * CR + j);
-          *reinterpret_cast<u32x4*>(s + (Q * CR + j) * (8 * WS_LD * 2)) = x;
-        }
+        for (int j = 0; j < CR; ++j) *reinterpret_cast<u32x4*>(s + (Q * CR + j) * (8 * WS_LD * 2)) = ra[Q * CR + j];
       } else {
 #pragma unroll
-        for (int j = 0; j < CR; ++j) {
-          u32x4 x = UA && nv > 0 ? shift_down(ra[Q * CR + j], 8 - nv) : keep_first(ra[Q * CR + j], nv);
-          if constexpr (H) x = to_half(x, Q * CR + j);
-          *reinterpret_cast<u32x4*>(s + (Q * CR + j) * (8 * WS_LD * 2)) = x;
-        }
-      }
-      if (H && zero_rows) {  // (rare)
-#pragma unroll
         for (int j = 0; j < CR; ++j)
-          if (zero_rows >> (Q * CR + j) & 1)
-            zero_row_ends |= (ra[Q * CR + j].x | ra[Q * CR + j].y | ra[Q * CR + j].z | ra[Q * CR + j].w) & 0x7FFF7FFFu;
+          *reinterpret_cast<u32x4*>(s + (Q * CR + j) * (8 * WS_LD * 2)) =
+              UA && nv > 0 ? shift_down(ra[Q * CR + j], 8 - nv) : keep_first(ra[Q * CR + j], nv);
       }
     };
 #define PRAC_IC(v) std::integral_constant<int, (v)> {}
-    // tile 0 (requested) to LDS, the first NIF chunks of tile 1, then tile by tile
-    auto stream = [&](auto hc, int reps) __attribute__((always_inline)) {
-      static_for<NCH>([&](auto q) { cstore(decltype(q)::value, q, hc); });
-      static_for<NIF>([&](auto q) { cload(NCH + decltype(q)::value, q); });
-      __syncthreads();  // tile 0 is in LDS
-      for (int kt = 0; kt < nk; ++kt) {
-        // interval q of tile kt: chunk q of tile kt+1 -> LDS (its stage was last read for tile kt-1, before
-        // the previous tile's last barrier), then chunk q + NIF of tile kt+1 is requested
-        static_for<NCH>([&](auto q) {
-          constexpr int Q = decltype(q)::value;
-          const int g = (kt + 1) * NCH + Q;
-          if (kt + 1 < nk) cstore(g, q, hc);
-          cload(g + NIF, PRAC_IC((Q + NIF) % NCH));
-          __syncthreads();
-        });
-        if constexpr (UA)  // the other steps read the same tile
-          for (int e = (reps - 1) * NCH; e > 0; --e) __syncthreads();
-      }
-    };
+    // tile 0 at once, then the first NIF chunks of tile 1
     static_for<NCH>([&](auto q) { cload(decltype(q)::value, q); });
-    if constexpr (HALVES) {
-      // a row's 256 columns of the first tile are in 32 lanes (past d: the row's last chunk again)
-      bool odd = false;
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        constexpr uint32_t M = 0x7FFF7FFFu;
-        uint32_t m = max_pk_u16(max_pk_u16(ra[q].x & M, ra[q].y & M), max_pk_u16(ra[q].z & M, ra[q].w & M));
-        m = max_half_wave(max(m & 0xFFFFu, m >> 16));
-        const uint32_t ex = m >> 7;
-        const bool zero = m == 0;
-        odd = odd || (!zero && (ex < 16 || ex == 255));
-        zero_rows |= zero ? 1u << q : 0u;
-        row_scale[q] = __uint_as_float(zero ? 127u << 23 : (257u - ex) << 23);  // 2^(3 - exponent)
-        if ((lt & 31) == 0) row_back[crow + 8 * q] = __uint_as_float((zero ? 127u - 12u : ex - 15u) << 23);
-      }
-      if ((tid & 63) == 0) {
-        flags[wave] = __any(odd);
-        flags[4 + wave] = 0;
-      }
-      __syncthreads();
-      bool redo = any_flag(0, 8);
-      if (!redo) {
-        stream(std::true_type{}, WS_HALVES);
-        if (__any(zero_row_ends != 0) && (tid & 63) == 0) flags[4 + wave] = 1;
+    static_for<NCH>([&](auto q) { cstore(decltype(q)::value, q); });
+    static_for<NIF>([&](auto q) { cload(NCH + decltype(q)::value, q); });
+    __syncthreads();  // tile 0 is in LDS
+    for (int kt = 0; kt < nk; ++kt) {
+      // interval q of tile kt: chunk q of tile kt+1 -> LDS (its stage was last read for tile kt-1, before
+      // the previous tile's last barrier), then chunk q + NIF of tile kt+1 is requested
+      static_for<NCH>([&](auto q) {
+        constexpr int Q = decltype(q)::value;
+        const int g = (kt + 1) * NCH + Q;
+        if (kt + 1 < nk) cstore(g, q);
+        cload(g + NIF, PRAC_IC((Q + NIF) % NCH));
         __syncthreads();
-        redo = any_flag(0, 4) || any_flag(8, 4);
-      }
-      if (tid == 256) a.redo[logical] = redo ? 1 : 0;
-    } else {
-      stream(std::false_type{}, parts);
+      });
+      if constexpr (UA)  // the other steps read the same tile
+        for (int e = (reps - 1) * NCH; e > 0; --e) __syncthreads();
     }
 #undef PRAC_IC
     return;
@@ -402,15 +318,12 @@ __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
   // -------------------------------------------------------------- matrix waves
   const int lane = tid & 63, li = lane & 31, lh = lane >> 5;
   const int cb0 = (fwd ? cg : cg - a.w_groups) * 4 * FN + wave * FN;  // first 32-column block of this wave
+  const char* pbase = reinterpret_cast<const char*>(fwd ? a.Wfrag : a.Pfrag);
   const uint32_t boff = (uint32_t)(cb0 * 64 + lane) * 16u;     // this lane's slot in a row of blocks
   const int64_t brow = (int64_t)(fwd ? a.ncb_w : a.ncb) * 1024;  // bytes per 16-row k-block of fragments
 
   constexpr int NACC = 4 * FN;
   f32x16 acc[NACC];
-#define PRAC_IC(v) std::integral_constant<int, (v)> {}
-  auto multiply = [&](auto hc, int reps) __attribute__((always_inline)) {
-  constexpr bool H = decltype(hc)::value;
-  const char* const pbase = reinterpret_cast<const char*>(fwd ? a.Wfrag : H ? a.Phalf : a.Pfrag);
 #pragma unroll
   for (int i = 0; i < NACC; ++i)
 #pragma unroll
@@ -422,7 +335,7 @@ __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
   // and jumps to the next tile's base after the tile's last one.
   u32x4 rb[8][FN];
   const int steps = nk * reps;
-  auto tile_of = [&](int st) { return H ? st / WS_HALVES : UA && reps > 1 ? st / WS_SPLIT : st; };
+  auto tile_of = [&](int st) { return UA && reps > 1 ? st / WS_SPLIT : st; };
   auto tile_base = [&](int st) {
     // past the last step: tile 0's fragments again (valid memory, an L2 hit, never used)
     const int kt = tile_of(st);
@@ -440,14 +353,15 @@ __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
   auto kblock = [&](auto oc, const u32x4 (&fcur)[4], u32x4 (&fnext)[4], auto kkc, unsigned lds) {
     constexpr int O = decltype(oc)::value, KK = decltype(kkc)::value;
     if constexpr (FN == 2)
-      kblock2<O, VM, H>(acc, fcur, fnext, rb[KK & 7][0], rb[KK & 7][1], lds, rb[(KK + 7) & 7][0], rb[(KK + 7) & 7][1],
+      kblock2<O, VM>(acc, fcur, fnext, rb[KK & 7][0], rb[KK & 7][1], lds, rb[(KK + 7) & 7][0], rb[(KK + 7) & 7][1],
                      boff, preq);
     else
-      kblock1<O, VM, H>(acc, fcur, fnext, rb[KK & 7][0], lds, rb[(KK + 7) & 7][0], boff, preq);
+      kblock1<O, VM>(acc, fcur, fnext, rb[KK & 7][0], lds, rb[(KK + 7) & 7][0], boff, preq);
     // the next request is k-block KK + 8 of this tile, or the next tile's first one
     if constexpr (KK == 8) preq = next_base;
     else preq += brow;
   };
+#define PRAC_IC(v) std::integral_constant<int, (v)> {}
 
   // LDS byte address of this lane's A fragment of row block 0, k-block 0, stage 0:
   // row li, 16-byte half lh of the k-block
@@ -476,52 +390,6 @@ __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
     // registers (it has no idea that matrix instructions are still writing them), and such
     // moves must find the pipeline empty.
     if (st == steps - 1) drain_mfma<NACC, FN>(acc, rb);
-  }
-  };
-  if constexpr (HALVES) {
-    bool odd = false;
-    if (lane < 32 * FN) {
-      float m = 0.f;
-      bool nan = false;
-      const float* q = a.pmax + cb0 * 32 + lane;
-#pragma unroll 8
-      for (int kt = 0; kt < (a.d + WS_BK - 1) / WS_BK; ++kt) {
-        const float x = q[(int64_t)kt * a.ncb * 32];
-        nan = nan || x != x;
-        m = fmaxf(m, x);
-      }
-      odd = nan || !(m < 16.f) || (m != 0.f && m < 0x1p-10f);
-    }
-    odd = __any(odd);
-    if (lane == 0) flags[wave] = odd;
-    __syncthreads();
-    if (any_flag(0, 8)) return;
-    multiply(std::true_type{}, WS_HALVES);
-    // back to X's scale.  An element that did not fit f16, or was not finite, has left no finite sum in its row.
-    odd = false;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < FN; ++j) {
-        f32x16& t = acc[i * FN + j];
-        asm volatile("" : "+a"(t) : : "memory");  // (a block at a time leaves the accumulation registers)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x4_t w = *reinterpret_cast<const f32x4_t*>(row_back + 32 * i + 8 * q + 4 * lh);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            odd = odd || !(fabsf(t[4 * q + e]) <= 3e38f);
-            t[4 * q + e] *= w[e];
-          }
-        }
-        asm volatile("" : "+a"(t) : : "memory");
-      }
-    odd = __any(odd);
-    if (lane == 0) flags[wave] = odd;
-    __syncthreads();
-    if (any_flag(0, 4) || any_flag(8, 4)) return;
-  } else {
-    multiply(std::false_type{}, parts);
   }
 #undef PRAC_IC
 
@@ -641,7 +509,6 @@ __global__ __launch_bounds__(512) void compress_ws_kernel(CompressWsArgs a) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   PRAC_STAMP(a, 3);
 #endif
-
 }
 
 // C, and Y of a fused forward, from the partial sums of the ranges of d (in their order).  A thread adds up eight tokens of one
@@ -1761,8 +1628,8 @@ int set_smem(prac_ctx* ctx, K kern, size_t bytes, bool& done) {
 // Only for calls that work in the ctx's scratch anyway (`part`): rows on any element, the fused forward, a refit's
 // product.  A compress of aligned rows with a packed basis keeps nothing in the ctx, so that calls on several
 // streams, and replays of graphs beside them, may overlap; it stays one launch (of few rows compress_tile_kernel's).
-static void compress_ranges(int n_cu, int tiles, int nk, int fn, int parts, int& splits, int& kt_per) {
-  const double tile_us = (fn == 2 ? 3.4 : 2.2) * parts, part_us = 2.0 * tiles * fn * 65536.0 / 3e6;
+static void compress_ranges(int n_cu, int tiles, int nk, int fn, bool parts, int& splits, int& kt_per) {
+  const double tile_us = (fn == 2 ? 3.4 : 2.2) * (parts ? WS_SPLIT : 1), part_us = 2.0 * tiles * fn * 65536.0 / 3e6;
   auto cost = [&](int s) { return tile_us * ((nk + s - 1) / s) + (s > 1 ? 5.0 + part_us * s : 0.0); };
   int best = 1;
   for (int s = 2; s <= nk && (int64_t)s * tiles <= n_cu; ++s)
@@ -1771,26 +1638,9 @@ static void compress_ranges(int n_cu, int tiles, int nk, int fn, int parts, int&
   splits = (nk + kt_per - 1) / kt_per;  // no empty range
 }
 
-// Two f16 parts of P instead of three bf16 ones for a compress of rows on any element: from d = 2048 on (up to 2^-23 of an element of P away
-// from it, but the fp32 sums of three parts, a third more of them, are further off there: elements of C that round otherwise than the exact
-// product, two / three parts, P orthonormal: d = 2049 3.0e-4 / 3.5e-4, 5461 4.8e-4 / 5.8e-4; 259 1.1e-4 / 0.9e-4), and where the part saved is
-// worth more than the second launch and the larger packing (7 us): 2.1 us per k-tile and round of workgroups, 0.8 with the narrow tile.
-// The step with three / two parts (N, d, c): 32768, 5461, 256 288 / 241 us; 23863, 6730, 37 172.4 / 156.9; 6754, 2132, 94 91.8 / 97.3; 9528, 2923, 74
-// 98.8 / 102.7; 970, 4111, 305 143.3 / 148.4.
-bool compress_halves(int n_cu, int64_t N, int64_t d, int c) {
-  if (d < 2048) return false;
-  const int64_t tiles_m = (N + WS_BM - 1) / WS_BM, wide = ((c + 31) / 32 + 7) / 8;
-  const int fn = c <= 128 || tiles_m * wide * 2 <= n_cu ? 1 : 2, nk = (int)((d + WS_BK - 1) / WS_BK);
-  const int64_t tiles = tiles_m * ((c + 128 * fn - 1) / (128 * fn));
-  int splits = 1, kt_per = nk;
-  if (tiles < n_cu) compress_ranges(n_cu, (int)tiles, nk, fn, WS_SPLIT, splits, kt_per);
-  return (double)((tiles * splits + n_cu - 1) / n_cu) * kt_per * (fn == 2 ? 2.1 : 0.8) > 9.0;
-}
-
 int launch_compress_ws(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d, const bf16_t* Pfrag, int ncb, int c,
                        bf16_t* C, int64_t ldc, bool packed, const bf16_t* Wfrag, int ncb_w, int m, bf16_t* Y,
-                       int64_t ldy, bool any_element, float* part, const bf16_t* Phalf, const float* pmax, int* redo) {
-  if (Phalf && (!any_element || Wfrag || !pmax || !redo)) return PRAC_EINVAL;
+                       int64_t ldy, bool any_element, float* part) {
   // callers route wider pitches, and rows shorter than one 16-byte chunk that start on any element, to the strided kernels
   if (ldx > PRAC_MAX_STREAM_PITCH || (any_element && d < 8)) return PRAC_EINVAL;
   const CompressTile small = Wfrag || any_element || part ? CompressTile::NONE : compress_tile(ctx->n_cu, N, c);
@@ -1819,38 +1669,28 @@ int launch_compress_ws(prac_ctx* ctx, const bf16_t* X, int64_t ldx, int N, int d
   a.splits = 1;
   a.kt_per = nk;
   a.part = part;
-  a.Phalf = Phalf;
-  a.pmax = pmax;
-  a.redo = redo;
-  if (part) compress_ranges(ctx->n_cu, tiles, nk, FN, Phalf ? WS_HALVES : any_element ? WS_SPLIT : 1, a.splits, a.kt_per);
-  const size_t smem_stages = (size_t)WS_STAGES * WS_STAGE, smem_halves = smem_stages + WS_BM * sizeof(float) + 12 * sizeof(int);
+  if (part) compress_ranges(ctx->n_cu, tiles, nk, FN, any_element, a.splits, a.kt_per);
+  const size_t smem = (size_t)WS_STAGES * WS_STAGE;
   const int total = tiles * a.splits;
   const dim3 grid(((total + 7) / 8) * 8), block(512);
-  // of several launches the first carries a timed product's start event, the last the stop
-  const hipEvent_t ev_stop = ctx->ev_stop;
-  if (a.splits > 1 || Phalf) ctx->ev_stop = nullptr;
-  static bool done_dev[PRAC_MAX_DEVICES][7] = {};  // the attribute is per device
+  // a timed product with ranges ends with their sum: the first launch carries the start event, the second the stop
+  const hipEvent_t ev_stop = a.splits > 1 ? ctx->ev_stop : nullptr;
+  if (a.splits > 1) ctx->ev_stop = nullptr;
+  static bool done_dev[PRAC_MAX_DEVICES][4] = {};  // the attribute is per device
   bool* done = done_dev[ctx->device % PRAC_MAX_DEVICES];
-#define PRAC_COMPRESS_CASE(I, FN, UA, HALVES, SMEM)                            \
-  case I: {                                                                    \
-    constexpr auto kern = compress_ws_kernel<FN, WS_NCH, WS_NIF, UA, HALVES>;  \
-    int rc = set_smem(ctx, kern, SMEM, done[I]);                               \
-    if (rc) return rc;                                                         \
-    PRAC_LAUNCH(ctx, kern, grid, block, SMEM, a);                              \
-    break;                                                                     \
+#define PRAC_COMPRESS_CASE(I, FN, UA)                                     \
+  case I: {                                                               \
+    constexpr auto kern = compress_ws_kernel<FN, WS_NCH, WS_NIF, UA>;     \
+    int rc = set_smem(ctx, kern, smem, done[I]);                          \
+    if (rc) return rc;                                                    \
+    PRAC_LAUNCH(ctx, kern, grid, block, smem, a);                         \
+    break;                                                                \
   }
-  if (Phalf) {
-    switch (FN) {
-      PRAC_COMPRESS_CASE(1, 1, true, true, smem_halves)
-      PRAC_COMPRESS_CASE(2, 2, true, true, smem_halves)
-    }
-    if (a.splits == 1) ctx->ev_stop = ev_stop;
-  }
-  switch (FN + (any_element ? 4 : 2)) {  // (behind the f16 parts: the tiles that those do not suit)
-    PRAC_COMPRESS_CASE(3, 1, false, false, smem_stages)
-    PRAC_COMPRESS_CASE(4, 2, false, false, smem_stages)
-    PRAC_COMPRESS_CASE(5, 1, true, false, smem_stages)
-    PRAC_COMPRESS_CASE(6, 2, true, false, smem_stages)
+  switch (FN - 1 + (any_element ? 2 : 0)) {
+    PRAC_COMPRESS_CASE(0, 1, false)
+    PRAC_COMPRESS_CASE(1, 2, false)
+    PRAC_COMPRESS_CASE(2, 1, true)
+    PRAC_COMPRESS_CASE(3, 2, true)
   }
 #undef PRAC_COMPRESS_CASE
   if (a.splits > 1) {

@@ -278,12 +278,11 @@ def test_rows_that_start_on_any_element_meet_the_fp32_basis(ctx, d, c):
     "plain", "late", "zero_first", "tiny", "huge", "wide_range", "p_small", "p_large", "p_mixed", "p_zero_columns")] + [
         (16600, 2819, 40, True, "plain"), (16600, 2819, 40, True, "late"), (16600, 2819, 40, True, "p_mixed"),      # the narrow tile
         (12700, 9473, 33, False, "plain"), (12700, 9473, 33, False, "zero_first"),                                 # two ranges of d
-        (6754, 2132, 94, False, "plain"), (300, 2049, 40, True, "late"), (4200, 2047, 1000, False, "plain")])      # three parts by the rule
-def test_rows_on_any_element_with_two_parts_of_the_basis(ctx, N, d, c, packed, what):
-    """From 2048 features on the basis goes in as two f16 parts, and three bf16 parts take over per tile where those do not hold X's rows or P's
-    columns: elements far above a row's first ones, rows that start with zeros, numbers at the ends of the range.  C against the
-    fp64 product: one rounding (2^-8 of the element), 2^-22 per element of P, fp32 sums (sqrt(d) 2^-24 of the norms, below 2^-18), of which what X's
-    numbers below 2^-28 of their row's largest may lose is a part."""
+        (6754, 2132, 94, False, "plain"), (300, 2049, 40, True, "late"), (4200, 2047, 1000, False, "plain")])
+def test_rows_on_any_element_over_the_range_of_numbers(ctx, N, d, c, packed, what):
+    """Elements far above a row's first ones, rows that start with zeros, numbers at the ends of the range, in X and in P, with both widths of
+    the tile and in ranges of d.  C against the fp64 product: one rounding (2^-8 of the element) and fp32 sums (sqrt(d) 2^-24 of the
+    norms, below 2^-18)."""
     from paper_2602_23111_amd.prac import C_PACKED, C_ROWMAJOR
     g = torch.Generator(device=DEV).manual_seed(d)
     X = torch.randn((N, d), generator=g, device=DEV)
@@ -318,7 +317,30 @@ def test_rows_on_any_element_with_two_parts_of_the_basis(ctx, N, d, c, packed, w
     assert ((C.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2.0 ** -18 * scale).all()
 
 
-def test_infinities_with_two_parts_of_the_basis(ctx):
+@pytest.mark.parametrize("N,d,c,packed", [(4200, 2049, 1000, False), (16600, 2819, 40, True), (300, 261, 40, False)])
+def test_rows_on_any_element_keep_small_elements_beside_large_ones(ctx, N, d, c, packed):
+    """Rows with one element 10^4 to 10^9 times the others, where P is zero, 2^-33 of its other elements, or as large as they are.  C against
+    the fp64 product, element by element: one rounding (2^-8 of the element) and fp32 sums of three products per feature
+    (3 d 2^-24 of the sum of the products' magnitudes), nothing in proportion to the row's largest element."""
+    from paper_2602_23111_amd.prac import C_PACKED, C_ROWMAJOR
+    g = torch.Generator(device=DEV).manual_seed(d)
+    X = torch.randn((N, d), generator=g, device=DEV)
+    P = torch.linalg.qr(torch.randn((d, c), generator=g, device=DEV))[0].contiguous()
+    X[3, 5], X[130, 5], X[N - 1, 5] = 1e9, -3e4, 2.0 ** 30
+    P[5, :c // 3] = 0.0
+    P[5, c // 3:2 * c // 3] *= 2.0 ** -33
+    X = X.bfloat16()
+    block = torch.full((N * d + 1,), float("nan"), dtype=torch.bfloat16, device=DEV)  # contiguous rows, 2 bytes past a 16-byte boundary
+    C = ctx.compress(block[1:].view(N, d).copy_(X), P, layout=C_PACKED if packed else C_ROWMAJOR)
+    if packed:
+        C = ctx.unpack_compressed(C, N, c)
+    ctx.sync_status()
+    X64, P64 = X.double(), P.double()
+    ref, mag = X64 @ P64, X64.abs() @ P64.abs()
+    assert ((C.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 3 * d * 2.0 ** -24 * mag).all()
+
+
+def test_infinities_in_long_rows_on_any_element(ctx):
     """Infinities and NaN in X and in P, from 2048 features on: as in the plain product, rows and columns beside them untouched."""
     N, d, c = 4200, 2051, 1000
     g = torch.Generator().manual_seed(3)
