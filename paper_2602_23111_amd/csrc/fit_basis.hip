@@ -476,7 +476,7 @@ __device__ __forceinline__ void split3(const float (&x)[8], u32x4 (&part)[3]) {
 // column 4 b + a: a lane then holds four neighbouring columns of its row.
 // 18.5 us at 2048 x 256, 9 us at 2048 x 128 (42 / 16.5 us in fp32 on the vector units, columns of R staged through LDS); R's lines not
 // requested ahead 64 us.
-// far != nullptr and zero (n <= 256): R holds src^T src instead, both triangles, which is within PANEL_NEAR of the identity, and dst is
+// far != nullptr and zero (n <= 256): R holds src^T src instead, both triangles, which is within PANEL_ONCE of the identity, and dst is
 // src (1.5 I - 0.5 src^T src), a Newton-Schulz step, also in fp64: no factorisation (57 us at n = 256).
 // gate != nullptr and zero: nothing to do.
 // PARTS (n <= 256): also the result as three bf16 parts for gram_times_block_kernel (its 16 rows are one k-block).
@@ -1186,11 +1186,14 @@ __global__ __launch_bounds__(256) void panel_gram64_kernel(const float* __restri
     }
 }
 
-// W (n x n) = sum over the ranges, a workgroup per block of the upper triangle (with far or gate both triangles).  far (zero before; not with a gate): set where an entry of W is further than
-// PANEL_NEAR from the identity's, or not finite.  A Newton-Schulz step leaves 0.75 e^2 of a distance e (in norm: up to n PANEL_NEAR, as a
-// rule a few times PANEL_NEAR), so it ends below fp32 rounding from there, or at 2e-6 at the very worst.
+// A Newton-Schulz step leaves 0.75 e^2 of W = I + E, e the norm of E: 4.7e-8 of this, below fp32 rounding.  (A norm, not the largest entry: of
+// n columns with every entry at x it is n x.)
+constexpr double PANEL_ONCE = 2.5e-4;
+
+// W (n x n) = sum over the ranges, a workgroup per block of the upper triangle (with far or gate both triangles).  far (zero before; not with a
+// gate): set where W may be further than PANEL_ONCE from the identity, or is not finite: a block's share of that is PANEL_ONCE over the blocks of a row, in
+// Frobenius norm, so that no sum has to meet another workgroup's.
 // gate: nullptr, or nothing to do where it is zero; then an entry further than `limit` from the identity's raises bit 1 of *flag.
-constexpr double PANEL_NEAR = 6e-6;
 __global__ __launch_bounds__(256) void panel_gram64_sum_kernel(const double* __restrict__ slabs, int splits, int n,
                                                                double* __restrict__ W, int* far, const int* gate, double limit, int* flag) {
   if (gate && *gate == 0) return;  // uniform
@@ -1211,37 +1214,56 @@ __global__ __launch_bounds__(256) void panel_gram64_sum_kernel(const double* __r
     if (row < c && (far || gate)) W[(int64_t)c * n + row] = s;
   }
   if (far || gate) {  // uniform
-    const double off = row < n && c < n && row <= c ? fabs(s - (row == c ? 1.0 : 0.0)) : 0.0;
-    if (far && __any(!(off <= PANEL_NEAR)) && lane == 0) atomicOr(far, 1);
+    const double off = row < n && c < n ? fabs(s - (row == c ? 1.0 : 0.0)) : 0.0;
+    if (far) {  // uniform
+      __shared__ double part[4];
+      double sq = off * off;
+#pragma unroll
+      for (int m = 1; m < 64; m *= 2) sq += __shfl_xor(sq, m);
+      if (lane == 0) part[threadIdx.x >> 6] = sq;
+      __syncthreads();
+      const double share = PANEL_ONCE / nb16;
+      if (threadIdx.x == 0 && !(part[0] + part[1] + part[2] + part[3] <= share * share)) atomicOr(far, 1);
+    }
     if (gate && __any(!(off <= limit)) && lane == 0) atomicOr(flag, 1);
   }
 }
 
-// The sum of the fp32 partial Gram matrices of a block, as fp64 (W64 != nullptr) or as the factor 1.5 I - 0.5 W of a Newton-Schulz step.
-// For the latter W is the Gram matrix of a block that should be close to orthonormal: an entry further than `limit` from the
+// The sum of the fp32 partial Gram matrices of a block, as fp64 (W64 != nullptr) or as the factor 1.5 I - 0.5 W of a Newton-Schulz step, a
+// workgroup per row.  For the latter W is the Gram matrix of a block that should be close to orthonormal: an entry further than `limit` from the
 // identity (or not finite) raises bit 1 of *flag - the step that follows squares the distance, so a block that far off
-// does not come out orthonormal to fp32 rounding.  again (or nullptr): set where an entry is further than PANEL_ONCE.  (slabs may be M32 itself)
-constexpr float PANEL_LAST = 3e-3f;  // up to here a last step ends below 1e-5 (0.75 e^2)
-constexpr float PANEL_ONCE = 1e-4f;  // and up to here below fp32 rounding
+// does not come out orthonormal to fp32 rounding.  again (or nullptr): set where a row sum of |W - I|, a bound of its norm, is above PANEL_ONCE.
+// (slabs may be M32 itself)
+// PANEL_LAST: a last step leaves 0.75 (3e-3)^2 < 1e-5 of an entry that is alone in its row and column, and 0.75 n (3e-3)^2 at the very worst, of n equal ones.
+constexpr float PANEL_LAST = 3e-3f;
 __global__ __launch_bounds__(256) void panel_gram32_sum_kernel(const float* slabs, int splits, int n, double* W64, float* M32,
                                                                float limit, int* flag, int* again) {
-  bool off = false, more = false;
-  const int total = n * n;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < total; i += gridDim.x * blockDim.x) {
+  bool off = false;
+  float sum = 0.f;
+  const int total = n * n, row = blockIdx.x;
+  for (int c = threadIdx.x; c < n; c += blockDim.x) {
+    const int i = row * n + c;
     float w = 0.f;
 #pragma unroll 8
     for (int z = 0; z < splits; ++z) w += slabs[(int64_t)z * total + i];
     if (W64) {
       W64[i] = (double)w;
     } else {
-      const float id = i / n == i % n ? 1.f : 0.f;
+      const float id = row == c ? 1.f : 0.f;
       off = off || !(fabsf(w - id) <= limit);
-      more = more || !(fabsf(w - id) <= PANEL_ONCE);
+      sum += fabsf(w - id);
       M32[i] = 1.5f * id - 0.5f * w;
     }
   }
   if (off) atomicOr(flag, 1);
-  if (more && again) atomicOr(again, 1);
+  if (again) {  // uniform
+    __shared__ float part[4];
+#pragma unroll
+    for (int m = 1; m < 64; m *= 2) sum += __shfl_xor(sum, m);
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0 && !(part[0] + part[1] + part[2] + part[3] <= (float)PANEL_ONCE)) atomicOr(again, 1);
+  }
 }
 
 // row ranges of a split panel product of width n
@@ -1413,7 +1435,7 @@ int panel_gram32(prac_ctx* ctx, const FitWs& w, const float* src, int64_t d, int
     rc = launch_gemm_generic(ctx, g);
   }
   if (rc) return rc;
-  hipLaunchKernelGGL(panel_gram32_sum_kernel, dim3((n * n + 255) / 256), dim3(256), 0, ctx->stream, sums, splits, n, W64, factor,
+  hipLaunchKernelGGL(panel_gram32_sum_kernel, dim3(n), dim3(256), 0, ctx->stream, sums, splits, n, W64, factor,
                      limit, ctx->d_flag, again);
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
@@ -1430,7 +1452,7 @@ int split_block(prac_ctx* ctx, const float* V, int64_t d, int n, u32x4* parts) {
 
 // dst (pitch ldd; may be src) = src R^-1 with R^T R = src^T src (+ shift): one Cholesky-QR pass.  parts: the result also as parts for G V
 // (their padding past d is there already).  any_basis: of src's span any orthonormal basis will do, so a block that is orthonormal but for
-// PANEL_NEAR gets a Newton-Schulz step instead (decided on the device).
+// PANEL_ONCE gets a Newton-Schulz step instead (decided on the device).
 int cholqr_pass(prac_ctx* ctx, const FitWs& w, const float* src, float* dst, int64_t ldd, int64_t d, int n, double shift, bool gram64,
                 u32x4* parts, bool any_basis) {
   double* W64 = reinterpret_cast<double*>(ctx->ws + w.W64);
@@ -1514,7 +1536,7 @@ int cholqr(prac_ctx* ctx, const FitWs& w, float* Y, float* V, int64_t d, int n, 
     // Later passes work on a block that is orthonormal up to the first pass's error, except in
     // directions where the input was rank deficient: there the Gram matrix is zero up to rounding
     // (a few 1e-16), and the shift has to be safely above that for the pivot to stay positive.
-    // the last Newton-Schulz step must start within PANEL_LAST of orthonormal to end below 1e-5; earlier
+    // the last Newton-Schulz step must start with every entry within PANEL_LAST of orthonormal (see there for where it ends); earlier
     // ones may start anywhere inside the step's region of convergence
     int rc = pass < passes ? cholqr_pass(ctx, w, src, dst, ldd, d, n, pass == 0 ? first_shift : 1e-13, pass > 0 || gram64_first,
                                          last ? parts : nullptr, pass >= any_basis_from)

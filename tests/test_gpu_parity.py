@@ -1575,6 +1575,33 @@ def batch_pair_with_gap(N, d, k, alpha, shrink, seed):
     return X0, X1
 
 
+@pytest.mark.parametrize("weak", [1.0, 2.0 ** -6, 2.0 ** -9, 2.0 ** -10, 1.75 * 2.0 ** -11])
+def test_fit_basis_tracking_refit_ends_orthonormal_in_norm(ctx, weak):
+    """256 columns of a batch with one strong feature and 255 weak ones, from a basis whose first column is nearly the strong one: behind the
+    factorisation every entry of P^T P - I has about the same size and sign, below 1e-4 each while their norm is up to
+    a hundred times that (weak = 2^-10 and 1.75 2^-11), and one Newton-Schulz step leaves 0.75 of its square, above what is allowed here.  In the
+    2-norm: two fp32 products of 256 terms, 16 x 2^-24 for each."""
+    n, d, N, r = 256, 512, 2048, 16
+    t = torch.full((n,), (0.5 / (n - 1)) ** 0.5, dtype=torch.double)
+    t[0] = 0.5 ** 0.5
+    w = -t
+    w[0] += 1.0
+    w /= w.norm()
+    P = torch.zeros((d, n + r))
+    P[:n, :n] = (torch.eye(n, dtype=torch.double) - 2 * w[:, None] * w[None]).float()  # its first row is t
+    P[n:n + r, n:] = torch.eye(r)
+    i = torch.arange(N)
+    X = torch.zeros((N, d))
+    X[i, i % n] = weak
+    X[::n, 0] = 1.0
+    P = P.to(DEV)
+    ctx.fit_basis(X.bfloat16().to(DEV), n, r, seed=1, draw=1, P=P, iters=1, oversample=-1, warm_start=True, pack=False)
+    ctx.sync_status()
+    E = P.double().t() @ P.double() - torch.eye(n + r, dtype=torch.double, device=DEV)
+    assert torch.linalg.matrix_norm(E[:n, :n], 2) <= 2 * 16 * 2.0 ** -24
+    assert E.abs().max() <= 2 * 16 * 2.0 ** -24
+
+
 @pytest.mark.parametrize("shrink,iters,must_meet", [(0.9, 2, False), (0.9, 10, True), (0.5, 2, True)])
 def test_fit_basis_tracking_refit_projector(ctx, shrink, iters, must_meet):
     """The Gram-free tracking refit (what bench.py's refreshes run) against the exact top-k projector of
