@@ -990,7 +990,12 @@ static inline size_t gv_g_bytes(int64_t d) { return (size_t)((d + 31) / 32) * gv
 static inline int gv_col_blocks(int b) { return (b + 63) / 64 * 2; }
 static inline size_t gv_v_bytes(int64_t d, int b) { return (size_t)gv_kblocks(d) * gv_col_blocks(b) * 3072; }
 
-// KF: line i, element k at src[i ld + k], pieces [line blocks][k-blocks]; otherwise at src[k ld + i], pieces [k-blocks][line blocks].
+// The matrix instructions take a subnormal bf16 part as zero, so a row of G whose diagonal entry is below 2^-40 (then no entry of it is above 2^44) goes in
+// times 2^48 and its Y comes back by as much: without that a batch of elements around 2^-64, whose third and then second parts are subnormal, lost its
+// weaker directions (1.9e-3 off instead of 1.6e-5; at 2^-68 0.3).
+__device__ __forceinline__ bool gv_tiny_row(float diag) { return diag < 0x1p-40f; }
+
+// KF (G): line i, element k at src[i ld + k], pieces [line blocks][k-blocks]; otherwise at src[k ld + i], pieces [k-blocks][line blocks].
 // Zeros outside lines x K.
 template <bool KF>
 __global__ __launch_bounds__(256) void split_parts_kernel(const float* __restrict__ src, int64_t ld, int lines, int64_t K, int nlb,
@@ -1008,14 +1013,20 @@ __global__ __launch_bounds__(256) void split_parts_kernel(const float* __restric
 #pragma unroll
     for (int e = 0; e < 8; ++e) x[e] = line < lines && k + e < K ? (KF ? src[line * ld + k + e] : src[(k + e) * ld + line]) : 0.f;
   }
+  if constexpr (KF) {
+    const float up = line < lines && gv_tiny_row(src[line * ld + line]) ? 0x1p48f : 1.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] *= up;
+  }
   u32x4 part[3];
   split3(x, part);
 #pragma unroll
   for (int p = 0; p < 3; ++p) out[(piece * 3 + p) * 64 + lane] = part[p];
 }
 
-__global__ __launch_bounds__(64 * GV_W, 2) void gram_times_block_kernel(const u32x4* __restrict__ Gf, const u32x4* __restrict__ Vf, int d,
-                                                                        int b, int nkb, int ncb, float* __restrict__ Y) {
+__global__ __launch_bounds__(64 * GV_W, 2) void gram_times_block_kernel(const u32x4* __restrict__ Gf, const u32x4* __restrict__ Vf,
+                                                                        const float* __restrict__ G, int d, int b, int nkb, int ncb,
+                                                                        float* __restrict__ Y) {
   extern __shared__ float gv_red[];  // [GV_W][32][64]
   // the column tiles of a few row blocks sit next to each other on one XCD
   const int tiles_n = ncb / 2, total = (d + 31) / 32 * tiles_n, per_xcd = (total + 7) / 8;
@@ -1056,6 +1067,14 @@ __global__ __launch_bounds__(64 * GV_W, 2) void gram_times_block_kernel(const u3
       for (int c = 0; c < 2; ++c)
         low[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(s.g[PG[t]]), as_frag(s.v[c][PV[t]]), low[c], 0, 0, 0);
   };
+  // row of register v in the result's layout
+  auto row_of = [&](int v) { return 32 * tm + 8 * (v / 4) + 4 * lh + v % 4; };
+  float diag[4];  // of the four rows that this thread stores
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int row = min(row_of((wave * 4 + u) & 15), d - 1);
+    diag[u] = G[(int64_t)row * d + row];
+  }
   const int n = nkb / GV_W;  // (a multiple)
   Step st[GV_D];
 #pragma unroll
@@ -1085,12 +1104,12 @@ __global__ __launch_bounds__(64 * GV_W, 2) void gram_times_block_kernel(const u3
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
-    const int r = wave * 4 + u, v = r & 15;
+    const int r = wave * 4 + u;
     float x = 0.f;
 #pragma unroll
     for (int w = 0; w < GV_W; ++w) x += gv_red[(w * 32 + r) * 64 + lane];
-    const int row = 32 * tm + 8 * (v / 4) + 4 * lh + v % 4, col = 64 * tn + 32 * (r >> 4) + li;
-    if (row < d && col < b) Y[(int64_t)row * b + col] = x;
+    const int row = row_of(r & 15), col = 64 * tn + 32 * (r >> 4) + li;
+    if (row < d && col < b) Y[(int64_t)row * b + col] = gv_tiny_row(diag[u]) ? x * 0x1p-48f : x;
   }
 }
 
@@ -1687,7 +1706,7 @@ int fit_basis_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, in
         if (rc) return rc;
       } else {
         hipLaunchKernelGGL(gram_times_block_kernel, dim3(((d + 31) / 32 * (gv_col_blocks(b) / 2) + 7) / 8 * 8), dim3(64 * GV_W),
-                           GV_W * 32 * 64 * sizeof(float), st, Gf, Vf, (int)d, b, gv_kblocks(d), gv_col_blocks(b), Y);
+                           GV_W * 32 * 64 * sizeof(float), st, Gf, Vf, G, (int)d, b, gv_kblocks(d), gv_col_blocks(b), Y);
       }
       PRAC_HIP_TRY(ctx, hipGetLastError());
       if (it == o.iters) break;  // the last product feeds Rayleigh-Ritz

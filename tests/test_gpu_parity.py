@@ -743,6 +743,27 @@ def test_cold_fit_at_edges_of_the_products_tiles(ctx, dt, N, d, k):
     assert np.abs(P64.T @ P64 - np.eye(k + 2)).max() < 1e-5
 
 
+@pytest.mark.parametrize("dt,N,d,k,exponent", [("bf16", 2048, 640, 64, 64), ("bf16", 2048, 640, 64, 66), ("f32", 2048, 640, 64, 64), ("f32", 700, 300, 16, 66)])
+def test_cold_fit_of_tiny_batches(ctx, dt, N, d, k, exponent):
+    """A batch of elements around 2^-64: its Gram matrix lies just above the smallest normal number, so that parts of its entries do not.  The
+    principal subspace against the exact one: as far off as that of the same batch around 1 (how far the iteration has come), and what
+    products X_ni X_nj that round to multiples of 2^-149 add: N of them 2^-150 sqrt(N) per entry of G, 2 sqrt(d) times that in norm, over the
+    gap; once more for the products G V."""
+    g = torch.Generator(device=DEV).manual_seed(7)
+    R = torch.linalg.qr(torch.randn((d, d), generator=g, device=DEV))[0]
+    X = ((torch.randn((N, d), generator=g, device=DEV) * torch.logspace(0, -3, d, device=DEV)) @ R).to(TORCH_DT[dt])
+    lam, U = torch.linalg.eigh(X.double().t() @ X.double())
+    U = U[:, -k:]
+    off = []
+    for scale in (1.0, 2.0 ** -exponent):
+        P, _, _ = ctx.fit_basis((X.float() * scale).to(TORCH_DT[dt]), k, 16, seed=1, draw=0, pack=False)
+        ctx.sync_status()
+        Q = P[:, :k].double()
+        off.append(torch.linalg.matrix_norm(Q - U @ (U.t() @ Q), 2).item())
+    gap = (lam[-k] - lam[-k - 1]).item() * 2.0 ** (-2 * exponent)
+    assert off[1] <= off[0] + 2 * 2 * d ** 0.5 * N ** 0.5 * 2.0 ** -150 / gap
+
+
 # ------------------------------------------------------------- reconstruction
 RECON_CASES = [
     # dtype, N, d, k, r, ldc, ldxh
