@@ -805,6 +805,10 @@ __global__ __launch_bounds__(512) void wide_ws_kernel(WideWsArgs a) {
           *reinterpret_cast<uint2*>(wrow + turn + (j * 32 + q * 8) * 2) = w;
         }
       }
+      // the strip changes lanes here, and a half of the tile is written again two turns later
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       u32x4 ro[4];
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
