@@ -1,8 +1,8 @@
 // Wave-specialised streaming contractions for gfx950.
 //
 //   compress        C = X P          (Alg. 1 compression step)          compress_ws_kernel
-//   reconstruction  X~ = C Ps^T      (Section 5.1; Alg. 2 backward)       wide_ws_kernel
-//   weight gradient dW = P T         (Lemma 1, wide layers)               wide_ws_kernel
+//   reconstruction  X~ = C Ps^T      (Section 5.1; Alg. 2 backward)       wide_ws_kernel, wide_strips_kernel
+//   weight gradient dW = P T         (Lemma 1, wide layers)               the same
 //   weight gradient T = C^T dY       (Lemma 1, reassociated)              ctdy_ws_kernel
 //
 // A workgroup is 8 waves: 4 matrix waves and 4 loader waves, one of each per SIMD.
@@ -555,15 +555,23 @@ __global__ __launch_bounds__(256) void compress_sum_kernel(CompressWsArgs a) {
 // ------------------------------------------------------------------ reconstruction
 // X~ = C Ps^T (Section 5.1; first step of the backward pass in Alg. 2) and dW_h = P T_h (Lemma 1) for c <= 256: a tall
 // narrow matrix A (C, P) times a short wide one B (Ps^T, T_h), the K dimension one k-tile of KB k-blocks.  A workgroup owns
-// 128 rows and a range of column groups (256 columns of the output each): all eight waves put its A tile into LDS, then each of
-// them walks by itself over every eighth strip of 64 columns with the same k-blocks as the compress kernel, B streaming through
-// its fragment ring, which runs on from strip to strip.  The MFMA operands are swapped (the fragment of B is the A operand), so
-// that a lane ends up with four consecutive columns of one row per accumulator quad: a strip goes out 32 rows at a time through
-// LDS of the wave's own (8 bytes per lane and store; read back along rows, 16 bytes per lane).  There is no barrier behind the
-// first one: of the two waves of a SIMD one multiplies while the other drains its ring and stores.
-// N = 32768, d = 2048, c = 256: 45.3 us (48.8 with four matrix waves that staged a whole group for four others to store, and waited
-// for them); without its stores 34, so it is neither its 16 us of matrix instructions nor the 27 us of writing alone that bound it.  dW of
-// 2 x 5461, 3 x 2048 and 5461 rows x 2048 columns: 28.6, 16.0, 13.8 us (30.5, 17.4, 15.3).
+// 128 rows and a range of column groups (256 columns of the output each): its A tile is put into LDS once, then
+// matrix waves walk over the range with the same k-blocks as the compress kernel, B streaming through
+// the fragment ring, which runs on.  The MFMA operands
+// are swapped (the fragment of B is the A operand), so that a lane ends up with four
+// consecutive columns of one row per accumulator quad; it goes through an LDS staging tile as bf16 (8 bytes per lane and store; read back
+// along rows, 16 bytes per lane).  Two forms:
+//   wide_ws_kernel      four waves multiply a group at a time and stage it; four others - idle once A is in LDS - store it with their own
+//                       memory counter while the next one is multiplied.  A barrier before and behind each tile.
+//   wide_strips_kernel  all eight waves load A, then each walks by itself over every eighth strip of 64 columns and stages it in LDS of its own,
+//                       32 rows at a time: no barrier behind the first one, and of the two waves of a SIMD one multiplies while the
+//                       other drains its ring and stores.
+// The strips start sooner; the other form keeps matrix instructions and stores going at the same time.  Whole calls, groups against strips, us:
+// up to three groups per workgroup 4096 x 2048 (one) 18.6 / 17.8, 8192 x 2048 24.2 / 22.2, 32768 x 512 23.4 / 20.4, 16384 x 1536 27.2 / 25.7, the
+// gradients of 512 tokens for 2 x 5461 columns 50.4 / 46.9, 3 x 2048 34.2 / 33.0; four 31.7 / 33.3 (16384 x 2048), 31.4 / 31.5 (32768 x 1024),
+// 33.3 / 30.2 (3000 x 8192); six 39.3 / 40.9 (32768 x 1536), 55.2 / 60.1 (gradient of 4096 x 11008); eight 48.2 / 58.4 (32768 x 2048), 63.0 / 72.9
+// (gradient of 8192 x 8192); eleven 69.5 / 88.5 (16384 x 5461).
+constexpr int WIDE_STRIP_GROUPS = 3;  // strips up to here
 struct WideWsArgs {
   const bf16_t* A;       // row-major N x c, or packed [ceil(N/128)*8][ccb][64][8] (see CtdyWsArgs)
   int64_t lda;
@@ -636,15 +644,229 @@ __device__ __forceinline__ void kblock2t(f32x16 (&acc)[8], const u32x4 (&fa)[4],
   }
 }
 
-constexpr int RW_OLD = 128 + 16;              // bytes per row of a wave's staging tile: 32 rows of 64 columns
-constexpr int RW_WAVE = 2 * 32 * RW_OLD;      // two of them, in turn
-constexpr int RW_SMEM = WS_STAGE + 8 * RW_WAVE;
+// The A tile (128 rows from m0 on) by THREADS threads.
+template <int THREADS>
+__device__ __forceinline__ void wide_load_tile(const WideWsArgs& a, unsigned char* smem, int m0, int t) {
+  if (a.packed) {
+    // Packed C holds, per lane slot, 8 tokens of one column; the tile needs 8 columns of one token per
+    // 16 bytes.  A thread takes 8 x 8 patches: 8 consecutive column slots (128 contiguous bytes),
+    // transposed in registers as the C^T dY loader does for dY.  Patch p of the tile's 512:
+    // column octet o = p & 3, token half h = (p >> 2) & 1, column block cb = (p >> 3) & 7, token block tb = p >> 6.
+    const u32x4* Cp = reinterpret_cast<const u32x4*>(a.A);
+#pragma unroll
+    for (int pp = 0; pp < 512 / THREADS; ++pp) {
+      const int p = t + THREADS * pp;
+      const int o = p & 3, h = (p >> 2) & 1, cb = (p >> 3) & 7, tb = p >> 6;
+      u32x4 rr[8];
+      const bool live = cb < a.ccb;  // column blocks past c are zero in the tile
+      const int64_t base = ((int64_t)((m0 >> 4) + tb) * a.ccb + (live ? cb : 0)) * 64 + h * 32 + 8 * o;
+#pragma unroll
+      for (int jj = 0; jj < 8; ++jj) rr[jj] = Cp[base + jj];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        // token slot e of the patch: 16-bit element e of each of the 8 column slots
+        uint32_t w[4];
+#pragma unroll
+        for (int e2 = 0; e2 < 4; ++e2) {
+          const uint32_t lo = rr[2 * e2][e >> 1], hi = rr[2 * e2 + 1][e >> 1];
+          w[e2] = __builtin_amdgcn_perm(hi, lo, (e & 1) ? 0x07060302u : 0x05040100u);
+        }
+        const int row = 16 * tb + (e < 4 ? 4 * h + e : 8 + 4 * h + (e - 4));
+        u32x4 v = {w[0], w[1], w[2], w[3]};
+        if (!live) v = u32x4{0u, 0u, 0u, 0u};
+        *reinterpret_cast<u32x4*>(smem + (row * WS_LD + 32 * cb + 8 * o) * 2) = v;
+      }
+    }
+  } else {
+    constexpr int STEP = THREADS / 32, ROWS = WS_BM / STEP;
+    const int crow = t >> 5, ccol = (t & 31) * 8;  // row crow + STEP q, 16-byte chunk at column ccol
+    const char* cbase = reinterpret_cast<const char*>(a.A + (int64_t)m0 * a.lda);
+    const int last_chunk = ((a.c - 1) / 8) * 8;
+    const int nv = a.c - ccol;  // valid columns of this thread's chunk (<= 0: none)
+    u32x4 rc[ROWS];
+#pragma unroll
+    for (int q = 0; q < ROWS; ++q) {
+      const int row = min(m0 + crow + STEP * q, a.N - 1) - m0;  // rows past N repeat the last one, never stored
+      rc[q] = *reinterpret_cast<const u32x4*>(cbase + ((int64_t)row * a.lda + min(ccol, last_chunk)) * 2);
+    }
+    unsigned char* st = smem + (crow * WS_LD + ccol) * 2;
+#pragma unroll
+    for (int q = 0; q < ROWS; ++q)
+      *reinterpret_cast<u32x4*>(st + q * (STEP * WS_LD * 2)) = nv >= 8 ? rc[q] : keep_first(rc[q], nv > 0 ? nv : 0);
+  }
+}
 
-// RECON: one output.  Rows that lie on whole 128-byte lines are stored with the streaming hint (the reconstruction 43.3 us instead of 48.1;
-// three gradients of 2048 columns 14.4 instead of 16.8), others plainly: there every strip ends in lines that it shares with its
-// neighbours, and those should meet in L2 (2 x 5461 columns 25.9 us instead of 34.4).
+// Staging tile behind the A tile in LDS, with room for a whole group.
+constexpr int RW_OLD = 512 + 16;  // bytes per row
+constexpr int RW_OUT = WS_STAGE;
+constexpr int RW_SMEM = WS_STAGE + WS_BM * RW_OLD;
+
+// Four waves load the A tile, then store what the other four stage.
+// RECON: one output, stored plainly (the streaming hint costs the reconstruction's 134 MB 8 us of 46); otherwise several
+// outputs, stored with the hint (without it the 25 MB of three gradients cost the kernels that follow 6 us).
 template <int KB, bool RECON>
 __global__ __launch_bounds__(512) void wide_ws_kernel(WideWsArgs a) {
+  static_assert(KB == 8 || KB == 16, "whole turns of the ring, one k-tile");
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int bid = touch_kernel_args<sizeof(WideWsArgs)>(blockIdx.x);
+  // neighbours on one XCD are the row tiles of one column range: they share its part of B in that XCD's L2
+  const int total = a.tiles_m * ((a.groups + a.gper - 1) / a.gper);
+  const int per_xcd = (total + 7) / 8;
+  const int xcd = bid & 7, slot = bid >> 3;
+  const int logical = xcd * per_xcd + slot;
+  if (slot >= per_xcd || logical >= total) return;
+  const int tm = logical % a.tiles_m;
+  const int gbeg = logical / a.tiles_m * a.gper, gend = min(gbeg + a.gper, a.groups);
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m0 = tm * WS_BM;
+  auto output_of = [&](int g) {
+    if constexpr (RECON) return 0;
+    int h = 0;
+#pragma unroll
+    for (int q = 1; q < PRAC_CTDY_MAX_OUT; ++q)
+      if (g >= a.g0[q]) h = q;  // (g0[q] = groups past the last output)
+    return h;
+  };
+
+  if (wave >= 4) {
+    // ------------------------------------------------ loader, then store waves
+    const int lt = tid - 256;
+    const int crow = lt >> 5, ccol = (lt & 31) * 8;  // row crow + 8 q, 16-byte chunk at column ccol
+    wide_load_tile<256>(a, smem_raw, m0, lt);
+    __syncthreads();  // the A tile is in LDS
+    // From here on plain barriers (no memory fence: a fence would wait for this wave's own stores
+    // to HBM); LDS traffic is ordered by explicit waits, and the empty statements keep the
+    // compiler from moving memory accesses across them.
+    __builtin_amdgcn_s_barrier();  // staging tile free (first group)
+    for (int g = gbeg; g < gend; ++g) {
+      __builtin_amdgcn_s_barrier();  // staging tile holds group g
+      asm volatile("" ::: "memory");
+      u32x4 ro[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        ro[q] = *reinterpret_cast<const u32x4*>(smem_raw + RW_OUT + (crow + 8 * q) * RW_OLD + ccol * 2);
+        // rows 8 .. 15 (mod 16) are staged with the 8-byte halves of every 16 bytes swapped (see the writers)
+        if (q & 1) ro[q] = u32x4{ro[q].z, ro[q].w, ro[q].x, ro[q].y};
+      }
+      const int h = output_of(g), n = (g - a.g0[h]) * 256 + ccol, cols = a.n[h];
+      bf16_t* const obase = a.out[h] + n;
+      const int64_t ldo = a.ldo[h];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int mrow = m0 + crow + 8 * q;
+        if (mrow < a.N && n < cols) {
+          bf16_t* o = obase + (int64_t)mrow * ldo;
+          if (n + 8 <= cols) {
+            // 16 bytes at the alignment of one element (rows may start on any: 5461 columns, contiguous)
+            if constexpr (RECON) *reinterpret_cast<u32x4_el*>(o) = ro[q];
+            else stream_store_el(o, ro[q]);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (n + e < cols) o[e] = (bf16_t)((ro[q][e >> 1] >> (16 * (e & 1))) & 0xFFFFu);
+          }
+        }
+      }
+      // the stores above have read their registers, hence the LDS reads are complete
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if (g + 1 < gend) __builtin_amdgcn_s_barrier();  // staging tile free again
+    }
+    return;
+  }
+
+  // -------------------------------------------------------------- matrix waves
+  const int lane = tid & 63, li = lane & 31, lh = lane >> 5;
+  const uint32_t boff = (uint32_t)(wave * 2 * 64 + lane) * 16u;  // this wave's two column blocks of a group
+  f32x16 acc[8];
+  // ring as in the compress kernel; a "tile" is a column group, 8 blocks (8 KB) further along each k-block row
+  u32x4 rb[8][2];
+  // and brow the bytes per k-block row of that group's output (past the last group: the first one again, never used)
+  auto group_base = [&](int g, int64_t& row_bytes) {  // uniform
+    const int gg = g < gend ? g : gbeg, h = output_of(gg);
+    row_bytes = (int64_t)a.ncb[h] * 1024;
+    return reinterpret_cast<const char*>(a.B[h]) + (int64_t)(gg - a.g0[h]) * 8192;
+  };
+  int64_t brow, next_brow;
+  const char* preq = group_base(gbeg, brow);
+  const char* next_base = group_base(gbeg + 1, next_brow);
+#pragma unroll
+  for (int kk = 0; kk < 7; ++kk) {
+    ring_request<0>(rb[kk][0], boff, preq);
+    ring_request<1024>(rb[kk][1], boff, preq);
+    preq += brow;
+  }
+  constexpr int VM = 12;
+#define PRAC_IC(v) std::integral_constant<int, (v)> {}
+  auto kblock = [&](auto oc, const u32x4 (&fcur)[4], u32x4 (&fnext)[4], auto kkc, unsigned lds) {
+    constexpr int O = decltype(oc)::value, KK = decltype(kkc)::value;
+    kblock2t<O, VM, KK == 0>(acc, fcur, fnext, rb[KK & 7][0], rb[KK & 7][1], lds, rb[(KK + 7) & 7][0],
+                             rb[(KK + 7) & 7][1], boff, preq);
+    if constexpr (KK == KB - 8) {
+      preq = next_base;
+      brow = next_brow;
+    } else {
+      preq += brow;
+    }
+  };
+  const unsigned lds0 =
+      (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem_raw + (unsigned)(li * WS_LD * 2 + lh * 16);
+  u32x4 fa[4], fb[4];
+  __builtin_amdgcn_s_barrier();  // the A tile is in LDS
+  frag_read4(fa, lds0);
+  // staging address of this lane: row li (+ 32 i), columns 64 wave (+ 32 j + 8 q) + 4 lh .. + 3
+  // (a row is 528 bytes: lanes li and li + 8 of an 8-byte store would meet in the same banks, so
+  // rows 8 .. 15 of every 16 swap the two 8-byte halves of each 16 bytes)
+  unsigned char* const orow = smem_raw + RW_OUT + li * RW_OLD + (((wave * 64 + 4 * lh) * 2) ^ (((li >> 3) & 1) << 3));
+  for (int g = gbeg; g < gend; ++g) {
+    static_for<KB>([&](auto jc) {
+      constexpr int J = decltype(jc)::value;
+      // the fragments read during the last k-block are those of k-block 0 again: the next group's first
+      if constexpr (J % 2 == 0) kblock(PRAC_IC(32 * ((J + 1) % KB)), fa, fb, jc, lds0);
+      else kblock(PRAC_IC(32 * ((J + 1) % KB)), fb, fa, jc, lds0);
+    });
+    // The matrix pipeline and the ring are drained before compiler-scheduled code runs (see the
+    // compress kernel): the code below needs registers, and the compiler may only move or spill
+    // ring registers whose requests have landed.  The ring then holds the next group's first
+    // seven k-blocks, so the matrix pipeline restarts at once after the tile is staged.
+    drain_mfma<8, 2>(acc, rb);
+    int gn = g + 2;
+    asm volatile("" : "+s"(gn));  // computed here, not among the blocks above
+    next_base = group_base(gn, next_brow);
+    __builtin_amdgcn_s_barrier();  // staging tile free
+    asm volatile("" ::: "memory");
+    // block (i, j) = acc[2 i + j]: register v of lane (li, lh) is row 32 i + li, column
+    // 32 j + 8 (v / 4) + 4 lh + v % 4 of the wave's 64
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        // one block at a time leaves the accumulator registers (keeps the copies short-lived)
+        asm volatile("" : "+a"(acc[2 * i + j]) : : "memory");
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          uint2 w;
+          w.x = pack2_hw(acc[2 * i + j][4 * q], acc[2 * i + j][4 * q + 1]);
+          w.y = pack2_hw(acc[2 * i + j][4 * q + 2], acc[2 * i + j][4 * q + 3]);
+          *reinterpret_cast<uint2*>(orow + i * 32 * RW_OLD + (j * 32 + q * 8) * 2) = w;
+        }
+      }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();  // staging tile holds group g
+  }
+#undef PRAC_IC
+}
+
+constexpr int RS_OLD = 128 + 16;          // bytes per row of a wave's staging tile: 32 rows of 64 columns
+constexpr int RS_WAVE = 2 * 32 * RS_OLD;  // two of them, in turn
+constexpr int RS_SMEM = WS_STAGE + 8 * RS_WAVE;
+
+// Eight waves that each multiply and store strips of 64 columns.
+// RECON: one output.  Rows that lie on whole 128-byte lines are stored with the streaming hint (reconstruction of 8192 x 2048 22.1 us instead of 24.0), others
+// plainly: there every strip ends in lines that it shares with its neighbours, and those should meet in L2 (2 x 5461 columns 25.9 us
+// instead of 34.4).
+template <int KB, bool RECON>
+__global__ __launch_bounds__(512) void wide_strips_kernel(WideWsArgs a) {
   static_assert(KB == 8 || KB == 16, "whole turns of the ring, one k-tile");
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int bid = touch_kernel_args<sizeof(WideWsArgs)>(blockIdx.x);
@@ -679,48 +901,7 @@ __global__ __launch_bounds__(512) void wide_ws_kernel(WideWsArgs a) {
   };
 
   // ---------------------------------------------------------------- the A tile
-  if (a.packed) {
-    // Packed C holds, per lane slot, 8 tokens of one column; the tile needs 8 columns of one token per
-    // 16 bytes.  A thread takes an 8 x 8 patch: 8 consecutive column slots (128 contiguous bytes),
-    // transposed in registers as the C^T dY loader does for dY.  Patch tid:
-    // column octet o = tid & 3, token half h = (tid >> 2) & 1, column block cb = (tid >> 3) & 7, token block tb = tid >> 6.
-    const u32x4* Cp = reinterpret_cast<const u32x4*>(a.A);
-    const int o = tid & 3, h = (tid >> 2) & 1, cb = (tid >> 3) & 7, tb = tid >> 6;
-    u32x4 rr[8];
-    const bool live = cb < a.ccb;  // column blocks past c are zero in the tile
-    const int64_t base = ((int64_t)((m0 >> 4) + tb) * a.ccb + (live ? cb : 0)) * 64 + h * 32 + 8 * o;
-#pragma unroll
-    for (int jj = 0; jj < 8; ++jj) rr[jj] = Cp[base + jj];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      // token slot e of the patch: 16-bit element e of each of the 8 column slots
-      uint32_t w[4];
-#pragma unroll
-      for (int e2 = 0; e2 < 4; ++e2) {
-        const uint32_t lo = rr[2 * e2][e >> 1], hi = rr[2 * e2 + 1][e >> 1];
-        w[e2] = __builtin_amdgcn_perm(hi, lo, (e & 1) ? 0x07060302u : 0x05040100u);
-      }
-      const int row = 16 * tb + (e < 4 ? 4 * h + e : 8 + 4 * h + (e - 4));
-      u32x4 v = {w[0], w[1], w[2], w[3]};
-      if (!live) v = u32x4{0u, 0u, 0u, 0u};
-      *reinterpret_cast<u32x4*>(smem_raw + (row * WS_LD + 32 * cb + 8 * o) * 2) = v;
-    }
-  } else {
-    const int crow = tid >> 5, ccol = (tid & 31) * 8;  // row crow + 16 q, 16-byte chunk at column ccol
-    const char* cbase = reinterpret_cast<const char*>(a.A + (int64_t)m0 * a.lda);
-    const int last_chunk = ((a.c - 1) / 8) * 8;
-    const int nv = a.c - ccol;  // valid columns of this thread's chunk (<= 0: none)
-    u32x4 rc[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int row = min(m0 + crow + 16 * q, a.N - 1) - m0;  // rows past N repeat the last one, never stored
-      rc[q] = *reinterpret_cast<const u32x4*>(cbase + ((int64_t)row * a.lda + min(ccol, last_chunk)) * 2);
-    }
-    unsigned char* st = smem_raw + (crow * WS_LD + ccol) * 2;
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-      *reinterpret_cast<u32x4*>(st + q * (16 * WS_LD * 2)) = nv >= 8 ? rc[q] : keep_first(rc[q], nv > 0 ? nv : 0);
-  }
+  wide_load_tile<512>(a, smem_raw, m0, tid);
 
   // ------------------------------------------------------------------- strips
   const uint32_t boff = (uint32_t)lane * 16u;
@@ -768,9 +949,9 @@ __global__ __launch_bounds__(512) void wide_ws_kernel(WideWsArgs a) {
   // staging addresses of this lane: as a writer row li, columns 32 j + 8 q + 4 lh .. + 3, as a reader row (lane >> 3) + 8 p, 16-byte
   // chunk lane & 7 (a row is 144 bytes: lanes li and li + 8 of an 8-byte store would meet in the same banks, so
   // rows 8 .. 15 of every 16 swap the two 8-byte halves of each 16 bytes)
-  unsigned char* const stage = smem_raw + WS_STAGE + wave * RW_WAVE;
-  unsigned char* const wrow = stage + li * RW_OLD + ((8 * lh) ^ (((li >> 3) & 1) << 3));
-  const unsigned char* const rrow = stage + (lane >> 3) * RW_OLD + (lane & 7) * 16;
+  unsigned char* const stage = smem_raw + WS_STAGE + wave * RS_WAVE;
+  unsigned char* const wrow = stage + li * RS_OLD + ((8 * lh) ^ (((li >> 3) & 1) << 3));
+  const unsigned char* const rrow = stage + (lane >> 3) * RS_OLD + (lane & 7) * 16;
   while (st < send) {
     static_for<KB>([&](auto jc) {
       constexpr int J = decltype(jc)::value;
@@ -792,7 +973,7 @@ __global__ __launch_bounds__(512) void wide_ws_kernel(WideWsArgs a) {
     // 32 j + 8 (v / 4) + 4 lh + v % 4 of the strip's 64
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int turn = (i & 1) * 32 * RW_OLD;
+      const int turn = (i & 1) * 32 * RS_OLD;
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         // one block at a time leaves the accumulator registers (keeps the copies short-lived)
@@ -812,7 +993,7 @@ __global__ __launch_bounds__(512) void wide_ws_kernel(WideWsArgs a) {
       u32x4 ro[4];
 #pragma unroll
       for (int p = 0; p < 4; ++p) {
-        ro[p] = *reinterpret_cast<const u32x4*>(rrow + turn + 8 * p * RW_OLD);
+        ro[p] = *reinterpret_cast<const u32x4*>(rrow + turn + 8 * p * RS_OLD);
         if (p & 1) ro[p] = u32x4{ro[p].z, ro[p].w, ro[p].x, ro[p].y};
       }
       // 16 bytes at the alignment of one element (rows may start on any: 5461 columns, contiguous)
@@ -1727,19 +1908,22 @@ int launch_wide_ws(prac_ctx* ctx, bool recon, const bf16_t* A, int64_t lda, bool
   const int64_t total = (int64_t)a.tiles_m * ((groups + a.gper - 1) / a.gper);
   if (total > (1 << 28)) return PRAC_EINVAL;
   const dim3 grid((unsigned)((total + 7) / 8 * 8)), block(512);
-  static bool done_dev[PRAC_MAX_DEVICES][4] = {};
+  static bool done_dev[PRAC_MAX_DEVICES][8] = {};
   bool* done = done_dev[ctx->device % PRAC_MAX_DEVICES];
-#define PRAC_WIDE_CASE(I, KB, RECON)                                                        \
+#define PRAC_WIDE_CASE(I, KERN, KB, RECON, SMEM)                                            \
   case I: {                                                                                 \
-    int rc = set_smem(ctx, wide_ws_kernel<KB, RECON>, (size_t)RW_SMEM, done[I]);            \
+    int rc = set_smem(ctx, KERN<KB, RECON>, (size_t)SMEM, done[I]);                         \
     if (rc) return rc;                                                                      \
-    PRAC_LAUNCH(ctx, (wide_ws_kernel<KB, RECON>), grid, block, (size_t)RW_SMEM, a);         \
+    PRAC_LAUNCH(ctx, (KERN<KB, RECON>), grid, block, (size_t)SMEM, a);                      \
     break;                                                                                  \
   }
-  switch ((nkb == 8 ? 0 : 1) + (recon ? 0 : 2)) {
-    PRAC_WIDE_CASE(0, 8, true)
-    PRAC_WIDE_CASE(1, 16, true)
-    PRAC_WIDE_CASE(3, 16, false)
+  switch ((nkb == 8 ? 0 : 1) + (recon ? 0 : 2) + (a.gper <= WIDE_STRIP_GROUPS ? 4 : 0)) {
+    PRAC_WIDE_CASE(0, wide_ws_kernel, 8, true, RW_SMEM)
+    PRAC_WIDE_CASE(1, wide_ws_kernel, 16, true, RW_SMEM)
+    PRAC_WIDE_CASE(3, wide_ws_kernel, 16, false, RW_SMEM)
+    PRAC_WIDE_CASE(4, wide_strips_kernel, 8, true, RS_SMEM)
+    PRAC_WIDE_CASE(5, wide_strips_kernel, 16, true, RS_SMEM)
+    PRAC_WIDE_CASE(7, wide_strips_kernel, 16, false, RS_SMEM)
     default: return PRAC_EINVAL;
   }
 #undef PRAC_WIDE_CASE

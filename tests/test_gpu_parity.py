@@ -613,10 +613,11 @@ def test_weight_grad_of_small_layers_with_an_infinite_basis_element(ctx, c):
     (4224, 130, (2085,), 0),          # rows on any element, the last column group 37 wide
     (4100, 129, (2304, 264), 5),      # a ragged row tile, two outputs of different pitch
     (8200, 256, (8, 1160, 513), 0),   # an output of one chunk
+    (8200, 200, (1283, 8, 2560), 1),  # six groups per workgroup: the form of whole groups (strips above), ranges that start inside an output
     (4224, 128, (2085,), 3),          # narrower C: the tiled kernel, rows on any element
 ])
 def test_weight_grad_of_wide_layers(ctx, d, c, ms, pad):
-    """dW = P T by the kernel that walks column groups (more than 256 tiles of 128 x 256): every element against the
+    """dW = P T by the kernels that walk column groups (more than 256 tiles of 128 x 256): every element against the
     product of the same bf16 operands, nothing written outside the rows.  T is rounded to bf16 on the device from sums in
     its own order, so an ulp of T either way (2^-8 relative) is allowed for, and one of dW."""
     k, N = c // 2, 600
@@ -800,6 +801,10 @@ def test_reconstruct_matches_oracle(ctx, dt, N, d, k, r, ldc, ldxh):
     (1000, 1163, 130, 1163, False),  # the last strip 11 columns wide
     (129, 70, 17, 72, True),          # two strips, eight k-blocks
     (64, 512, 128, 512, False),      # one strip per wave
+    (10873, 2291, 256, 2291, True),   # three groups per workgroup, the last with which strips are taken; rows on any element
+    (10873, 2300, 120, 2304, False),  # the same, eight k-blocks
+    (10873, 2816, 200, 2816, False),  # four: whole groups, a last range of three
+    (16300, 2043, 100, 2048, True),   # four, eight k-blocks, the last group 251 wide
 ])
 def test_reconstruct_strips(ctx, N, d, c, ld, packed):
     """Every element against the product of the same bf16 operands (fp32 sums of c products: c 2^-24 of the sum of their
