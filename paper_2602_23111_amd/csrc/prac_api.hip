@@ -130,28 +130,46 @@ inline int gram_splits(int n_cu, int64_t d, int64_t rows) {
 namespace {
 // Large Gram matrices run on the C^T dY kernel with X in both places (its streaming rate at
 // d = 2048 is 2.5 times that of the tiled GEMM): X is first copied into the packed layout the
-// kernel reads its C operand from.  Only tiles on and above the diagonal are formed (72 of 128 at d = 2048, three token ranges
-// instead of two), and their sum is written to both sides: 32768 x 2048 239 us and 11.9 for the sum, now 165 and 15.6.
+// kernel reads its C operand from.  Two forms: all tiles, whose sum of token ranges goes straight through the slabs, or only those on and above the
+// diagonal (72 of 128 at d = 2048, three ranges instead of two), whose sum is written to both sides.  The latter wherever the estimate below
+// says so.  Kernel and sum, all / upper, us: 32768 x 2048 233 + 10 / 155 + 15, 32768 x 768 45 + 8 / 34 + 12, 8192 x 4096 248 + 0 / 204 + 27; but
+// 32768 x 256 15 + 4 / 15 + 23 (64 ranges either way, and few workgroups in the second sum), 8192 x 512 15 + 6 / 13 + 15, 2048 x 1500 22 + 7 / 18 + 16,
+// 2048 x 4096 88 + 0 / 65 + 29.
 inline bool gram_streaming(int64_t rows, int64_t d) { return rows >= 2048 && d >= 256; }
-inline int gram_stream_splits(int n_cu, int64_t d, int64_t rows) {
-  const int64_t tiles = ctdy_upper_tiles((int)((d + 127) / 128), (int)((d + 255) / 256));
-  int64_t s = n_cu / tiles;
+inline int64_t gram_stream_tiles(int64_t d, bool upper) {
+  const int tiles_n = (int)((d + 127) / 128), row_groups = (int)((d + 255) / 256);
+  return upper ? ctdy_upper_tiles(tiles_n, row_groups) : (int64_t)tiles_n * row_groups;
+}
+inline int gram_stream_splits(int n_cu, int64_t d, int64_t rows, bool upper) {
+  int64_t s = n_cu / gram_stream_tiles(d, upper);
   if (s > rows / 256) s = rows / 256;
   if (s > 64) s = 64;
   return s < 1 ? 1 : (int)s;
 }
+// us of a form, fitted to the kernels' times in 12 shapes of d 256 to 4096: 9.5 and 1.75 per 128 tokens for a round of workgroups (0.65 of that for a last
+// one that is not full), then the sum: by its bytes, in the upper form (half of the slabs read, rows that start off 128-byte lines at 2 / 3 of
+// the rate) not below its trips over the slabs
+inline double gram_stream_us(int n_cu, int64_t d, int64_t rows, bool upper) {
+  const int splits = gram_stream_splits(n_cu, d, rows, upper);
+  const int64_t wgs = gram_stream_tiles(d, upper) * splits, steps = ((rows + 127) / 128 + splits - 1) / splits;
+  const double rounds = wgs <= n_cu ? 1.0 : (double)(wgs / n_cu) + (wgs % n_cu ? 0.65 : 0.0), mb = 4e-6 * (double)d * (double)d;
+  const double sum = !upper ? (splits > 1 ? 1.5 + (splits + 1) * mb / 5.5 : 0.0)
+                            : std::max(3.0 + 0.36 * splits, 1.0 + (0.5 * splits + 1) * mb / 3.5 * (d % 32 ? 1.5 : 1.0));
+  return rounds * (9.5 + 1.75 * (double)steps) + sum;
+}
 struct GramPlan {
-  bool streaming;
+  bool streaming, upper;
   int splits;
   size_t o_part, o_g, o_pack, bytes;
 };
 inline GramPlan plan_gram(int n_cu, int64_t rows, int64_t d, int64_t ldg) {
   GramPlan g{};
   g.streaming = gram_streaming(rows, d);
-  g.splits = g.streaming ? gram_stream_splits(n_cu, d, rows) : gram_splits(n_cu, d, rows);
+  g.upper = g.streaming && gram_stream_us(n_cu, d, rows, true) < gram_stream_us(n_cu, d, rows, false);
+  g.splits = g.streaming ? gram_stream_splits(n_cu, d, rows, g.upper) : gram_splits(n_cu, d, rows);
   WsPlan plan;
   g.o_part = plan.take(g.splits > 1 ? (size_t)g.splits * d * d * sizeof(float) : 0);
-  g.o_g = plan.take(ldg == d || (g.streaming && g.splits > 1) ? 0 : (size_t)d * d * sizeof(float));
+  g.o_g = plan.take(ldg == d || (g.upper && g.splits > 1) ? 0 : (size_t)d * d * sizeof(float));
   g.o_pack = plan.take(g.streaming ? packed_c_bytes(rows, (int)d) : 0);
   g.bytes = plan.off;
   return g;
@@ -199,10 +217,10 @@ int gram_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, int64_t
       float* out = splits > 1 ? partial : dense;
       {
         ProfScope ps(ctx, PRAC_KERNEL_GRAM);
-        rc = launch_ctdy_ws(ctx, Xpk, dm, (int)rows, 1, &Xb, &ld, &dm, &out, splits, how == GramRows::ANY, 0, nullptr, nullptr, true);
+        rc = launch_ctdy_ws(ctx, Xpk, dm, (int)rows, 1, &Xb, &ld, &dm, &out, splits, how == GramRows::ANY, 0, nullptr, nullptr, gp.upper);
       }
       if (rc) return rc;
-      return launch_reduce_symmetric(ctx, out, splits, dm, G, ldg);
+      if (gp.upper) return launch_reduce_symmetric(ctx, out, splits, dm, G, ldg);
     } else {
       GemmBf16Args g{};
       g.A = reinterpret_cast<const bf16_t*>(X);

@@ -1141,9 +1141,11 @@ def test_gram_matches_oracle(ctx, dt, N, d, ldx, stride):
 
 
 @pytest.mark.parametrize("N,d,ldg", [(2048, 256, 256), (2100, 257, 260), (2048, 384, 384), (3000, 385, 385), (2048, 640, 645),
-                                     (4096, 1031, 1031), (2048, 4161, 4161)])  # the last: a single token range, mirrored in place
+                                     (4096, 1031, 1031), (2048, 4161, 4161),   # up to here: all tiles
+                                     (16384, 768, 768), (16500, 769, 773), (12000, 1153, 1153), (8192, 1281, 1281), (4096, 2305, 2310),
+                                     (4096, 4161, 4161), (4096, 4161, 4165)])  # single token ranges, the first mirrored in place
 def test_gram_from_its_upper_tiles(ctx, N, d, ldg):
-    """Edges of the 256 x 128 tiles that reach the diagonal and of the 64 x 64 blocks of their sum, both triangles the same bits;
+    """Edges of the 256 x 128 tiles, of those that reach the diagonal and of the 64 x 64 blocks of their sum, both triangles the same bits;
     fp32 sums of N products (a few N^1/2 2^-24 of the column norms' product, below 2e-5)."""
     g = torch.Generator(device=DEV).manual_seed(d)
     X = torch.zeros((N, (d + 7) // 8 * 8), dtype=torch.bfloat16, device=DEV)[:, :d]
