@@ -1248,10 +1248,10 @@ __global__ __launch_bounds__(256) void panel_gram64_sum_kernel(const double* __r
   }
 }
 
-// The sum of the fp32 partial Gram matrices of a block, as fp64 (W64 != nullptr) or as the factor 1.5 I - 0.5 W of a Newton-Schulz step, a
-// workgroup per row.  For the latter W is the Gram matrix of a block that should be close to orthonormal: an entry further than `limit` from the
+// The sum of the fp32 partial Gram matrices of a block, as fp64 (W64 != nullptr) or as the factor 1.5 I - 0.5 W of a Newton-Schulz step.
+// For the latter W is the Gram matrix of a block that should be close to orthonormal: an entry further than `limit` from the
 // identity (or not finite) raises bit 1 of *flag - the step that follows squares the distance, so a block that far off
-// does not come out orthonormal to fp32 rounding.  again (or nullptr): set where a row sum of |W - I|, a bound of its norm, is above PANEL_ONCE.
+// does not come out orthonormal to fp32 rounding.  again (or nullptr; then a workgroup per row): set where a row sum of |W - I|, a bound of its norm, is above PANEL_ONCE.
 // (slabs may be M32 itself)
 // PANEL_LAST: a last step leaves 0.75 (3e-3)^2 < 1e-5 of an entry that is alone in its row and column, and 0.75 n (3e-3)^2 at the very worst, of n equal ones.
 constexpr float PANEL_LAST = 3e-3f;
@@ -1259,16 +1259,17 @@ __global__ __launch_bounds__(256) void panel_gram32_sum_kernel(const float* slab
                                                                float limit, int* flag, int* again) {
   bool off = false;
   float sum = 0.f;
-  const int total = n * n, row = blockIdx.x;
-  for (int c = threadIdx.x; c < n; c += blockDim.x) {
-    const int i = row * n + c;
+  const int total = n * n;
+  const int first = again ? blockIdx.x * n + threadIdx.x : blockIdx.x * blockDim.x + threadIdx.x;
+  const int end = again ? (blockIdx.x + 1) * n : total, step = again ? blockDim.x : gridDim.x * blockDim.x;
+  for (int i = first; i < end; i += step) {
     float w = 0.f;
 #pragma unroll 8
     for (int z = 0; z < splits; ++z) w += slabs[(int64_t)z * total + i];
     if (W64) {
       W64[i] = (double)w;
     } else {
-      const float id = row == c ? 1.f : 0.f;
+      const float id = i / n == i % n ? 1.f : 0.f;
       off = off || !(fabsf(w - id) <= limit);
       sum += fabsf(w - id);
       M32[i] = 1.5f * id - 0.5f * w;
@@ -1454,7 +1455,7 @@ int panel_gram32(prac_ctx* ctx, const FitWs& w, const float* src, int64_t d, int
     rc = launch_gemm_generic(ctx, g);
   }
   if (rc) return rc;
-  hipLaunchKernelGGL(panel_gram32_sum_kernel, dim3(n), dim3(256), 0, ctx->stream, sums, splits, n, W64, factor,
+  hipLaunchKernelGGL(panel_gram32_sum_kernel, dim3(again ? n : (n * n + 255) / 256), dim3(256), 0, ctx->stream, sums, splits, n, W64, factor,
                      limit, ctx->d_flag, again);
   PRAC_HIP_TRY(ctx, hipGetLastError());
   return PRAC_OK;
