@@ -984,6 +984,14 @@ __global__ __launch_bounds__(256) void copy_cols_kernel(const float* __restrict_
 // (see CholShift), and of batches of lower rank than the block the noise that rounding leaves in the surplus columns has to be above that.
 // With less of it 4 of 92 such fits of 240 drawn ones that were accepted were refused.
 constexpr int GV_MAX = 256;
+// Narrower blocks and fewer features keep the fp32 instructions too: a launch costs more than their product (fixed 5 us against 3), cutting G into parts 3 to 120 us
+// more, and G in parts is half as many bytes again, read once per 64 columns.  Fits on fp32 instructions less fits on parts, us (2048 rows, d x b):
+// 1024 x 65 -8, x 128 -1, x 130 24; 768 x 130 -2, x 256 8; 1536 x 64 -2, x 66 16, x 128 54; 2048 x 64 -28, x 66 9; 2502 x 32 -20, x 64 31; 4096 x 32 -54, x 64 10,
+// x 256 264; 6007 x 64 212; 7001 x 32 -202, x 64 54; 8192 x 64 -158 (parts past the last cache), x 66 84, x 128 66.
+inline bool gv_parts(int64_t d, int b) {
+  if (b > GV_MAX) return false;
+  return b > 128 ? d >= 1024 : b > 64 ? d >= 1536 : b > 32 && d >= 2500 && d <= 7000;
+}
 constexpr int GV_W = 8, GV_D = 4;  // waves, k-blocks in flight
 static inline int gv_kblocks(int64_t d) { return (int)(round_up64(d, 16 * GV_W) / 16); }
 static inline size_t gv_g_bytes(int64_t d) { return (size_t)((d + 31) / 32) * gv_kblocks(d) * 3072; }
@@ -1308,7 +1316,8 @@ struct FitWs {
   int b;
   int kq;         // principal columns the iteration computes (see principal_rank); the other k - kq are drawn
   int splits_bb;  // split count of the b x b fp64 Gram products
-  int splits_gv;  // split count of G V for b > GV_MAX
+  bool gv_parts;  // G V as bf16 parts
+  int splits_gv;  // split count of G V on fp32 instructions
 };
 
 int block_width(int64_t d, int k, const prac_fit_opts& o) {
@@ -1364,7 +1373,8 @@ FitWs plan_fit(int64_t d, int k, int r, const prac_fit_opts& o, int n_cu, bool n
   const int s = panel_splits(n_cu, d, bb);
   w.splits_bb = s;
   // G V (d x b, fp32): split the sum over k until the tiles fill the chip
-  const bool gv_f32 = need_g && b > GV_MAX;
+  w.gv_parts = need_g && gv_parts(d, b);
+  const bool gv_f32 = need_g && !w.gv_parts;
   const int tiles_gv = (int)((d + 63) / 64) * ((b + 63) / 64);
   int sg = gv_f32 ? (n_cu + tiles_gv - 1) / tiles_gv : 1;
   if (sg > d / 256) sg = (int)(d / 256);
@@ -1380,8 +1390,8 @@ FitWs plan_fit(int64_t d, int k, int r, const prac_fit_opts& o, int n_cu, bool n
     w.slab_bytes = std::max(w.slab_bytes, pg_need(n_cu, d, n));
   w.slabs = p.take(w.slab_bytes);
   w.gram = p.take(gram_bytes);
-  w.gv_g = p.take(need_g && !gv_f32 ? gv_g_bytes(d) : 0);
-  w.gv_v = p.take(need_g && !gv_f32 ? gv_v_bytes(d, b) : 0);
+  w.gv_g = p.take(w.gv_parts ? gv_g_bytes(d) : 0);
+  w.gv_v = p.take(w.gv_parts ? gv_v_bytes(d, b) : 0);
   if (track) {
     w.trk_nkb = (int)(round_up64(d, 256) / 16);
     w.trk_ncb = (int)round_up64((k + 31) / 32, 8);
@@ -1683,7 +1693,7 @@ int fit_basis_device(prac_ctx* ctx, const void* X, prac_dtype xdt, int64_t N, in
       PRAC_HIP_TRY(ctx, hipGetLastError());
     }
     u32x4* const Gf = reinterpret_cast<u32x4*>(ctx->ws + L.gv_g);
-    u32x4* const Vf = b <= GV_MAX ? reinterpret_cast<u32x4*>(ctx->ws + L.gv_v) : nullptr;
+    u32x4* const Vf = L.gv_parts ? reinterpret_cast<u32x4*>(ctx->ws + L.gv_v) : nullptr;
     if (Vf) {
       const int nkb = gv_kblocks(d), nrb = (int)((d + 31) / 32);
       hipLaunchKernelGGL(split_parts_kernel<true>, dim3((unsigned)(((int64_t)nrb * nkb + 3) / 4)), dim3(256), 0, st, G, d, (int)d, d, nrb,

@@ -727,10 +727,12 @@ def test_static_weight_grad_takes_narrow_outputs_of_many_tokens(ctx, N, d, c, m,
 
 
 @pytest.mark.parametrize("dt,N,d,k", [("bf16", 900, 129, 32), ("bf16", 900, 127, 33), ("bf16", 1000, 256, 16), ("bf16", 2100, 257, 65),
-                                      ("f32", 700, 33, 3), ("f32", 1200, 385, 128), ("bf16", 2048, 640, 129), ("f32", 600, 1030, 31)])
+                                      ("f32", 700, 33, 3), ("f32", 1200, 385, 128), ("bf16", 2048, 640, 129), ("f32", 600, 1030, 31),
+                                      # G V as bf16 parts up to 64, 128 and 256 columns, and the sizes before the first that take them
+                                      ("bf16", 900, 2501, 17), ("f32", 900, 2528, 32), ("bf16", 900, 1537, 33), ("f32", 900, 1567, 64), ("bf16", 900, 1024, 65),
+                                      ("f32", 900, 1057, 128), ("bf16", 900, 1120, 100), ("bf16", 900, 1023, 65), ("bf16", 900, 1535, 33), ("f32", 900, 2499, 32)])
 def test_cold_fit_at_edges_of_the_products_tiles(ctx, dt, N, d, k):
-    """Block widths 2 k and feature counts around the 32 x 64 tiles and the 128 k of a turn of the waves in G V, and blocks
-    of up to 128, 256 and more columns (whose parts are written by the solve or by a kernel of their own).  k directions ten times the
+    """Block widths 2 k and feature counts around the tiles and the turns of the waves in G V, on fp32 instructions and as bf16 parts.  k directions ten times the
     noise: the projector is defined to far below 1e-3, and eight iterations reach it."""
     g = torch.Generator().manual_seed(d + k)
     X = torch.randn((N, k), generator=g) @ torch.randn((k, d), generator=g) * 10.0 / k ** 0.5 + torch.randn((N, d), generator=g)
@@ -744,7 +746,8 @@ def test_cold_fit_at_edges_of_the_products_tiles(ctx, dt, N, d, k):
     assert np.abs(P64.T @ P64 - np.eye(k + 2)).max() < 1e-5
 
 
-@pytest.mark.parametrize("dt,N,d,k,exponent", [("bf16", 2048, 640, 64, 64), ("bf16", 2048, 640, 64, 66), ("f32", 2048, 640, 64, 64), ("f32", 700, 300, 16, 66)])
+@pytest.mark.parametrize("dt,N,d,k,exponent", [("bf16", 2048, 1600, 64, 64), ("bf16", 2048, 1600, 64, 66), ("f32", 2048, 1100, 70, 64), ("f32", 700, 1100, 70, 66),
+                                               ("bf16", 2048, 640, 64, 66), ("f32", 700, 300, 16, 66)])  # G V on fp32 instructions
 def test_cold_fit_of_tiny_batches(ctx, dt, N, d, k, exponent):
     """A batch of elements around 2^-64: its Gram matrix lies just above the smallest normal number, so that parts of its entries do not.  The
     principal subspace against the exact one: as far off as that of the same batch around 1 (how far the iteration has come), and what
