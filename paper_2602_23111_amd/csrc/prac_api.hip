@@ -521,7 +521,7 @@ namespace {
 // How a compress / fused-forward call runs: STREAM, the bf16 kernels on aligned rows; STREAM_ANY, the same kernels on
 // rows that start on any element, with the fp32 P as three bf16 parts; STRIDED, everything else (fp32 data, rows
 // of fewer than 8 elements, pitches above PRAC_MAX_STREAM_PITCH).  At N = 32768, d = 5461 (contiguous rows), c = 256
-// STREAM_ANY takes 0.25 ms, packing included, where the strided kernel and its cast take 2.5 ms (and STREAM with
+// STREAM_ANY takes 0.23 ms, packing included, where the strided kernel and its cast take 2.5 ms (and STREAM with
 // padded rows 0.11 ms: a third of the matrix instructions).
 enum class CompressPath { STREAM, STREAM_ANY, STRIDED };
 struct CompressPlan {
